@@ -4,6 +4,11 @@ Every function has the name of the C-ABI entry point it calls (include/mnnq.h)
 and takes torch tensors that already live on the GPU; torch supplies device
 memory and the current stream, nothing else.  No step of the path runs in
 Python or on the CPU: if the library is missing this module raises.
+
+The calls that a program makes for every token or prompt, and the packing of a
+weight matrix, come from the CPython module _native (csrc/native_binding.cpp):
+a decode call is 4 - 15 us of GPU work, which marshalling through ctypes did not
+keep up with.  The others go through ctypes.
 """
 from __future__ import annotations
 
@@ -18,6 +23,17 @@ MODE_W4_MIN_FLOAT = 1   # Eq. 1 as printed: fp32 group minimum per (row, group)
 MODE_W8_MIN_FLOAT = 2   # int8 weights (codes 0..255), fp32 group minimum; K must be a multiple of 128
 WITH_MATRIX_PLANE = 16  # flag for MODE_W4_ZP_INT: the packed buffer also holds the fp6 matrix-core plane
 NATIVE_8BIT = 32        # flag for MODE_W8_MIN_FLOAT: the codes as bytes q8 - 128 instead of two 4-bit planes
+
+try:
+    # names, arguments and defaults: help(mnnq_linear_decode_fused) etc.
+    from ._native import (  # noqa: F401
+        mnnq_linear_decode, mnnq_linear_decode_f16, mnnq_linear_decode_f16_o16, mnnq_linear_decode_fused,
+        mnnq_linear_decode_fused_o16, mnnq_linear_decode_o16, mnnq_linear_prefill, mnnq_linear_prefill_f16,
+        mnnq_linear_prefill_f16_o16, mnnq_linear_prefill_fused, mnnq_linear_prefill_fused_o16,
+        mnnq_linear_prefill_o16, mnnq_pack_weights)
+except ImportError as e:
+    raise RuntimeError("the native library is not built (%s); run `python -c 'import __graft_entry__ as g; g.build()'`"
+                       % e) from e
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libmnnq.so")
@@ -138,21 +154,6 @@ def mnnq_workspace_size(M: int, N: int, K: int, group: int = GROUP, mode: int = 
     return int(lib().mnnq_workspace_size(M, N, K, group, mode))
 
 
-def mnnq_pack_weights(W: torch.Tensor, out: torch.Tensor | None = None, mode: int = MODE_W4_ZP_INT) -> torch.Tensor:
-    """W fp32 [N, K] on the GPU -> packed uint8 buffer."""
-    _dev(W, torch.float32, "W")
-    N, K = W.shape
-    size = mnnq_packed_size(N, K, GROUP, mode)
-    if size == 0:
-        _check(lib().mnnq_pack_weights(_ptr(W), N, K, GROUP, mode, _ptr(W), 0, _stream()),
-               "mnnq_pack_weights")
-    if out is None:
-        out = torch.empty(size, dtype=torch.uint8, device=W.device)
-    _check(lib().mnnq_pack_weights(_ptr(W), N, K, GROUP, mode, _ptr(out), out.numel(), _stream()),
-           "mnnq_pack_weights")
-    return out
-
-
 def mnnq_unpack_weights(packed: torch.Tensor, N: int, K: int, mode: int = MODE_W4_ZP_INT):
     """Canonical view: (q u8 [N,K], scale f32 [N,G], zero u8 [N,G]); in mode MODE_W4_MIN_FLOAT the
     third array holds the fp32 group minima."""
@@ -181,56 +182,6 @@ def mnnq_quant_act(x: torch.Tensor, want_xsum: bool = True, out=None):
     _check(lib().mnnq_quant_act(_ptr(x), M, K, GROUP, _ptr(xq), _ptr(sx), _ptr(xsum), _stream()),
            "mnnq_quant_act")
     return xq, sx, xsum
-
-
-def mnnq_linear_decode(packed, N: int, K: int, xq, sx, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
-    """One token: xq i8 [K] (or [1,K]), sx f32 [1] -> y f32 [N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(xq, torch.int8, "xq"); _dev(sx, torch.float32, "sx")
-    _need_packed(packed, N, K, mode)
-    if xq.numel() != K:
-        raise ValueError("xq must hold K values")
-    y = torch.empty((N,), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    _check(lib().mnnq_linear_decode(_ptr(packed), N, K, GROUP, mode, _ptr(xq), _ptr(sx), _ptr(bias),
-                                    _ptr(y), None, 0, _stream()), "mnnq_linear_decode")
-    return y
-
-
-def mnnq_linear_decode_fused(packed, N: int, K: int, x, bias=None, out=None, workspace=None,
-                             mode: int = MODE_W4_ZP_INT):
-    """One token, activation quantizer fused in: x f32 [K] (or [1,K]) -> y f32 [N].
-    workspace: optional uint8 tensor of mnnq_workspace_size(1, N, K) bytes."""
-    _dev(packed, torch.uint8, "packed"); _dev(x, torch.float32, "x")
-    _need_packed(packed, N, K, mode)
-    if x.numel() != K:
-        raise ValueError("x must hold K values")
-    y = torch.empty((N,), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    if workspace is not None:
-        _dev(workspace, torch.uint8, "workspace")
-    _check(lib().mnnq_linear_decode_fused(_ptr(packed), N, K, GROUP, mode, _ptr(x), _ptr(bias),
-                                          _ptr(y), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                          _stream()), "mnnq_linear_decode_fused")
-    return y
-
-
-def mnnq_linear_prefill(packed, N: int, K: int, xq, sx, bias=None, out=None, mode: int = MODE_W4_ZP_INT,
-                        workspace=None):
-    """M tokens: xq i8 [M,K], sx f32 [M] -> y f32 [M,N].  workspace: optional uint8 tensor
-    (mnnq_workspace_size bytes); with the matrix-core plane in `packed` it selects the fp6 GEMM."""
-    _dev(packed, torch.uint8, "packed"); _dev(xq, torch.int8, "xq"); _dev(sx, torch.float32, "sx")
-    _need_packed(packed, N, K, mode)
-    M = xq.shape[0]
-    if xq.shape[1] != K or sx.numel() != M:
-        raise ValueError("xq must be [M,K] and sx [M]")
-    if workspace is not None:
-        _dev(workspace, torch.uint8, "workspace")
-    y = torch.empty((M, N), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _check(lib().mnnq_linear_prefill(_ptr(packed), M, N, K, GROUP, mode, _ptr(xq), _ptr(sx),
-                                     _ptr(bias), _ptr(y), _ptr(workspace),
-                                     0 if workspace is None else workspace.numel(), _stream()), "mnnq_linear_prefill")
-    return y
 
 
 def mnnq_linear_acc_debug_planes(packed, N: int, K: int, xq, mode: int, workspace=None):
@@ -276,35 +227,6 @@ def mnnq_debug_set(key: str, value) -> None:
     _check(lib().mnnq_debug_set(key.encode(), None if value is None else str(value).encode()), "mnnq_debug_set")
 
 
-def mnnq_linear_decode_f16(packed, N: int, K: int, x16, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
-    """One token, fp16 activations (W4A16; W8A16 with MODE_W8_MIN_FLOAT): x16 fp16 [K] -> y f32 [N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(x16, torch.float16, "x16")
-    _need_packed(packed, N, K, mode)
-    if x16.numel() != K:
-        raise ValueError("x16 must hold K values")
-    y = torch.empty((N,), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    _check(lib().mnnq_linear_decode_f16(_ptr(packed), N, K, GROUP, mode, _ptr(x16), _ptr(bias),
-                                        _ptr(y), None, 0, _stream()), "mnnq_linear_decode_f16")
-    return y
-
-
-def mnnq_linear_prefill_f16(packed, N: int, K: int, x16, bias=None, out=None, row_scale=None,
-                            mode: int = MODE_W4_ZP_INT):
-    """M tokens, fp16 activations (W4A16; W8A16 with MODE_W8_MIN_FLOAT): x16 fp16 [M,K] -> y f32 [M,N];
-    row_scale f32 [M] optional."""
-    _dev(packed, torch.uint8, "packed"); _dev(x16, torch.float16, "x16")
-    _need_packed(packed, N, K, mode)
-    M = x16.shape[0]
-    if x16.shape[1] != K:
-        raise ValueError("x16 must be [M,K]")
-    y = torch.empty((M, N), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _check(lib().mnnq_linear_prefill_f16(_ptr(packed), M, N, K, GROUP, mode, _ptr(x16), _ptr(row_scale),
-                                         _ptr(bias), _ptr(y), None, 0, _stream()), "mnnq_linear_prefill_f16")
-    return y
-
-
 def mnnq_pack_from_quantized(q, scale, zero, out=None, mode: int = MODE_W4_ZP_INT):
     """q u8 [N,K], scale f32 [N,G], zero u8 [N,G] (fp32 group minima in mode MODE_W4_MIN_FLOAT) on the
     GPU -> packed uint8 buffer."""
@@ -336,89 +258,6 @@ def mnnq_linear_acc_debug(packed, N: int, K: int, xq, use_prefill_kernel: bool, 
     return acc
 
 
-# ---- the same linear calls with IEEE binary16 output
-
-def mnnq_linear_decode_o16(packed, N: int, K: int, xq, sx, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
-    """One token: xq i8 [K], sx f32 [1] -> y fp16 [N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(xq, torch.int8, "xq"); _dev(sx, torch.float32, "sx")
-    _need_packed(packed, N, K, mode)
-    if xq.numel() != K:
-        raise ValueError("xq must hold K values")
-    y = torch.empty((N,), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    _check(lib().mnnq_linear_decode_o16(_ptr(packed), N, K, GROUP, mode, _ptr(xq), _ptr(sx), _ptr(bias),
-                                        _ptr(y), _stream()), "mnnq_linear_decode_o16")
-    return y
-
-
-def mnnq_linear_prefill_o16(packed, N: int, K: int, xq, sx, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
-    """M tokens: xq i8 [M,K], sx f32 [M] -> y fp16 [M,N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(xq, torch.int8, "xq"); _dev(sx, torch.float32, "sx")
-    _need_packed(packed, N, K, mode)
-    M = xq.shape[0]
-    if xq.shape[1] != K or sx.numel() != M:
-        raise ValueError("xq must be [M,K] and sx [M]")
-    y = torch.empty((M, N), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    _check(lib().mnnq_linear_prefill_o16(_ptr(packed), M, N, K, GROUP, mode, _ptr(xq), _ptr(sx),
-                                         _ptr(bias), _ptr(y), _stream()), "mnnq_linear_prefill_o16")
-    return y
-
-
-def mnnq_linear_decode_f16_o16(packed, N: int, K: int, x16, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
-    """One token, fp16 activations: x16 fp16 [K] -> y fp16 [N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(x16, torch.float16, "x16")
-    _need_packed(packed, N, K, mode)
-    if x16.numel() != K:
-        raise ValueError("x16 must hold K values")
-    y = torch.empty((N,), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    _check(lib().mnnq_linear_decode_f16_o16(_ptr(packed), N, K, GROUP, mode, _ptr(x16), _ptr(bias),
-                                            _ptr(y), _stream()), "mnnq_linear_decode_f16_o16")
-    return y
-
-
-def mnnq_linear_prefill_f16_o16(packed, N: int, K: int, x16, bias=None, out=None, row_scale=None,
-                                mode: int = MODE_W4_ZP_INT):
-    """M tokens, fp16 activations: x16 fp16 [M,K] -> y fp16 [M,N]; row_scale f32 [M] optional."""
-    _dev(packed, torch.uint8, "packed"); _dev(x16, torch.float16, "x16")
-    _need_packed(packed, N, K, mode)
-    M = x16.shape[0]
-    if x16.shape[1] != K:
-        raise ValueError("x16 must be [M,K]")
-    y = torch.empty((M, N), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    _check(lib().mnnq_linear_prefill_f16_o16(_ptr(packed), M, N, K, GROUP, mode, _ptr(x16), _ptr(row_scale),
-                                             _ptr(bias), _ptr(y), _stream()), "mnnq_linear_prefill_f16_o16")
-    return y
-
-
-def mnnq_linear_prefill_fused(packed, N: int, K: int, x, bias=None, out=None, workspace=None,
-                              mode: int = MODE_W4_ZP_INT):
-    """M tokens, activation quantizer inside the call: x f32 [M,K] -> y f32 [M,N].
-    workspace: uint8 tensor of at least mnnq_workspace_size(M, N, K) bytes (required by the library;
-    this wrapper brings one along when none is given)."""
-    _dev(packed, torch.uint8, "packed"); _dev(x, torch.float32, "x")
-    _need_packed(packed, N, K, mode)
-    M = x.shape[0]
-    if x.shape[1] != K:
-        raise ValueError("x must be [M,K]")
-    if workspace is None:
-        workspace = torch.empty(max(16, mnnq_workspace_size(M, N, K, GROUP, mode)), dtype=torch.uint8,
-                                device=packed.device)
-    _dev(workspace, torch.uint8, "workspace")
-    y = torch.empty((M, N), dtype=torch.float32, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _check(lib().mnnq_linear_prefill_fused(_ptr(packed), M, N, K, GROUP, mode, _ptr(x), _ptr(bias), _ptr(y),
-                                           _ptr(workspace), workspace.numel(), _stream()),
-           "mnnq_linear_prefill_fused")
-    return y
-
-
 def mnnq_linear_prefill_fused_static(packed, N: int, K: int, x, bias=None, out=None, mode: int = MODE_W4_ZP_INT):
     """mnnq_linear_prefill_fused through the library's own scratch array: x f32 [M,K] -> y f32 [M,N];
     `out` must be given by callers that may not allocate (this wrapper allocates it otherwise)."""
@@ -436,45 +275,6 @@ def mnnq_linear_prefill_fused_static(packed, N: int, K: int, x, bias=None, out=N
 
 def mnnq_static_scratch_bytes() -> int:
     return int(lib().mnnq_static_scratch_bytes())
-
-
-def mnnq_linear_decode_fused_o16(packed, N: int, K: int, x, bias=None, out=None, workspace=None,
-                                 mode: int = MODE_W4_ZP_INT):
-    """One token, activation quantizer fused in: x f32 [K] -> y fp16 [N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(x, torch.float32, "x")
-    _need_packed(packed, N, K, mode)
-    if x.numel() != K:
-        raise ValueError("x must hold K values")
-    y = torch.empty((N,), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    if workspace is not None:
-        _dev(workspace, torch.uint8, "workspace")
-    _check(lib().mnnq_linear_decode_fused_o16(_ptr(packed), N, K, GROUP, mode, _ptr(x), _ptr(bias), _ptr(y),
-                                              _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                              _stream()), "mnnq_linear_decode_fused_o16")
-    return y
-
-
-def mnnq_linear_prefill_fused_o16(packed, N: int, K: int, x, bias=None, out=None, workspace=None,
-                                  mode: int = MODE_W4_ZP_INT):
-    """M tokens, activation quantizer inside the call: x f32 [M,K] -> y fp16 [M,N]."""
-    _dev(packed, torch.uint8, "packed"); _dev(x, torch.float32, "x")
-    _need_packed(packed, N, K, mode)
-    M = x.shape[0]
-    if x.shape[1] != K:
-        raise ValueError("x must be [M,K]")
-    if workspace is None:
-        workspace = torch.empty(max(16, mnnq_workspace_size(M, N, K, GROUP, mode)), dtype=torch.uint8,
-                                device=packed.device)
-    _dev(workspace, torch.uint8, "workspace")
-    y = torch.empty((M, N), dtype=torch.float16, device=packed.device) if out is None else out
-    _need(y, M * N, "out"); _need(bias, N, "bias")
-    _dev(y, torch.float16, "out")
-    _check(lib().mnnq_linear_prefill_fused_o16(_ptr(packed), M, N, K, GROUP, mode, _ptr(x), _ptr(bias), _ptr(y),
-                                               _ptr(workspace), workspace.numel(), _stream()),
-           "mnnq_linear_prefill_fused_o16")
-    return y
 
 
 def mnnq_plan_debug(what: int, M: int, N: int, K: int, mode: int = MODE_W4_ZP_INT):

@@ -1,9 +1,10 @@
-"""Builds libmnnq.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libmnnq.so (HIP, gfx950 only) in-tree with hipcc, and the CPython module of its per-token calls with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +18,9 @@ SOURCES = ["mnnq_api.hip", "mnnq_pack.hip", "mnnq_quant_act.hip", "mnnq_decode.h
 # measurement helpers of bench.py: a library of their own, not part of the product's C-ABI
 BENCH_SOURCES = ["bench_kernels.hip"]
 BENCH_LIB = os.path.join(LIB_DIR, "libmnnq_bench.so")
+# the calls of a serving loop as CPython functions (host code against torch's C++ tensors), linked to libmnnq.so
+NATIVE_SOURCE = "native_binding.cpp"
+NATIVE = os.path.join(HERE, "_native.so")
 # The quantizers are fixed sequences of IEEE binary32 operations: no contraction.
 STRICT_FP = {"mnnq_pack.hip", "mnnq_quant_act.hip", "mnnq_decode.hip"}
 # MFMA results stay in architectural VGPRs so that the VALU epilogue reads them directly.
@@ -51,10 +55,39 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_native() -> str:
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    obj = os.path.join(OBJ, NATIVE_SOURCE.replace(".cpp", ".o"))
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))) if os.path.isabs(hipcc()) else "/opt/rocm"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-w", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(rocm, "include"),
+           "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for %s:\n%s\n%s" % (NATIVE_SOURCE, r.stdout, r.stderr))
+    return obj
+
+
+def _link_native(obj: str) -> None:
+    import torch
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-shared", "-o", tmp, obj, "-L", LIB_DIR, "-l:libmnnq.so", "-Wl,-rpath,$ORIGIN/lib",
+           "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
+    os.replace(tmp, NATIVE)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     os.makedirs(LIB_DIR, exist_ok=True)
     with ThreadPoolExecutor(8) as pool:
+        native_obj = pool.submit(_compile_native)
         objs = list(pool.map(_compile, SOURCES + BENCH_SOURCES))
     for lib, lib_objs in ((LIB, objs[:len(SOURCES)]), (BENCH_LIB, objs[len(SOURCES):])):
         tmp = lib + ".tmp.%d" % os.getpid()
@@ -65,6 +98,9 @@ def build(verbose: bool = False) -> str:
         os.replace(tmp, lib)
         if verbose:
             print("built", lib)
+    _link_native(native_obj.result())
+    if verbose:
+        print("built", NATIVE)
     return LIB
 
 
