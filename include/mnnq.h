@@ -86,7 +86,7 @@ typedef enum {
      * per weight: Section 5.1's rearrangement for the instruction that consumes the data) instead of two
      * 4-bit planes.  Same quantizer, same results up to the order of the fp32 sums.  Supported by the
      * pack / unpack / import calls and the W8A8 linear calls (decode, prefill, their fused and binary16
-     * forms; a few tokens at once run through the tiled GEMM); the fp16-activation calls and the
+     * forms); the fp16-activation calls and the
      * accumulator dumps return MNNQ_ERR_UNSUPPORTED for it - they read the plane form. */
     MNNQ_NATIVE_8BIT = 32
 } mnnq_mode;
@@ -183,8 +183,8 @@ int mnnq_linear_prefill_fused(const void *packed, int64_t M, int64_t N, int64_t 
  *   mnnq_linear_prefill_planes: y [M, N] from those planes, the scales sx [M] and the packed weights;
  *     mode must carry MNNQ_WITH_MATRIX_PLANE and M must exceed 32 (MNNQ_ERR_UNSUPPORTED otherwise).
  * The result is that of mnnq_linear_prefill with a workspace, bit for bit, whenever that call takes
- * the fp6 GEMM as well (it leaves shapes with very few output tiles and a long K to the int8 GEMM;
- * mnnq_plan_debug tells). */
+ * the fp6 GEMM as well (it leaves up to 48 tokens to the few-token kernels, and shapes with very few
+ * output tiles and a long K to the int8 GEMM; mnnq_plan_debug tells for the GEMMs). */
 size_t mnnq_act_planes_size(int64_t M, int64_t K, int group);
 int mnnq_act_planes(const int8_t *xq, int64_t M, int64_t K, int group, void *planes, size_t planes_bytes,
                     void *stream);

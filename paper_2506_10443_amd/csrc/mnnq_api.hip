@@ -111,6 +111,18 @@ Layout layout_for(int64_t N, int64_t K, int mode, bool out16)
     return L;
 }
 
+// Up to this many tokens the few-token kernels beat the tiled GEMMs: 64 where the call's own quantizer lays the codes
+// out for them, 48 on int8 rows (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us from token blocks, 32 / 40 us
+// from rows, 35 / 36 us tiled).
+constexpr int64_t kFewTokensBlocks = 64, kFewTokensRows = 48;
+
+bool few_tokens_wanted(int64_t M, bool blocks)
+{
+    // (a forced tile or plan, tests and tuning: the tiled GEMMs)
+    return M <= (blocks ? kFewTokensBlocks : kFewTokensRows) && !debug_option(kDbgNoSkinny) &&
+           (M <= 16 || (!debug_option(kDbgPrefillTile) && !debug_option(kDbgPrefill6Plan)));
+}
+
 // The four linear calls that exist with fp32 and with binary16 output; y points to the output array
 // of the requested kind (the kernels store through it according to Layout::out16).
 int decode_impl(const void* packed, int64_t N, int64_t K, int group, int mode, const int8_t* xq, const float* sx,
@@ -150,15 +162,15 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
     }
     // A few tokens (batched or speculative decoding) are still memory-bound: one pass over the
     // weights in the GEMV's streaming order, all tokens at once in the matrix cores.
+    if (few_tokens_wanted(M, false))
+        return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
+                             static_cast<hipStream_t>(stream));
     // With the matrix-core plane and room for the activations' planes: the GEMM on the fp6 matrix instructions.
     if (prefill6_wanted(L, M) && workspace && workspace_bytes >= prefill6_ws_bytes(M, K)) {
         if (int s = launch_act_planes(xq, M, K, workspace, static_cast<hipStream_t>(stream))) return s;
         return launch_prefill6(static_cast<const uint8_t*>(packed), L, M, workspace, sx, bias, static_cast<float*>(y),
                                nullptr, static_cast<hipStream_t>(stream));
     }
-    if (M <= 16 && !debug_option(kDbgNoSkinny) && !L.native8)   // (the byte form: a few tokens through the tiled GEMM)
-        return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, sx, bias, static_cast<float*>(y),
-                             static_cast<hipStream_t>(stream));
     return launch_prefill(static_cast<const uint8_t*>(packed), L, M, xq, sx, bias, static_cast<float*>(y), nullptr,
                           static_cast<hipStream_t>(stream));
 }
@@ -239,7 +251,21 @@ int prefill_fused_impl(const void* packed, int64_t M, int64_t N, int64_t K, int 
     if (workspace_bytes < planes + fused_prefill_ws_bytes(M, K)) planes = 0;
     int8_t* xq = static_cast<int8_t*>(workspace) + planes;
     float* sx = reinterpret_cast<float*>(xq + fused_prefill_codes_bytes(M, K));
-    if (int s = launch_quant_act(x, M, K, xq, sx, nullptr, static_cast<hipStream_t>(stream))) return s;
+    // Where one launch takes all tokens, the quantizer writes its codes in the order of the kernel that follows.
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const Layout L = layout_for(N, K, mode, out16);
+    if (quant_packed_possible(K) && prefill_fits(M, N, K, mode)) {
+        if (few_tokens_wanted(M, true)) {
+            if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
+            return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
+        }
+        if (planes && prefill6_wanted(L, M)) {
+            if (int s = launch_quant_planes(x, M, K, prefill6_row_tiles(M), workspace, sx, st)) return s;
+            return launch_prefill6(static_cast<const uint8_t*>(packed), L, M, workspace, sx, bias, static_cast<float*>(y),
+                                   nullptr, st);
+        }
+    }
+    if (int s = launch_quant_act(x, M, K, xq, sx, nullptr, st)) return s;
     return prefill_impl(packed, M, N, K, group, mode, xq, sx, bias, y, out16, planes ? workspace : nullptr, planes, stream);
 }
 

@@ -226,6 +226,11 @@ int launch_unpack(const uint8_t* packed, const Layout& L, uint8_t* q, float* sca
                   hipStream_t st);
 int launch_quant_act(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, int32_t* xsum,
                      hipStream_t st);
+// The same quantizer with the codes in the order of the kernel behind it (fused prefill): token blocks for
+// launch_skinny, activation planes for launch_prefill6 (TMp: prefill6_row_tiles(M)).  possible: the row length fits.
+bool quant_packed_possible(int64_t K);
+int launch_quant_token_blocks(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, hipStream_t st);
+int launch_quant_planes(const float* x, int64_t M, int64_t K, int TMp, void* planes, float* sx, hipStream_t st);
 int launch_decode(const uint8_t* packed, const Layout& L, const int8_t* xq, const float* sx,
                   const float* bias, float* y, hipStream_t st);
 int launch_decode_fused(const uint8_t* packed, const Layout& L, const float* x, const float* bias, float* y,
@@ -247,8 +252,9 @@ size_t prefill6_ws_bytes(int64_t M, int64_t K);
 bool prefill6_possible(const Layout& L, int64_t M);
 bool prefill6_wanted(const Layout& L, int64_t M);
 void describe_prefill6(const Layout& L, int64_t M, int32_t out[8]);
-// M <= 16 tokens sharing one pass over the weights.
-int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
+int prefill6_row_tiles(int64_t M);
+// A few tokens sharing one pass over the weights; token_blocks: xq as launch_quant_token_blocks writes it.
+int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st);
 int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x16, const float* bias,
                       float* y, hipStream_t st);

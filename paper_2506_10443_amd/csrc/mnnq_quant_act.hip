@@ -6,6 +6,7 @@
 // with a multiply by fl(1 / scale) and the division only next to a tie, which gives
 // the same integers (quant4_fast) at a fraction of the vector instructions.
 #include "mnnq_common.h"
+#include "mnnq_fp6.h"
 
 namespace mnnq {
 
@@ -110,7 +111,128 @@ __global__ __launch_bounds__(kQThreads) void quant_act_rows_kernel(const float* 
     }
 }
 
+// The fused prefill call: the quantizer writes the codes in the order in which the contraction kernel behind it reads
+// them, so that no pass over the codes rearranges them (Section 5.1) and the kernel's loads are whole lines.
+//   kTokenBlocks - the few-token kernels: [group][token block of 16][k block of 16][token][16 codes], the last block as
+//                  narrow as its tokens (M K bytes in all);
+//   kPlanes      - the fp6 GEMM: the activation planes [group][TMp][2][1536 B] (see planes_kernel).
+// A workgroup of 1024 threads quantizes R rows, each in the registers of 1024 / R threads (NV float4 per thread) between
+// the maximum and the codes, collects the codes in LDS and stores them from there: R tokens lie side by side in the
+// output, i.e. pieces of 16 R bytes.
+enum ActOrder { kTokenBlocks = 0, kPlanes = 1 };
+constexpr int kPackThreads = 1024;
+
+template <int R, int NV, int ORDER>
+__global__ __launch_bounds__(kPackThreads) void quant_pack_kernel(const float* __restrict__ x, int M, int K, int TMp,
+                                                                  uint8_t* __restrict__ out, float* __restrict__ sx)
+{
+    extern __shared__ __align__(16) uint8_t lds_codes[];   // [R][K + 16]: rows 16 bytes apart in the banks; maxima
+    constexpr int TPR = kPackThreads / R, WPR = TPR / 64;
+    const int tid = threadIdx.x;
+    const int r = __builtin_amdgcn_readfirstlane(tid / TPR), i0 = tid % TPR;
+    const int first = blockIdx.x * R;
+    const int m = first + r;
+    const int K4 = K / 4, stride = K + 16;
+    float* const s_part = reinterpret_cast<float*>(lds_codes + R * stride);
+    const float4* xr = reinterpret_cast<const float4*>(x + (int64_t)m * K);
+
+    float4 v[NV];
+    float amax = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int i = i0 + j * TPR;
+        v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (i < K4 && m < M) v[j] = xr[i];
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+        amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v[j].x), fabsf(v[j].y)), fmaxf(fabsf(v[j].z), fabsf(v[j].w))));
+    amax = wave_max_nonneg(amax);
+    if ((tid & 63) == 0) s_part[tid >> 6] = amax;
+    __syncthreads();
+    amax = s_part[r * WPR];
+#pragma unroll
+    for (int w = 1; w < WPR; ++w) amax = fmaxf(amax, s_part[r * WPR + w]);
+
+    const bool zero_row = (amax == 0.0f);
+    const float scale = zero_row ? 0.0f : amax / 127.0f;
+    if (i0 == 0 && m < M) sx[m] = scale;
+    const float inv = zero_row ? 0.0f : 1.0f / scale;
+    const float lim = quant_fast_limit(scale, inv);
+    int* codes = reinterpret_cast<int*>(lds_codes + r * stride);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int i = i0 + j * TPR;
+        int c = 0;
+        if (!zero_row) c = quant4_fast(v[j], scale, inv, lim);
+        if (i < K4) codes[i] = c;
+    }
+    __syncthreads();
+
+    if (ORDER == kTokenBlocks) {
+        const int units = R * (K / 16);      // 16 codes of one token
+        for (int u = tid; u < units; u += kPackThreads) {
+            const int rr = u % R, kk = u / R, mm = first + rr;
+            const int tb = mm >> 4, left = M - tb * 16, width = left < 16 ? left : 16;
+            const uint4 c = *reinterpret_cast<const uint4*>(lds_codes + rr * stride + kk * 16);
+            if (mm < M)
+                *reinterpret_cast<uint4*>(out + ((int64_t)(kk >> 2) * M * 4 + tb * 64 + (kk & 3) * width + (mm & 15)) * 16) = c;
+        }
+    } else {
+        const int units = R * (K / 32);      // 32 codes of one token: a lane of two blocks
+        for (int u = tid; u < units; u += kPackThreads) {
+            const int rr = u % R, kk = u / R, mm = first + rr;
+            const uint4* p = reinterpret_cast<const uint4*>(lds_codes + rr * stride + kk * 32);
+            const uint4 a = p[0], b = p[1];
+            const uint32_t q[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            uint32_t hi[8], lo[8], dh[6], dl[6];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) split_act(q[i], hi[i], lo[i]);
+            pack_fp6(hi, dh);
+            pack_fp6(lo, dl);
+            uint8_t* block = out + ((int64_t)(kk >> 1) * TMp + (mm >> 5)) * (2 * kPlaneBlockBytes);
+            const int lane = (mm & 31) + 32 * (kk & 1);
+            store_block(block, lane, dh);
+            store_block(block + kPlaneBlockBytes, lane, dl);
+        }
+    }
+}
+
+template <int R, int ORDER>
+int launch_quant_pack(const float* x, int64_t M, int64_t K, int TMp, int64_t rows, uint8_t* out, float* sx, hipStream_t st)
+{
+    const int nv = (int)((K / 4 + kPackThreads / R - 1) / (kPackThreads / R));
+    const size_t smem = (size_t)R * (K + 16) + kPackThreads / 64 * sizeof(float);
+    const unsigned grid = (unsigned)((rows + R - 1) / R);
+#define MNNQ_PACK(NV)                                                                                             \
+    if (nv <= NV) {                                                                                               \
+        static thread_local int allowed = -1;                                                                     \
+        auto kern = quant_pack_kernel<R, NV, ORDER>;                                                              \
+        if (int s = allow_large_lds(kern, smem, allowed)) return s;                                               \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kPackThreads), smem, st, x, (int)M, (int)K, TMp, out, sx);      \
+        MNNQ_HIP_TRY(hipGetLastError());                                                                          \
+        return MNNQ_OK;                                                                                           \
+    }
+    MNNQ_PACK(R) MNNQ_PACK(2 * R) MNNQ_PACK(5 * R)
+#undef MNNQ_PACK
+    return MNNQ_ERR_UNSUPPORTED;
+}
+
 }  // namespace
+
+// The row stays in registers: five float4 per thread of the whole workgroup at most.
+bool quant_packed_possible(int64_t K) { return K <= 5 * 4 * kPackThreads; }
+
+int launch_quant_token_blocks(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, hipStream_t st)
+{
+    return launch_quant_pack<1, kTokenBlocks>(x, M, K, 0, M, reinterpret_cast<uint8_t*>(xq), sx, st);
+}
+
+int launch_quant_planes(const float* x, int64_t M, int64_t K, int TMp, void* planes, float* sx, hipStream_t st)
+{
+    // (rows up to the next whole block of 32 are written as zeros; the blocks behind are not read for results)
+    return launch_quant_pack<4, kPlanes>(x, M, K, TMp, (M + 31) / 32 * 32, static_cast<uint8_t*>(planes), sx, st);
+}
 
 int launch_quant_act(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, int32_t* xsum,
                      hipStream_t st)

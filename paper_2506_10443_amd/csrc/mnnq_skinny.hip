@@ -1,26 +1,26 @@
-// A few tokens at once (M <= 16): batched or speculative decoding.  The step is
-// still memory-bound (Section 2.1), so the weights are streamed exactly once, as in
-// the one-token GEMV, and every chunk meets all M activation rows in the matrix
-// cores: one v_mfma_i32_16x16x64_i8 per quantization group contracts the 16 weight
-// rows of a row tile with up to 16 tokens, which costs the vector ALU no more than
-// the one-token dot products do.
+// A few tokens at once (batched or speculative decoding).  The step is still memory-bound (Section 2.1), so the
+// weights are streamed exactly once, as in the one-token GEMV, and every chunk meets all M activation rows in the
+// matrix cores: one v_mfma_i32_16x16x64_i8 per quantization group contracts the 16 weight rows of a row tile with up
+// to 16 tokens; up to TM = 4 blocks of 16 tokens share one unpacking of the weights.
 //
 //   y[m,n] = sx[m] * sum_g scale[n,g] * sum_{k in g} xq[m,k] * (q[n,k] - zero[n,g]) (+ bias[n])
 //
-// (float-minimum form: sx[m] * sum_g (scale * sum xq q + min * sum xq), the row sums
-// from one more MFMA with an all-ones operand.)
+// (float-minimum forms: sx[m] * sum_g (scale * sum xq q + min * sum xq), the row sums from one more matrix
+// instruction with an all-ones operand.)
 //
-// Work split as in the GEMV: a wave owns one row tile and a contiguous chunk range,
-// KSPLIT waves share a row tile and add their partial sums in a fixed order through
-// LDS.  The activations are small (M * K bytes) and stay in L2: each lane loads its A
-// operand - 16 consecutive k of token lane % 16 - straight from there (skinny_kernel),
-// or, for large layers whose 16 rows fit in LDS (K <= 4096), a persistent workgroup
-// copies them there once and shares them between all its row tiles
-// (skinny_persist_kernel).
+// Work split: the K range of a row tile is dealt to the KS waves of a workgroup, whose partial sums are added in a
+// fixed order through LDS.  Every wave meets its own part of K only, so nothing of the activations is shared
+// between the waves of a workgroup and they go straight from L2 into registers:
+//   resident form (few_resident_kernel): a wave's part is at most NCH chunks; its A operands stay in registers while
+//     the workgroup walks over row tiles (grid-stride), so that the loop streams weights and nothing else.  The
+//     registers of a chunk are refilled with the same chunk of the next row tile as soon as it has been unpacked,
+//     without a branch: only then does the compiler wait by count, with the refills in flight.
+//   streaming form (few_stream_kernel): longer rows; weights and activations of a chunk are requested together, DEPTH
+//     chunks ahead.
 //
 // MFMA lane mapping (A: 16 x 64 tokens x k, B: 64 x 16 k x weight rows, D: 16 x 16):
-//   A: lane l holds token l % 16, k block l / 16;  B: lane l holds weight row l % 16,
-//   the same k block - exactly the lane's 8 bytes of the chunk, unpacked;
+//   A: lane l holds token l % 16, k block l / 16;  B: lane l holds weight row l % 16, the same k block - exactly the
+//   lane's 8 bytes of the chunk, unpacked (16 bytes in the byte form of int8 weights, as they are);
 //   D: lane l holds weight row l % 16, tokens 4 (l / 16) + r, r = 0..3.
 #include "mnnq_common.h"
 
@@ -30,369 +30,452 @@ namespace mnnq {
 
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-struct SkinnyRegs {
-    u32x4 w;       // 32 codes: .x,.y group 2c ; .z,.w group 2c+1
-    float2 s;      // scales of the lane's weight row for both groups
-    uint32_t z;    // zero points of both groups                       (integer zero point form)
-    float2 mn;     // group minima of both groups                      (float minimum form)
-    v4i xa, xb;    // the lane's 16 activations of group 2c and of group 2c+1
+enum Form { kZp = 0, kMin = 1, kBytes = 2 };   // integer zero point; float minimum; int8 weights as bytes
+
+template <int FORM>
+struct WeightRegs {
+    v4i w[FORM == kBytes ? 2 : 1];   // .x,.y group 2c, .z,.w group 2c + 1; byte form: one register quad per group
+    v2f s;                           // scales of the lane's weight row for both groups
+    int z;                           // zero points of both groups of two weight rows, the lane's and its neighbour (kZp)
+    v2f mn;                          // group minima of both groups                    (kMin, kBytes)
+};
+
+// Memory is read through buffer descriptors whose sizes are exact: a chunk that is not the wave's own, a row tile past
+// the matrix, a token past M or the missing half of an odd row lies outside and arrives as zeros without a branch and
+// without traffic.  (Plain loads in a loop that refills its registers are no alternative: the compiler moves a load
+// whose value crosses the back edge down to its use.)
+constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
+constexpr int kOutOfRange = 0x7ffffff0;   // a byte offset beyond every buffer
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufFlags);
+}
+
+// The chunks of one row tile (an empty buffer past the last one).
+template <int FORM>
+struct TileBuffers {
+    __amdgpu_buffer_rsrc_t w, s, z;
+    __device__ __forceinline__ TileBuffers(const uint8_t* __restrict__ packed, const Layout& L, int64_t tile)
+    {
+        const bool have = tile < L.T;
+        const int64_t first = have ? tile * L.C : 0, n = have ? L.C : 0;   // (K <= 2^24: under 2^28 bytes)
+        constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = FORM == kZp ? 32 : 128;
+        w = rsrc(packed + first * WB, n * WB);
+        s = rsrc(packed + L.scales_off() + first * 128, n * 128);
+        z = rsrc(packed + L.zeros_off() + first * ZB, n * ZB);
+    }
+    __device__ __forceinline__ WeightRegs<FORM> load(int c, int lane, int row) const   // c: chunk (uniform)
+    {
+        WeightRegs<FORM> r;
+        const int off = __builtin_amdgcn_readfirstlane(c);
+        // (aux 2: the weights pass once and need not stay in the caches)
+        r.w[0] = __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16, off * (FORM == kBytes ? 2048 : 1024), 2);
+        if (FORM == kBytes)
+            r.w[FORM == kBytes ? 1 : 0] = __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16 + 1024, off * 2048, 2);
+        r.s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(s, row * 8, off * 128, 0));
+        if (FORM == kZp) r.z = __builtin_amdgcn_raw_buffer_load_b32(z, (row >> 1) * 4, off * 32, 0);
+        else r.mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(z, row * 8, off * 128, 0));
+        return r;
+    }
 };
 
 // q - z per byte for four codes in the bytes of v (c4 = 0x80 - z in every byte).
-__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4)
-{
-    return (int)((v + c4) ^ 0x80808080u);
-}
+__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
 
-template <bool MINF>
-__device__ __forceinline__ v4i unpack_group(uint32_t w0, uint32_t w1, uint32_t z)
+template <int FORM>
+__device__ __forceinline__ v4i unpack_group(const WeightRegs<FORM>& r, int h, uint32_t zsel)
 {
-    v4i b;
-    if (MINF) {
-        b.x = (int)(w0 & 0x0f0f0f0fu);
-        b.y = (int)((w0 >> 4) & 0x0f0f0f0fu);
-        b.z = (int)(w1 & 0x0f0f0f0fu);
-        b.w = (int)((w1 >> 4) & 0x0f0f0f0fu);
-    } else {
-        const uint32_t c4 = 0x80808080u - z * 0x01010101u;
-        b.x = sub_zero(w0 & 0x0f0f0f0fu, c4);
-        b.y = sub_zero((w0 >> 4) & 0x0f0f0f0fu, c4);
-        b.z = sub_zero(w1 & 0x0f0f0f0fu, c4);
-        b.w = sub_zero((w1 >> 4) & 0x0f0f0f0fu, c4);
+    if (FORM == kBytes) {
+        return r.w[FORM == kBytes ? h : 0];
     }
-    return b;
+    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
+    const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
+    const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
+    if (FORM == kMin) return v4i{(int)n0, (int)n1, (int)n2, (int)n3};
+    // 0x80 - zero point in every byte; zsel picks the byte of the lane's row and first group
+    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, h ? zsel + 0x01010101u : zsel);
+    return v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
 }
 
-template <int WAVES, int KSPLIT, int UNROLL, bool PREFETCH, bool MINF>
-__global__ __launch_bounds__(WAVES * 64) void skinny_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                            const int8_t* __restrict__ xq,
-                                                            const float* __restrict__ sx,
-                                                            const float* __restrict__ bias,
-                                                            float* __restrict__ y)
-{
-    __shared__ float lds_part[WAVES * 4 * 64];   // [wave][r][lane]
-    const int64_t C = L.C;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: addresses start in scalar registers
-    const int row = lane & 15;     // weight row of the B operand and of the results; token of the A operand
-    const int kb = lane >> 4;
-    constexpr int TILES_PER_WG = WAVES / KSPLIT;
-    const int64_t tile = (int64_t)blockIdx.x * TILES_PER_WG + wave / KSPLIT;
-    const int ks = wave % KSPLIT;
-    const bool active = tile < L.T;
-    const int64_t c0 = C * ks / KSPLIT;
-    const int64_t c1 = C * (ks + 1) / KSPLIT;
-    const u32x4* wp = reinterpret_cast<const u32x4*>(packed) + (tile * C + c0) * 64 + lane;
-    const float2* sp = reinterpret_cast<const float2*>(packed + L.scales_off()) + (tile * C + c0) * 16 + row;
-    const void* zp = MINF ? static_cast<const void*>(reinterpret_cast<const float2*>(packed + L.zeros_off()) +
-                                                     (tile * C + c0) * 16 + row)
-                          : static_cast<const void*>(reinterpret_cast<const uint16_t*>(packed + L.zeros_off()) +
-                                                     (tile * C + c0) * 16 + row);
-    const int64_t n_chunks = active ? (c1 - c0) : 0;
-    // Tokens past M repeat the last one; their results are not stored.
-    const int8_t* xrow = xq + (int64_t)(row < M ? row : M - 1) * L.Kx + kb * 16;
-    const int64_t Cx = L.Cx;      // chunk c of the packed axis meets chunk c % Cx of the activation row
-    const bool odd_tail = (L.G & 1) != 0;   // the last chunk of a row holds one real group only
+// float(I) from a matrix instruction that accumulated on the bit pattern of 1.5 * 2^23: the register holds
+// 0x4B400000 + I, i.e. the float 12582912 + I (|I| < 2^22), and one exact subtraction - full rate, unlike a convert -
+// leaves I.
+constexpr int kMagicBits = 0x4B400000;
+__device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
 
-    auto load = [&](int64_t i) {
-        SkinnyRegs r;
-        const int64_t c = c0 + i;
-        r.w = __builtin_nontemporal_load(wp + i * 64);
-        r.s = sp[i * 16];
-        if (MINF) {
-            r.mn = static_cast<const float2*>(zp)[i * 16];
-            r.z = 0;
-        } else {
-            r.z = static_cast<const uint16_t*>(zp)[i * 16];
-            r.mn = make_float2(0.0f, 0.0f);
+// The vector side runs one group behind the matrix side: while a group's matrix instructions execute (a result is
+// readable 32 cycles after its issue, and at two waves per SIMD nothing else covers that), the results of the group
+// before are scaled and added.
+template <int TM, int FORM>
+struct Pending {
+    v4i d[TM], xs[FORM == kZp ? 1 : TM];
+    float s, mn;
+    __device__ __forceinline__ Pending() : s(0.0f), mn(0.0f)   // (nothing yet: zeros, whatever the form makes of them)
+    {
+        const int z = FORM == kBytes ? 0 : kMagicBits;
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            d[t] = v4i{z, z, z, z};
+            if (FORM != kZp) xs[t] = v4i{0, 0, 0, 0};
         }
-        r.xa = *reinterpret_cast<const v4i*>(xrow + (c % Cx) * 128);
-        r.xb = (odd_tail && c == C - 1) ? v4i{0, 0, 0, 0} : *reinterpret_cast<const v4i*>(xrow + (c % Cx) * 128 + 64);
-        return r;
-    };
-
-    SkinnyRegs cur[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        if (u < n_chunks) cur[u] = load(u);
-        else cur[u] = SkinnyRegs{};
     }
-
-    const v4i zero = {0, 0, 0, 0};
-    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-    float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int64_t i = 0; i < n_chunks; i += UNROLL) {
-        SkinnyRegs nxt[PREFETCH ? UNROLL : 1];
-        if (PREFETCH) {
+    __device__ __forceinline__ void add(int t, float (&acc)[TM][4]) const
+    {
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                if (i + UNROLL + u < n_chunks) nxt[u] = load(i + UNROLL + u);
-                else nxt[u] = SkinnyRegs{};
+        for (int rr = 0; rr < 4; ++rr) {
+            if (FORM == kZp) {
+                acc[t][rr] = fmaf(s, from_magic(d[t][rr]), acc[t][rr]);
+            } else {
+                const int x = xs[FORM == kZp ? 0 : t][rr];
+                // byte form: sum xq q8 = D + 128 xs as an integer (below 2^22) before it meets the step
+                const float i = FORM == kMin ? from_magic(d[t][rr]) : (float)(d[t][rr] + (x << 7));
+                acc[t][rr] = fmaf(s, i, acc[t][rr]);
+                acc[t][rr] = fmaf(mn, (float)x, acc[t][rr]);
             }
         }
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            if (i + u < n_chunks) {
-                const SkinnyRegs& r = cur[u];
-                const v4i xa = r.xa, xb = r.xb;
-                const v4i b0 = unpack_group<MINF>(r.w.x, r.w.y, r.z & 0xffu);
-                const v4i b1 = unpack_group<MINF>(r.w.z, r.w.w, r.z >> 8);
-                const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, b0, zero, 0, 0, 0);
-                const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb, b1, zero, 0, 0, 0);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    acc[rr] = fmaf(r.s.x, (float)d0[rr], acc[rr]);
-                    acc[rr] = fmaf(r.s.y, (float)d1[rr], acc[rr]);
-                }
-                if (MINF) {
-                    const v4i x0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, ones, zero, 0, 0, 0);
-                    const v4i x1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb, ones, zero, 0, 0, 0);
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        acc[rr] = fmaf(r.mn.x, (float)x0[rr], acc[rr]);
-                        acc[rr] = fmaf(r.mn.y, (float)x1[rr], acc[rr]);
-                    }
-                }
-            }
-        }
-        if (!PREFETCH) break;   // the host guarantees n_chunks <= UNROLL
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) cur[u] = nxt[u];
     }
-
-    // Sum over the KSPLIT waves of the row tile, in a fixed order.
-    if (KSPLIT > 1) {
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) lds_part[(wave * 4 + rr) * 64 + lane] = acc[rr];
-        __syncthreads();
-        if (ks != 0) return;
-#pragma unroll
-        for (int j = 1; j < KSPLIT; ++j)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) acc[rr] += lds_part[((wave + j) * 4 + rr) * 64 + lane];
-    }
-    if (!active) return;
-    const int64_t n = tile * kTileN + row;
-    const float b = bias ? bias[n] : 0.0f;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int m = kb * 4 + rr;
-        if (m < M) store_out(y, (int64_t)m * L.N + n, fmaf(acc[rr], sx[m], b), L.out16);
-    }
-}
-
-// Large layers with rows of up to 4096 values: a persistent workgroup of 8 waves copies the
-// 16 token rows into LDS once, in the order the A operand is read, and then walks over its
-// share of the row tiles (8 / KSPLIT at a time).  Every wave's chunk range (<= 8 chunks) is
-// held in registers; as soon as a chunk has been consumed, the same chunk of the next step is
-// fetched into its registers, so a wave keeps its whole range in flight all the time.
-struct WeightRegs {
-    u32x4 w;
-    float2 s;
-    uint32_t z;
-    float2 mn;
 };
 
-template <int KSPLIT, bool MINF>
-__global__ __launch_bounds__(512, 2) void skinny_persist_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                             const int8_t* __restrict__ xq,
-                                                             const float* __restrict__ sx,
-                                                             const float* __restrict__ bias,
-                                                             float* __restrict__ y)
+// One chunk: both groups of 16 weight rows against TM blocks of 16 tokens.
+template <int TM, int FORM>
+__device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const v4i (&a)[2][TM], uint32_t zsel,
+                                         Pending<TM, FORM>& p, float (&acc)[TM][4])
 {
-    constexpr int WAVES = 8, UNROLL = 8;
-    extern __shared__ __align__(16) uint8_t smem[];
-    float* lds_part = reinterpret_cast<float*>(smem);                                 // [wave][r][lane]
-    v4i* lds_a = reinterpret_cast<v4i*>(smem + WAVES * 4 * 64 * 4);                   // [C * 8 units][16 tokens]
-    const int64_t C = L.C;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: addresses start in scalar registers
-    const int row = lane & 15;
-    const int kb = lane >> 4;
-    constexpr int TILES_PER_STEP = WAVES / KSPLIT;
-    const int ks = wave % KSPLIT;
-    const int64_t c0 = C * ks / KSPLIT;
-    const int64_t c1 = C * (ks + 1) / KSPLIT;
-    const int n_own = (int)(c1 - c0);
-    const int64_t n_steps = (L.T + TILES_PER_STEP - 1) / TILES_PER_STEP;
-
-    // One chunk of this wave's range for the given step (nothing past the last step / tile).
-    auto load_chunk = [&](int64_t step, int u) {
-        WeightRegs r{};
-        const int64_t tile = step * TILES_PER_STEP + wave / KSPLIT;
-        if (step < n_steps && tile < L.T && u < n_own) {
-            const int64_t ci = (tile * C + c0 + u);
-            r.w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(packed) + ci * 64 + lane);
-            r.s = (reinterpret_cast<const float2*>(packed + L.scales_off()) + ci * 16)[row];
-            if (MINF) r.mn = (reinterpret_cast<const float2*>(packed + L.zeros_off()) + ci * 16)[row];
-            else r.z = (reinterpret_cast<const uint16_t*>(packed + L.zeros_off()) + ci * 16)[row];
-        }
-        return r;
-    };
-
-    int64_t step = blockIdx.x;
-    WeightRegs cur[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) cur[u] = load_chunk(step, u);
-
-    // The first weights are in flight; copy the token rows (tokens past M repeat the last one,
-    // k past K is zero) in units of 16 bytes: unit (ku, m) = k 16 ku .. 16 ku + 15 of token m,
-    // stored at index ku * 16 + m.
-    {
-        const int units = (int)C * 8 * 16;
-        const int valid_ku = (int)(L.K / 16);
-        const int row_ku = (int)(L.Kx / 16);
-        for (int u = tid; u < units; u += WAVES * 64) {
-            const int m = u & 15, ku = u >> 4;
-            v4i v = {0, 0, 0, 0};
-            if (ku < valid_ku)
-                v = *reinterpret_cast<const v4i*>(xq + (int64_t)(m < M ? m : M - 1) * L.Kx + (ku % row_ku) * 16);
-            lds_a[u] = v;
-        }
-    }
-    __syncthreads();
-
+    const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
     const v4i zero = {0, 0, 0, 0};
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-    // All waves of a workgroup share `step`, so the workgroup-wide barriers below are uniform.
-    for (; step < n_steps; step += gridDim.x) {
-        const int64_t tile = step * TILES_PER_STEP + wave / KSPLIT;
-        const bool active = tile < L.T;
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const WeightRegs r = cur[u];
-            // the registers of this chunk are free: fetch the same chunk of the next step into them
-            cur[u] = load_chunk(step + gridDim.x, u);
-            if (active && u < n_own) {
-                const int64_t c = c0 + u;
-                const v4i xa = lds_a[((c * 8 + kb) << 4) + row];
-                const v4i xb = lds_a[((c * 8 + 4 + kb) << 4) + row];
-                const v4i b0 = unpack_group<MINF>(r.w.x, r.w.y, r.z & 0xffu);
-                const v4i b1 = unpack_group<MINF>(r.w.z, r.w.w, r.z >> 8);
-                const v4i d0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, b0, zero, 0, 0, 0);
-                const v4i d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb, b1, zero, 0, 0, 0);
+    for (int h = 0; h < 2; ++h) {
+        const v4i b = unpack_group<FORM>(r, h, zsel);
+        Pending<TM, FORM> n;
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    acc[rr] = fmaf(r.s.x, (float)d0[rr], acc[rr]);
-                    acc[rr] = fmaf(r.s.y, (float)d1[rr], acc[rr]);
-                }
-                if (MINF) {
-                    const v4i x0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa, ones, zero, 0, 0, 0);
-                    const v4i x1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(xb, ones, zero, 0, 0, 0);
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        acc[rr] = fmaf(r.mn.x, (float)x0[rr], acc[rr]);
-                        acc[rr] = fmaf(r.mn.y, (float)x1[rr], acc[rr]);
-                    }
-                }
-            }
+        for (int t = 0; t < TM; ++t) {
+            n.d[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t], b, FORM == kBytes ? zero : magic, 0, 0, 0);
+            if (FORM != kZp) n.xs[FORM == kZp ? 0 : t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t], ones, zero, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            p.add(t, acc);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (KSPLIT > 1) {
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) lds_part[(wave * 4 + rr) * 64 + lane] = acc[rr];
-            __syncthreads();
-            if (ks == 0) {
-#pragma unroll
-                for (int j = 1; j < KSPLIT; ++j)
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) acc[rr] += lds_part[((wave + j) * 4 + rr) * 64 + lane];
-            }
-            __syncthreads();   // the partial sums are read before the next round overwrites them
-        }
-        if (active && ks == 0) {
-            const int64_t n = tile * kTileN + row;
-            const float b = bias ? bias[n] : 0.0f;
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int m = kb * 4 + rr;
-                if (m < M) store_out(y, (int64_t)m * L.N + n, fmaf(acc[rr], sx[m], b), L.out16);
-            }
-        }
+        n.s = h ? r.s.y : r.s.x;
+        if (FORM != kZp) n.mn = h ? r.mn.y : r.mn.x;
+        p = n;
     }
 }
 
-template <int KSPLIT>
-int launch_persist(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, const float* sx, const float* bias,
-                   float* y, hipStream_t st)
-{
-    constexpr int tiles_per_step = 8 / KSPLIT;
-    const int64_t n_steps = (L.T + tiles_per_step - 1) / tiles_per_step;
-    // Two workgroups per CU (LDS: two copies of the activations; registers: 16 waves).
-    const int64_t grid = n_steps < 2 * (int64_t)num_cus() ? n_steps : 2 * (int64_t)num_cus();
-    const size_t smem = (size_t)8 * 4 * 64 * 4 + (size_t)L.C * 8 * 16 * 16;
-    auto launch = [&](auto kern) -> int {
-        if (smem > 64 * 1024) {
-            // More than 64 KiB of dynamic LDS has to be allowed once per kernel and device.
-            static thread_local int allowed_dev = -1;
-            int dev = 0;
-            MNNQ_HIP_TRY(hipGetDevice(&dev));
-            if (allowed_dev != dev) {
-                MNNQ_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024));
-                allowed_dev = dev;
+// The activations of one slice of tokens.  A operand of group g, token block t: 16 consecutive k of one token per lane,
+// from int8 rows or from the token blocks the fused call's quantizer writes ([group][block of 16 tokens][k block][token],
+// the last block as narrow as its tokens): there a wave reads one contiguous piece per group and block, and the
+// few-token kernels, which are bound by this traffic from L2 where K is long, gain a third (48 tokens, 3584 x 18944:
+// 32 -> 22 us).  Chunk c of the packed axis meets chunk c % Cx of the row; an odd row's last chunk has one group only.
+template <int TM>
+struct Acts {
+    __amdgpu_buffer_rsrc_t x;
+    int voff[TM];
+    int Cx, odd_last, step;     // step: bytes from group to group
+    __device__ __forceinline__ Acts(const int8_t* __restrict__ xq, const Layout& L, int M, bool blocks, int m0, int lane)
+        : x(rsrc(xq, (int64_t)M * L.Kx)), Cx((int)L.Cx), odd_last((L.G & 1) ? (int)L.C - 1 : -1), step(blocks ? M * 64 : 64)
+    {
+        const int kb = lane >> 4;
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            const int first = m0 + t * 16, left = M - first, width = left < 16 ? left : 16, m = lane & 15;
+            const int at = blocks ? first * 64 + (kb * width + m) * 16 : (first + m) * (int)L.Kx + kb * 16;
+            voff[t] = m < width ? at : kOutOfRange;      // (tokens past M: zeros, no traffic)
+        }
+    }
+    __device__ __forceinline__ void load(v4i (&a)[2][TM], int c, bool have) const
+    {
+        const int cx = c >= Cx ? c - Cx : c;
+        const int o0 = __builtin_amdgcn_readfirstlane(have ? 2 * cx * step : kOutOfRange);
+        const int o1 = __builtin_amdgcn_readfirstlane(have && c != odd_last ? (2 * cx + 1) * step : kOutOfRange);
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            a[0][t] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t], o0, 0);
+            a[1][t] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t], o1, 0);
+        }
+    }
+};
+
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Sum of the KS waves' partial results of a row tile and its output, token block t by wave (t + turn) % KS - the turn
+// passes on from tile to tile, so that the same waves are not always the late ones.
+template <int TM>
+struct Output {
+    __amdgpu_buffer_rsrc_t y;
+    const float* sx;     // scales of the slice's tokens, in LDS
+    int ks, KS, lane, m0, N;
+    bool out16;
+    __device__ __forceinline__ Output(float* __restrict__ yp, const float* lds_sx, const Layout& L, int M, int m0_, int ks_,
+                                      int KS_, int lane_)
+        : y(rsrc(yp, (int64_t)M * L.N * (L.out16 ? 2 : 4))), sx(lds_sx), ks(ks_), KS(KS_), lane(lane_), m0(m0_),
+          N((int)L.N), out16(L.out16)
+    {
+    }
+    // Requests the slice's scales (first wave; a lane per token, tokens past M: zeros), to be stored before a barrier.
+    static __device__ __forceinline__ float fetch_sx(const float* __restrict__ sxp, int M, int m0, int lane)
+    {
+        return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc(sxp, (int64_t)M * 4), (m0 + lane) * 4, 0, 0));
+    }
+    __device__ __forceinline__ void store(const float4* part, int turn, int64_t tile, float bias) const
+    {
+        for (int t = ks >= turn ? ks - turn : ks - turn + KS; t < TM; t += KS) {
+            float4 v = part[t * 64 + lane];
+            for (int j = 1; j < KS; ++j) {
+                const float4 p = part[(j * TM + t) * 64 + lane];
+                v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w;
+            }
+            const float o[4] = {v.x, v.y, v.z, v.w};
+            const int mt = t * 16 + (lane >> 4) * 4;
+            const float4 s4 = *reinterpret_cast<const float4*>(sx + mt);
+            const float s[4] = {s4.x, s4.y, s4.z, s4.w};
+            const int n = (int)tile * kTileN + (lane & 15);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float f = fmaf(o[r], s[r], bias);
+                const int at = (m0 + mt + r) * N + n;   // tokens past M: past the end of y, dropped
+                if (out16) {
+                    const _Float16 h = (_Float16)f;
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, h), y, at * 2, 0, 0);
+                } else {
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(f), y, at * 4, 0, 0);
+                }
             }
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), smem, st, packed, L, M, xq, sx, bias, y);
-        MNNQ_HIP_TRY(hipGetLastError());
-        return MNNQ_OK;
+    }
+};
+
+template <int TM, int NCH, int FORM, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
+                                                                const int8_t* __restrict__ xq, bool blocks,
+                                                                const float* __restrict__ sx,
+                                                                const float* __restrict__ bias, float* __restrict__ y)
+{
+    extern __shared__ __align__(16) float4 lds_part[];   // [2][KS][TM][64], then the tokens' scales
+    const int KS = blockDim.x >> 6;
+    float* const lds_sx = reinterpret_cast<float*>(lds_part + 2 * KS * TM * 64);
+    const int lane = threadIdx.x & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15;
+    const uint32_t zsel = (row & 1) * 0x02020202u;
+    const int C = (int)L.C;
+    const int c0 = C * ks / KS, own = C * (ks + 1) / KS - c0;   // 1 .. NCH chunks
+    const int m0 = blockIdx.y * (16 * TM);
+
+    const Output<TM> out(y, lds_sx, L, M, m0, ks, KS, lane);
+    const float sx_own = out.fetch_sx(sx, M, m0, lane);
+    const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
+    const Acts<TM> acts(xq, L, M, blocks, m0, lane);
+    v4i a[NCH][2][TM];
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) acts.load(a[u], c0 + u, u < own);
+
+    int64_t tile = blockIdx.x;
+    WeightRegs<FORM> cur[NCH];
+    const TileBuffers<FORM> first(packed, L, tile);
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) {
+        cur[u] = first.load(u < own ? c0 + u : C, lane, row);
+        __builtin_amdgcn_sched_barrier(0);      // (the order of the loop: the waits are counts)
+    }
+    auto bias_of = [&](int64_t t) {
+        return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, ((int)t * kTileN + row) * 4, 0, 0));
     };
-    if (L.minf) return launch(skinny_persist_kernel<KSPLIT, true>);
-    return launch(skinny_persist_kernel<KSPLIT, false>);
+    float b = bias_of(tile);
+
+    int buf = 0, turn = 0;
+    do {   // (the grid has no more workgroups than there are row tiles)
+        const float b_next = bias_of(tile + gridDim.x);
+        const TileBuffers<FORM> next(packed, L, tile + gridDim.x);
+        float acc[TM][4];
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) acc[t][rr] = 0.0f;
+        Pending<TM, FORM> pend;
+#pragma unroll
+        for (int u = 0; u < NCH; ++u) {
+            contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);     // (a chunk that is not the wave's own is zero)
+            cur[u] = next.load(u < own ? c0 + u : C, lane, row);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        float4* part = lds_part + buf * KS * TM * 64;
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            pend.add(t, acc);
+            part[(ks * TM + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+        }
+        if (ks == 0) lds_sx[lane] = sx_own;
+        // One barrier per row tile: the buffer written now was read two tiles ago, before the barrier in between.
+        lds_barrier();
+        out.store(part, turn, tile, b);
+        turn = turn + TM < KS ? turn + TM : 0;
+        b = b_next;
+        buf ^= 1;
+        tile += gridDim.x;
+    } while (tile < L.T);
 }
 
-template <int WAVES, int KSPLIT, int UNROLL, bool PREFETCH>
-int launch_cfg(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, const float* sx, const float* bias,
-               float* y, hipStream_t st)
+template <int TM, int DEPTH, int FORM, int MAXW>
+__global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
+                                                              const int8_t* __restrict__ xq, bool blocks,
+                                                              const float* __restrict__ sx,
+                                                              const float* __restrict__ bias, float* __restrict__ y)
 {
-    constexpr int tiles_per_wg = WAVES / KSPLIT;
-    const int64_t blocks = (L.T + tiles_per_wg - 1) / tiles_per_wg;
-    if (L.minf)
-        hipLaunchKernelGGL((skinny_kernel<WAVES, KSPLIT, UNROLL, PREFETCH, true>), dim3((unsigned)blocks),
-                           dim3(WAVES * 64), 0, st, packed, L, M, xq, sx, bias, y);
-    else
-        hipLaunchKernelGGL((skinny_kernel<WAVES, KSPLIT, UNROLL, PREFETCH, false>), dim3((unsigned)blocks),
-                           dim3(WAVES * 64), 0, st, packed, L, M, xq, sx, bias, y);
+    extern __shared__ __align__(16) float4 lds_part[];   // [KS][TM][64], then the tokens' scales
+    const int KS = blockDim.x >> 6;
+    float* const lds_sx = reinterpret_cast<float*>(lds_part + KS * TM * 64);
+    const int lane = threadIdx.x & 63;
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15;
+    const uint32_t zsel = (row & 1) * 0x02020202u;
+    const int C = (int)L.C;
+    const int c0 = C * ks / KS, c1 = C * (ks + 1) / KS;   // at least one chunk
+    const int m0 = blockIdx.y * (16 * TM);
+    const int64_t tile = blockIdx.x;
+
+    const Output<TM> out(y, lds_sx, L, M, m0, ks, KS, lane);
+    const float sx_own = out.fetch_sx(sx, M, m0, lane);
+    const float b = __int_as_float(
+        __builtin_amdgcn_raw_buffer_load_b32(rsrc(bias, bias ? L.N * 4 : 0), ((int)tile * kTileN + row) * 4, 0, 0));
+    const Acts<TM> acts(xq, L, M, blocks, m0, lane);
+    const TileBuffers<FORM> weights(packed, L, tile);
+    v4i a[DEPTH][2][TM];
+    WeightRegs<FORM> cur[DEPTH];
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+        const int c = c0 + u;
+        cur[u] = weights.load(c < c1 ? c : C, lane, row);
+        acts.load(a[u], c, c < c1);
+        __builtin_amdgcn_sched_barrier(0);      // (the order of the loop: the waits are counts)
+    }
+    float acc[TM][4];
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) acc[t][rr] = 0.0f;
+    Pending<TM, FORM> pend;
+    int c = c0;
+    do {
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) {
+            contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);     // (past the wave's chunks everything is zero)
+            const int next = c + u + DEPTH;
+            cur[u] = weights.load(next < c1 ? next : C, lane, row);
+            acts.load(a[u], next, next < c1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        c += DEPTH;
+    } while (c < c1);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+        pend.add(t, acc);
+        lds_part[(ks * TM + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    }
+    if (ks == 0) lds_sx[lane] = sx_own;
+    lds_barrier();
+    out.store(lds_part, 0, tile, b);
+}
+
+struct FewPlan {
+    bool resident;
+    int nch;     // chunks of a wave held in registers (resident form)
+    int ks;      // waves of a workgroup
+};
+
+// Waves a CU holds, by registers: sixteen (128 registers each) or eight (256).
+constexpr int resident_waves(int tm, int nch, int form)
+{
+    return tm == 1 || (nch == 2 && (tm == 2 || (tm == 3 && form == kZp))) ? 16 : 8;
+}
+constexpr int stream_waves(int tm) { return tm == 1 ? 16 : 8; }
+
+FewPlan few_plan(const Layout& L, int tm, int form)
+{
+    FewPlan p{};
+    const int64_t C = L.C;
+    auto fits = [&](int nch) { return (C + nch - 1) / nch <= resident_waves(tm, nch, form); };
+    // short rows of layers with few row tiles: two chunks per wave, twice the waves
+    int nch = 4;
+    if (L.T <= 2 * (int64_t)num_cus() && (C + 1) / 2 <= 8) nch = 2;
+    if (const char* e = debug_option(kDbgDecodeWaves)) { const int v = atoi(e); if ((v == 2 || v == 4) && fits(v)) nch = v; }
+    int64_t ks = (C + nch - 1) / nch;
+    p.resident = fits(nch);
+    if (const char* e = debug_option(kDbgSkinnyStaged)) p.resident = p.resident && e[0] == '1';   // tests
+    if (!p.resident) {
+        ks = stream_waves(tm);
+        if (C < ks) ks = C;
+    }
+    if (const char* e = debug_option(kDbgDecodeKsplit)) {   // tests and tuning: force the split
+        const int v = atoi(e);
+        if (v >= 1 && v <= stream_waves(tm) && v <= C) {
+            ks = v;
+            if ((C + v - 1) / v > 4) p.resident = false;
+            else nch = 4;
+        }
+    }
+    p.nch = nch;
+    p.ks = (int)ks;
+    return p;
+}
+
+template <int TM, int FORM>
+int launch_form(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, bool blocks, const float* sx, const float* bias,
+                float* y, hipStream_t st)
+{
+    const FewPlan p = few_plan(L, TM, FORM);
+    const unsigned slices = (unsigned)((M + 16 * TM - 1) / (16 * TM));
+    if (p.resident) {
+        // as many workgroups as the chip holds at once
+        const int per_cu = resident_waves(TM, p.nch, FORM) / p.ks;
+        const int64_t slots = (int64_t)num_cus() * (per_cu > 0 ? per_cu : 1);
+        const int64_t grid = L.T < slots ? L.T : slots;
+        const size_t smem = (size_t)2 * p.ks * TM * 64 * 16 + 256;
+        static thread_local int allowed[2] = {-1, -1};
+        auto go = [&](auto kern, int& dev) -> int {
+            if (int s = allow_large_lds(kern, smem, dev)) return s;
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid, slices), dim3(64 * p.ks), smem, st, packed, L, M, xq, blocks, sx, bias, y);
+            MNNQ_HIP_TRY(hipGetLastError());
+            return MNNQ_OK;
+        };
+        if (p.nch == 2) return go(few_resident_kernel<TM, 2, FORM, resident_waves(TM, 2, FORM)>, allowed[0]);
+        return go(few_resident_kernel<TM, 4, FORM, resident_waves(TM, 4, FORM)>, allowed[1]);
+    }
+    constexpr int DEPTH = TM <= 3 ? 4 : 3;   // (8 TM + 7 registers per chunk in flight; more would spill)
+    const size_t smem = (size_t)p.ks * TM * 64 * 16 + 256;
+    hipLaunchKernelGGL((few_stream_kernel<TM, DEPTH, FORM, stream_waves(TM)>), dim3((unsigned)L.T, slices), dim3(64 * p.ks),
+                       smem, st, packed, L, M, xq, blocks, sx, bias, y);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
 }
 
+template <int FORM>
+int launch_tokens(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, bool blocks, const float* sx, const float* bias,
+                  float* y, hipStream_t st)
+{
+    // token blocks per workgroup: all of them up to 64 tokens, beyond that an even share of at most four
+    const int n = (M + 15) / 16;
+    const int slices = (n + 3) / 4;
+    switch ((n + slices - 1) / slices) {
+        case 1: return launch_form<1, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
+        case 2: return launch_form<2, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
+        case 3: return launch_form<3, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
+        default: return launch_form<4, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
+    }
+}
+
 }  // namespace
 
-// The smallest number of waves per row tile (up to 8) for which a wave's chunk range fits in
-// its registers, so that all loads are issued at once; longer rows use a prefetching loop.
-// Large layers with rows of up to 4096 values take the persistent variant, which shares one
-// LDS copy of the activations between all the row tiles a workgroup processes.
-int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
+int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st)
 {
-    // At most 8 waves per row tile: without staging a chunk costs 17 registers (weights and
-    // activations), which a workgroup of 16 waves could not hold for 8 chunks.
-    int ks = 1;
-    while (ks < 8 && (L.C + ks - 1) / ks > 8) ks *= 2;
-    if (const char* e = debug_option(kDbgDecodeKsplit)) {   // tests and tuning: force the split
-        const int v = atoi(e);
-        if (v == 1 || v == 2 || v == 4 || v == 8 || v == 16) ks = v > 8 ? 8 : v;
-    }
-    const bool prefetch = (L.C + ks - 1) / ks > 8;
-    // Staging pays once the layer is large enough to be bandwidth bound (measured: above ~16 MiB).
-    bool staged = L.C <= 32 && !prefetch && L.T * L.C >= 16384;
-    if (const char* e = debug_option(kDbgSkinnyStaged)) staged = L.C <= 32 && !prefetch && e[0] == '1';   // tests
-    const int m = (int)M;
-#define MNNQ_CFG(W, K)                                                                                 \
-    if (ks == K) {                                                                                     \
-        if (staged) return launch_persist<K>(packed, L, m, xq, sx, bias, y, st);                       \
-        return prefetch ? launch_cfg<W, K, 4, true>(packed, L, m, xq, sx, bias, y, st)                 \
-                        : launch_cfg<W, K, 8, false>(packed, L, m, xq, sx, bias, y, st);               \
-    }
-    MNNQ_CFG(4, 1) MNNQ_CFG(4, 2) MNNQ_CFG(4, 4) MNNQ_CFG(8, 8)
-#undef MNNQ_CFG
-    return MNNQ_ERR_UNSUPPORTED;
+    if (L.native8) return launch_tokens<kBytes>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
+    if (L.minf) return launch_tokens<kMin>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
+    return launch_tokens<kZp>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
 }
 
 }  // namespace mnnq

@@ -1,0 +1,75 @@
+"""Few tokens at once (the kernels behind mnnq_linear_prefill and mnnq_linear_prefill_fused for small M) against the
+oracle: token counts at the edges of the 16-token blocks, rows of one chunk, of an odd number of groups and beyond what a
+wave holds in registers, more row tiles than the chip holds workgroups, every weight form.  int8 rows given (row-major)
+and quantized by the call (codes in token blocks) run the same sums in the same order: equal bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_10443_amd import binding as B, synth
+
+pytestmark = pytest.mark.gpu
+W8N = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
+FORMS = {
+    "w4": (B.MODE_W4_ZP_INT, oracle.quant_weights, oracle.linear_w4a8),
+    "w4min": (B.MODE_W4_MIN_FLOAT, oracle.quant_weights_minf, oracle.linear_w4a8_minf),
+    "w8": (W8N, oracle.quant_weights8, oracle.linear_w8a8),
+    "w8planes": (B.MODE_W8_MIN_FLOAT, oracle.quant_weights8, oracle.linear_w8a8),
+}
+# (M, N, K): the last ones walk over several row tiles per workgroup, and stream a long row
+SHAPES = [(2, 16, 64), (3, 48, 192), (15, 80, 1536), (16, 32, 4096), (17, 48, 4160), (32, 64, 960), (33, 48, 512),
+          (48, 32, 8960), (49, 16, 320), (64, 80, 3584), (4, 16 * 1100, 128), (40, 16 * 600, 256), (5, 32, 18944),
+          (2, 16, 24576)]
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("form", list(FORMS))
+def test_few_tokens_match_oracle(form, M, N, K):
+    mode, quant, linear = FORMS[form]
+    if form.startswith("w8") and K % 128:
+        pytest.skip("int8 weights: K a multiple of 128")
+    print("few tokens", form, M, N, K, flush=True)
+    W = synth.weights(N, K, 3000 + M + N + K)
+    W[0, :64] = 0.25                                # a constant group
+    x = synth.activations(M, K, 3001 + M + N + K)
+    x[M // 2] = 0.0                                 # a zero token
+    q, s, z = quant(W)
+    xq, sx, _ = oracle.quant_act(x)
+    bias = synth.weights(1, N, 9)[0] * 10
+    y_o = linear(xq, sx, q, s, z, bias=bias, want_acc=False)[1]
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    bd, xd = dev(bias), dev(x)
+    y = B.mnnq_linear_prefill(packed, N, K, dev(xq), dev(sx), bias=bd, mode=mode)
+    # fp32 sums of up to 2 K / 64 group terms: the layer's tolerance
+    assert np.abs(y.cpu().numpy() - y_o).max() <= 1e-5 * np.abs(y_o).max()
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    yf = B.mnnq_linear_prefill_fused(packed, N, K, xd, bias=bd, out=out[:M], mode=mode)
+    assert torch.isnan(out[M]).all()                # nothing behind the last token
+    if M <= 48:
+        assert torch.equal(yf, y)
+    assert np.abs(yf.cpu().numpy() - y_o).max() <= 1e-5 * np.abs(y_o).max()
+    y16 = B.mnnq_linear_prefill_fused_o16(packed, N, K, xd, bias=bd, mode=mode)
+    assert torch.equal(y16, yf.half())
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 32, 64), (65, 48, 192), (100, 64, 4160), (130, 272, 3584), (257, 32, 18944)])
+def test_quantizer_writes_the_planes_of_the_two_steps(M, N, K):
+    """The fused call on a buffer with the matrix-core plane: bit for bit the result of quantizer, planes and GEMM as
+    calls of their own (the quantizer writes the operand planes itself)."""
+    mode = B.MODE_W4_ZP_INT | B.WITH_MATRIX_PLANE
+    print("fused planes", M, N, K, flush=True)
+    packed = B.mnnq_pack_weights(dev(synth.weights(N, K, 3100 + K)), mode=mode)
+    xd = dev(synth.activations(M, K, 3101 + M))
+    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 0)       # (shapes this small are left to other kernels)
+    try:
+        yf = B.mnnq_linear_prefill_fused(packed, N, K, xd, mode=mode)
+        xq, sx, _ = B.mnnq_quant_act(xd)
+        y = B.mnnq_linear_prefill_planes(packed, M, N, K, B.mnnq_act_planes(xq), sx, mode=mode)
+    finally:
+        B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", None)
+    assert torch.equal(yf, y)
