@@ -183,8 +183,7 @@ int mnnq_linear_prefill_fused(const void *packed, int64_t M, int64_t N, int64_t 
  *   mnnq_linear_prefill_planes: y [M, N] from those planes, the scales sx [M] and the packed weights;
  *     mode must carry MNNQ_WITH_MATRIX_PLANE and M must exceed 32 (MNNQ_ERR_UNSUPPORTED otherwise).
  * The result is that of mnnq_linear_prefill with a workspace, bit for bit, whenever that call takes
- * the fp6 GEMM as well (it leaves up to 48 tokens to the few-token kernels, and shapes with very few
- * output tiles and a long K to the int8 GEMM; mnnq_plan_debug tells for the GEMMs). */
+ * the fp6 GEMM as well (it leaves up to 64 tokens to the few-token kernels). */
 size_t mnnq_act_planes_size(int64_t M, int64_t K, int group);
 int mnnq_act_planes(const int8_t *xq, int64_t M, int64_t K, int group, void *planes, size_t planes_bytes,
                     void *stream);
@@ -274,7 +273,7 @@ int mnnq_linear_acc_debug_planes(const void *packed, int64_t M, int64_t N, int64
  * library never reads the environment).  key: one of MNNQ_DECODE_KSPLIT (waves per row tile of the GEMV:
  * 1, 2, 4, 8, 16), MNNQ_DECODE_WAVES (4, 8, 16), MNNQ_DECODE_EARLY (0/1), MNNQ_PREFILL_TILE (tile letter,
  * K split digit, k/q), MNNQ_NO_SKINNY, MNNQ_SKINNY_STAGED (0/1), MNNQ_W8_PLANES (1), MNNQ_FUSED_TWO_KERNEL_MIB,
- * MNNQ_PREFILL6_PLAN (0..5: tile plan of the fp6 GEMM), MNNQ_PREFILL6_STAGES (2..4: depth of its LDS rings);
+ * MNNQ_PREFILL6_PLAN (0..8: tile plan of the fp6 GEMM), MNNQ_PREFILL6_STAGES (2..4: depth of its LDS rings);
  * value: a string of at most 15 characters, or NULL to clear the override.  Applies to all later calls of the process; not thread safe.  MNNQ_ERR_UNSUPPORTED
  * for an unknown key. */
 int mnnq_debug_set(const char *key, const char *value);
@@ -285,7 +284,8 @@ int mnnq_debug_set(const char *key, const char *value);
  *           K parts inside a workgroup, K split over workgroups, waves per workgroup, LDS bytes per
  *           workgroup, workgroups, form: 0 int4 on the int8 matrix instruction, 1 int8 weights with the two
  *           nibble planes merged in registers, 2 int8 weights in the byte form, 6 the GEMM on the fp6 matrix
- *           instructions (what a call with a workspace runs for a buffer with the matrix-core plane)};
+ *           instructions (what a call with a workspace runs for a buffer with the matrix-core plane), 7 the same where
+ *           K is long and the output tiles are few (always with K split over the waves)};
  * what = 1: mnnq_linear_decode; what = 2: mnnq_linear_decode_fused without workspace; out8 = {waves per
  *           workgroup, waves per row tile, weight chunks a wave holds in registers, 1 if it loops with a
  *           prefetch, LDS bytes per workgroup, workgroups, row tiles per workgroup, 1 if the activation

@@ -111,15 +111,16 @@ Layout layout_for(int64_t N, int64_t K, int mode, bool out16)
     return L;
 }
 
-// Up to this many tokens the few-token kernels beat the tiled GEMMs: 64 where the call's own quantizer lays the codes
-// out for them, 48 on int8 rows (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us from token blocks, 32 / 40 us
-// from rows, 35 / 36 us tiled).
-constexpr int64_t kFewTokensBlocks = 64, kFewTokensRows = 48;
+// Up to this many tokens the few-token kernels beat the tiled GEMMs where the call's own quantizer lays the codes out for
+// them (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us against 35 / 36 us tiled).  On int8 rows they lose a little
+// beyond 48 tokens (40 against 36 us), but the line is the same for both, so that the fused call stays bit for bit the
+// two calls.
+constexpr int64_t kFewTokens = 64;
 
-bool few_tokens_wanted(int64_t M, bool blocks)
+bool few_tokens_wanted(int64_t M)
 {
     // (a forced tile or plan, tests and tuning: the tiled GEMMs)
-    return M <= (blocks ? kFewTokensBlocks : kFewTokensRows) && !debug_option(kDbgNoSkinny) &&
+    return M <= kFewTokens && !debug_option(kDbgNoSkinny) &&
            (M <= 16 || (!debug_option(kDbgPrefillTile) && !debug_option(kDbgPrefill6Plan)));
 }
 
@@ -162,7 +163,7 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
     }
     // A few tokens (batched or speculative decoding) are still memory-bound: one pass over the
     // weights in the GEMV's streaming order, all tokens at once in the matrix cores.
-    if (few_tokens_wanted(M, false))
+    if (few_tokens_wanted(M))
         return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
                              static_cast<hipStream_t>(stream));
     // With the matrix-core plane and room for the activations' planes: the GEMM on the fp6 matrix instructions.
@@ -255,7 +256,7 @@ int prefill_fused_impl(const void* packed, int64_t M, int64_t N, int64_t K, int 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Layout L = layout_for(N, K, mode, out16);
     if (quant_packed_possible(K) && prefill_fits(M, N, K, mode)) {
-        if (few_tokens_wanted(M, true)) {
+        if (few_tokens_wanted(M)) {
             if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
             return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
         }

@@ -253,6 +253,10 @@ bool prefill6_possible(const Layout& L, int64_t M);
 bool prefill6_wanted(const Layout& L, int64_t M);
 void describe_prefill6(const Layout& L, int64_t M, int32_t out[8]);
 int prefill6_row_tiles(int64_t M);
+// The same product with K split over the waves of a workgroup (mnnq_ksplit6.hip), for shapes with few output tiles.
+size_t ksplit6_lds_bytes(int form);
+int launch_ksplit6(int form, const uint8_t* packed, const Layout& L, int64_t M, const void* planes, const float* sx,
+                   const float* bias, float* y, hipStream_t st);
 // A few tokens sharing one pass over the weights; token_blocks: xq as launch_quant_token_blocks writes it.
 int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st);

@@ -47,6 +47,18 @@ __device__ __forceinline__ void store_block(uint8_t* block, int lane, const uint
     *reinterpret_cast<uint2*>(block + 1024 + lane * 8) = make_uint2(d[4], d[5]);
 }
 
+// One pair of blocks of the activation planes (3072 B, high and low parts of 32 rows and one group): twelve dwords per
+// lane - six of the high part, six of the low part - as three kilobytes of 16-byte units, so that three 128-bit loads
+// bring both operands into consecutive registers.  (The vector memory pipe takes as long for a 64-bit load as for a
+// 128-bit one.)
+__device__ __forceinline__ void store_pair(uint8_t* pair, int lane, const uint32_t (&hi)[6], const uint32_t (&lo)[6])
+{
+    uint4* p = reinterpret_cast<uint4*>(pair) + lane;
+    p[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    p[64] = make_uint4(hi[4], hi[5], lo[0], lo[1]);
+    p[128] = make_uint4(lo[2], lo[3], lo[4], lo[5]);
+}
+
 // Four int8 activations (bytes) -> six-bit codes of their high and low parts: xq = s (16 hi + lo) with s = +-1,
 // hi = |xq| >> 4 (0..8), lo = |xq| & 15; the code of a part is its magnitude with the sign in bit 5, zero parts stay
 // all-zero codes.

@@ -93,8 +93,8 @@ __global__ __launch_bounds__(256) void plane_build_kernel(uint8_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Per call: the activation planes [Gx][TMp][2][1536 B] from the int8 codes [M, K] - block (g, tm, 0)
-// the high parts, block (g, tm, 1) the low parts of xq = sign(xq) (16 hi + lo), hi = |xq| >> 4,
+// Per call: the activation planes [Gx][TMp][3072 B] from the int8 codes [M, K] - pair (g, tm): the
+// high and the low parts (store_pair) of xq = sign(xq) (16 hi + lo), hi = |xq| >> 4,
 // lo = |xq| & 15, both carrying the sign of xq (so that small values have an all-zero high part), of rows 32 tm .. 32 tm + 31
 // and group g, lane l holding row l % 32 and k = 64 g + 32 (l / 32) + j.  Rows past M are zero.
 // One wave per (tm, g); consecutive waves take consecutive groups of the same rows, so that the
@@ -120,9 +120,7 @@ __global__ __launch_bounds__(256) void planes_kernel(const int8_t* __restrict__ 
     uint32_t dh[6], dl[6];
     pack_fp6(hi, dh);
     pack_fp6(lo, dl);
-    uint8_t* block = out + ((g * TMp + tm) * 2) * (int64_t)kPlaneBlockBytes;
-    store_block(block, lane, dh);
-    store_block(block + kPlaneBlockBytes, lane, dl);
+    store_pair(out + (g * TMp + tm) * (int64_t)(2 * kPlaneBlockBytes), lane, dh, dl);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -288,8 +286,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void prefill6_kernel(
     v8i ahi[TMW], alo[TMW], b[JO ? 2 : TNW];
     float sc[JO ? 2 : TNW], scn[JO ? 1 : TNW];
     auto read_a = [&](const uint8_t* st, int i) {
-        ahi[i] = frag6(st + a_frag + i * 2 * kPlaneBlockBytes, off16, off8);
-        alo[i] = frag6(st + a_frag + i * 2 * kPlaneBlockBytes + kPlaneBlockBytes, off16, off8x);
+        const uint8_t* pair = st + a_frag + i * 2 * kPlaneBlockBytes + off16;
+        const v4i p0 = *reinterpret_cast<const v4i*>(pair), p1 = *reinterpret_cast<const v4i*>(pair + 1024);
+        const v4i p2 = *reinterpret_cast<const v4i*>(pair + 2048);
+        ahi[i] = v8i{p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, 0, 0};
+        alo[i] = v8i{p1.z, p1.w, p2.x, p2.y, p2.z, p2.w, 0, 0};
     };
     auto read_b = [&](const uint8_t* st, int j) {
         b[j] = frag6(st + b_frag + j * kPlaneBlockBytes, off16, (j & 1) ? off8x : off8);
@@ -572,32 +573,54 @@ int tmp_tiles(int64_t M) { return (int)(((M + 31) / 32 + kPlaneTilePad - 1) / kP
 // Tile plans (all waves own 64 rows): 0 = 128 x 128 tiles of four waves (two workgroups per CU),
 // 1 = 128 x 128 with the K range in two parts (eight waves), 2 = 128 x 256 of four waves (64 x 128
 // outputs per wave, two workgroups per CU), 3 = 128 x 256 with two K parts, 4 = 256 x 256 of eight waves,
-// 5 = 128 x 320 of four waves (64 x 160 outputs per wave, the column-major loop, two workgroups per CU).
+// 5 = 128 x 320 of four waves (64 x 160 outputs per wave, the column-major loop, two workgroups per CU);
+// the K-split kernel (mnnq_ksplit6.hip): 6 = 64 x 64 tiles of eight waves, 7 = 64 x 64 of four waves (two workgroups
+// per CU), 8 = 64 x 32 of eight waves.
+constexpr int kPlans6 = 9;
+
+int64_t tiles6(const Layout& L, int64_t M, int bm, int bn) { return ((M + bm - 1) / bm) * ((L.N + bn - 1) / bn); }
+
+// Plans 0 .. 5, for shapes the K-split kernel does not take.
+int choose_tiled6(const Layout& L, int64_t M)
+{
+    const int64_t cus = num_cus();
+    // At most one 128 x 128 tile per CU: its K range in two parts keeps every SIMD busy (measured on Qwen2-7B's o and
+    // down at 1024 tokens: 1.3 and 1.5 times faster than one part).
+    const int64_t t0 = tiles6(L, M, 128, 128);
+    if (t0 <= cus) return 1;
+    // Else two workgroups of four waves per CU, and what decides is how the tiles divide into rounds of workgroups: a
+    // round takes `full` where CUs hold two workgroups and `half` where they hold at most one (us at K = 3584; the
+    // ratios hold at K = 1536); a last round behind others spreads over the CUs as they come free and takes its share.
+    // The choice was the best measured one, or within 5 % of it, on 28 shapes between 8192 x 3584 and 25600 x 4096 at
+    // 700 - 1900 tokens and on 37888 x 3584 at 128 - 1024 (512 tokens: 128 x 320 tiles 89 us, 128 x 128 tiles 106 us).
+    auto cost = [&](int bn, double half, double full) {
+        const int64_t t = tiles6(L, M, 128, bn), rest = t % (2 * cus);
+        const double last = rest == 0 ? 0.0 : rest <= cus ? half
+                            : t < 2 * cus ? full : half + (full - half) * (double)(rest - cus) / (double)cus;
+        return (double)(t / (2 * cus)) * full + last;
+    };
+    const double c0 = cost(128, 27, 42), c2 = cost(256, 49, 68), c5 = cost(320, 54, 88);
+    if (c5 < c2 && c5 < 0.97 * c0) return 5;
+    return c2 < 0.97 * c0 ? 2 : 0;
+}
+
+// Few output tiles: the K-split kernel, as long as its 64 x 64 tiles are at most two per CU (measured, one tile per CU
+// against plan 1: 128 tokens of 3584 x 18944 44 against 93 us, two per CU: 512 tokens 78 against 93 us; at 2.25 per CU the
+// two are even).  Where 64 x 32 tiles are at most one per CU they are faster still (38 us).
+bool ksplit_wanted(const Layout& L, int64_t M)
+{
+    const int64_t lim = 0x7fff0000;      // (its out-of-range offset has to lie beyond the operands)
+    return tiles6(L, M, 64, 64) <= 2 * (int64_t)num_cus() && (int64_t)L.plane_bytes() < lim &&
+           (int64_t)prefill6_ws_bytes(M, L.Kx) < lim && M * L.N * (L.out16 ? 2 : 4) < lim;
+}
+
 int choose_plan6(const Layout& L, int64_t M)
 {
     if (const char* e = debug_option(kDbgPrefill6Plan))   // tests and tuning
-        if (e[0] >= '0' && e[0] <= '5') return e[0] - '0';
+        if (e[0] >= '0' && e[0] < '0' + kPlans6) return e[0] - '0';
+    if (!ksplit_wanted(L, M)) return choose_tiled6(L, M);
     const int64_t cus = num_cus();
-    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((L.N + bn - 1) / bn); };
-    auto rounds = [&](int64_t t, int64_t slots) { return (double)((t + slots - 1) / slots); };
-    // Fewer 128 x 128 tiles than CUs: one tile per CU with its K range in two parts keeps every SIMD busy
-    // (measured on Qwen2-7B's o and down at 1024 tokens: 1.3 and 1.5 times faster than one part).
-    const int64_t t0 = tiles(128, 128);
-    if (t0 <= cus) return 1;
-    // Else two workgroups of four waves per CU.  A 128 x 256 tile takes 1.54 times as long as a 128 x 128
-    // one (measured at K = 3584) for twice the outputs; what decides is how many rounds of workgroups
-    // each form needs.  With a single round the larger tile loses (its writes of 128 KiB per workgroup
-    // all come at the end, with nothing left to overlap them).
-    // (The K-split forms of these sizes lost everywhere they were measured: their loops are short and the
-    // exchange of the sums is a fixed cost per tile.)
-    // A 128 x 320 tile (column-major loop) takes 2.21 times a 128 x 128 one for 2.5 times the outputs:
-    // worth it where it saves a round (Qwen2-7B's gate|up: two rounds instead of three of 128 x 256).
-    const double r2 = rounds(tiles(128, 256), 2 * cus), r5 = rounds(tiles(128, 320), 2 * cus);
-    const double c0 = rounds(t0, 2 * cus) * 1.0;
-    const double c2 = r2 >= 2 ? r2 * 1.54 : 1e30;
-    const double c5 = r5 >= 2 ? r5 * 2.21 : 1e30;
-    if (c5 < c2 && c5 < c0) return 5;
-    return c2 < c0 ? 2 : 0;
+    return tiles6(L, M, 64, 32) <= cus ? 8 : tiles6(L, M, 64, 64) <= cus ? 6 : 7;
 }
 
 // Stages of the LDS rings for a plan (groups in flight or ready beside the one being contracted, plus one):
@@ -633,6 +656,9 @@ Plan6Info plan6_info(int plan, const Layout& L, int64_t M)
         case 3: return {128, 256, 2, 8, ns == 3 ? lds_bytes6<128, 256, 2, 3>() : lds_bytes6<128, 256, 2>()};
         case 4: return {256, 256, 1, 8, lds_bytes6<256, 256, 1>()};
         case 5: return {128, 320, 1, 4, lds_bytes6<128, 320, 1>()};
+        case 6: return {64, 64, 8, 8, ksplit6_lds_bytes(0)};
+        case 7: return {64, 64, 4, 4, ksplit6_lds_bytes(1)};
+        case 8: return {64, 32, 8, 8, ksplit6_lds_bytes(2)};
         default: return {128, 128, 1, 4, ns == 4 ? lds_bytes6<128, 128, 1, 4>() : ns == 3 ? lds_bytes6<128, 128, 1, 3>() : lds_bytes6<128, 128, 1>()};
     }
 }
@@ -650,14 +676,15 @@ bool prefill6_possible(const Layout& L, int64_t M)
            (int64_t)prefill6_ws_bytes(M, L.Kx) <= lim;
 }
 
+// Without its K-split kernel this GEMM would leave the shape to the int8 one, which splits K over workgroups and in more
+// parts: fewer 128 x 128 tiles than a quarter of the CUs and a long K.
+static bool few_tiles_long_k(const Layout& L, int64_t M) { return 4 * tiles6(L, M, 128, 128) < num_cus() && L.Kx >= 4096; }
+
 bool prefill6_wanted(const Layout& L, int64_t M)
 {
     if (!prefill6_possible(L, M)) return false;
     if (debug_option(kDbgPrefill6Plan)) return true;   // a forced plan: tests and tuning
-    // fewer 128 x 128 tiles than a quarter of the CUs and a long K: the int8 GEMM, which splits K four
-    // ways, fills the chip better than this one's two parts
-    const int64_t t0 = ((M + 127) / 128) * ((L.N + 127) / 128);
-    return 4 * t0 >= num_cus() || L.Kx < 4096;
+    return ksplit_wanted(L, M) || !few_tiles_long_k(L, M);
 }
 
 void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
@@ -671,7 +698,8 @@ void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
     out[4] = p.waves;
     out[5] = (int32_t)p.lds;
     out[6] = (int32_t)(MT * ((NT + 7) / 8) * 8);
-    out[7] = 6;   // operands in fp6
+    // operands in fp6; 7: where that takes the K-split kernel (a long K and few tiles)
+    out[7] = !debug_option(kDbgPrefill6Plan) && few_tiles_long_k(L, M) ? 7 : 6;
 }
 
 int launch_plane_build(uint8_t* packed, const Layout& L, hipStream_t st)
@@ -700,6 +728,7 @@ int launch_prefill6(const uint8_t* packed, const Layout& L, int64_t M, const voi
     const uint8_t* a6 = static_cast<const uint8_t*>(planes);
     if (acc_debug) return launch6<128, 128, 2, 2, 1, true, 4>(packed, L, M, a6, TMp, sx, bias, y, acc_debug, st);   // plan 0 as it runs
     const int plan = choose_plan6(L, M), ns = choose_stages6(plan, L, M);
+    if (plan >= 6) return launch_ksplit6(plan - 6, packed, L, M, planes, sx, bias, y, st);
 #define MNNQ_ARGS6 packed, L, M, a6, TMp, sx, bias, y, nullptr, st
     if (ns == 4) {
         if (plan == 1) return launch6<128, 128, 2, 2, 2, false, 4>(MNNQ_ARGS6);

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kQThreads) void quant_act_rows_kernel(const float* 
 // them, so that no pass over the codes rearranges them (Section 5.1) and the kernel's loads are whole lines.
 //   kTokenBlocks - the few-token kernels: [group][token block of 16][k block of 16][token][16 codes], the last block as
 //                  narrow as its tokens (M K bytes in all);
-//   kPlanes      - the fp6 GEMM: the activation planes [group][TMp][2][1536 B] (see planes_kernel).
+//   kPlanes      - the fp6 GEMM: the activation planes [group][TMp][3072 B] (see planes_kernel).
 // A workgroup of 1024 threads quantizes R rows, each in the registers of 1024 / R threads (NV float4 per thread) between
 // the maximum and the codes, collects the codes in LDS and stores them from there: R tokens lie side by side in the
 // output, i.e. pieces of 16 R bytes.
@@ -190,10 +190,8 @@ __global__ __launch_bounds__(kPackThreads) void quant_pack_kernel(const float* _
             for (int i = 0; i < 8; ++i) split_act(q[i], hi[i], lo[i]);
             pack_fp6(hi, dh);
             pack_fp6(lo, dl);
-            uint8_t* block = out + ((int64_t)(kk >> 1) * TMp + (mm >> 5)) * (2 * kPlaneBlockBytes);
-            const int lane = (mm & 31) + 32 * (kk & 1);
-            store_block(block, lane, dh);
-            store_block(block + kPlaneBlockBytes, lane, dl);
+            uint8_t* pair = out + ((int64_t)(kk >> 1) * TMp + (mm >> 5)) * (2 * kPlaneBlockBytes);
+            store_pair(pair, (mm & 31) + 32 * (kk & 1), dh, dl);
         }
     }
 }

@@ -196,3 +196,22 @@ def test_act_planes_and_gemm_as_separate_calls():
     y_pl = B.mnnq_linear_prefill_planes(packed, M, N, K, planes, dev(sx), mode=MODE)
     assert torch.equal(y_pl, y_ws)
     assert np.abs(y_pl.cpu().numpy() - y_o).max() <= TOL_A8 * np.abs(y_o).max()
+
+
+@pytest.mark.parametrize("plan", [6, 7, 8])
+@pytest.mark.parametrize("M,N,K", [(33, 48, 64), (129, 592, 448), (200, 400, 1536), (333, 1040, 192), (64, 32, 5056)])
+def test_k_split_plans(plan, M, N, K):
+    """The K-split kernel: fewer groups than waves, shares of unequal length, ragged rows and columns, both output types."""
+    note("prefill6 K-split plan", plan, "M", M, "N", N, "K", K)
+    W, x, q, s, z, xq, sx = make(N, K, M, 4700 + plan, special=True)
+    bias = (0.5 * np.random.default_rng(4701).standard_normal(N)).astype(np.float32)
+    _, y_o = oracle.linear_w4a8(xq, sx, q, s, z, bias=bias)
+    packed = B.mnnq_pack_weights(dev(W), mode=MODE)
+    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", plan)
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    B.mnnq_linear_prefill_fused(packed, N, K, dev(x), bias=dev(bias), out=out[:M], mode=MODE)
+    y = out[:M].cpu().numpy()
+    assert np.abs(y - y_o).max() <= TOL_A8 * np.abs(y_o).max()
+    assert torch.isnan(out[M]).all()
+    y16 = B.mnnq_linear_prefill_fused_o16(packed, N, K, dev(x), bias=dev(bias), mode=MODE).cpu().numpy()
+    assert np.array_equal(y16, y.astype(np.float16))
