@@ -345,8 +345,7 @@ int mnnq_pack_weights(const float* W, int64_t N, int64_t K, int group, int mode,
     if (misaligned(W) || misaligned(packed)) return MNNQ_ERR_ALIGN;
     const Layout L = make_layout(N, K, mode);
     if (packed_bytes < L.full_total()) return MNNQ_ERR_SIZE;
-    if (int s = launch_pack(W, L, static_cast<uint8_t*>(packed), static_cast<hipStream_t>(stream))) return s;
-    return L.plane ? launch_plane_build(static_cast<uint8_t*>(packed), L, static_cast<hipStream_t>(stream)) : MNNQ_OK;
+    return launch_pack(W, L, static_cast<uint8_t*>(packed), static_cast<hipStream_t>(stream));   // (the plane included)
 }
 
 int mnnq_pack_from_quantized(const uint8_t* q, const float* scale, const void* zero, int64_t N, int64_t K,

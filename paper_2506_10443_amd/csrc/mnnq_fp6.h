@@ -28,23 +28,25 @@ __device__ __forceinline__ void pack_fp6(const uint32_t (&c)[8], uint32_t (&out)
 // Sign-magnitude six-bit codes of four small integers held as bytes 0x80 + v (|v| <= 15).
 __device__ __forceinline__ uint32_t signmag_from_biased(uint32_t b)
 {
-    uint32_t r = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int v = (int)((b >> (8 * i)) & 0xffu) - 0x80;
-        const uint32_t code = v < 0 ? (32u | (uint32_t)(-v)) : (uint32_t)v;
-        r |= code << (8 * i);
-    }
-    return r;
+    const uint32_t neg = (~b >> 7) & 0x01010101u;             // 1 in the bytes of negative values
+    const uint32_t v = b ^ 0x80808080u;                       // the values as two's complement bytes
+    return ((v ^ (neg * 255u)) + neg) | (neg << 5);           // (|v| <= 15: no carry between bytes; zero has no sign)
 }
+
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// Load-time stores: nothing reads them back soon (see pack_kernel).
+template <typename V>
+__device__ __forceinline__ void store_once(uint8_t* p, V v) { __builtin_nontemporal_store(v, reinterpret_cast<V*>(p)); }
 
 // One block (1536 B) of a plane: six dwords per lane, dwords 0..3 of lane l at 16 l, dwords 4..5 at
 // 1024 + 8 l - a kilobyte of 16-byte units and half a kilobyte of 8-byte units, both read without
 // bank conflicts.
 __device__ __forceinline__ void store_block(uint8_t* block, int lane, const uint32_t (&d)[6])
 {
-    *reinterpret_cast<uint4*>(block + lane * 16) = make_uint4(d[0], d[1], d[2], d[3]);
-    *reinterpret_cast<uint2*>(block + 1024 + lane * 8) = make_uint2(d[4], d[5]);
+    store_once(block + lane * 16, v4u{d[0], d[1], d[2], d[3]});
+    store_once(block + 1024 + lane * 8, v2u{d[4], d[5]});
 }
 
 // One pair of blocks of the activation planes (3072 B, high and low parts of 32 rows and one group): twelve dwords per

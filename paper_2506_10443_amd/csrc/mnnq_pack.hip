@@ -8,153 +8,218 @@
 // sequence of IEEE binary32 operations (subtract, divide, round-to-nearest-even,
 // add, clamp) and must not be fused.
 #include "mnnq_common.h"
+#include "mnnq_fp6.h"
 
 namespace mnnq {
 
 namespace {
 
-constexpr int kTeam = 16;           // lanes per (row, group): 16 x float4 = 64 weights
-constexpr int kPackThreads = 256;   // 16 teams per workgroup
+constexpr int kPackThreads = 256;
+constexpr int kPackRows = 32;       // rows of a workgroup
 
-// Stores one quantization group into the chunk layout.  Called by the 16 lanes of a
-// team; lane li holds the codes c0..c3 (each 0..15) of k = 4 li .. 4 li + 3 of group g
-// of the packed reduction axis.
-__device__ __forceinline__ void store_group(uint8_t* __restrict__ packed, const Layout& L, int64_t n, int64_t g,
-                                            int li, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                            float scale, float mn, float zero)
+enum PackForm { kPackZp = 0, kPackZpPlane = 1, kPackMin = 2, kPackBytes = 3, kPackNibbles = 4 };
+
+// Four codes (0 .. MAX, one per byte) of the weights v of a group with the given scale: rint(x / scale) with IEEE
+// operations, x = v (integer zero point, which is added to the rounded quotient) or v - mn (float minimum), clamped.
+// The correctly rounded divisions are replaced as in quant4_fast: r = x * rcp(scale) differs from fl(x / scale) by less
+// than |x / scale| * 2^-22 (one unit of the reciprocal, two roundings), i.e. 4e-6 for 4-bit and 6.1e-5 for 8-bit codes,
+// so both round to the same integer unless r lies within that of a half-integer; only then - one value in 50000 (4 bits)
+// or 5000 (8 bits) - the divisions are done.  The integer is the low part of r + 1.5 * 2^23.  (A scale near the ends of
+// the exponent range, where the reciprocal is no normal number, always divides.)
+template <int FORM>
+__device__ __forceinline__ uint32_t quant_group(const float4 v, float scale, float mn, int& zero)
 {
-    // Lane li holds codes j = 4 (li % 4) .. +3 of k-block kb = li / 4.  Codes
-    // j % 8 < 4 go to low nibbles, the others to high nibbles of the same bytes.
-    uint32_t v = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-    if (li & 1) v <<= 4;
-    v |= __shfl_xor(v, 1, kTeam);
-
-    const int64_t t = n / kTileN;
-    const int r = (int)(n % kTileN);
-    const int64_t c = g / 2;
-    const int half = (int)(g & 1);
-    const int kb = li / 4;
-    const int d = (li % 4) / 2;
-    const int64_t chunk = t * L.C + c;
-    uint32_t* slot = reinterpret_cast<uint32_t*>(packed + chunk * kChunkBytes + (16 * kb + r) * 16);
-    float* sc = reinterpret_cast<float*>(packed + L.scales_off()) + (chunk * 16 + r) * 2;
-    uint8_t* zp = packed + L.zeros_off() + (chunk * 16 + r) * 2;
-    float* mp = reinterpret_cast<float*>(packed + L.zeros_off()) + (chunk * 16 + r) * 2;
-    if ((li & 1) == 0) slot[half * 2 + d] = v;
-    if (li == 0) {
-        sc[half] = scale;
-        if (L.minf) mp[half] = mn;
-        else zp[half] = (uint8_t)zero;
+    constexpr bool ZP = FORM == kPackZp || FORM == kPackZpPlane;
+    constexpr int MAX = FORM >= kPackBytes ? 255 : 15;
+    constexpr float LIM = 0.5f - (FORM >= kPackBytes ? 1.0e-4f : 1.0e-5f), MAGIC = 12582912.0f;
+    const float inv = __builtin_amdgcn_rcpf(scale);
+    const float lim = (scale > 1.0e-30f && scale < 1.0e30f) ? LIM : -1.0f;
+    const float x[4] = {ZP ? v.x : v.x - mn, ZP ? v.y : v.y - mn, ZP ? v.z : v.z - mn, ZP ? v.w : v.w - mn};
+    float m[4], dmax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float r = x[i] * inv;
+        m[i] = r + MAGIC;
+        dmax = fmaxf(dmax, fabsf(r - (m[i] - MAGIC)));
     }
-    // Odd number of groups: the second half of the last chunk is padding that
-    // contributes nothing (codes 0, scale 0, zero / minimum 0).
-    if ((L.G & 1) && g == L.G - 1) {
-        if ((li & 1) == 0) slot[2 + d] = 0u;
-        if (li == 0) {
-            sc[1] = 0.0f;
-            if (L.minf) mp[1] = 0.0f;
-            else zp[1] = 0;
-        }
+    float mz = MAGIC;
+    if (ZP) {
+        const float r = -mn * inv;
+        mz = r + MAGIC;
+        dmax = fmaxf(dmax, fabsf(r - (mz - MAGIC)));
     }
+    // (fmaxf drops a NaN, which an infinite reciprocal gives: the limit is negative then)
+    if (!(dmax <= lim)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = rintf(x[i] / scale) + MAGIC;
+        if (ZP) mz = rintf(-mn / scale) + MAGIC;
+    }
+    constexpr int BITS = 0x4B400000;
+    zero = ZP ? __float_as_int(mz) - BITS : 0;
+    uint32_t c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int q = __float_as_int(m[i]) - BITS + zero;
+        c[i] = (uint32_t)(q < 0 ? 0 : q > MAX ? MAX : q);
+    }
+    return c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
 }
 
-// int4 forms.  A workgroup takes kPackChunks consecutive chunks of the layout (16 rows x 128 weights each):
-// team r (16 lanes, one float4 each) quantizes the two groups of row 16 t + r, the chunk images are put
-// together in LDS in the layout's lane order, and the workgroup stores them - codes, scales, zero points or
-// minima - as whole consecutive kilobytes (Section 5.1: consecutive lanes on consecutive addresses; the
-// one-group-per-team form before this one wrote 8 bytes here and 8 bytes a kilobyte further on, and the
-// memory system wrote 2.4 times the bytes).  All loads are issued before the first is used.
-constexpr int kPackChunks = 4;
-
-__global__ __launch_bounds__(kPackThreads) void pack_kernel(const float* __restrict__ W, Layout L,
-                                                            uint8_t* __restrict__ packed)
+// (the weights pass once: they need not stay in the caches)
+__device__ __forceinline__ float4 load_once(const float* p)
 {
-    __shared__ __align__(16) uint32_t img[kPackChunks * 256];   // codes: 64 lanes x 16 bytes per chunk
-    __shared__ float sc_s[kPackChunks * 32], mn_s[kPackChunks * 32];
-    __shared__ uint8_t z_s[kPackChunks * 32];
-    const int tid = threadIdx.x;
-    const int r = tid / kTeam, li = tid % kTeam;
-    const int64_t chunk0 = (int64_t)blockIdx.x * kPackChunks;
-    const int64_t n_chunks = L.T * L.C;
-    const bool minf = L.minf;
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    const v4f v = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
 
-    float4 w[kPackChunks][2];
+// A workgroup takes 32 rows (two row tiles, one column tile of the matrix-core plane) and CH consecutive chunks of 128
+// weights (four; two where that leaves CUs without a workgroup).  A wave reads a kilobyte of one row per load - sixteen lanes, one float4 each, are a group -
+// and issues all its loads before it uses the first.  Minimum and maximum of a group are DPP exchanges in its row of
+// sixteen lanes.  The codes are put together in LDS in the layout's lane order and leave as whole consecutive kilobytes
+// (Section 5.1: consecutive lanes on consecutive addresses), and with the plane flag the operand blocks of the matrix
+// instructions are built from the same image: the weights are read once, the plane is not built from a second pass over
+// the chunk layout.  Loads and stores are marked as passing once, which is worth 15 % (37888 x 3584,
+// int4: 125 -> 107 - 115 us).  Bound by HBM: 37888 x 3584 with the plane, 543 MB in and 189 MB out, 187 us as two kernels
+// with one group per team of lanes -> 137 us = 5.35 TB/s (a large copy: 4.85); int8 bytes 210 -> 122 us.
+template <int FORM, int CH>
+__global__ __launch_bounds__(kPackThreads) void pack_kernel(const float* __restrict__ W, Layout L,
+                                                            uint8_t* __restrict__ packed, int chunk_blocks)
+{
+    constexpr bool ZP = FORM == kPackZp || FORM == kPackZpPlane, MINF = !ZP, BYTES = FORM == kPackBytes;
+    // chunk images: [plane of codes][row tile][chunk] of four k-blocks (eight in the byte form: two halves), 16 rows of
+    // 16 bytes each, padded by 16 bytes so that a wave's writes fall into different banks
+    constexpr int IMAGES = FORM == kPackNibbles ? 2 : 1, KBS = BYTES ? 8 : 4, KB_DW = 68;
+    __shared__ __align__(16) uint32_t img[IMAGES * 2 * CH * KBS * KB_DW];
+    __shared__ float sc_s[2 * CH * 32], mn_s[2 * CH * 32];
+    __shared__ uint8_t z_s[2 * CH * 32];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t tn = blockIdx.x / chunk_blocks;
+    const int c0 = (int)(blockIdx.x % chunk_blocks) * CH;     // first chunk of the activation row
+    const int G = (int)L.Gx;
+
+    constexpr int RPW = kPackRows / 4;       // rows of a wave
+    float4 w[RPW][CH / 2];
 #pragma unroll
-    for (int i = 0; i < kPackChunks; ++i) {
-        const int64_t chunk = chunk0 + i;          // uniform over the workgroup
-        const int64_t t = chunk / L.C, c = chunk % L.C;
+    for (int j = 0; j < RPW; ++j) {
+        const int64_t n = tn * kPackRows + wave * RPW + j;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int64_t g = 2 * c + half;
-            w[i][half] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (chunk < n_chunks && g < L.G)
-                w[i][half] = reinterpret_cast<const float4*>(W + ((t * kTileN + r) * L.G + g) * kGroup)[li];
+        for (int h = 0; h < CH / 2; ++h) {
+            const int g = c0 * 2 + h * 4 + (lane >> 4);
+            w[j][h] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (n < L.N && g < G) w[j][h] = load_once(W + n * L.Kx + g * kGroup + li * 4);
         }
     }
 #pragma unroll
-    for (int i = 0; i < kPackChunks; ++i) {
-        const int64_t chunk = chunk0 + i;
-        const int64_t c = chunk % L.C;
+    for (int j = 0; j < RPW; ++j) {
+        const int rr = wave * RPW + j, rt = rr >> 4, r = rr & 15;
+        const bool row_ok = tn * kPackRows + rr < L.N;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const float4 v4 = w[i][half];
-            float scale = 0.0f, zero = 0.0f, mn = 0.0f;
-            uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-            // (an odd number of groups: the second half of the last chunk is padding that contributes nothing -
-            // codes 0, scale 0, zero / minimum 0)
-            if (chunk < n_chunks && 2 * c + half < L.G) {
-                mn = fminf(fminf(v4.x, v4.y), fminf(v4.z, v4.w));
-                float mx = fmaxf(fmaxf(v4.x, v4.y), fmaxf(v4.z, v4.w));
+        for (int h = 0; h < CH / 2; ++h) {
+            const float4 v = w[j][h];
+            const int cl = h * 2 + (lane >> 5), half = (lane >> 4) & 1;
+            const bool ok = row_ok && c0 * 2 + h * 4 + (lane >> 4) < G;
+            float mn = fminf(fminf(v.x, v.y), fminf(v.z, v.w)), mx = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+#define MNNQ_STEP(CTRL)                                                                        \
+    mn = fminf(mn, __int_as_float(row_exchange<CTRL>(__float_as_int(mn))));                    \
+    mx = fmaxf(mx, __int_as_float(row_exchange<CTRL>(__float_as_int(mx))));
+            MNNQ_STEP(0xB1) MNNQ_STEP(0x4E) MNNQ_STEP(0x141) MNNQ_STEP(0x140)
+#undef MNNQ_STEP
+            if (ZP) {
+                // Integer zero point: a group that does not straddle zero gets its range widened to contain it.
+                mn = fminf(mn, 0.0f);
+                mx = fmaxf(mx, 0.0f);
+            }
+            // (a constant group: scale 1, codes 0; outside the matrix, and the half that pads an odd row: all zero)
+            float scale = 1.0f;
+            int zero = 0;
+            uint32_t codes = 0;
+            if (mx != mn) {
+                scale = (mx - mn) / (FORM >= kPackBytes ? 255.0f : 15.0f);
+                codes = quant_group<FORM>(v, scale, mn, zero);
+            }
+            if (!ok) scale = mn = 0.0f;
+
+            const int kb = li >> 2, image = rt * CH + cl;
+            if (BYTES) {
+                img[((image * 2 + half) * 4 + kb) * KB_DW + r * 4 + (li & 3)] = ok ? codes ^ 0x80808080u : 0u;
+            } else {
+                // Lane li holds codes j = 4 (li % 4) .. +3 of the k-block.  Codes j % 8 < 4 go to low nibbles, the others
+                // to high nibbles of the same bytes.
 #pragma unroll
-                for (int o = 1; o < kTeam; o <<= 1) {
-                    mn = fminf(mn, __shfl_xor(mn, o, kTeam));
-                    mx = fmaxf(mx, __shfl_xor(mx, o, kTeam));
-                }
-                if (!minf) {
-                    // Integer zero point: a group that does not straddle zero gets its range widened to contain it.
-                    mn = fminf(mn, 0.0f);
-                    mx = fmaxf(mx, 0.0f);
-                }
-                scale = 1.0f;
-                if (mx != mn) {
-                    scale = (mx - mn) / 15.0f;
-                    if (minf) {
-                        // Eq. 1 as printed: the minimum is subtracted before the division.
-                        c0 = (uint32_t)fminf(fmaxf(rintf((v4.x - mn) / scale), 0.0f), 15.0f);
-                        c1 = (uint32_t)fminf(fmaxf(rintf((v4.y - mn) / scale), 0.0f), 15.0f);
-                        c2 = (uint32_t)fminf(fmaxf(rintf((v4.z - mn) / scale), 0.0f), 15.0f);
-                        c3 = (uint32_t)fminf(fmaxf(rintf((v4.w - mn) / scale), 0.0f), 15.0f);
-                    } else {
-                        zero = rintf((-mn) / scale);
-                        c0 = (uint32_t)fminf(fmaxf(rintf(v4.x / scale) + zero, 0.0f), 15.0f);
-                        c1 = (uint32_t)fminf(fmaxf(rintf(v4.y / scale) + zero, 0.0f), 15.0f);
-                        c2 = (uint32_t)fminf(fmaxf(rintf(v4.z / scale) + zero, 0.0f), 15.0f);
-                        c3 = (uint32_t)fminf(fmaxf(rintf(v4.w / scale) + zero, 0.0f), 15.0f);
-                    }
+                for (int p = 0; p < IMAGES; ++p) {
+                    uint32_t x = FORM != kPackNibbles ? codes : p == 0 ? (codes >> 4) & 0x0f0f0f0fu : codes & 0x0f0f0f0fu;
+                    if (li & 1) x <<= 4;
+                    x |= (uint32_t)row_exchange<0xB1>((int)x);
+                    if ((li & 1) == 0)
+                        img[((p * 2 * CH + image) * 4 + kb) * KB_DW + r * 4 + half * 2 + ((li & 3) >> 1)] = x;
                 }
             }
-            // Lane li holds codes j = 4 (li % 4) .. +3 of k-block kb = li / 4.  Codes j % 8 < 4 go to low
-            // nibbles, the others to high nibbles of the same bytes.
-            uint32_t v = c0 | (c1 << 8) | (c2 << 16) | (c3 << 24);
-            if (li & 1) v <<= 4;
-            v |= __shfl_xor(v, 1, kTeam);
-            const int kb = li / 4, d = (li % 4) / 2;
-            if ((li & 1) == 0) img[i * 256 + (16 * kb + r) * 4 + half * 2 + d] = v;
             if (li == 0) {
-                sc_s[i * 32 + r * 2 + half] = scale;
-                mn_s[i * 32 + r * 2 + half] = mn;
-                z_s[i * 32 + r * 2 + half] = (uint8_t)zero;
+                sc_s[image * 32 + r * 2 + half] = scale;
+                if (MINF) mn_s[image * 32 + r * 2 + half] = mn;
+                else z_s[image * 32 + r * 2 + half] = (uint8_t)zero;
             }
         }
     }
     __syncthreads();
-    // kPackChunks consecutive chunks are consecutive in all three arrays of the layout
-    const int live = (int)((n_chunks - chunk0 < kPackChunks) ? (n_chunks - chunk0) : kPackChunks);
-    if (tid < live * 64) reinterpret_cast<uint4*>(packed + chunk0 * kChunkBytes)[tid] = reinterpret_cast<const uint4*>(img)[tid];
-    if (tid < live * 32) {
-        (reinterpret_cast<float*>(packed + L.scales_off()) + chunk0 * 32)[tid] = sc_s[tid];
-        if (minf) (reinterpret_cast<float*>(packed + L.zeros_off()) + chunk0 * 32)[tid] = mn_s[tid];
-        else (packed + L.zeros_off() + chunk0 * 32)[tid] = z_s[tid];
+
+    // Chunk layout: the images of a row tile are consecutive in all three arrays.
+    const int Cx = (int)L.Cx;
+    const int live = Cx - c0 < CH ? Cx - c0 : CH;
+#pragma unroll
+    for (int p = 0; p < IMAGES; ++p) {
+        constexpr int UNITS = BYTES ? 128 : 64;       // 16-byte units of a chunk
+#pragma unroll
+        for (int u0 = 0; u0 < 2 * CH * UNITS; u0 += kPackThreads) {
+            const int u = u0 + tid, image = u / UNITS, v = u % UNITS, rt = image / CH, cl = image % CH;
+            const int64_t t = tn * 2 + rt;
+            if (t < L.T && cl < live)
+                store_once(packed + ((t * L.C + p * Cx + c0 + cl) * UNITS + v) * 16,
+                           *reinterpret_cast<const v4u*>(img + ((p * 2 * CH + image) * KBS + v / 16) * KB_DW + (v % 16) * 4));
+        }
+        const int image = tid / 32, rt = image / CH, cl = image % CH;
+        const int64_t t = tn * 2 + rt, at = (t * L.C + p * Cx + c0 + cl) * 32 + tid % 32;
+        if (tid < 2 * CH * 32 && t < L.T && cl < live) {
+            const float s = sc_s[tid];
+            // int8 weights as nibbles: high nibbles with step 16 s and the minimum, low nibbles with step s and minimum 0
+            reinterpret_cast<float*>(packed + L.scales_off())[at] = FORM == kPackNibbles && p == 0 ? 16.0f * s : s;
+            if (MINF) reinterpret_cast<float*>(packed + L.zeros_off())[at] = p == 0 ? mn_s[tid] : 0.0f;
+            else (packed + L.zeros_off())[at] = z_s[tid];
+        }
+    }
+
+    if (FORM == kPackZpPlane) {
+        // The plane's blocks of these 32 columns: eight groups of 64 lanes.
+        uint8_t* plane = packed + L.plane_off();
+#pragma unroll
+        for (int k = 0; k < CH / 2; ++k) {
+            const int u = k * kPackThreads + tid, gl = u / 64, ln = u % 64, cl = gl >> 1, half = gl & 1;
+            const int col = ln & 31, image = (col >> 4) * CH + cl, r = col & 15;
+            const int64_t g = c0 * 2 + gl;
+            if (g < G) {
+                const uint32_t bias4 = 0x80808080u - z_s[image * 32 + r * 2 + half] * 0x01010101u;   // 0x80 - zero per byte
+                uint32_t c[8], d[6];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const uint2 x = *reinterpret_cast<const uint2*>(img + (image * 4 + 2 * (ln >> 5) + q) * KB_DW + r * 4 + half * 2);
+                    c[q * 4 + 0] = signmag_from_biased((x.x & 0x0f0f0f0fu) + bias4);
+                    c[q * 4 + 1] = signmag_from_biased(((x.x >> 4) & 0x0f0f0f0fu) + bias4);
+                    c[q * 4 + 2] = signmag_from_biased((x.y & 0x0f0f0f0fu) + bias4);
+                    c[q * 4 + 3] = signmag_from_biased(((x.y >> 4) & 0x0f0f0f0fu) + bias4);
+                }
+                pack_fp6(c, d);
+                const int64_t blk = g * L.T32p + tn;
+                store_block(plane + blk * kPlaneBlockBytes, ln, d);
+                if (ln < 32)
+                    *reinterpret_cast<float*>(plane + L.plane_codes_bytes() + blk * 128 + ln * 4) = sc_s[image * 32 + r * 2 + half];
+            }
+        }
+        // (the few bytes between the chunk layout and the plane's 256-byte boundary: zero, so that equal weights give
+        // equal buffers)
+        if (blockIdx.x == 0)
+            for (size_t i = L.total() + tid; i < L.plane_off(); i += kPackThreads) packed[i] = 0;
     }
 }
 
@@ -169,51 +234,6 @@ __device__ __forceinline__ size_t native8_codes_off(const Layout& L, int64_t n, 
 __device__ __forceinline__ int64_t param_index(const Layout& L, int64_t n, int64_t g)
 {
     return (((n / kTileN) * L.C + g / 2) * 16 + n % kTileN) * 2 + (g & 1);
-}
-
-// int8 weights: Eq. 1 with clip range 0..255 and a float minimum, stored as two 4-bit
-// planes along the doubled reduction axis (see Layout): group g holds the high nibbles
-// with step 16 s and the minimum, group G8 + g the low nibbles with step s and minimum 0;
-// or, in the byte form, as the bytes q8 - 128 with step s and the minimum.
-__global__ __launch_bounds__(kPackThreads) void pack8_kernel(const float* __restrict__ W, Layout L,
-                                                             uint8_t* __restrict__ packed)
-{
-    const int64_t team = (int64_t)blockIdx.x * (kPackThreads / kTeam) + threadIdx.x / kTeam;
-    const int li = threadIdx.x % kTeam;
-    const int64_t G8 = L.Kx / kGroup;
-    if (team >= L.N * G8) return;
-    const int64_t n = team / G8;
-    const int64_t g = team % G8;
-
-    const float4 w = reinterpret_cast<const float4*>(W + team * kGroup)[li];
-    float mn = fminf(fminf(w.x, w.y), fminf(w.z, w.w));
-    float mx = fmaxf(fmaxf(w.x, w.y), fmaxf(w.z, w.w));
-#pragma unroll
-    for (int o = 1; o < kTeam; o <<= 1) {
-        mn = fminf(mn, __shfl_xor(mn, o, kTeam));
-        mx = fmaxf(mx, __shfl_xor(mx, o, kTeam));
-    }
-    float step = 1.0f;
-    uint32_t c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-    if (mx != mn) {
-        step = (mx - mn) / 255.0f;
-        c0 = (uint32_t)fminf(fmaxf(rintf((w.x - mn) / step), 0.0f), 255.0f);
-        c1 = (uint32_t)fminf(fmaxf(rintf((w.y - mn) / step), 0.0f), 255.0f);
-        c2 = (uint32_t)fminf(fmaxf(rintf((w.z - mn) / step), 0.0f), 255.0f);
-        c3 = (uint32_t)fminf(fmaxf(rintf((w.w - mn) / step), 0.0f), 255.0f);
-    }
-    if (L.native8) {
-        // lane li holds k = 4 li .. 4 li + 3: dword li % 4 of k-block li / 4
-        const uint32_t v = (c0 | (c1 << 8) | (c2 << 16) | (c3 << 24)) ^ 0x80808080u;
-        *reinterpret_cast<uint32_t*>(packed + native8_codes_off(L, n, g, li / 4) + (li % 4) * 4) = v;
-        if (li == 0) {
-            reinterpret_cast<float*>(packed + L.scales_off())[param_index(L, n, g)] = step;
-            reinterpret_cast<float*>(packed + L.zeros_off())[param_index(L, n, g)] = mn;
-        }
-        return;
-    }
-    store_group(packed, L, n, g, li, c0 >> 4, c1 >> 4, c2 >> 4, c3 >> 4, 16.0f * step, mn, 0.0f);
-    store_group(packed, L, n, G8 + g, li, c0 & 15u, c1 & 15u, c2 & 15u, c3 & 15u, step, 0.0f, 0.0f);
 }
 
 // 16 codes (one per byte) of k-block kb of group g of the packed axis, row n.
@@ -359,17 +379,27 @@ int launch_repack(const uint8_t* q, const float* scale, const void* zero, const 
     return MNNQ_OK;
 }
 
+template <int FORM>
+static int launch_pack_form(const float* W, const Layout& L, uint8_t* packed, hipStream_t st)
+{
+    const int64_t row_blocks = L.plane ? L.T32p : (L.T + 1) / 2;     // (the plane's padding tiles are written as zeros)
+    auto go = [&](auto kern, int ch) -> int {
+        const int chunk_blocks = (int)((L.Cx + ch - 1) / ch);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(row_blocks * chunk_blocks)), dim3(kPackThreads), 0, st, W, L, packed,
+                           chunk_blocks);
+        MNNQ_HIP_TRY(hipGetLastError());
+        return MNNQ_OK;
+    };
+    if (row_blocks * ((L.Cx + 3) / 4) < 8 * (int64_t)num_cus()) return go(pack_kernel<FORM, 2>, 2);
+    return go(pack_kernel<FORM, 4>, 4);
+}
+
 int launch_pack(const float* W, const Layout& L, uint8_t* packed, hipStream_t st)
 {
-    const int64_t teams = L.N * (L.Kx / kGroup);
-    const int64_t blocks = (teams + (kPackThreads / kTeam) - 1) / (kPackThreads / kTeam);
-    if (L.mode == MNNQ_W8_MIN_FLOAT)
-        hipLaunchKernelGGL(pack8_kernel, dim3((unsigned)blocks), dim3(kPackThreads), 0, st, W, L, packed);
-    else
-        hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((L.T * L.C + kPackChunks - 1) / kPackChunks)), dim3(kPackThreads), 0, st,
-                           W, L, packed);
-    MNNQ_HIP_TRY(hipGetLastError());
-    return MNNQ_OK;
+    if (L.native8) return launch_pack_form<kPackBytes>(W, L, packed, st);
+    if (L.mode == MNNQ_W8_MIN_FLOAT) return launch_pack_form<kPackNibbles>(W, L, packed, st);
+    if (L.minf) return launch_pack_form<kPackMin>(W, L, packed, st);
+    return L.plane ? launch_pack_form<kPackZpPlane>(W, L, packed, st) : launch_pack_form<kPackZp>(W, L, packed, st);
 }
 
 int launch_unpack(const uint8_t* packed, const Layout& L, uint8_t* q, float* scale, void* zero,
