@@ -111,16 +111,17 @@ Layout layout_for(int64_t N, int64_t K, int mode, bool out16)
     return L;
 }
 
-// Up to this many tokens the few-token kernels beat the tiled GEMMs where the call's own quantizer lays the codes out for
-// them (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us against 35 / 36 us tiled).  On int8 rows they lose a little
+// Up to this many tokens the few-token kernels beat the GEMMs where the call's own quantizer lays the codes out for them
+// (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us against 35 / 36 us tiled).  On int8 rows they lose a little
 // beyond 48 tokens (40 against 36 us), but the line is the same for both, so that the fused call stays bit for bit the
-// two calls.
-constexpr int64_t kFewTokens = 64;
+// two calls.  Small layers stay with them up to 128 tokens in two slices: row tiles x chunks up to 7000 (128 tokens of
+// 2048 x 1536 7.7 against 11.3 us, of 1536 x 8960 - 6720 - 19 against 24 us; of 4608 x 3584 - 8064 - 18 against 15 us).
+constexpr int64_t kFewTokens = 64, kFewTokensSmall = 128, kSmallCells = 7000;
 
-bool few_tokens_wanted(int64_t M)
+bool few_tokens_wanted(const Layout& L, int64_t M)
 {
     // (a forced tile or plan, tests and tuning: the tiled GEMMs)
-    return M <= kFewTokens && !debug_option(kDbgNoSkinny) &&
+    return (M <= kFewTokens || (M <= kFewTokensSmall && L.T * L.C <= kSmallCells)) && !debug_option(kDbgNoSkinny) &&
            (M <= 16 || (!debug_option(kDbgPrefillTile) && !debug_option(kDbgPrefill6Plan)));
 }
 
@@ -163,7 +164,7 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
     }
     // A few tokens (batched or speculative decoding) are still memory-bound: one pass over the
     // weights in the GEMV's streaming order, all tokens at once in the matrix cores.
-    if (few_tokens_wanted(M))
+    if (few_tokens_wanted(L, M))
         return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
                              static_cast<hipStream_t>(stream));
     // With the matrix-core plane and room for the activations' planes: the GEMM on the fp6 matrix instructions.
@@ -172,6 +173,9 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
         return launch_prefill6(static_cast<const uint8_t*>(packed), L, M, workspace, sx, bias, static_cast<float*>(y),
                                nullptr, static_cast<hipStream_t>(stream));
     }
+    if (ksplit8_wanted(L, M))
+        return launch_ksplit8(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
+                              static_cast<hipStream_t>(stream));
     return launch_prefill(static_cast<const uint8_t*>(packed), L, M, xq, sx, bias, static_cast<float*>(y), nullptr,
                           static_cast<hipStream_t>(stream));
 }
@@ -256,9 +260,13 @@ int prefill_fused_impl(const void* packed, int64_t M, int64_t N, int64_t K, int 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Layout L = layout_for(N, K, mode, out16);
     if (quant_packed_possible(K) && prefill_fits(M, N, K, mode)) {
-        if (few_tokens_wanted(M)) {
+        if (few_tokens_wanted(L, M)) {
             if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
             return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
+        }
+        if (!(planes && prefill6_wanted(L, M)) && ksplit8_wanted(L, M)) {
+            if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
+            return launch_ksplit8(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
         }
         if (planes && prefill6_wanted(L, M)) {
             if (int s = launch_quant_planes(x, M, K, prefill6_row_tiles(M), workspace, sx, st)) return s;

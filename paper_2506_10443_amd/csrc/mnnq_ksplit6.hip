@@ -125,6 +125,7 @@ __global__ __launch_bounds__(64 * KS) void ksplit6_kernel(const uint8_t* __restr
     do {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
+            if (u > 0 && g + u >= g1) break;      // (T is even: the last result is in d[1] either way)
             float s[TN];
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -163,6 +164,23 @@ __global__ __launch_bounds__(64 * KS) void ksplit6_kernel(const uint8_t* __restr
     for (int r = 0; r < 16; ++r) acc[T - 1][r] = fmaf(s_last, d[1][r], acc[T - 1][r]);
 
     // Sum over the waves in a fixed order: piece p = four rows per half of a tile (a float4 per lane), dealt to the waves.
+    // The scales and biases of a wave's pieces are requested before the exchange, which their latency would follow.
+    constexpr int NP = T * 4 / KS;
+    const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, M * 4);
+    const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, M * L.N * (L.out16 ? 2 : 4));
+    const int N = (int)L.N;
+    float bn[NP], sm[NP][4];
+    int m[NP], n[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int p = ks * NP + k, t = p / 4, q = p % 4;
+        m[k] = (tile_m * TM + t / TN) * 32 + 8 * q + 4 * (lane >> 5);   // the lane's four rows
+        n[k] = (tile_n * TN + t % TN) * 32 + (lane & 31);
+        bn[k] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n[k] * 4, 0, 0));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sm[k][r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m[k] + r) * 4, 0, 0));
+    }
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -170,29 +188,21 @@ __global__ __launch_bounds__(64 * KS) void ksplit6_kernel(const uint8_t* __restr
             lds_sum[(ks * T * 4 + t * 4 + q) * 64 + lane] =
                 make_float4(acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]);
     __syncthreads();
-    const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, M * 4);
-    const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
-    const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, M * L.N * (L.out16 ? 2 : 4));
-    const int N = (int)L.N;
 #pragma unroll
-    for (int k = 0; k < T * 4 / KS; ++k) {
-        const int p = ks * (T * 4 / KS) + k, t = p / 4, q = p % 4;
+    for (int k = 0; k < NP; ++k) {
+        const int p = ks * NP + k;
         float4 v = lds_sum[p * 64 + lane];
 #pragma unroll
         for (int w = 1; w < KS; ++w) {
             const float4 o = lds_sum[(w * T * 4 + p) * 64 + lane];
             v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
         }
-        const int m = (tile_m * TM + t / TN) * 32 + 8 * q + 4 * (lane >> 5);   // the lane's four rows
-        const int n = (tile_n * TN + t % TN) * 32 + (lane & 31);
-        const float bn = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n * 4, 0, 0));
         const float f[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float sm = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0));
-            const float o = fmaf(f[r], sm, bn);
+            const float o = fmaf(f[r], sm[k][r], bn[k]);
             // rows past M lie past the end of y
-            const int at = n < N ? ((m + r) * N + n) * (L.out16 ? 2 : 4) : kOutOfRange;
+            const int at = n[k] < N ? ((m[k] + r) * N + n[k]) * (L.out16 ? 2 : 4) : kOutOfRange;
             if (L.out16) {
                 const _Float16 h = (_Float16)o;
                 __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, h), rs_y, at, 0, 0);

@@ -1,0 +1,299 @@
+// Prefill GEMM on the int8 matrix instruction with K split over the waves of a workgroup: for the weight forms without a
+// matrix-core plane (int4 with a zero point or a float minimum, int8 bytes) wherever the tiled GEMM of mnnq_prefill.hip
+// leaves the chip partly idle.
+//
+// The tiled GEMM works on 128 x 128 outputs per workgroup: 333 tokens of a 4096-wide projection are 96 such tiles on 256
+// CUs.  Here a wave owns 64 x 64 outputs and a part of K, the KS waves of a workgroup share the tile and add their parts
+// through LDS at the end, in a fixed order.  The waves share no operand, so everything goes from L2 straight into
+// registers, refilled for the next chunk of 128 values as soon as it has been used, with no LDS and no barrier in the loop.
+// What bounds it is vector issue: per group of a 16 x 16 tile two instructions per output for the scale (three with a
+// float minimum) behind one matrix instruction; unpacking a column tile is shared by four row tiles.
+//
+// Operand layout and arithmetic as in mnnq_skinny.hip (A: 16 tokens x 64 k, B: 64 k x 16 weight rows, D: lane l holds
+// weight row l % 16, tokens 4 (l / 16) + r).
+#include "mnnq_common.h"
+
+namespace mnnq {
+
+namespace {
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+enum Form { kZp = 0, kMin = 1, kBytes = 2 };   // integer zero point; float minimum; int8 weights as bytes
+
+constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
+constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit8_possible): loads give 0, stores are dropped
+constexpr int kMagicBits = 0x4B400000;    // 1.5 * 2^23: see from_magic in mnnq_skinny.hip
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufFlags);
+}
+__device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
+__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
+
+constexpr int TM = 4, TN = 4, T = TM * TN;   // 16 x 16 tiles of a wave: 64 tokens x 64 weight rows
+
+// One column tile of one chunk.
+template <int FORM>
+struct Weights {
+    v4i w[FORM == kBytes ? 2 : 1];
+    v2f s, mn;
+    int z;
+};
+
+template <int FORM>
+__device__ __forceinline__ v4i unpack(const Weights<FORM>& r, int h, uint32_t zsel)
+{
+    if (FORM == kBytes) return r.w[FORM == kBytes ? h : 0];
+    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
+    const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
+    const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
+    if (FORM == kMin) return v4i{(int)n0, (int)n1, (int)n2, (int)n3};
+    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, h ? zsel + 0x01010101u : zsel);
+    return v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
+}
+
+template <int FORM, int KS>
+__global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
+                                                          const int8_t* __restrict__ xq, bool blocks,
+                                                          const float* __restrict__ sx, const float* __restrict__ bias,
+                                                          float* __restrict__ y, int MT, int NT)
+{
+    extern __shared__ __align__(16) float4 lds_sum[];   // [KS][T][64]
+    const int lane = threadIdx.x & 63, row = lane & 15, kb = lane >> 4;
+    const int ks = uniform(threadIdx.x >> 6);
+    // each XCD takes whole columns of tiles, so that a weight chunk is fetched into one L2 only
+    const int xcd = blockIdx.x % 8, seq = blockIdx.x / 8;
+    const int tile_m = seq % MT, tile_n = (seq / MT) * 8 + xcd;
+    if (tile_n >= NT) return;
+    const int C = (int)L.C, m0 = tile_m * 64;
+    const int c0 = C * ks / KS, c1 = C * (ks + 1) / KS;
+    const int odd_last = (L.G & 1) ? C - 1 : -1;
+
+    // activations: int8 rows, or the token blocks of launch_quant_token_blocks
+    const __amdgpu_buffer_rsrc_t rs_x = rsrc(xq, (int64_t)M * L.Kx);
+    const int x_step = blocks ? M * 64 : 64;            // bytes from group to group
+    int x_voff[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int first = m0 + i * 16, left = M - first, width = left < 16 ? left : 16;
+        x_voff[i] = row < width ? (blocks ? first * 64 + (kb * width + row) * 16 : (first + row) * (int)L.Kx + kb * 16)
+                                : kOutOfRange;
+    }
+    // weights: column tile j of this workgroup is row tile t0 + j of the layout (past the matrix: outside the buffers)
+    constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = FORM == kZp ? 32 : 128;
+    const int t0 = tile_n * TN;
+    const int live = (int)L.T - t0 < TN ? (int)L.T - t0 : TN;
+    const __amdgpu_buffer_rsrc_t rs_w = rsrc(packed + (int64_t)t0 * C * WB, (int64_t)live * C * WB);
+    const __amdgpu_buffer_rsrc_t rs_s = rsrc(packed + L.scales_off() + (int64_t)t0 * C * 128, (int64_t)live * C * 128);
+    const __amdgpu_buffer_rsrc_t rs_z = rsrc(packed + L.zeros_off() + (int64_t)t0 * C * ZB, (int64_t)live * C * ZB);
+    const uint32_t zsel = (row & 1) * 0x02020202u;
+
+    v4i a[2][TM];
+    // weights two chunks ahead (they come from HBM), activations one (from L2)
+    Weights<FORM> w[2][TN];
+    auto load_a = [&](int h, int i, int c) {
+        a[h][i] = __builtin_amdgcn_raw_buffer_load_b128(
+            rs_x, x_voff[i], uniform(c < c1 && (h == 0 || c != odd_last) ? (2 * c + h) * x_step : kOutOfRange), 0);
+    };
+    auto load_codes = [&](int u, int j, int h, int c) {   // (the byte form: a kilobyte per group; else both groups with h = 0)
+        const int off = uniform(c < c1 ? (j * C + c) * WB : kOutOfRange);
+        w[u][j].w[FORM == kBytes ? h : 0] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, lane * 16 + h * 1024, off, 0);
+    };
+    auto load_params = [&](int u, int j, int c) {
+        const int cell = uniform(j * C + c);
+        const bool have = c < c1;
+        w[u][j].s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_s, row * 8, uniform(have ? cell * 128 : kOutOfRange), 0));
+        if (FORM == kZp)
+            w[u][j].z = __builtin_amdgcn_raw_buffer_load_b32(rs_z, (row >> 1) * 4, uniform(have ? cell * ZB : kOutOfRange), 0);
+        else
+            w[u][j].mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_z, row * 8, uniform(have ? cell * ZB : kOutOfRange), 0));
+    };
+    // in the order of the loop's refills: the waits are counts
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (u == 1) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) load_a(h, i, c0);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (FORM == kBytes || h == 1) load_codes(u, j, FORM == kBytes ? h : 0, c0 + u);
+                if (h == 1) load_params(u, j, c0 + u);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
+    float acc[T][4];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[t][r] = 0.0f;
+
+    const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
+    const v4i zero4 = {0, 0, 0, 0};
+    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    int c = c0;
+    do {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (u == 1 && c + 1 >= c1) break;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            v4i b[TN];
+            float s[TN], mn[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                b[j] = unpack<FORM>(w[u][j], h, zsel);
+                s[j] = h ? w[u][j].s.y : w[u][j].s.x;
+                if (FORM != kZp) mn[j] = h ? w[u][j].mn.y : w[u][j].mn.x;
+            }
+            if (h == 1) {      // the second group is unpacked: the chunk's registers take the next chunk
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    // (copies: the refilled registers stay where they are)
+                    asm volatile("v_mov_b32 %0, %1" : "=v"(s[j]) : "v"(w[u][j].s.y));
+                    if (FORM != kZp) asm volatile("v_mov_b32 %0, %1" : "=v"(mn[j]) : "v"(w[u][j].mn.y));
+                    if (FORM != kBytes) load_codes(u, j, 0, c + u + 2);
+                    load_params(u, j, c + u + 2);
+                }
+            }
+            v4i d[2];
+            float xf[2][4];
+            v4i cbase = zero4;
+#pragma unroll
+            for (int t = 0; t <= T; ++t) {
+                if (t < T) {
+                    const int i = t / TN, j = t % TN;
+                    if (FORM == kZp) {
+                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], b[j], magic, 0, 0, 0);
+                    } else {
+                        if (j == 0) {
+                            // sums of the activations, for the minimum; byte form: and for the 128 that the bytes lack,
+                            // which the accumulator starts from - D + 128 xs as an integer (below 2^22)
+                            const v4i xs = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], ones, zero4, 0, 0, 0);
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) xf[i & 1][r] = (float)xs[r];
+                            if (FORM == kBytes) {
+#pragma unroll
+                                for (int r = 0; r < 4; ++r) cbase[r] = (xs[r] << 7) + kMagicBits;
+                            }
+                        }
+                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], b[j], FORM == kBytes ? cbase : magic, 0, 0, 0);
+                    }
+                    if (j == TN - 1) load_a(h, i, c + u + 1);
+                    if (FORM == kBytes && i == TM - 1) load_codes(u, j, h, c + u + 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (t > 0) {
+                    const int p = t - 1, i = p / TN, j = p % TN;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        acc[p][r] = fmaf(s[j], from_magic(d[p & 1][r]), acc[p][r]);
+                        if (FORM != kZp) acc[p][r] = fmaf(mn[j], xf[i & 1][r], acc[p][r]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+      }
+      c += 2;
+    } while (c < c1);
+
+    // Sum over the waves in a fixed order, the tiles dealt to the waves; their scales and biases are requested before the
+    // exchange, which their latency would follow.
+    constexpr int NP = T / KS;
+    const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, (int64_t)M * 4);
+    const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
+    const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, (int64_t)M * L.N * (L.out16 ? 2 : 4));
+    const int N = (int)L.N;
+    float bn[NP], sm[NP][4];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int t = ks * NP + k, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        bn[k] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n * 4, 0, 0));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sm[k][r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0));
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        lds_sum[(ks * T + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int t = ks * NP + k, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        float4 v = lds_sum[t * 64 + lane];
+#pragma unroll
+        for (int p = 1; p < KS; ++p) {
+            const float4 o = lds_sum[(p * T + t) * 64 + lane];
+            v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
+        const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float o = fmaf(f[r], sm[k][r], bn[k]);
+            const int at = n < N ? ((m + r) * N + n) * (L.out16 ? 2 : 4) : kOutOfRange;   // rows past M: past the end of y
+            if (L.out16) {
+                const _Float16 q = (_Float16)o;
+                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, q), rs_y, at, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(o), rs_y, at, 0, 0);
+            }
+        }
+    }
+}
+
+template <int FORM, int KS>
+int launch(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
+           const float* bias, float* y, hipStream_t st)
+{
+    const int MT = (int)((M + 63) / 64), NT = (int)((L.T + TN - 1) / TN);
+    constexpr size_t smem = (size_t)KS * T * 64 * 16;
+    static_assert(smem <= kLdsPerWorkgroup && T % KS == 0, "partial tiles in LDS");
+    auto kern = ksplit8_kernel<FORM, KS>;
+    static thread_local int allowed_dev = -1;
+    if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
+    const int64_t grid = (int64_t)MT * ((NT + 7) / 8) * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * KS), smem, st, packed, L, (int)M, xq, blocks, sx, bias, y, MT, NT);
+    MNNQ_HIP_TRY(hipGetLastError());
+    return MNNQ_OK;
+}
+
+template <int FORM>
+int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
+                const float* bias, float* y, hipStream_t st)
+{
+    const int64_t tiles = ((M + 63) / 64) * ((L.T + TN - 1) / TN);
+    if (tiles <= num_cus()) return launch<FORM, 8>(packed, L, M, xq, blocks, sx, bias, y, st);
+    return launch<FORM, 4>(packed, L, M, xq, blocks, sx, bias, y, st);
+}
+
+}  // namespace
+
+// At most three 64 x 64 tiles per CU: measured against the tiled GEMM (int4 / int8 bytes), 333 tokens of 4096 x 4096
+// 23.9 / 27.2 against 36.7 / 45.2 us, 512 tokens of 6144 x 4096 (three per CU) 34.9 / 43.3 against 39.4 / 47.8 us; at four
+// per CU (1024 tokens of 4096 x 4096) it loses 5 %, beyond more: with the chip full, the tiled form's sharing of operands
+// through LDS counts.
+bool ksplit8_wanted(const Layout& L, int64_t M)
+{
+    if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
+    if (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8) return false;     // (nibble planes: the tiled GEMM merges them)
+    const int64_t lim = kOutOfRange;                                 // 32-bit offsets
+    return ((M + 63) / 64) * ((L.T + TN - 1) / TN) <= 3 * (int64_t)num_cus() && (M + 64) * L.Kx < lim &&
+           (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 2048 < lim;
+}
+
+int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
+                   const float* bias, float* y, hipStream_t st)
+{
+    if (L.native8) return launch_form<kBytes>(packed, L, M, xq, blocks, sx, bias, y, st);
+    if (L.minf) return launch_form<kMin>(packed, L, M, xq, blocks, sx, bias, y, st);
+    return launch_form<kZp>(packed, L, M, xq, blocks, sx, bias, y, st);
+}
+
+}  // namespace mnnq

@@ -223,13 +223,22 @@ bool quant_packed_possible(int64_t K) { return K <= 5 * 4 * kPackThreads; }
 
 int launch_quant_token_blocks(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, hipStream_t st)
 {
-    return launch_quant_pack<1, kTokenBlocks>(x, M, K, 0, M, reinterpret_cast<uint8_t*>(xq), sx, st);
+    uint8_t* out = reinterpret_cast<uint8_t*>(xq);
+    if (M <= 256) return launch_quant_pack<1, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
+    if (M <= 640) return launch_quant_pack<2, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
+    return launch_quant_pack<4, kTokenBlocks>(x, M, K, 0, M, out, sx, st);   // (as for the planes below)
 }
 
 int launch_quant_planes(const float* x, int64_t M, int64_t K, int TMp, void* planes, float* sx, hipStream_t st)
 {
     // (rows up to the next whole block of 32 are written as zeros; the blocks behind are not read for results)
-    return launch_quant_pack<4, kPlanes>(x, M, K, TMp, (M + 31) / 32 * 32, static_cast<uint8_t*>(planes), sx, st);
+    // One row per workgroup fills more CUs, four rows make the stores whole lines: the lines lie where the measured times
+    // cross (K = 18944: 96 tokens 7 us faster with one row, 1024 tokens 11 us slower; two rows are best or even between).
+    const int64_t rows = (M + 31) / 32 * 32;
+    uint8_t* out = static_cast<uint8_t*>(planes);
+    if (rows <= 256) return launch_quant_pack<1, kPlanes>(x, M, K, TMp, rows, out, sx, st);
+    if (rows <= 640) return launch_quant_pack<2, kPlanes>(x, M, K, TMp, rows, out, sx, st);
+    return launch_quant_pack<4, kPlanes>(x, M, K, TMp, rows, out, sx, st);
 }
 
 int launch_quant_act(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, int32_t* xsum,

@@ -20,7 +20,7 @@ FORMS = {
 # (M, N, K): the last ones walk over several row tiles per workgroup, and stream a long row
 SHAPES = [(2, 16, 64), (3, 48, 192), (15, 80, 1536), (16, 32, 4096), (17, 48, 4160), (32, 64, 960), (33, 48, 512),
           (48, 32, 8960), (49, 16, 320), (64, 80, 3584), (4, 16 * 1100, 128), (40, 16 * 600, 256), (5, 32, 18944),
-          (2, 16, 24576)]
+          (2, 16, 24576), (81, 48, 1536), (128, 32, 320)]
 
 
 def dev(a):
@@ -72,3 +72,36 @@ def test_quantizer_writes_the_planes_of_the_two_steps(M, N, K):
     finally:
         B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", None)
     assert torch.equal(yf, y)
+
+
+# K split over the waves (65 tokens and more on layers too large for the few-token kernels): fewer chunks than waves, odd
+# shares, rows and columns past the tile, an odd number of groups, one and several tiles per CU
+GEMM_SHAPES = [(129, 48, 64), (130, 16, 192), (192, 80, 1088), (333, 272, 1536), (200, 1040, 640), (65, 16 * 520, 2048),
+               (700, 16 * 60, 256), (129, 32, 8960)]
+
+
+@pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
+@pytest.mark.parametrize("form", ["w4", "w4min", "w8"])
+def test_k_split_int8_gemm_matches_oracle(form, M, N, K):
+    mode, quant, linear = FORMS[form]
+    if form == "w8" and K % 128:
+        pytest.skip("int8 weights: K a multiple of 128")
+    print("K-split int8 GEMM", form, M, N, K, flush=True)
+    W = synth.weights(N, K, 3200 + M + N + K)
+    W[0, :64] = 0.25                                # a constant group
+    x = synth.activations(M, K, 3201 + M + N + K)
+    x[M // 2] = 0.0                                 # a zero token
+    q, s, z = quant(W)
+    xq, sx, _ = oracle.quant_act(x)
+    bias = synth.weights(1, N, 9)[0] * 10
+    y_o = linear(xq, sx, q, s, z, bias=bias, want_acc=False)[1]
+    tol = 1e-5 * np.abs(y_o).max()
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    bd, xd = dev(bias), dev(x)
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    y = B.mnnq_linear_prefill(packed, N, K, dev(xq), dev(sx), bias=bd, out=out[:M], mode=mode)
+    assert torch.isnan(out[M]).all()                # nothing behind the last token
+    assert np.abs(y.cpu().numpy() - y_o).max() <= tol
+    yf = B.mnnq_linear_prefill_fused(packed, N, K, xd, bias=bd, mode=mode)
+    assert torch.equal(yf, y)
+    assert torch.equal(B.mnnq_linear_prefill_fused_o16(packed, N, K, xd, bias=bd, mode=mode), yf.half())
