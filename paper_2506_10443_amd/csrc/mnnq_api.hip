@@ -214,8 +214,17 @@ int prefill_f16_impl(const void* packed, int64_t M, int64_t N, int64_t K, int gr
         }
         return MNNQ_OK;
     }
-    return launch_prefill_f16(static_cast<const uint8_t*>(packed), layout_for(N, K, mode, out16), M, x16, row_scale,
-                              bias, static_cast<float*>(y), static_cast<hipStream_t>(stream));
+    const Layout L = layout_for(N, K, mode, out16);
+    // (with a row factor the activations may be int8 codes: the tiled kernel adds the groups in the order of the tiled int8
+    // GEMM, whose result is then met bit for bit)
+    if (!row_scale && skinny_f16_wanted(L, M))
+        return launch_skinny_f16(static_cast<const uint8_t*>(packed), L, M, x16, bias, static_cast<float*>(y),
+                                 static_cast<hipStream_t>(stream));
+    if (!row_scale && ksplit_f16_wanted(L, M))
+        return launch_ksplit_f16(static_cast<const uint8_t*>(packed), L, M, x16, bias, static_cast<float*>(y),
+                                 static_cast<hipStream_t>(stream));
+    return launch_prefill_f16(static_cast<const uint8_t*>(packed), L, M, x16, row_scale, bias, static_cast<float*>(y),
+                              static_cast<hipStream_t>(stream));
 }
 
 // The fused calls: activation quantizer and linear layer in one call.

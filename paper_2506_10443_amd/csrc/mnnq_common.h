@@ -260,10 +260,17 @@ int launch_ksplit6(int form, const uint8_t* packed, const Layout& L, int64_t M, 
 // A few tokens sharing one pass over the weights; token_blocks: xq as launch_quant_token_blocks writes it.
 int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st);
-// The int8 GEMM with K split over the waves of a workgroup (mnnq_ksplit8.hip); token_blocks as for launch_skinny.
+// The same with fp16 activations.
+bool skinny_f16_wanted(const Layout& L, int64_t M);
+int launch_skinny_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,
+                      hipStream_t st);
+// The GEMMs with K split over the waves of a workgroup (mnnq_ksplit.hip); token_blocks as for launch_skinny.
 bool ksplit8_wanted(const Layout& L, int64_t M);
 int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,
                    const float* bias, float* y, hipStream_t st);
+bool ksplit_f16_wanted(const Layout& L, int64_t M);
+int launch_ksplit_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,
+                      hipStream_t st);
 int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x16, const float* bias,
                       float* y, hipStream_t st);
 // rs: optional per-row factor applied to the fp32 sums before the bias (NULL = none).

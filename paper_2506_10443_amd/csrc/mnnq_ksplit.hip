@@ -1,13 +1,14 @@
-// Prefill GEMM on the int8 matrix instruction with K split over the waves of a workgroup: for the weight forms without a
-// matrix-core plane (int4 with a zero point or a float minimum, int8 bytes) wherever the tiled GEMM of mnnq_prefill.hip
-// leaves the chip partly idle.
+// Prefill GEMM on the int8 and fp16 matrix instructions with K split over the waves of a workgroup: for the weight forms
+// without a matrix-core plane (int4 with a zero point or a float minimum, int8 bytes; int4 and nibble planes with fp16
+// activations) wherever the tiled GEMMs of mnnq_prefill.hip and mnnq_prefill_f16.hip leave the chip partly idle.
 //
 // The tiled GEMM works on 128 x 128 outputs per workgroup: 333 tokens of a 4096-wide projection are 96 such tiles on 256
 // CUs.  Here a wave owns 64 x 64 outputs and a part of K, the KS waves of a workgroup share the tile and add their parts
 // through LDS at the end, in a fixed order.  The waves share no operand, so everything goes from L2 straight into
 // registers, refilled for the next chunk of 128 values as soon as it has been used, with no LDS and no barrier in the loop.
 // What bounds it is vector issue: per group of a 16 x 16 tile two instructions per output for the scale (three with a
-// float minimum) behind one matrix instruction; unpacking a column tile is shared by four row tiles.
+// float minimum) behind one matrix instruction - with fp16 activations one behind two, and twice the unpacking -;
+// unpacking a column tile is shared by four row tiles.
 //
 // Operand layout and arithmetic as in mnnq_skinny.hip (A: 16 tokens x 64 k, B: 64 k x 16 weight rows, D: lane l holds
 // weight row l % 16, tokens 4 (l / 16) + r).
@@ -18,9 +19,15 @@ namespace mnnq {
 namespace {
 
 typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
-enum Form { kZp = 0, kMin = 1, kBytes = 2 };   // integer zero point; float minimum; int8 weights as bytes
+// Weights with an integer zero point or a float minimum, int8 weights as bytes; the first two with fp16 activations.
+enum Form { kZp = 0, kMin = 1, kBytes = 2, kZpF16 = 3, kMinF16 = 4 };
+constexpr bool is_f16(int form) { return form >= kZpF16; }
+constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
 
 constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
 constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit8_possible): loads give 0, stores are dropped
@@ -44,21 +51,57 @@ struct Weights {
     int z;
 };
 
+// The B operands of a group: one register quad of int8, or two of halves (see halves8 in mnnq_skinny.hip).
 template <int FORM>
-__device__ __forceinline__ v4i unpack(const Weights<FORM>& r, int h, uint32_t zsel)
+struct Operand {
+    v4i q[is_f16(FORM) ? 2 : 1];
+};
+
+__device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
 {
-    if (FORM == kBytes) return r.w[FORM == kBytes ? h : 0];
+    const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
+    auto pair = [&](uint32_t v, uint32_t sel) {
+        return __builtin_bit_cast(int, __builtin_bit_cast(h2, __builtin_amdgcn_perm(0x64646464u, v, sel)) - zb);
+    };
+    return v4i{pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u)};
+}
+
+__device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
+}
+
+template <int FORM>
+__device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, uint32_t zsel)
+{
+    Operand<FORM> o;
+    if (FORM == kBytes) {
+        o.q[0] = r.w[FORM == kBytes ? h : 0];
+        return o;
+    }
     const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
+    const uint32_t sel = h ? zsel + 0x01010101u : zsel;      // the byte of the lane's row and group
+    if (is_f16(FORM)) {
+        const h2 zb = __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, (sel & 0x00ff00ffu) | 0x04000400u)
+                                                            : 0x64006400u);
+        o.q[0] = halves8(w0, zb);
+        o.q[is_f16(FORM) ? 1 : 0] = halves8(w1, zb);
+        return o;
+    }
     const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
     const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
-    if (FORM == kMin) return v4i{(int)n0, (int)n1, (int)n2, (int)n3};
-    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, h ? zsel + 0x01010101u : zsel);
-    return v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
+    if (FORM == kMin) {
+        o.q[0] = v4i{(int)n0, (int)n1, (int)n2, (int)n3};
+        return o;
+    }
+    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, sel);
+    o.q[0] = v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
+    return o;
 }
 
 template <int FORM, int KS>
-__global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                          const int8_t* __restrict__ xq, bool blocks,
+__global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
+                                                          const void* __restrict__ xq, bool blocks,
                                                           const float* __restrict__ sx, const float* __restrict__ bias,
                                                           float* __restrict__ y, int MT, int NT)
 {
@@ -73,18 +116,21 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
     const int c0 = C * ks / KS, c1 = C * (ks + 1) / KS;
     const int odd_last = (L.G & 1) ? C - 1 : -1;
 
-    // activations: int8 rows, or the token blocks of launch_quant_token_blocks
-    const __amdgpu_buffer_rsrc_t rs_x = rsrc(xq, (int64_t)M * L.Kx);
-    const int x_step = blocks ? M * 64 : 64;            // bytes from group to group
+    // activations: int8 or fp16 rows, or the token blocks of launch_quant_token_blocks; chunk c of the packed axis meets
+    // chunk c % Cx of the row
+    constexpr int E = is_f16(FORM) ? 2 : 1;
+    const int Cx = (int)L.Cx;
+    const __amdgpu_buffer_rsrc_t rs_x = rsrc(xq, (int64_t)M * L.Kx * E);
+    const int x_step = blocks ? M * 64 : 64 * E;        // bytes from group to group
     int x_voff[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int first = m0 + i * 16, left = M - first, width = left < 16 ? left : 16;
-        x_voff[i] = row < width ? (blocks ? first * 64 + (kb * width + row) * 16 : (first + row) * (int)L.Kx + kb * 16)
+        x_voff[i] = row < width ? (blocks ? first * 64 + (kb * width + row) * 16 : (first + row) * (int)L.Kx * E + kb * 16 * E)
                                 : kOutOfRange;
     }
     // weights: column tile j of this workgroup is row tile t0 + j of the layout (past the matrix: outside the buffers)
-    constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = FORM == kZp ? 32 : 128;
+    constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = has_zero(FORM) ? 32 : 128;
     const int t0 = tile_n * TN;
     const int live = (int)L.T - t0 < TN ? (int)L.T - t0 : TN;
     const __amdgpu_buffer_rsrc_t rs_w = rsrc(packed + (int64_t)t0 * C * WB, (int64_t)live * C * WB);
@@ -92,12 +138,14 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
     const __amdgpu_buffer_rsrc_t rs_z = rsrc(packed + L.zeros_off() + (int64_t)t0 * C * ZB, (int64_t)live * C * ZB);
     const uint32_t zsel = (row & 1) * 0x02020202u;
 
-    v4i a[2][TM];
+    v4i a[2][TM][E];
     // weights two chunks ahead (they come from HBM), activations one (from L2)
     Weights<FORM> w[2][TN];
     auto load_a = [&](int h, int i, int c) {
-        a[h][i] = __builtin_amdgcn_raw_buffer_load_b128(
-            rs_x, x_voff[i], uniform(c < c1 && (h == 0 || c != odd_last) ? (2 * c + h) * x_step : kOutOfRange), 0);
+        const int cx = c >= Cx ? c - Cx : c;
+        const int off = uniform(c < c1 && (h == 0 || c != odd_last) ? (2 * cx + h) * x_step : kOutOfRange);
+#pragma unroll
+        for (int e = 0; e < E; ++e) a[h][i][e] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_voff[i] + e * 16, off, 0);
     };
     auto load_codes = [&](int u, int j, int h, int c) {   // (the byte form: a kilobyte per group; else both groups with h = 0)
         const int off = uniform(c < c1 ? (j * C + c) * WB : kOutOfRange);
@@ -107,7 +155,7 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
         const int cell = uniform(j * C + c);
         const bool have = c < c1;
         w[u][j].s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_s, row * 8, uniform(have ? cell * 128 : kOutOfRange), 0));
-        if (FORM == kZp)
+        if (has_zero(FORM))
             w[u][j].z = __builtin_amdgcn_raw_buffer_load_b32(rs_z, (row >> 1) * 4, uniform(have ? cell * ZB : kOutOfRange), 0);
         else
             w[u][j].mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_z, row * 8, uniform(have ? cell * ZB : kOutOfRange), 0));
@@ -138,6 +186,8 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
     const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
     const v4i zero4 = {0, 0, 0, 0};
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    const v4i onesh = {0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00};
+    const v4f zerof = {0.0f, 0.0f, 0.0f, 0.0f};
     int c = c0;
     do {
 #pragma unroll
@@ -145,20 +195,20 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
         if (u == 1 && c + 1 >= c1) break;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            v4i b[TN];
+            Operand<FORM> b[TN];
             float s[TN], mn[TN];
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 b[j] = unpack<FORM>(w[u][j], h, zsel);
                 s[j] = h ? w[u][j].s.y : w[u][j].s.x;
-                if (FORM != kZp) mn[j] = h ? w[u][j].mn.y : w[u][j].mn.x;
+                if (!has_zero(FORM)) mn[j] = h ? w[u][j].mn.y : w[u][j].mn.x;
             }
             if (h == 1) {      // the second group is unpacked: the chunk's registers take the next chunk
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
                     // (copies: the refilled registers stay where they are)
                     asm volatile("v_mov_b32 %0, %1" : "=v"(s[j]) : "v"(w[u][j].s.y));
-                    if (FORM != kZp) asm volatile("v_mov_b32 %0, %1" : "=v"(mn[j]) : "v"(w[u][j].mn.y));
+                    if (!has_zero(FORM)) asm volatile("v_mov_b32 %0, %1" : "=v"(mn[j]) : "v"(w[u][j].mn.y));
                     if (FORM != kBytes) load_codes(u, j, 0, c + u + 2);
                     load_params(u, j, c + u + 2);
                 }
@@ -170,13 +220,16 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
             for (int t = 0; t <= T; ++t) {
                 if (t < T) {
                     const int i = t / TN, j = t % TN;
-                    if (FORM == kZp) {
-                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], b[j], magic, 0, 0, 0);
-                    } else {
-                        if (j == 0) {
-                            // sums of the activations, for the minimum; byte form: and for the 128 that the bytes lack,
-                            // which the accumulator starts from - D + 128 xs as an integer (below 2^22)
-                            const v4i xs = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], ones, zero4, 0, 0, 0);
+                    constexpr int X = E - 1;
+                    if (!has_zero(FORM) && j == 0) {
+                        // sums of the activations, for the minimum; byte form: and for the 128 that the bytes lack,
+                        // which the accumulator starts from - D + 128 xs as an integer (below 2^22)
+                        if (is_f16(FORM)) {
+                            const v4f xs = mfma_f16(a[h][i][X], onesh, mfma_f16(a[h][i][0], onesh, zerof));
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) xf[i & 1][r] = xs[r];
+                        } else {
+                            const v4i xs = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], ones, zero4, 0, 0, 0);
 #pragma unroll
                             for (int r = 0; r < 4; ++r) xf[i & 1][r] = (float)xs[r];
                             if (FORM == kBytes) {
@@ -184,8 +237,11 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
                                 for (int r = 0; r < 4; ++r) cbase[r] = (xs[r] << 7) + kMagicBits;
                             }
                         }
-                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i], b[j], FORM == kBytes ? cbase : magic, 0, 0, 0);
                     }
+                    if (is_f16(FORM))
+                        d[t & 1] = __builtin_bit_cast(v4i, mfma_f16(a[h][i][X], b[j].q[X], mfma_f16(a[h][i][0], b[j].q[0], zerof)));
+                    else
+                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], b[j].q[0], FORM == kBytes ? cbase : magic, 0, 0, 0);
                     if (j == TN - 1) load_a(h, i, c + u + 1);
                     if (FORM == kBytes && i == TM - 1) load_codes(u, j, h, c + u + 2);
                     __builtin_amdgcn_sched_barrier(0);
@@ -194,8 +250,9 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
                     const int p = t - 1, i = p / TN, j = p % TN;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        acc[p][r] = fmaf(s[j], from_magic(d[p & 1][r]), acc[p][r]);
-                        if (FORM != kZp) acc[p][r] = fmaf(mn[j], xf[i & 1][r], acc[p][r]);
+                        const float v = is_f16(FORM) ? __int_as_float(d[p & 1][r]) : from_magic(d[p & 1][r]);
+                        acc[p][r] = fmaf(s[j], v, acc[p][r]);
+                        if (!has_zero(FORM)) acc[p][r] = fmaf(mn[j], xf[i & 1][r], acc[p][r]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -218,7 +275,7 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
         const int t = ks * NP + k, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
         bn[k] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n * 4, 0, 0));
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sm[k][r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0));
+        for (int r = 0; r < 4; ++r) sm[k][r] = sx ? __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0)) : 1.0f;
     }
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -249,13 +306,13 @@ __global__ __launch_bounds__(64 * KS) void ksplit8_kernel(const uint8_t* __restr
 }
 
 template <int FORM, int KS>
-int launch(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
+int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
            const float* bias, float* y, hipStream_t st)
 {
     const int MT = (int)((M + 63) / 64), NT = (int)((L.T + TN - 1) / TN);
     constexpr size_t smem = (size_t)KS * T * 64 * 16;
     static_assert(smem <= kLdsPerWorkgroup && T % KS == 0, "partial tiles in LDS");
-    auto kern = ksplit8_kernel<FORM, KS>;
+    auto kern = ksplit_kernel<FORM, KS>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
     const int64_t grid = (int64_t)MT * ((NT + 7) / 8) * 8;
@@ -265,7 +322,7 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, 
 }
 
 template <int FORM>
-int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
+int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
                 const float* bias, float* y, hipStream_t st)
 {
     const int64_t tiles = ((M + 63) / 64) * ((L.T + TN - 1) / TN);
@@ -294,6 +351,23 @@ int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8
     if (L.native8) return launch_form<kBytes>(packed, L, M, xq, blocks, sx, bias, y, st);
     if (L.minf) return launch_form<kMin>(packed, L, M, xq, blocks, sx, bias, y, st);
     return launch_form<kZp>(packed, L, M, xq, blocks, sx, bias, y, st);
+}
+
+// At most two 64 x 64 tiles per CU: 128 tokens of 4096 x 14336 63 against 135 us tiled, 512 tokens (two per CU) 121
+// against 133 us; 512 tokens of 4608 x 3584 (2.25 per CU) 49 against 38 us.
+bool ksplit_f16_wanted(const Layout& L, int64_t M)
+{
+    if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
+    const int64_t lim = kOutOfRange;                                 // 32-bit offsets
+    return ((M + 63) / 64) * ((L.T + TN - 1) / TN) <= 2 * (int64_t)num_cus() && (M + 64) * L.Kx * 2 < lim &&
+           (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 1024 < lim;
+}
+
+int launch_ksplit_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,
+                      hipStream_t st)
+{
+    if (L.minf) return launch_form<kMinF16>(packed, L, M, x16, false, nullptr, bias, y, st);
+    return launch_form<kZpF16>(packed, L, M, x16, false, nullptr, bias, y, st);
 }
 
 }  // namespace mnnq

@@ -33,7 +33,14 @@ namespace {
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-enum Form { kZp = 0, kMin = 1, kBytes = 2 };   // integer zero point; float minimum; int8 weights as bytes
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+// Weights with an integer zero point or a float minimum, int8 weights as bytes; the first two with fp16 activations.
+enum Form { kZp = 0, kMin = 1, kBytes = 2, kZpF16 = 3, kMinF16 = 4 };
+constexpr bool is_f16(int form) { return form >= kZpF16; }
+constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
 
 template <int FORM>
 struct WeightRegs {
@@ -63,7 +70,7 @@ struct TileBuffers {
     {
         const bool have = tile < L.T;
         const int64_t first = have ? tile * L.C : 0, n = have ? L.C : 0;   // (K <= 2^24: under 2^28 bytes)
-        constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = FORM == kZp ? 32 : 128;
+        constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = has_zero(FORM) ? 32 : 128;
         w = rsrc(packed + first * WB, n * WB);
         s = rsrc(packed + L.scales_off() + first * 128, n * 128);
         z = rsrc(packed + L.zeros_off() + first * ZB, n * ZB);
@@ -77,7 +84,7 @@ struct TileBuffers {
         if (FORM == kBytes)
             r.w[FORM == kBytes ? 1 : 0] = __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16 + 1024, off * 2048, 2);
         r.s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(s, row * 8, off * 128, 0));
-        if (FORM == kZp) r.z = __builtin_amdgcn_raw_buffer_load_b32(z, (row >> 1) * 4, off * 32, 0);
+        if (has_zero(FORM)) r.z = __builtin_amdgcn_raw_buffer_load_b32(z, (row >> 1) * 4, off * 32, 0);
         else r.mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(z, row * 8, off * 128, 0));
         return r;
     }
@@ -101,6 +108,30 @@ __device__ __forceinline__ v4i unpack_group(const WeightRegs<FORM>& r, int h, ui
     return v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
 }
 
+// Eight codes (dword w) as halves q - z in natural order: a byte c under the high byte 0x64 is the half 1024 + c, and
+// subtracting the half 1024 + z (zb, twice) leaves c - z exactly (float minimum: 1024, the codes stay as they are).
+__device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
+{
+    const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
+    auto pair = [&](uint32_t v, uint32_t sel) {
+        return __builtin_bit_cast(int, __builtin_bit_cast(h2, __builtin_amdgcn_perm(0x64646464u, v, sel)) - zb);
+    };
+    return v4i{pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u)};
+}
+
+template <int FORM>
+__device__ __forceinline__ h2 half_zero(const WeightRegs<FORM>& r, int h, uint32_t zsel)
+{
+    // (bytes 1 and 3 of the selector pick 0x64)
+    const uint32_t sel = ((h ? zsel + 0x01010101u : zsel) & 0x00ff00ffu) | 0x04000400u;
+    return __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, sel) : 0x64006400u);
+}
+
+__device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
+}
+
 // float(I) from a matrix instruction that accumulated on the bit pattern of 1.5 * 2^23: the register holds
 // 0x4B400000 + I, i.e. the float 12582912 + I (|I| < 2^22), and one exact subtraction - full rate, unlike a convert -
 // leaves I.
@@ -112,56 +143,73 @@ __device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 
 // before are scaled and added.
 template <int TM, int FORM>
 struct Pending {
-    v4i d[TM], xs[FORM == kZp ? 1 : TM];
+    v4i d[TM], xs[has_zero(FORM) ? 1 : TM];     // (fp16 activations: the bits of floats)
     float s, mn;
     __device__ __forceinline__ Pending() : s(0.0f), mn(0.0f)   // (nothing yet: zeros, whatever the form makes of them)
     {
-        const int z = FORM == kBytes ? 0 : kMagicBits;
+        const int z = FORM == kZp || FORM == kMin ? kMagicBits : 0;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
             d[t] = v4i{z, z, z, z};
-            if (FORM != kZp) xs[t] = v4i{0, 0, 0, 0};
+            if (!has_zero(FORM)) xs[t] = v4i{0, 0, 0, 0};
         }
     }
     __device__ __forceinline__ void add(int t, float (&acc)[TM][4]) const
     {
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-            if (FORM == kZp) {
-                acc[t][rr] = fmaf(s, from_magic(d[t][rr]), acc[t][rr]);
-            } else {
-                const int x = xs[FORM == kZp ? 0 : t][rr];
-                // byte form: sum xq q8 = D + 128 xs as an integer (below 2^22) before it meets the step
-                const float i = FORM == kMin ? from_magic(d[t][rr]) : (float)(d[t][rr] + (x << 7));
-                acc[t][rr] = fmaf(s, i, acc[t][rr]);
-                acc[t][rr] = fmaf(mn, (float)x, acc[t][rr]);
-            }
+            const int v = d[t][rr], x = has_zero(FORM) ? 0 : xs[has_zero(FORM) ? 0 : t][rr];
+            // byte form: sum xq q8 = D + 128 xs as an integer (below 2^22) before it meets the step
+            const float i = is_f16(FORM) ? __int_as_float(v) : FORM == kBytes ? (float)(v + (x << 7)) : from_magic(v);
+            acc[t][rr] = fmaf(s, i, acc[t][rr]);
+            if (!has_zero(FORM)) acc[t][rr] = fmaf(mn, is_f16(FORM) ? __int_as_float(x) : (float)x, acc[t][rr]);
         }
     }
 };
 
+// A operands of one chunk: per group and token block 16 consecutive k of a token per lane - one register quad of int8
+// codes, or two of halves (for the two matrix instructions of 32 k a group takes; the weights follow suit).
+template <int TM, int FORM>
+using ActRegs = v4i[2][TM][is_f16(FORM) ? 2 : 1];
+
 // One chunk: both groups of 16 weight rows against TM blocks of 16 tokens.
 template <int TM, int FORM>
-__device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const v4i (&a)[2][TM], uint32_t zsel,
+__device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const ActRegs<TM, FORM>& a, uint32_t zsel,
                                          Pending<TM, FORM>& p, float (&acc)[TM][4])
 {
     const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
     const v4i zero = {0, 0, 0, 0};
+    const v4f zerof = {0.0f, 0.0f, 0.0f, 0.0f};
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    const v4i onesh = {0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const v4i b = unpack_group<FORM>(r, h, zsel);
+        v4i b, b1;
+        if (is_f16(FORM)) {
+            const h2 zb = half_zero<FORM>(r, h, zsel);
+            b = halves8((uint32_t)(h ? r.w[0].z : r.w[0].x), zb);
+            b1 = halves8((uint32_t)(h ? r.w[0].w : r.w[0].y), zb);
+        } else {
+            b = unpack_group<FORM>(r, h, zsel);
+        }
         Pending<TM, FORM> n;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
-            n.d[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t], b, FORM == kBytes ? zero : magic, 0, 0, 0);
-            if (FORM != kZp) n.xs[FORM == kZp ? 0 : t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t], ones, zero, 0, 0, 0);
+            constexpr int X = is_f16(FORM) ? 1 : 0;
+            const int tx = has_zero(FORM) ? 0 : t;
+            if (is_f16(FORM)) {
+                n.d[t] = __builtin_bit_cast(v4i, mfma_f16(a[h][t][X], b1, mfma_f16(a[h][t][0], b, zerof)));
+                if (!has_zero(FORM)) n.xs[tx] = __builtin_bit_cast(v4i, mfma_f16(a[h][t][X], onesh, mfma_f16(a[h][t][0], onesh, zerof)));
+            } else {
+                n.d[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t][0], b, FORM == kBytes ? zero : magic, 0, 0, 0);
+                if (!has_zero(FORM)) n.xs[tx] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t][0], ones, zero, 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
             p.add(t, acc);
             __builtin_amdgcn_sched_barrier(0);
         }
         n.s = h ? r.s.y : r.s.x;
-        if (FORM != kZp) n.mn = h ? r.mn.y : r.mn.x;
+        if (!has_zero(FORM)) n.mn = h ? r.mn.y : r.mn.x;
         p = n;
     }
 }
@@ -171,32 +219,36 @@ __device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const v4i (&
 // the last block as narrow as its tokens): there a wave reads one contiguous piece per group and block, and the
 // few-token kernels, which are bound by this traffic from L2 where K is long, gain a third (48 tokens, 3584 x 18944:
 // 32 -> 22 us).  Chunk c of the packed axis meets chunk c % Cx of the row; an odd row's last chunk has one group only.
-template <int TM>
+template <int TM, int FORM>
 struct Acts {
+    static constexpr int E = is_f16(FORM) ? 2 : 1;     // bytes of a value
     __amdgpu_buffer_rsrc_t x;
     int voff[TM];
     int Cx, odd_last, step;     // step: bytes from group to group
-    __device__ __forceinline__ Acts(const int8_t* __restrict__ xq, const Layout& L, int M, bool blocks, int m0, int lane)
-        : x(rsrc(xq, (int64_t)M * L.Kx)), Cx((int)L.Cx), odd_last((L.G & 1) ? (int)L.C - 1 : -1), step(blocks ? M * 64 : 64)
+    __device__ __forceinline__ Acts(const void* __restrict__ xp, const Layout& L, int M, bool blocks, int m0, int lane)
+        : x(rsrc(xp, (int64_t)M * L.Kx * E)), Cx((int)L.Cx), odd_last((L.G & 1) ? (int)L.C - 1 : -1),
+          step(blocks ? M * 64 : 64 * E)
     {
         const int kb = lane >> 4;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
             const int first = m0 + t * 16, left = M - first, width = left < 16 ? left : 16, m = lane & 15;
-            const int at = blocks ? first * 64 + (kb * width + m) * 16 : (first + m) * (int)L.Kx + kb * 16;
+            const int at = blocks ? first * 64 + (kb * width + m) * 16 : (first + m) * (int)L.Kx * E + kb * 16 * E;
             voff[t] = m < width ? at : kOutOfRange;      // (tokens past M: zeros, no traffic)
         }
     }
-    __device__ __forceinline__ void load(v4i (&a)[2][TM], int c, bool have) const
+    __device__ __forceinline__ void load(ActRegs<TM, FORM>& a, int c, bool have) const
     {
         const int cx = c >= Cx ? c - Cx : c;
         const int o0 = __builtin_amdgcn_readfirstlane(have ? 2 * cx * step : kOutOfRange);
         const int o1 = __builtin_amdgcn_readfirstlane(have && c != odd_last ? (2 * cx + 1) * step : kOutOfRange);
 #pragma unroll
-        for (int t = 0; t < TM; ++t) {
-            a[0][t] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t], o0, 0);
-            a[1][t] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t], o1, 0);
-        }
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                a[0][t][e] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t] + e * 16, o0, 0);
+                a[1][t][e] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t] + e * 16, o1, 0);
+            }
     }
 };
 
@@ -219,6 +271,7 @@ struct Output {
     // Requests the slice's scales (first wave; a lane per token, tokens past M: zeros), to be stored before a barrier.
     static __device__ __forceinline__ float fetch_sx(const float* __restrict__ sxp, int M, int m0, int lane)
     {
+        if (!sxp) return 1.0f;      // (fp16 activations have no scales)
         return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc(sxp, (int64_t)M * 4), (m0 + lane) * 4, 0, 0));
     }
     __device__ __forceinline__ void store(const float4* part, int turn, int64_t tile, float bias) const
@@ -251,7 +304,7 @@ struct Output {
 
 template <int TM, int NCH, int FORM, int MAXW>
 __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                                const int8_t* __restrict__ xq, bool blocks,
+                                                                const void* __restrict__ xq, bool blocks,
                                                                 const float* __restrict__ sx,
                                                                 const float* __restrict__ bias, float* __restrict__ y)
 {
@@ -269,8 +322,8 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
     const Output<TM> out(y, lds_sx, L, M, m0, ks, KS, lane);
     const float sx_own = out.fetch_sx(sx, M, m0, lane);
     const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
-    const Acts<TM> acts(xq, L, M, blocks, m0, lane);
-    v4i a[NCH][2][TM];
+    const Acts<TM, FORM> acts(xq, L, M, blocks, m0, lane);
+    ActRegs<TM, FORM> a[NCH];
 #pragma unroll
     for (int u = 0; u < NCH; ++u) acts.load(a[u], c0 + u, u < own);
 
@@ -322,7 +375,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
 
 template <int TM, int DEPTH, int FORM, int MAXW>
 __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                              const int8_t* __restrict__ xq, bool blocks,
+                                                              const void* __restrict__ xq, bool blocks,
                                                               const float* __restrict__ sx,
                                                               const float* __restrict__ bias, float* __restrict__ y)
 {
@@ -342,9 +395,9 @@ __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __
     const float sx_own = out.fetch_sx(sx, M, m0, lane);
     const float b = __int_as_float(
         __builtin_amdgcn_raw_buffer_load_b32(rsrc(bias, bias ? L.N * 4 : 0), ((int)tile * kTileN + row) * 4, 0, 0));
-    const Acts<TM> acts(xq, L, M, blocks, m0, lane);
+    const Acts<TM, FORM> acts(xq, L, M, blocks, m0, lane);
     const TileBuffers<FORM> weights(packed, L, tile);
-    v4i a[DEPTH][2][TM];
+    ActRegs<TM, FORM> a[DEPTH];
     WeightRegs<FORM> cur[DEPTH];
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
@@ -387,12 +440,18 @@ struct FewPlan {
     int ks;      // waves of a workgroup
 };
 
-// Waves a CU holds, by registers: sixteen (128 registers each) or eight (256).
+// Waves a CU holds, by registers: sixteen (128 registers each) or eight (256); 0: the operands do not fit.
 constexpr int resident_waves(int tm, int nch, int form)
 {
+    if (is_f16(form)) {     // 16 TM registers per chunk
+        if (tm * nch > 8) return 0;
+        return tm * nch <= 2 || (tm * nch <= 4 && form == kZpF16 && tm == 2) ? 16 : 8;
+    }
     return tm == 1 || (nch == 2 && (tm == 2 || (tm == 3 && form == kZp))) ? 16 : 8;
 }
-constexpr int stream_waves(int tm) { return tm == 1 ? 16 : 8; }
+constexpr int stream_waves(int tm, int form) { return tm == 1 && !(form == kMinF16) ? 16 : 8; }
+// chunks in flight in the streaming form: what the registers hold without spilling
+constexpr int stream_depth(int tm, int form) { return is_f16(form) ? (tm == 1 ? 3 : tm <= 2 ? 4 : 2) : (tm <= 3 ? 4 : 3); }
 
 FewPlan few_plan(const Layout& L, int tm, int form)
 {
@@ -402,20 +461,19 @@ FewPlan few_plan(const Layout& L, int tm, int form)
     // short rows of layers with few row tiles: two chunks per wave, twice the waves
     int nch = 4;
     if (L.T <= 2 * (int64_t)num_cus() && (C + 1) / 2 <= 8) nch = 2;
-    if (const char* e = debug_option(kDbgDecodeWaves)) { const int v = atoi(e); if ((v == 2 || v == 4) && fits(v)) nch = v; }
+    if (!fits(nch) && fits(2)) nch = 2;
     int64_t ks = (C + nch - 1) / nch;
     p.resident = fits(nch);
     if (const char* e = debug_option(kDbgSkinnyStaged)) p.resident = p.resident && e[0] == '1';   // tests
     if (!p.resident) {
-        ks = stream_waves(tm);
+        ks = stream_waves(tm, form);
         if (C < ks) ks = C;
     }
     if (const char* e = debug_option(kDbgDecodeKsplit)) {   // tests and tuning: force the split
         const int v = atoi(e);
-        if (v >= 1 && v <= stream_waves(tm) && v <= C) {
+        if (v >= 1 && v <= stream_waves(tm, form) && v <= C) {
+            p.resident = p.resident && (C + v - 1) / v <= nch;
             ks = v;
-            if ((C + v - 1) / v > 4) p.resident = false;
-            else nch = 4;
         }
     }
     p.nch = nch;
@@ -424,7 +482,7 @@ FewPlan few_plan(const Layout& L, int tm, int form)
 }
 
 template <int TM, int FORM>
-int launch_form(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, bool blocks, const float* sx, const float* bias,
+int launch_form(const uint8_t* packed, const Layout& L, int M, const void* xq, bool blocks, const float* sx, const float* bias,
                 float* y, hipStream_t st)
 {
     const FewPlan p = few_plan(L, TM, FORM);
@@ -442,19 +500,19 @@ int launch_form(const uint8_t* packed, const Layout& L, int M, const int8_t* xq,
             MNNQ_HIP_TRY(hipGetLastError());
             return MNNQ_OK;
         };
-        if (p.nch == 2) return go(few_resident_kernel<TM, 2, FORM, resident_waves(TM, 2, FORM)>, allowed[0]);
-        return go(few_resident_kernel<TM, 4, FORM, resident_waves(TM, 4, FORM)>, allowed[1]);
+        if constexpr (resident_waves(TM, 4, FORM) != 0)
+            if (p.nch == 4) return go(few_resident_kernel<TM, 4, FORM, resident_waves(TM, 4, FORM)>, allowed[1]);
+        return go(few_resident_kernel<TM, 2, FORM, resident_waves(TM, 2, FORM)>, allowed[0]);
     }
-    constexpr int DEPTH = TM <= 3 ? 4 : 3;   // (8 TM + 7 registers per chunk in flight; more would spill)
     const size_t smem = (size_t)p.ks * TM * 64 * 16 + 256;
-    hipLaunchKernelGGL((few_stream_kernel<TM, DEPTH, FORM, stream_waves(TM)>), dim3((unsigned)L.T, slices), dim3(64 * p.ks),
-                       smem, st, packed, L, M, xq, blocks, sx, bias, y);
+    hipLaunchKernelGGL((few_stream_kernel<TM, stream_depth(TM, FORM), FORM, stream_waves(TM, FORM)>), dim3((unsigned)L.T, slices),
+                       dim3(64 * p.ks), smem, st, packed, L, M, xq, blocks, sx, bias, y);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
 }
 
 template <int FORM>
-int launch_tokens(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, bool blocks, const float* sx, const float* bias,
+int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq, bool blocks, const float* sx, const float* bias,
                   float* y, hipStream_t st)
 {
     // token blocks per workgroup: all of them up to 64 tokens, beyond that an even share of at most four
@@ -476,6 +534,29 @@ int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_
     if (L.native8) return launch_tokens<kBytes>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
     if (L.minf) return launch_tokens<kMin>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
     return launch_tokens<kZp>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
+}
+
+// fp16 activations.  Up to 16 tokens always; beyond, where the activation operands stay in registers (up to 32 tokens:
+// K <= 4096, up to 64: K <= 2048) or few row tiles read them again (measured, few-token / K-split / tiled: 32 tokens of
+// 28672 x 4096 22 / 31 / 42 us, 64 tokens of 4096 x 14336 56 / 63 / 129 us, of 4608 x 3584 35 / 20 / 36 us, 128 tokens of
+// 2048 x 1536 in two slices 8.6 / 12 / 19 us).
+bool skinny_f16_wanted(const Layout& L, int64_t M)
+{
+    if (debug_option(kDbgNoSkinny) || debug_option(kDbgPrefillTile)) return false;   // tests and tuning: the tiled GEMM
+    if (M <= 16) return true;
+    const int blocks = (int)(M + 15) / 16;
+    const int form = L.minf ? kMinF16 : kZpF16, tm = blocks <= 4 ? blocks : (blocks + 1) / 2;
+    const bool resident = M <= 128 && few_plan(L, tm, form).resident;
+    if (M <= 32) return resident || L.T <= 2 * (int64_t)num_cus();
+    if (M <= 64) return resident || L.T <= num_cus();
+    return M <= 128 && resident && L.T * L.C <= 4096;
+}
+
+int launch_skinny_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,
+                      hipStream_t st)
+{
+    if (L.minf) return launch_tokens<kMinF16>(packed, L, (int)M, x16, false, nullptr, bias, y, st);
+    return launch_tokens<kZpF16>(packed, L, (int)M, x16, false, nullptr, bias, y, st);
 }
 
 }  // namespace mnnq

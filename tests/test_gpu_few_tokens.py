@@ -105,3 +105,37 @@ def test_k_split_int8_gemm_matches_oracle(form, M, N, K):
     yf = B.mnnq_linear_prefill_fused(packed, N, K, xd, bias=bd, mode=mode)
     assert torch.equal(yf, y)
     assert torch.equal(B.mnnq_linear_prefill_fused_o16(packed, N, K, xd, bias=bd, mode=mode), yf.half())
+
+
+# fp16 activations: the few-token kernels (resident and streaming, both slices) and the K-split GEMM behind them
+F16_SHAPES = [(2, 16, 64), (15, 80, 1536), (16, 32, 8960), (17, 48, 4160), (33, 48, 1984), (40, 16 * 300, 2304), (64, 80, 2048),
+              (100, 48, 1536), (65, 48, 192), (130, 272, 1088), (3, 16 * 1100, 128), (200, 1040, 640), (129, 32, 8960)]
+
+
+@pytest.mark.parametrize("M,N,K", F16_SHAPES)
+@pytest.mark.parametrize("form", ["w4", "w4min", "w8planes"])
+def test_fp16_activations_match_oracle(form, M, N, K):
+    mode, quant, _ = FORMS[form]
+    if form == "w8planes" and K % 128:
+        pytest.skip("int8 weights: K a multiple of 128")
+    print("fp16 activations", form, M, N, K, flush=True)
+    W = synth.weights(N, K, 3300 + M + N + K)
+    W[0, :64] = 0.25                                # a constant group
+    x16 = synth.activations_f16(M, K, 3301 + M + N + K, outliers=True)
+    q, s, z = quant(W)
+    bias = synth.weights(1, N, 9)[0] * 10
+    linear = oracle.linear_w4a16 if form == "w4" else oracle.linear_a16_minf
+    y_o = linear(x16, q, s, z, bias=bias)
+    # exact products, fp32 sums of 64 products and then of up to 2 K / 64 groups
+    tol = 1e-5 * np.abs(y_o).max()
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    bd, xd = dev(bias), dev(x16)
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    y = B.mnnq_linear_prefill_f16(packed, N, K, xd, bias=bd, out=out[:M], mode=mode)
+    assert torch.isnan(out[M]).all()                # nothing behind the last token
+    assert np.abs(y.cpu().numpy() - y_o).max() <= tol
+    assert torch.equal(B.mnnq_linear_prefill_f16_o16(packed, N, K, xd, bias=bd, mode=mode), y.half())
+    rs = np.linspace(0.5, 2.0, M).astype(np.float32)
+    y_rs = linear(x16, q, s, z) * rs[:, None].astype(np.float64)
+    yr = B.mnnq_linear_prefill_f16(packed, N, K, xd, row_scale=dev(rs), mode=mode).cpu().numpy()
+    assert np.abs(yr - y_rs).max() <= 2 * tol
