@@ -243,7 +243,11 @@ int decode_fused_impl(const void* packed, int64_t N, int64_t K, int group, int m
     if (workspace && workspace_bytes >= fused_ws_bytes(K) && L.total() > two_kernel_bytes) {
         int8_t* xq = static_cast<int8_t*>(workspace);
         float* sx = reinterpret_cast<float*>(xq + (K + 127) / 128 * 128);
-        if (int s = launch_quant_act(x, 1, K, xq, sx, nullptr, st)) return s;
+        // (a block of one token is a plain row: 3584 values 4.9 -> 2.5 us against the kernel that splits rows, which long
+        // rows still take)
+        if (int s = quant_packed_possible(K) ? launch_quant_token_blocks(x, 1, K, xq, sx, st)
+                                             : launch_quant_act(x, 1, K, xq, sx, nullptr, st))
+            return s;
         return launch_decode(static_cast<const uint8_t*>(packed), L, xq, sx, bias, static_cast<float*>(y), st);
     }
     return launch_decode_fused(static_cast<const uint8_t*>(packed), L, x, bias, static_cast<float*>(y), st);

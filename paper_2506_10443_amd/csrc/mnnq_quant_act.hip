@@ -116,21 +116,36 @@ __global__ __launch_bounds__(kQThreads) void quant_act_rows_kernel(const float* 
 //   kTokenBlocks - the few-token kernels: [group][token block of 16][k block of 16][token][16 codes], the last block as
 //                  narrow as its tokens (M K bytes in all);
 //   kPlanes      - the fp6 GEMM: the activation planes [group][TMp][3072 B] (see planes_kernel).
-// A workgroup of 1024 threads quantizes R rows, each in the registers of 1024 / R threads (NV float4 per thread) between
+// A workgroup of 512 threads quantizes R rows, each in the registers of 512 / R threads (NV float4 per thread) between
 // the maximum and the codes, collects the codes in LDS and stores them from there: R tokens lie side by side in the
 // output, i.e. pieces of 16 R bytes.
+//
+// Bound: latency for few rows (load, maximum, codes, store in a row), HBM for many.  A line of the output holds the
+// pieces of eight tokens, so eight rows in a row go to workgroups of one XCD (workgroup b runs on XCD b % 8), whose L2
+// puts the line together; spread over the XCDs every line left the chip in pieces, and small workgroups - several per CU,
+// one storing while another loads - did not pay.  Planes, one row per workgroup: 1024 x 18944 38.6 -> 26.6 us; against
+// 1024 threads with one, two or four rows and no such order: 5 x 4096 (token blocks) 3.0 -> 2.2 us, 512 x 3584 7.9 -> 6.8,
+// 512 x 18944 14.5 -> 13.7, 2048 x 18944 48.3 -> 44.8 us (4.7 TB/s; a large copy reaches 5.0 TB/s).
 enum ActOrder { kTokenBlocks = 0, kPlanes = 1 };
-constexpr int kPackThreads = 1024;
+constexpr int kPackThreads = 512;
+constexpr int kPackMaxVec = 10 * kPackThreads;   // float4 of the longest row: ten registers quads per thread with R = 1
+constexpr int kLineRows = 8;                     // tokens that share a 128-byte line of the output
+constexpr int kXcds = 8;
 
 template <int R, int NV, int ORDER>
 __global__ __launch_bounds__(kPackThreads) void quant_pack_kernel(const float* __restrict__ x, int M, int K, int TMp,
-                                                                  uint8_t* __restrict__ out, float* __restrict__ sx)
+                                                                  int rows, uint8_t* __restrict__ out,
+                                                                  float* __restrict__ sx)
 {
     extern __shared__ __align__(16) uint8_t lds_codes[];   // [R][K + 16]: rows 16 bytes apart in the banks; maxima
     constexpr int TPR = kPackThreads / R, WPR = TPR / 64;
     const int tid = threadIdx.x;
     const int r = __builtin_amdgcn_readfirstlane(tid / TPR), i0 = tid % TPR;
-    const int first = blockIdx.x * R;
+    // (the grid covers whole sets of kXcds * kLineRows rows)
+    constexpr int per_line = kLineRows / R;
+    const int set = blockIdx.x / kXcds, xcd = blockIdx.x % kXcds;
+    const int first = (set / per_line * kXcds + xcd) * kLineRows + set % per_line * R;
+    if (first >= rows) return;
     const int m = first + r;
     const int K4 = K / 4, stride = K + 16;
     float* const s_part = reinterpret_cast<float*>(lds_codes + R * stride);
@@ -201,44 +216,45 @@ int launch_quant_pack(const float* x, int64_t M, int64_t K, int TMp, int64_t row
 {
     const int nv = (int)((K / 4 + kPackThreads / R - 1) / (kPackThreads / R));
     const size_t smem = (size_t)R * (K + 16) + kPackThreads / 64 * sizeof(float);
-    const unsigned grid = (unsigned)((rows + R - 1) / R);
+    constexpr int set_rows = kXcds * kLineRows;
+    const unsigned grid = (unsigned)((rows + set_rows - 1) / set_rows * (set_rows / R));
 #define MNNQ_PACK(NV)                                                                                             \
     if (nv <= NV) {                                                                                               \
         static thread_local int allowed = -1;                                                                     \
         auto kern = quant_pack_kernel<R, NV, ORDER>;                                                              \
         if (int s = allow_large_lds(kern, smem, allowed)) return s;                                               \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kPackThreads), smem, st, x, (int)M, (int)K, TMp, out, sx);      \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kPackThreads), smem, st, x, (int)M, (int)K, TMp, (int)rows, out, sx); \
         MNNQ_HIP_TRY(hipGetLastError());                                                                          \
         return MNNQ_OK;                                                                                           \
     }
-    MNNQ_PACK(R) MNNQ_PACK(2 * R) MNNQ_PACK(5 * R)
+    MNNQ_PACK(R) MNNQ_PACK(2 * R) MNNQ_PACK(4 * R) MNNQ_PACK(5 * R) MNNQ_PACK(7 * R) MNNQ_PACK(10 * R)
 #undef MNNQ_PACK
     return MNNQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace
 
-// The row stays in registers: five float4 per thread of the whole workgroup at most.
-bool quant_packed_possible(int64_t K) { return K <= 5 * 4 * kPackThreads; }
+// The row stays in registers.
+bool quant_packed_possible(int64_t K) { return K / 4 <= kPackMaxVec; }
+
+// One row per workgroup fills more CUs, two rows make larger stores (measured, one / two rows: 256 x 3584 4.7 / 5.0 us,
+// 256 x 18944 9.9 / 11.1, 352 x 3584 5.9 / 5.6, 1024 x 3584 8.4 / 8.0, 1024 x 18944 26.6 / 23.8 us).
+constexpr int64_t kOneRowMax = 256;
 
 int launch_quant_token_blocks(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, hipStream_t st)
 {
     uint8_t* out = reinterpret_cast<uint8_t*>(xq);
-    if (M <= 256) return launch_quant_pack<1, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
-    if (M <= 640) return launch_quant_pack<2, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
-    return launch_quant_pack<4, kTokenBlocks>(x, M, K, 0, M, out, sx, st);   // (as for the planes below)
+    if (M <= kOneRowMax) return launch_quant_pack<1, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
+    return launch_quant_pack<2, kTokenBlocks>(x, M, K, 0, M, out, sx, st);
 }
 
 int launch_quant_planes(const float* x, int64_t M, int64_t K, int TMp, void* planes, float* sx, hipStream_t st)
 {
     // (rows up to the next whole block of 32 are written as zeros; the blocks behind are not read for results)
-    // One row per workgroup fills more CUs, four rows make the stores whole lines: the lines lie where the measured times
-    // cross (K = 18944: 96 tokens 7 us faster with one row, 1024 tokens 11 us slower; two rows are best or even between).
     const int64_t rows = (M + 31) / 32 * 32;
     uint8_t* out = static_cast<uint8_t*>(planes);
-    if (rows <= 256) return launch_quant_pack<1, kPlanes>(x, M, K, TMp, rows, out, sx, st);
-    if (rows <= 640) return launch_quant_pack<2, kPlanes>(x, M, K, TMp, rows, out, sx, st);
-    return launch_quant_pack<4, kPlanes>(x, M, K, TMp, rows, out, sx, st);
+    if (rows <= kOneRowMax) return launch_quant_pack<1, kPlanes>(x, M, K, TMp, rows, out, sx, st);
+    return launch_quant_pack<2, kPlanes>(x, M, K, TMp, rows, out, sx, st);
 }
 
 int launch_quant_act(const float* x, int64_t M, int64_t K, int8_t* xq, float* sx, int32_t* xsum,

@@ -139,3 +139,37 @@ def test_fp16_activations_match_oracle(form, M, N, K):
     y_rs = linear(x16, q, s, z) * rs[:, None].astype(np.float64)
     yr = B.mnnq_linear_prefill_f16(packed, N, K, xd, row_scale=dev(rs), mode=mode).cpu().numpy()
     assert np.abs(yr - y_rs).max() <= 2 * tol
+
+
+@pytest.mark.parametrize("K", [64, 2112, 20480])
+@pytest.mark.parametrize("M", [5, 8, 9, 64, 65, 256, 257, 330])
+def test_quantizer_row_sets(M, K):
+    """The packing quantizer deals sets of 64 rows to workgroups, one or two rows each (the line at 256): every row is
+    quantized and nothing past the last one, at the edges of sets and of the shortest and longest rows it holds."""
+    print("quantizer rows", M, K, flush=True)
+    x = dev(synth.activations(M, K, 77 + M))
+    xq, sx, _ = B.mnnq_quant_act(x)
+    forms = [B.MODE_W4_ZP_INT] + ([W8N] if K % 128 == 0 else [])
+    for mode in forms:
+        packed = B.mnnq_pack_weights(dev(synth.weights(32, K, 78)), mode=mode)
+        rows = B.mnnq_linear_prefill(packed, 32, K, xq, sx, mode=mode)
+        out = torch.full((M + 1, 32), float("nan"), device="cuda:0")
+        B.mnnq_linear_prefill_fused(packed, 32, K, x, out=out[:M], mode=mode)
+        assert torch.equal(out[:M], rows) and torch.isnan(out[M]).all()
+
+
+@pytest.mark.parametrize("K", [64, 3584, 20480, 20544])
+def test_two_kernel_decode(K):
+    """The fused one-token call with its quantizer as a kernel of its own (large layers; here forced): the packing
+    quantizer up to 20480 values, the row-splitting one beyond, both as the separate calls."""
+    print("two-kernel decode", K, flush=True)
+    x = dev(synth.activations(1, K, 79))
+    packed = B.mnnq_pack_weights(dev(synth.weights(48, K, 80)))
+    xq, sx, _ = B.mnnq_quant_act(x)
+    ws = torch.empty(B.mnnq_workspace_size(1, 48, K), dtype=torch.uint8, device="cuda:0")
+    B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", 0)
+    try:
+        y = B.mnnq_linear_decode_fused(packed, 48, K, x[0].contiguous(), workspace=ws)
+    finally:
+        B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", None)
+    assert torch.equal(y, B.mnnq_linear_decode(packed, 48, K, xq[0].contiguous(), sx))
