@@ -3,12 +3,12 @@
 // activations) wherever the tiled GEMMs of mnnq_prefill.hip and mnnq_prefill_f16.hip leave the chip partly idle.
 //
 // The tiled GEMM works on 128 x 128 outputs per workgroup: 333 tokens of a 4096-wide projection are 96 such tiles on 256
-// CUs.  Here a wave owns 64 x 64 outputs and a part of K, the KS waves of a workgroup share the tile and add their parts
+// CUs.  Here a wave owns 64 x 64 outputs (48, 32 or 16 x 64: tile_height) and a part of K, the KS waves of a workgroup share the tile and add their parts
 // through LDS at the end, in a fixed order.  The waves share no operand, so everything goes from L2 straight into
 // registers, refilled for the next chunk of 128 values as soon as it has been used, with no LDS and no barrier in the loop.
 // What bounds it is vector issue: per group of a 16 x 16 tile two instructions per output for the scale (three with a
 // float minimum) behind one matrix instruction - with fp16 activations one behind two, and twice the unpacking -;
-// unpacking a column tile is shared by four row tiles.
+// unpacking a column tile is shared by the row tiles.
 //
 // Operand layout and arithmetic as in mnnq_skinny.hip (A: 16 tokens x 64 k, B: 64 k x 16 weight rows, D: lane l holds
 // weight row l % 16, tokens 4 (l / 16) + r).
@@ -41,7 +41,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t by
 __device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
 __device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
 
-constexpr int TM = 4, TN = 4, T = TM * TN;   // 16 x 16 tiles of a wave: 64 tokens x 64 weight rows
+constexpr int TN = 4;   // 16 x 16 tiles of a wave: 16 TM tokens x 64 weight rows
 
 // One column tile of one chunk.
 template <int FORM>
@@ -99,12 +99,13 @@ __device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, u
     return o;
 }
 
-template <int FORM, int KS>
+template <int FORM, int KS, int TM>
 __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
                                                           const void* __restrict__ xq, bool blocks,
                                                           const float* __restrict__ sx, const float* __restrict__ bias,
                                                           float* __restrict__ y, int MT, int NT)
 {
+    constexpr int T = TM * TN;
     extern __shared__ __align__(16) float4 lds_sum[];   // [KS][T][64]
     const int lane = threadIdx.x & 63, row = lane & 15, kb = lane >> 4;
     const int ks = uniform(threadIdx.x >> 6);
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     const int xcd = blockIdx.x % 8, seq = blockIdx.x / 8;
     const int tile_m = seq % MT, tile_n = (seq / MT) * 8 + xcd;
     if (tile_n >= NT) return;
-    const int C = (int)L.C, m0 = tile_m * 64;
+    const int C = (int)L.C, m0 = tile_m * (16 * TM);
     const int c0 = C * ks / KS, c1 = C * (ks + 1) / KS;
     const int odd_last = (L.G & 1) ? C - 1 : -1;
 
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
 
     // Sum over the waves in a fixed order, the tiles dealt to the waves; their scales and biases are requested before the
     // exchange, which their latency would follow.
-    constexpr int NP = T / KS;
+    constexpr int NP = (T + KS - 1) / KS;
     const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, (int64_t)M * 4);
     const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
     const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, (int64_t)M * L.N * (L.out16 ? 2 : 4));
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     float bn[NP], sm[NP][4];
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int t = ks * NP + k, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        const int t = ks + k * KS, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
         bn[k] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n * 4, 0, 0));
 #pragma unroll
         for (int r = 0; r < 4; ++r) sm[k][r] = sx ? __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0)) : 1.0f;
@@ -283,7 +284,8 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int t = ks * NP + k, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        const int t = ks + k * KS, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        if (T % KS != 0 && t >= T) break;
         float4 v = lds_sum[t * 64 + lane];
 #pragma unroll
         for (int p = 1; p < KS; ++p) {
@@ -305,14 +307,15 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     }
 }
 
-template <int FORM, int KS>
+template <int FORM, int KS, int TM>
 int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
            const float* bias, float* y, hipStream_t st)
 {
-    const int MT = (int)((M + 63) / 64), NT = (int)((L.T + TN - 1) / TN);
+    constexpr int T = TM * TN;
+    const int MT = (int)((M + 16 * TM - 1) / (16 * TM)), NT = (int)((L.T + TN - 1) / TN);
     constexpr size_t smem = (size_t)KS * T * 64 * 16;
-    static_assert(smem <= kLdsPerWorkgroup && T % KS == 0, "partial tiles in LDS");
-    auto kern = ksplit_kernel<FORM, KS>;
+    static_assert(smem <= kLdsPerWorkgroup, "partial tiles in LDS");
+    auto kern = ksplit_kernel<FORM, KS, TM>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
     const int64_t grid = (int64_t)MT * ((NT + 7) / 8) * 8;
@@ -321,27 +324,82 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bo
     return MNNQ_OK;
 }
 
+// The height of the tiles, 16 tm tokens: a launch takes as many rounds as its busiest CU has tiles, and a round as long as
+// a tile's tm row tiles and a part that does not depend on them (weights, minima).  The tallest of the cheapest is taken,
+// so that 333 tokens of 4096 columns, 384 tiles of 64 x 64 - two rounds -, run as 448 tiles of 48 x 64, two shorter ones.
+// Measured rounds at K = 4096 with tm = 4 / 3 / 2 / 1: int8 bytes 11.4 / 9.5 / 7.4 / 6 us, int4 9.3 / 7.9 / 5.8 / 4.3, with
+// fp16 activations 17.0 / 13.4 / 10.0 / 5.7.  Over 314 shapes of the listed layers, 80 - 2048 tokens, the choice is within
+// 1 % (geometric mean) of the best of tm = 1 .. 4 and the tiled GEMM, and 12 % faster than tm = 4 alone up to three (fp16
+// activations: two) tiles per CU: 333 tokens of 4096 x 14336 65 -> 58 us (int8 bytes), 130 tokens of 1536 x 8960
+// 27 -> 19 us, 1500 tokens of 4096 x 14336 253 -> 206 us.
+struct Height {
+    int tm;
+    float rounds;      // in rounds of tm = 4
+};
+
+Height tile_height(const Layout& L, int64_t M, int form)
+{
+    const float fixed = is_f16(form) ? 0.65f : form == kBytes ? 2.3f : 1.4f;   // in row tiles
+    const int64_t NT = (L.T + TN - 1) / TN, cus = num_cus();
+    Height best{4, 0.0f};
+    for (int tm = 4; tm >= 1; --tm) {
+        const int64_t tiles = (M + 16 * tm - 1) / (16 * tm) * NT;
+        const float cost = (float)((tiles + cus - 1) / cus) * (tm + fixed) / (4 + fixed);
+        if (tm == 4 || cost < 0.97f * best.rounds) best = Height{tm, cost};
+    }
+    return best;
+}
+
+// Rounds of the tiled GEMM (128 x 128 tiles) in the same unit; the constants are fitted to the same measurements.  The
+// first round weighs more than the next ones, with a CU's second workgroup beside it.
+float tiled_rounds(const Layout& L, int64_t M, int form)
+{
+    const int64_t tiles = (M + 127) / 128 * ((L.T + 7) / 8), cus = num_cus();
+    const float n = (float)((tiles + cus - 1) / cus);
+    if (is_f16(form)) return 1.8f * n + 0.4f;
+    return form == kBytes ? 3.1f * n + 1.0f : form == kMin ? 2.6f * n + 1.5f : 2.25f * n + 1.8f;
+}
+
+int form_of(const Layout& L, bool f16)
+{
+    if (f16) return L.minf ? kMinF16 : kZpF16;
+    return L.native8 ? kBytes : L.minf ? kMin : kZp;
+}
+
+template <int FORM, int TM>
+int launch_height(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
+                  const float* bias, float* y, hipStream_t st)
+{
+    // one tile per CU: eight waves share it, else four, and a CU holds two workgroups
+    const int64_t tiles = (M + 16 * TM - 1) / (16 * TM) * ((L.T + TN - 1) / TN);
+    if (tiles <= num_cus()) return launch<FORM, 8, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
+    return launch<FORM, 4, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
+}
+
 template <int FORM>
 int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
                 const float* bias, float* y, hipStream_t st)
 {
-    const int64_t tiles = ((M + 63) / 64) * ((L.T + TN - 1) / TN);
-    if (tiles <= num_cus()) return launch<FORM, 8>(packed, L, M, xq, blocks, sx, bias, y, st);
-    return launch<FORM, 4>(packed, L, M, xq, blocks, sx, bias, y, st);
+    switch (tile_height(L, M, FORM).tm) {
+        case 1: return launch_height<FORM, 1>(packed, L, M, xq, blocks, sx, bias, y, st);
+        case 2: return launch_height<FORM, 2>(packed, L, M, xq, blocks, sx, bias, y, st);
+        case 3: return launch_height<FORM, 3>(packed, L, M, xq, blocks, sx, bias, y, st);
+        default: return launch_height<FORM, 4>(packed, L, M, xq, blocks, sx, bias, y, st);
+    }
 }
 
 }  // namespace
 
-// At most three 64 x 64 tiles per CU: measured against the tiled GEMM (int4 / int8 bytes), 333 tokens of 4096 x 4096
-// 23.9 / 27.2 against 36.7 / 45.2 us, 512 tokens of 6144 x 4096 (three per CU) 34.9 / 43.3 against 39.4 / 47.8 us; at four
-// per CU (1024 tokens of 4096 x 4096) it loses 5 %, beyond more: with the chip full, the tiled form's sharing of operands
-// through LDS counts.
+// Where its rounds cost less than the tiled GEMM's: 1024 tokens of 6144 x 4096 in int8 bytes (six rounds against two) 68
+// against 76 us, 512 tokens of 17920 x 1536 (nine against three) 48 against 52 us; int4 57 against 60 and 41 against 39 us -
+// with the chip full, the tiled form's sharing of operands through LDS counts.
 bool ksplit8_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
     if (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8) return false;     // (nibble planes: the tiled GEMM merges them)
     const int64_t lim = kOutOfRange;                                 // 32-bit offsets
-    return ((M + 63) / 64) * ((L.T + TN - 1) / TN) <= 3 * (int64_t)num_cus() && (M + 64) * L.Kx < lim &&
+    const int form = form_of(L, false);
+    return tile_height(L, M, form).rounds <= tiled_rounds(L, M, form) && (M + 64) * L.Kx < lim &&
            (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 2048 < lim;
 }
 
@@ -353,13 +411,14 @@ int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8
     return launch_form<kZp>(packed, L, M, xq, blocks, sx, bias, y, st);
 }
 
-// At most two 64 x 64 tiles per CU: 128 tokens of 4096 x 14336 63 against 135 us tiled, 512 tokens (two per CU) 121
-// against 133 us; 512 tokens of 4608 x 3584 (2.25 per CU) 49 against 38 us.
+// The same rule: 333 tokens of 4096 x 14336 (two rounds of 48 rows) 93 against 130 us tiled, 512 tokens (two of 64) 119
+// against 132 us; 700 tokens (three) 176 against 133 us.
 bool ksplit_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
     const int64_t lim = kOutOfRange;                                 // 32-bit offsets
-    return ((M + 63) / 64) * ((L.T + TN - 1) / TN) <= 2 * (int64_t)num_cus() && (M + 64) * L.Kx * 2 < lim &&
+    const int form = form_of(L, true);
+    return tile_height(L, M, form).rounds <= tiled_rounds(L, M, form) && (M + 64) * L.Kx * 2 < lim &&
            (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 1024 < lim;
 }
 

@@ -173,3 +173,33 @@ def test_two_kernel_decode(K):
     finally:
         B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", None)
     assert torch.equal(y, B.mnnq_linear_decode(packed, 48, K, xq[0].contiguous(), sx))
+
+
+# one shape per tile height of the K-split kernel (16, 32, 48, 64 rows), ragged in rows and columns, with four and eight
+# waves, and more rounds than the limit of the 64-row tiles alone was
+@pytest.mark.parametrize("M,N,K", [(131, 1040, 320), (131, 2064, 320), (333, 4080, 192), (500, 4112, 192), (1100, 4096, 128)])
+@pytest.mark.parametrize("form", ["w4", "w4min", "w8"])
+def test_k_split_tile_heights(form, M, N, K):
+    mode, quant, linear = FORMS[form]
+    if form == "w8":
+        K = (K + 127) // 128 * 128
+    print("K-split heights", form, M, N, K, flush=True)
+    W, x = synth.weights(N, K, 3300 + M), synth.activations(M, K, 3301 + M)
+    q, s, z = quant(W)
+    xq, sx, _ = oracle.quant_act(x)
+    bias = synth.weights(1, N, 9)[0] * 10
+    y_o = linear(xq, sx, q, s, z, bias=bias, want_acc=False)[1]
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    B.mnnq_linear_prefill_fused(packed, N, K, dev(x), bias=dev(bias), out=out[:M], mode=mode)
+    assert torch.isnan(out[M]).all()
+    assert np.abs(out[:M].cpu().numpy() - y_o).max() <= 1e-5 * np.abs(y_o).max()
+    if form != "w8":        # fp16 activations: fp32 sums as the tiled kernel's, in another order
+        x16 = dev(synth.activations_f16(M, K, 3302 + M))
+        y16 = B.mnnq_linear_prefill_f16(packed, N, K, x16, mode=mode)
+        B.mnnq_debug_set("MNNQ_NO_SKINNY", 1)
+        try:
+            ref = B.mnnq_linear_prefill_f16(packed, N, K, x16, mode=mode)
+        finally:
+            B.mnnq_debug_set("MNNQ_NO_SKINNY", None)
+        assert (y16 - ref).abs().max() <= 1e-5 * ref.abs().max()
