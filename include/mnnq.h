@@ -280,7 +280,8 @@ int mnnq_debug_set(const char *key, const char *value);
 
 /* Test view of the host logic (Section 5.1 chooses loop tiling from the problem's dimensions; here:
  * which kernel configuration a call would launch).  Nothing is launched and no device is needed.
- * what = 0: mnnq_linear_prefill with M > 16 tokens (the tiled GEMM); out8 = {tile rows, tile columns,
+ * what = 0: the tiled GEMM of mnnq_linear_prefill (few tokens, and the chunk layout where tiles are few,
+ *           have kernels of their own); out8 = {tile rows, tile columns,
  *           K parts inside a workgroup, K split over workgroups, waves per workgroup, LDS bytes per
  *           workgroup, workgroups, form: 0 int4 on the int8 matrix instruction, 1 int8 weights with the two
  *           nibble planes merged in registers, 2 int8 weights in the byte form, 6 the GEMM on the fp6 matrix

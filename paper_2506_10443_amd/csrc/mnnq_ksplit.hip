@@ -30,7 +30,7 @@ constexpr bool is_f16(int form) { return form >= kZpF16; }
 constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
 
 constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
-constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit8_possible): loads give 0, stores are dropped
+constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit8_wanted): loads give 0, stores are dropped
 constexpr int kMagicBits = 0x4B400000;    // 1.5 * 2^23: see from_magic in mnnq_skinny.hip
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -20,7 +20,7 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
-constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit6_possible): loads give 0, stores are dropped
+constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (prefill6_possible and the limits on y): loads give 0, stores are dropped
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 

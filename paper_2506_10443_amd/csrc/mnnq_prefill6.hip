@@ -22,8 +22,8 @@
 //     result is the int32 group accumulator, bit for bit (the accumulator dump of this kernel is
 //     compared with the oracle's integers).
 // Both operands are prepared ahead: the weights at load time (the matrix-core plane of the packed
-// buffer, see mnnq_common.h), the activations by a small kernel per call (planes_kernel below), so
-// the GEMM's loop holds nothing but LDS reads, matrix instructions and the multiply-adds.
+// buffer, see mnnq_common.h), the activations per call (by the quantizer of the fused call itself,
+// mnnq_quant_act.hip, or from int8 codes by planes_kernel below), so the GEMM's loop holds nothing but LDS reads, matrix instructions and the multiply-adds.
 //
 // Lane mapping of the 32x32x64 instruction as used here (A: 32 x 64, B: 64 x 32, D: 32 x 32):
 //   A / B operand: lane l holds row / column l % 32 and the 32 values of k-block l / 32, value j at
