@@ -461,12 +461,19 @@ int launch_tiles(const uint8_t* packed, const Layout& L, int64_t M, const uint16
 int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* rs,
                        const float* bias, float* y, hipStream_t st)
 {
-    const int cus = num_cus();
-    const int64_t tiles_big = ((M + 255) / 256) * ((L.N + 127) / 128);
-    const int64_t tiles_small = ((M + 127) / 128) * ((L.N + 127) / 128);
-    bool big = M > 128 && tiles_big >= 2 * (int64_t)cus;
-    // at most one 128-row tile per CU: split the chunks over the two halves of an eight-wave workgroup
-    int ks = (!big && tiles_small <= (int64_t)cus && L.C >= 4) ? 2 : 1;
+    // The tile by what the busiest CU has to do: 256 x 128 unpacks the weights for twice the rows, so that it costs as much as
+    // 1.75 tiles of 128 x 128 instead of two, but leaves more of a last round empty.  Measured at K = 4096, 128-row against
+    // 256-row tiles, in tiles per CU: 3 / 2 (6144 columns, 2048 tokens) 111 / 120 us, 4 / 2 (28672, 512) 141 / 122, 5 / 3
+    // (12288, 1300) 165 / 187, 6 / 3 (12288, 2048) 213 / 199, 10 / 6 (28672, 1300) 331 / 345, 14 / 7 (28672, 2048) 485 / 437.
+    const int64_t cus = num_cus(), nt = (L.N + 127) / 128;
+    const int64_t per_cu_small = ((M + 127) / 128 * nt + cus - 1) / cus, per_cu_big = ((M + 255) / 256 * nt + cus - 1) / cus;
+    bool big = 4 * per_cu_small >= 7 * per_cu_big;
+    // One tile per CU: the chunks are split over the two halves of an eight-wave workgroup, else half the wave slots are
+    // empty.  Of 256-row tiles that fill a CU alone, two small ones are as fast on short rows: 4096 columns, 1536 tokens of
+    // 1536 / 4096 / 14336 values 30.8 / 70.9 / 237 us in two small tiles, 32.1 / 67.6 / 219 us in one split tile (2048 tokens of
+    // 14336: 260 / 230).  (A row factor, see prefill_f16_impl, asks for the groups in order.)
+    if (big && per_cu_big == 1 && (L.C < 24 || rs)) big = false;
+    int ks = (big ? per_cu_big : per_cu_small) == 1 && L.C >= 4 ? 2 : 1;
     if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: "b"/"s" tile, third letter "k" = K parts
         if (e[0] == 'b') big = true;
         if (e[0] == 's') big = false;

@@ -203,3 +203,26 @@ def test_k_split_tile_heights(form, M, N, K):
         finally:
             B.mnnq_debug_set("MNNQ_NO_SKINNY", None)
         assert (y16 - ref).abs().max() <= 1e-5 * ref.abs().max()
+
+
+# The fp16 GEMM's tile by tiles per CU (three rows of 128-row tiles, two of 256-row tiles, 86 columns on 256 CUs): one
+# 256 x 128 tile split over K where the rows are long (an odd number of groups, so that the halves differ, among them), two
+# of 128 x 128 where they are short or one column too many makes a second tile.  (1100 and 20000 columns: one and four)
+@pytest.mark.parametrize("M,N,K", [(380, 10992, 3072), (380, 10992, 3136), (380, 10992, 3008), (380, 16400, 3072),
+                                   (257, 1104, 3136), (513, 26608, 192)])
+@pytest.mark.parametrize("mode", [B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT])
+def test_fp16_tiles_by_tiles_per_cu(mode, M, N, K):
+    print("fp16 tiles", mode, M, N, K, flush=True)
+    gen = torch.Generator(device="cuda:0").manual_seed(M + N + K)
+    packed = B.mnnq_pack_weights(torch.randn((N, K), generator=gen, device="cuda:0") * 0.02, mode=mode)
+    x = torch.randn((M, K), generator=gen, device="cuda:0").half()
+    q, s, z = (t.double() for t in B.mnnq_unpack_weights(packed, N, K, mode=mode))
+    s, z, q = s[:, :, None], z[:, :, None], q.view(N, K // 64, 64)
+    w = ((q - z) * s if mode == B.MODE_W4_ZP_INT else q * s + z).view(N, K)
+    bias = torch.randn(N, generator=gen, device="cuda:0")
+    exact = x.double() @ w.t() + bias.double()
+    out = torch.full((M + 1, N), float("nan"), device="cuda:0")
+    y = B.mnnq_linear_prefill_f16(packed, N, K, x, bias=bias, out=out[:M], mode=mode)
+    assert torch.isnan(out[M]).all()                # nothing behind the last token
+    assert (y.double() - exact).abs().max() <= 1e-5 * exact.abs().max()     # the layer's tolerance
+    assert torch.equal(B.mnnq_linear_prefill_f16_o16(packed, N, K, x, bias=bias, mode=mode), y.half())
