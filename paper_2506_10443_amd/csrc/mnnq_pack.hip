@@ -48,20 +48,23 @@ __device__ __forceinline__ uint32_t quant_group(const float4 v, float scale, flo
         mz = r + MAGIC;
         dmax = fmaxf(dmax, fabsf(r - (mz - MAGIC)));
     }
-    // (fmaxf drops a NaN, which an infinite reciprocal gives: the limit is negative then)
+    float base = MAGIC - (mz - MAGIC);     // the sum that stands for code 0: MAGIC less the zero point
+    zero = ZP ? __float_as_int(mz) - __float_as_int(MAGIC) : 0;
+    // (fmaxf drops a NaN: the limit is negative where the reciprocal gives one; of a NaN weight see below)
     if (!(dmax <= lim)) {
+        // the definition itself, its clamp included: a range that rounds to scale 0 or overflows gives quotients and zero
+        // points that no integer holds (NaN: code 0, as below; a zero point past the byte: 255)
+        const float zf = ZP ? rintf(-mn / scale) : 0.0f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = rintf(x[i] / scale) + MAGIC;
-        if (ZP) mz = rintf(-mn / scale) + MAGIC;
+        for (int i = 0; i < 4; ++i) m[i] = fminf(fmaxf(rintf(x[i] / scale) + zf, 0.0f), (float)MAX) + MAGIC;
+        zero = (int)fminf(fmaxf(zf, 0.0f), 255.0f);
+        base = MAGIC;
     }
-    constexpr int BITS = 0x4B400000;
-    zero = ZP ? __float_as_int(mz) - BITS : 0;
+    // clamped as floats, in which a NaN becomes the lower end
     uint32_t c[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int q = __float_as_int(m[i]) - BITS + zero;
-        c[i] = (uint32_t)(q < 0 ? 0 : q > MAX ? MAX : q);
-    }
+    for (int i = 0; i < 4; ++i)
+        c[i] = (uint32_t)(__float_as_int(fminf(fmaxf(m[i], base), base + (float)MAX)) - __float_as_int(base));
     return c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
 }
 

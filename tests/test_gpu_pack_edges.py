@@ -62,3 +62,71 @@ def test_pack_edges(form, N, K):
     imported = torch.full_like(packed, 0x5a)
     B.mnnq_pack_from_quantized(dev(q), dev(s), dev(z), out=imported, mode=mode)
     assert torch.equal(packed, imported)
+
+
+def definition(W, levels, zero_point):
+    """The quantizer's sequence of binary32 operations with the clamp min(max(c, 0), levels) of C (a NaN becomes 0)."""
+    w = W.reshape(W.shape[0], -1, 64)
+    with np.errstate(all="ignore"):
+        mn, mx = np.fmin.reduce(w, axis=2), np.fmax.reduce(w, axis=2)
+        if zero_point:
+            mn, mx = np.fmin(mn, np.float32(0)), np.fmax(mx, np.float32(0))
+        flat = mx == mn
+        s = np.where(flat, np.float32(1), (mx - mn) / np.float32(levels))
+        if zero_point:
+            z = np.where(flat, np.float32(0), np.rint(-mn / s))
+            c = np.rint(w / s[:, :, None]) + z[:, :, None]
+            z = np.fmin(np.fmax(z, np.float32(0)), np.float32(255)).astype(np.uint8)
+        else:
+            z = mn
+            c = np.rint((w - mn[:, :, None]) / s[:, :, None])
+        q = np.where(flat[:, :, None], np.float32(0), np.fmin(np.fmax(c, np.float32(0)), np.float32(levels)))
+    return q.astype(np.uint8).reshape(W.shape), s, z
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+def test_pack_ends_of_the_range(form):
+    """Groups whose range rounds to scale 0 (subnormal) or overflows, and groups with a NaN or an infinity among ordinary
+    weights: codes and parameters of the definition."""
+    mode = FORMS[form][0]
+    levels = 255 if form.startswith("w8") else 15
+    N, K = 48, 384
+    print("pack ends", form, flush=True)
+    W = synth.weights(N, K, 5500)
+    g = W.reshape(N, K // 64, 64)
+    tiny = np.float32(1.4e-45)
+    rng = np.random.default_rng(5501)
+    for i in range(N):
+        kind = i % 12
+        v = g[i, i % 6]
+        if kind == 0:
+            v[:] = tiny * rng.integers(0, 8, 64).astype(np.float32)           # scale 0, minimum 0
+        elif kind == 1:
+            v[:] = tiny * rng.integers(-3, 4, 64).astype(np.float32)          # scale 0, minimum below 0
+        elif kind == 2:
+            v[:] = tiny * rng.integers(-22, 23, 64).astype(np.float32)        # a scale of few units
+        elif kind == 3:
+            v[:] = np.float32(3e38) * rng.uniform(-1, 1, 64).astype(np.float32)
+            v[:2] = np.float32(3e38), np.float32(-3e38)                       # the range overflows
+        elif kind == 4:
+            v[5] = np.nan
+        elif kind == 5:
+            v[rng.integers(0, 64, 20)] = np.nan
+        elif kind == 6:
+            v[:] = np.nan
+        elif kind == 7:
+            v[9] = np.inf
+        elif kind == 8:
+            v[63] = -np.inf
+        elif kind == 9:
+            v[0], v[1], v[2] = np.inf, -np.inf, np.nan
+        elif kind == 10:
+            v[:] = 0.0
+            v[7] = np.nan
+    q, s, z = definition(W, levels, mode & 15 == B.MODE_W4_ZP_INT)
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    qg, sg, zg = (t.cpu().numpy() for t in B.mnnq_unpack_weights(packed, N, K, mode=mode))
+    bad = np.argwhere((qg != q).reshape(N, K // 64, 64).any(axis=2))
+    assert bad.size == 0, [(int(n), int(n) % 12) for n, _ in bad]
+    np.testing.assert_array_equal(sg, s)            # (NaN equals NaN)
+    np.testing.assert_array_equal(zg, z)
