@@ -195,16 +195,17 @@ struct Workspace {
     void* ptr = nullptr;
     size_t bytes = 0;
     at::Tensor own;
-    explicit Workspace(PyObject* o)
+    const bool callers;
+    explicit Workspace(PyObject* o) : callers(given(o))
     {
-        if (!given(o)) return;
+        if (!callers) return;
         const at::Tensor& t = on_gpu(o, at::kByte, "workspace");
         ptr = t.data_ptr();
         bytes = (size_t)t.numel();
     }
     void bring(const at::Tensor& like, int64_t M, int64_t N, int64_t K, int mode)
     {
-        if (ptr) return;
+        if (callers) return;     // (too small or empty: the call says so)
         const size_t n = mnnq_workspace_size(M, N, K, kGroup, mode);
         own = at::empty({(int64_t)(n < 16 ? 16 : n)}, like.options());
         ptr = own.data_ptr();
