@@ -213,9 +213,11 @@ struct Workspace {
     }
 };
 
+// M of an [M, K] array; dimensions behind the second are not looked at ([M, K, 1] is one).
 int64_t rows_of(const at::Tensor& t, int64_t K, const char* message)
 {
-    if (t.dim() != 2 || t.size(1) != K) fail(PyExc_ValueError, "%s", message);
+    if (t.dim() < 2) fail(PyExc_IndexError, "%s", message);
+    if (t.size(1) != K) fail(PyExc_ValueError, "%s", message);
     return t.size(0);
 }
 

@@ -21,3 +21,19 @@ def test_an_empty_workspace_is_refused(packed, call):
         with pytest.raises(B.MnnqError) as e:
             call(packed, N, K, x, workspace=torch.empty(size, dtype=torch.uint8, device="cuda:0"))
         assert e.value.status == status
+
+
+def test_activations_with_trailing_dimensions(packed):
+    """[M, K, 1] holds the rows of [M, K]; fewer than two dimensions are an IndexError, another K is a ValueError."""
+    x = torch.randn(3, K, device="cuda:0")
+    xq, sx, _ = B.mnnq_quant_act(x)
+    calls = [(B.mnnq_linear_prefill_fused, x, ()), (B.mnnq_linear_prefill_fused_o16, x, ()),
+             (B.mnnq_linear_prefill, xq, (sx,)), (B.mnnq_linear_prefill_o16, xq, (sx,)),
+             (B.mnnq_linear_prefill_f16, x.half(), ()), (B.mnnq_linear_prefill_f16_o16, x.half(), ())]
+    for call, a, rest in calls:
+        y = call(packed, N, K, a, *rest)
+        assert torch.equal(call(packed, N, K, a[:, :, None], *rest), y)
+        with pytest.raises(IndexError):
+            call(packed, N, K, a.view(-1), *rest)
+        with pytest.raises(ValueError):
+            call(packed, N, K, a.view(-1, K // 2), *rest)
