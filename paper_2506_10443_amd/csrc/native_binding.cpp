@@ -9,9 +9,10 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-#include <new>
+#include <exception>
 
 #include "../../include/mnnq.h"
 
@@ -391,10 +392,8 @@ PyObject* run(Params& p, Body body, PyObject* const* args, Py_ssize_t nargs, PyO
         parse(p, args, nargs, kwnames, v);
         return body(p, v);
     } catch (const PyError&) {
-    } catch (const std::bad_alloc&) {
-        PyErr_NoMemory();
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {     // torch's own errors as its Python calls raise them (OutOfMemoryError among them)
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }

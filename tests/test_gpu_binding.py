@@ -37,3 +37,18 @@ def test_activations_with_trailing_dimensions(packed):
             call(packed, N, K, a.view(-1), *rest)
         with pytest.raises(ValueError):
             call(packed, N, K, a.view(-1, K // 2), *rest)
+
+
+def test_memory_that_torch_does_not_give(packed):
+    """An output that the allocator refuses (here: for a limit set on this process) is torch's own error."""
+    x = torch.randn(4096, K, device="cuda:0").half()
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            for _ in range(256):        # (whatever the allocator still holds runs out first)
+                held = [B.mnnq_linear_prefill_f16(packed, N, K, x) for _ in range(256)]
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    del x
+    torch.cuda.synchronize()
