@@ -31,9 +31,21 @@ try:
         mnnq_linear_decode_fused_o16, mnnq_linear_decode_o16, mnnq_linear_prefill, mnnq_linear_prefill_f16,
         mnnq_linear_prefill_f16_o16, mnnq_linear_prefill_fused, mnnq_linear_prefill_fused_o16,
         mnnq_linear_prefill_o16, mnnq_pack_weights)
-except ImportError as e:
-    raise RuntimeError("the native library is not built (%s); run `python -c 'import __graft_entry__ as g; g.build()'`"
-                       % e) from e
+except ImportError as _e:
+    # not built, or built against another torch: the constants and the host-side calls are there all the same, and a call
+    # that needs the module says what is missing
+    def _missing(name, why=_e):
+        def call(*args, **kwargs):
+            raise RuntimeError("%s: the native library is not built (%s); run `python -c 'import __graft_entry__ as g; "
+                               "g.build()'`" % (name, why)) from why
+        call.__name__ = name
+        return call
+
+    for _name in ("mnnq_linear_decode", "mnnq_linear_decode_f16", "mnnq_linear_decode_f16_o16", "mnnq_linear_decode_fused",
+                  "mnnq_linear_decode_fused_o16", "mnnq_linear_decode_o16", "mnnq_linear_prefill",
+                  "mnnq_linear_prefill_f16", "mnnq_linear_prefill_f16_o16", "mnnq_linear_prefill_fused",
+                  "mnnq_linear_prefill_fused_o16", "mnnq_linear_prefill_o16", "mnnq_pack_weights"):
+        globals()[_name] = _missing(_name)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libmnnq.so")

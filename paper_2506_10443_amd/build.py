@@ -60,14 +60,16 @@ def _compile_native() -> str:
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     obj = os.path.join(OBJ, NATIVE_SOURCE.replace(".cpp", ".o"))
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))) if os.path.isabs(hipcc()) else "/opt/rocm"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-w", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
-           "-I", inc, "-I", os.path.join(inc, "torch", "csrc", "api", "include"),
-           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(rocm, "include"),
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
            "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed for %s:\n%s\n%s" % (NATIVE_SOURCE, r.stdout, r.stderr))
+    if r.stderr:
+        sys.stderr.write(r.stderr)
     return obj
 
 
