@@ -316,7 +316,7 @@ def main() -> int:
                 tq = time_graph([(lambda x=xs[b], xq=xq, sx=sx: B.mnnq_quant_act(x, want_xsum=False, out=(xq, sx, None)))
                                  for b in range(nb)], 2)
                 entry = {"quant_us": round(tq * 1e3, 2)}
-                if self.plane and B.mnnq_plan_debug(0, self.M, N, K, mode=self.mode)[7] == 6:   # the pass takes the fp6 GEMM here
+                if self.plane and B.mnnq_plan_debug(0, self.M, N, K, mode=self.mode)[7] in (6, 7):   # the pass takes an fp6 GEMM here
                     planes = ws[:B.lib().mnnq_act_planes_size(self.M, K, 64)]
                     tp = time_graph([lambda xq=xq, planes=planes: B.mnnq_act_planes(xq, out=planes)] * nb, 2)
                     lay = [(lambda p=self.packed[name][b], N=N, K=K, planes=planes, sx=sx, y=y:

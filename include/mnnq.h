@@ -285,8 +285,8 @@ int mnnq_debug_set(const char *key, const char *value);
  *           K parts inside a workgroup, K split over workgroups, waves per workgroup, LDS bytes per
  *           workgroup, workgroups, form: 0 int4 on the int8 matrix instruction, 1 int8 weights with the two
  *           nibble planes merged in registers, 2 int8 weights in the byte form, 6 the GEMM on the fp6 matrix
- *           instructions (what a call with a workspace runs for a buffer with the matrix-core plane), 7 the same where
- *           K is long and the output tiles are few (always with K split over the waves)};
+ *           instructions (what a call with a workspace runs for a buffer with the matrix-core plane), 7 the same
+ *           product with K split over the waves (few output tiles)};
  * what = 1: mnnq_linear_decode; what = 2: mnnq_linear_decode_fused without workspace; out8 = {waves per
  *           workgroup, waves per row tile, weight chunks a wave holds in registers, 1 if it loops with a
  *           prefetch, LDS bytes per workgroup, workgroups, row tiles per workgroup, 1 if the activation

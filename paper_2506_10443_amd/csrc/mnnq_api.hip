@@ -168,7 +168,7 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
         return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
                              static_cast<hipStream_t>(stream));
     // With the matrix-core plane and room for the activations' planes: the GEMM on the fp6 matrix instructions.
-    if (prefill6_wanted(L, M) && workspace && workspace_bytes >= prefill6_ws_bytes(M, K)) {
+    if (prefill6_possible(L, M) && workspace && workspace_bytes >= prefill6_ws_bytes(M, K)) {
         if (int s = launch_act_planes(xq, M, K, workspace, static_cast<hipStream_t>(stream))) return s;
         return launch_prefill6(static_cast<const uint8_t*>(packed), L, M, workspace, sx, bias, static_cast<float*>(y),
                                nullptr, static_cast<hipStream_t>(stream));
@@ -277,11 +277,11 @@ int prefill_fused_impl(const void* packed, int64_t M, int64_t N, int64_t K, int 
             if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
             return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
         }
-        if (!(planes && prefill6_wanted(L, M)) && ksplit8_wanted(L, M)) {
+        if (!(planes && prefill6_possible(L, M)) && ksplit8_wanted(L, M)) {
             if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
             return launch_ksplit8(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
         }
-        if (planes && prefill6_wanted(L, M)) {
+        if (planes && prefill6_possible(L, M)) {
             if (int s = launch_quant_planes(x, M, K, prefill6_row_tiles(M), workspace, sx, st)) return s;
             return launch_prefill6(static_cast<const uint8_t*>(packed), L, M, workspace, sx, bias, static_cast<float*>(y),
                                    nullptr, st);
@@ -519,7 +519,7 @@ int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mo
         const int64_t slab = prefill_fits(M, N, K, mode) ? M : prefill_slab_rows(N, K, mode);
         if (slab <= 0) return MNNQ_ERR_UNSUPPORTED;
         const int64_t rows = slab < M ? slab : M;         // (of the first slab, for batches beyond one launch)
-        if (prefill6_wanted(L, rows)) describe_prefill6(L, rows, out8);   // (when the call is given its workspace)
+        if (prefill6_possible(L, rows)) describe_prefill6(L, rows, out8);   // (when the call is given its workspace)
         else describe_prefill(L, rows, out8);
     } else {
         if (L.K > kMaxDecodeK) return MNNQ_ERR_UNSUPPORTED;

@@ -676,20 +676,10 @@ bool prefill6_possible(const Layout& L, int64_t M)
            (int64_t)prefill6_ws_bytes(M, L.Kx) <= lim;
 }
 
-// Without its K-split kernel this GEMM would leave the shape to the int8 one, which splits K over workgroups and in more
-// parts: fewer 128 x 128 tiles than a quarter of the CUs and a long K.
-static bool few_tiles_long_k(const Layout& L, int64_t M) { return 4 * tiles6(L, M, 128, 128) < num_cus() && L.Kx >= 4096; }
-
-bool prefill6_wanted(const Layout& L, int64_t M)
-{
-    if (!prefill6_possible(L, M)) return false;
-    if (debug_option(kDbgPrefill6Plan)) return true;   // a forced plan: tests and tuning
-    return ksplit_wanted(L, M) || !few_tiles_long_k(L, M);
-}
-
 void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
 {
-    const Plan6Info p = plan6_info(choose_plan6(L, M), L, M);
+    const int plan = choose_plan6(L, M);
+    const Plan6Info p = plan6_info(plan, L, M);
     const int64_t MT = (M + p.BM - 1) / p.BM, NT = (L.N + p.BN - 1) / p.BN;
     out[0] = p.BM;
     out[1] = p.BN;
@@ -698,8 +688,7 @@ void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
     out[4] = p.waves;
     out[5] = (int32_t)p.lds;
     out[6] = (int32_t)(MT * ((NT + 7) / 8) * 8);
-    // operands in fp6; 7: where that takes the K-split kernel (a long K and few tiles)
-    out[7] = !debug_option(kDbgPrefill6Plan) && few_tiles_long_k(L, M) ? 7 : 6;
+    out[7] = plan >= 6 ? 7 : 6;   // operands in fp6: the K-split kernel, the tiled one
 }
 
 int launch_plane_build(uint8_t* packed, const Layout& L, hipStream_t st)

@@ -171,10 +171,10 @@ def test_prefill6_binary16_output_and_bias(plan):
         assert y16.dtype == np.float16 and np.array_equal(y16, y32.astype(np.float16))
 
 
-def test_few_output_tiles_take_the_int8_gemm_unless_a_plan_is_forced():
+def test_few_output_tiles_take_the_k_split_kernel_unless_a_plan_is_forced():
     M, N, K = 150, 512, 4096
-    assert B.mnnq_plan_debug(0, M, N, K, mode=MODE)[7] != 6
-    assert B.mnnq_plan_debug(0, M, N, 1536, mode=MODE)[7] == 6      # short K: nothing to split
+    for k in (K, 1536):         # long and short rows: 64 x 32 tiles, at most one per CU
+        assert B.mnnq_plan_debug(0, M, N, k, mode=MODE)[:3] == [64, 32, 8] and B.mnnq_plan_debug(0, M, N, k, mode=MODE)[7] == 7
     assert B.mnnq_plan_debug(0, 1024, 4608, 3584, mode=MODE)[7] == 6
     B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 2)
     assert B.mnnq_plan_debug(0, M, N, K, mode=MODE)[:2] == [128, 256] and B.mnnq_plan_debug(0, M, N, K, mode=MODE)[7] == 6
