@@ -511,11 +511,30 @@ int mnnq_linear_prefill_f16_o16(const void* packed, int64_t M, int64_t N, int64_
 int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mode, int32_t* out8)
 {
     if (!out8) return MNNQ_ERR_NULL;
-    if (what < 0 || what > 2) return MNNQ_ERR_UNSUPPORTED;
-    if (what == 0 && M <= 0) return MNNQ_ERR_SHAPE;
+    if (what < 0 || what == 3 || what > 5) return MNNQ_ERR_UNSUPPORTED;
+    if ((what == 0 || what >= 4) && M <= 0) return MNNQ_ERR_SHAPE;
     if (int s = check_shape(N, K, group, mode)) return s;
     const Layout L = make_layout(N, K, mode);
-    if (what == 0) {
+    if (what >= 4) {
+        const bool f16 = what == 5;
+        if (f16 && L.native8) return MNNQ_ERR_UNSUPPORTED;
+        const int64_t slab = prefill_fits(M, N, K, mode, f16 ? 2 : 1) ? M : prefill_slab_rows(N, K, mode, f16 ? 2 : 1);
+        if (slab <= 0) return MNNQ_ERR_UNSUPPORTED;
+        const int64_t rows = slab < M ? slab : M;
+        for (int i = 0; i < 8; ++i) out8[i] = 0;
+        if (f16 ? skinny_f16_wanted(L, rows) : few_tokens_wanted(L, rows)) {
+            describe_skinny(L, rows, f16, out8);
+        } else if (!f16 && prefill6_possible(L, rows)) {
+            int32_t p[8];
+            describe_prefill6(L, rows, p);
+            out8[0] = p[7];
+            out8[1] = p[0];
+            out8[2] = p[1];
+            out8[3] = out8[4] = p[4];
+        } else if (f16 ? ksplit_f16_wanted(L, rows) : ksplit8_wanted(L, rows)) {
+            describe_ksplit(L, rows, f16, out8);
+        }
+    } else if (what == 0) {
         const int64_t slab = prefill_fits(M, N, K, mode) ? M : prefill_slab_rows(N, K, mode);
         if (slab <= 0) return MNNQ_ERR_UNSUPPORTED;
         const int64_t rows = slab < M ? slab : M;         // (of the first slab, for batches beyond one launch)

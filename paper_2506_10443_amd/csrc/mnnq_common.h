@@ -305,6 +305,10 @@ int allow_large_lds(Kernel kern, size_t bytes, int& allowed_dev)
 // decode: {waves per workgroup, waves per row tile, chunks held in registers, 1 if the wave loops with
 // a prefetch, LDS bytes, workgroups, row tiles per workgroup, 0}.
 void describe_prefill(const Layout& L, int64_t M, int32_t out[8]);
+// few tokens and K split: {family (mnnq_plan_debug, what = 4), tile tokens, tile weight rows, waves, waves the kernel is
+// built for, chunks held in registers}
+void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8]);
+void describe_ksplit(const Layout& L, int64_t M, bool f16, int32_t out[8]);
 void describe_decode(const Layout& L, bool fused, int32_t out[8]);
 
 }  // namespace mnnq

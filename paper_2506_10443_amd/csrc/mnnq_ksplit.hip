@@ -367,13 +367,17 @@ int form_of(const Layout& L, bool f16)
     return L.native8 ? kBytes : L.minf ? kMin : kZp;
 }
 
+// Waves that share a tile: eight where there is one tile per CU, else four, and a CU holds two workgroups.
+int waves_of(const Layout& L, int64_t M, int tm)
+{
+    return (M + 16 * tm - 1) / (16 * tm) * ((L.T + TN - 1) / TN) <= num_cus() ? 8 : 4;
+}
+
 template <int FORM, int TM>
 int launch_height(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st)
 {
-    // one tile per CU: eight waves share it, else four, and a CU holds two workgroups
-    const int64_t tiles = (M + 16 * TM - 1) / (16 * TM) * ((L.T + TN - 1) / TN);
-    if (tiles <= num_cus()) return launch<FORM, 8, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
+    if (waves_of(L, M, TM) == 8) return launch<FORM, 8, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
     return launch<FORM, 4, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
 }
 
@@ -402,6 +406,15 @@ bool ksplit8_wanted(const Layout& L, int64_t M)
     const int form = form_of(L, false);
     return tile_height(L, M, form).rounds <= tiled_rounds(L, M, form) && (M + 64) * L.Kx < lim &&
            (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 2048 < lim;
+}
+
+void describe_ksplit(const Layout& L, int64_t M, bool f16, int32_t out[8])
+{
+    const int tm = tile_height(L, M, form_of(L, f16)).tm;
+    out[0] = 3;
+    out[1] = 16 * tm;
+    out[2] = 16 * TN;
+    out[3] = out[4] = waves_of(L, M, tm);
 }
 
 int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,

@@ -472,7 +472,8 @@ FewPlan few_plan(const Layout& L, int tm, int form)
     if (const char* e = debug_option(kDbgDecodeKsplit)) {   // tests and tuning: force the split
         const int v = atoi(e);
         if (v >= 1 && v <= stream_waves(tm, form) && v <= C) {
-            p.resident = p.resident && (C + v - 1) / v <= nch;
+            // (the resident kernel is built for its own number of waves, which may be the smaller one)
+            p.resident = p.resident && (C + v - 1) / v <= nch && v <= resident_waves(tm, nch, form);
             ks = v;
         }
     }
@@ -511,14 +512,25 @@ int launch_form(const uint8_t* packed, const Layout& L, int M, const void* xq, b
     return MNNQ_OK;
 }
 
+// Token blocks per workgroup: all of them up to 64 tokens, beyond that an even share of at most four.
+int blocks_of(int64_t M)
+{
+    const int n = (int)(M + 15) / 16;
+    const int slices = (n + 3) / 4;
+    return (n + slices - 1) / slices;
+}
+
+int form_of(const Layout& L, bool f16)
+{
+    if (f16) return L.minf ? kMinF16 : kZpF16;
+    return L.native8 ? kBytes : L.minf ? kMin : kZp;
+}
+
 template <int FORM>
 int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq, bool blocks, const float* sx, const float* bias,
                   float* y, hipStream_t st)
 {
-    // token blocks per workgroup: all of them up to 64 tokens, beyond that an even share of at most four
-    const int n = (M + 15) / 16;
-    const int slices = (n + 3) / 4;
-    switch ((n + slices - 1) / slices) {
+    switch (blocks_of(M)) {
         case 1: return launch_form<1, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
         case 2: return launch_form<2, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
         case 3: return launch_form<3, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
@@ -544,12 +556,23 @@ bool skinny_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgNoSkinny) || debug_option(kDbgPrefillTile)) return false;   // tests and tuning: the tiled GEMM
     if (M <= 16) return true;
-    const int blocks = (int)(M + 15) / 16;
-    const int form = L.minf ? kMinF16 : kZpF16, tm = blocks <= 4 ? blocks : (blocks + 1) / 2;
-    const bool resident = M <= 128 && few_plan(L, tm, form).resident;
+    const bool resident = M <= 128 && few_plan(L, blocks_of(M), form_of(L, true)).resident;
     if (M <= 32) return resident || L.T <= 2 * (int64_t)num_cus();
     if (M <= 64) return resident || L.T <= num_cus();
     return M <= 128 && resident && L.T * L.C <= 4096;
+}
+
+void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8])
+{
+    const int tm = blocks_of(M), form = form_of(L, f16);
+    const FewPlan p = few_plan(L, tm, form);
+    const int waves = p.resident ? resident_waves(tm, p.nch, form) : stream_waves(tm, form);
+    out[0] = p.resident ? 1 : 2;
+    out[1] = 16 * tm;
+    out[2] = kTileN;
+    out[3] = p.ks;
+    out[4] = waves;
+    out[5] = p.resident ? p.nch : 0;
 }
 
 int launch_skinny_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,

@@ -152,3 +152,22 @@ def test_switches_and_errors():
     assert L.mnnq_plan_debug(1, 1, 16, 100, 64, 0, p) == -2
     assert L.mnnq_plan_debug(1, 1, 16, 131072, 64, 0, p) == -3    # longer than the GEMV stages in LDS
     assert L.mnnq_plan_debug(1, 1, 16, 53248, 64, 0, p) == 0 and out[4] > 64 * 1024 and out[4] <= 160 * 1024
+
+
+@pytest.mark.parametrize("what,mode", [(4, B.MODE_W4_ZP_INT), (4, B.MODE_W4_MIN_FLOAT), (4, B.MODE_W8_MIN_FLOAT),
+                                       (4, B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT), (5, B.MODE_W4_ZP_INT),
+                                       (5, B.MODE_W4_MIN_FLOAT), (5, B.MODE_W8_MIN_FLOAT)])
+def test_few_token_kernels_run_with_the_waves_they_are_built_for(what, mode):
+    """No split of K, a forced one among them, launches more waves than the chosen kernel's registers allow."""
+    try:
+        for force in (None, 1, 2, 4, 8, 16):
+            B.mnnq_debug_set("MNNQ_DECODE_KSPLIT", force)
+            for m in (2, 16, 17, 33, 49, 64):
+                for n, k in ((1536, 1536), (4608, 3584), (3584, 18944), (28672, 4096), (48, 128)):
+                    family, tokens, rows, waves, most, held = B.mnnq_plan_debug(what, m, n, k, mode)[:6]
+                    assert 1 <= waves <= most or family == 0
+                    if family == 1:     # every chunk of the packed row in a wave's registers
+                        chunks = -(-k // 128) * (2 if mode == B.MODE_W8_MIN_FLOAT else 1)
+                        assert -(-chunks // waves) <= held
+    finally:
+        B.mnnq_debug_set("MNNQ_DECODE_KSPLIT", None)
