@@ -99,9 +99,25 @@ __device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, u
     return o;
 }
 
-template <int FORM, int KS, int TM>
+// Rows of int8 codes (calls that bring their codes).  Read in the operand's order - lane l: token l % 16, k block l / 16 -
+// four neighbouring lanes ask for 16 bytes of four tokens each, and the calls lost to the tiled GEMM wherever the token
+// blocks won; here they take 64 consecutive bytes of one token (lane l: token l / 4, k block l % 4), the two groups of a
+// chunk - one line - are requested together, and the operand's order is made in registers, through the LDS crossbar, a row
+// of tiles ahead (1024 tokens of 3584 x 18944 183 -> 141 us, 128 of 3584 x 3584 24.6 -> 13.6 us, int8 bytes 1024 tokens of
+// 3584 x 18944 216 -> 172 us; whole lines staged through LDS instead: the same within 2 %).
+struct RowExchange {
+    int from;       // byte address of the lane that holds this lane's piece
+    __device__ __forceinline__ explicit RowExchange(int lane) : from((4 * (lane & 15) + (lane >> 4)) * 4) {}
+    __device__ __forceinline__ void operator()(v4i& v) const
+    {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_ds_bpermute(from, v[d]);
+    }
+};
+
+template <int FORM, int KS, int TM, bool BLOCKS>
 __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                          const void* __restrict__ xq, bool blocks,
+                                                          const void* __restrict__ xq,
                                                           const float* __restrict__ sx, const float* __restrict__ bias,
                                                           float* __restrict__ y, int MT, int NT)
 {
@@ -122,13 +138,16 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     constexpr int E = is_f16(FORM) ? 2 : 1;
     const int Cx = (int)L.Cx;
     const __amdgpu_buffer_rsrc_t rs_x = rsrc(xq, (int64_t)M * L.Kx * E);
-    const int x_step = blocks ? M * 64 : 64 * E;        // bytes from group to group
+    const int x_step = BLOCKS ? M * 64 : 64 * E;        // bytes from group to group
+    constexpr bool XCH = !BLOCKS && !is_f16(FORM);
+    const RowExchange exchange(lane);
     int x_voff[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int first = m0 + i * 16, left = M - first, width = left < 16 ? left : 16;
-        x_voff[i] = row < width ? (blocks ? first * 64 + (kb * width + row) * 16 : (first + row) * (int)L.Kx * E + kb * 16 * E)
-                                : kOutOfRange;
+        const int m = XCH ? lane >> 2 : row, k = XCH ? lane & 3 : kb;
+        x_voff[i] = m < width ? (BLOCKS ? first * 64 + (k * width + m) * 16 : (first + m) * (int)L.Kx * E + k * 16 * E)
+                              : kOutOfRange;
     }
     // weights: column tile j of this workgroup is row tile t0 + j of the layout (past the matrix: outside the buffers)
     constexpr int WB = FORM == kBytes ? 2048 : 1024, ZB = has_zero(FORM) ? 32 : 128;
@@ -214,6 +233,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
                     load_params(u, j, c + u + 2);
                 }
             }
+            if (XCH && h == 0) exchange(a[0][0][0]);
             v4i d[2];
             float xf[2][4];
             v4i cbase = zero4;
@@ -243,8 +263,15 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
                         d[t & 1] = __builtin_bit_cast(v4i, mfma_f16(a[h][i][X], b[j].q[X], mfma_f16(a[h][i][0], b[j].q[0], zerof)));
                     else
                         d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], b[j].q[0], FORM == kBytes ? cbase : magic, 0, 0, 0);
-                    if (j == TN - 1) load_a(h, i, c + u + 1);
+                    if (!XCH && j == TN - 1) load_a(h, i, c + u + 1);
+                    if (XCH && h == 1 && j == TN - 1) {      // (both groups of a line)
+                        load_a(0, i, c + u + 1);
+                        load_a(1, i, c + u + 1);
+                    }
                     if (FORM == kBytes && i == TM - 1) load_codes(u, j, h, c + u + 2);
+                    // the next operand, a row of tiles ahead
+                    if (XCH && j == 0 && i + 1 < TM) exchange(a[h][(i + 1) % TM][0]);
+                    if (XCH && j == 0 && i + 1 == TM && h == 0) exchange(a[1][0][0]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (t > 0) {
@@ -307,19 +334,19 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     }
 }
 
-template <int FORM, int KS, int TM>
-int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
-           const float* bias, float* y, hipStream_t st)
+template <int FORM, int KS, int TM, bool BLOCKS>
+int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, const float* sx, const float* bias, float* y,
+           hipStream_t st)
 {
     constexpr int T = TM * TN;
     const int MT = (int)((M + 16 * TM - 1) / (16 * TM)), NT = (int)((L.T + TN - 1) / TN);
     constexpr size_t smem = (size_t)KS * T * 64 * 16;
     static_assert(smem <= kLdsPerWorkgroup, "partial tiles in LDS");
-    auto kern = ksplit_kernel<FORM, KS, TM>;
+    auto kern = ksplit_kernel<FORM, KS, TM, BLOCKS>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
     const int64_t grid = (int64_t)MT * ((NT + 7) / 8) * 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * KS), smem, st, packed, L, (int)M, xq, blocks, sx, bias, y, MT, NT);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * KS), smem, st, packed, L, (int)M, xq, sx, bias, y, MT, NT);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
 }
@@ -377,8 +404,13 @@ template <int FORM, int TM>
 int launch_height(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, bool blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st)
 {
-    if (waves_of(L, M, TM) == 8) return launch<FORM, 8, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
-    return launch<FORM, 4, TM>(packed, L, M, xq, blocks, sx, bias, y, st);
+    const bool eight = waves_of(L, M, TM) == 8;
+    if constexpr (!is_f16(FORM)) {
+        if (blocks && eight) return launch<FORM, 8, TM, true>(packed, L, M, xq, sx, bias, y, st);
+        if (blocks) return launch<FORM, 4, TM, true>(packed, L, M, xq, sx, bias, y, st);
+    }
+    if (eight) return launch<FORM, 8, TM, false>(packed, L, M, xq, sx, bias, y, st);
+    return launch<FORM, 4, TM, false>(packed, L, M, xq, sx, bias, y, st);
 }
 
 template <int FORM>

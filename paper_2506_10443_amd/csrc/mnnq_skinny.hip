@@ -214,26 +214,40 @@ __device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const ActReg
     }
 }
 
+// Lanes of a load that brings rows of int8 codes: four in a row take 64 consecutive bytes of one token (lane l: token
+// l / 4, k block l % 4); the operand's order (token l % 16, k block l / 16) is made in registers, see mnnq_ksplit.hip.
+struct RowExchange {
+    int from;       // byte address of the lane that holds this lane's piece
+    __device__ __forceinline__ explicit RowExchange(int lane) : from((4 * (lane & 15) + (lane >> 4)) * 4) {}
+    __device__ __forceinline__ void operator()(v4i& v) const
+    {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_ds_bpermute(from, v[d]);
+    }
+};
+
 // The activations of one slice of tokens.  A operand of group g, token block t: 16 consecutive k of one token per lane,
 // from int8 rows or from the token blocks the fused call's quantizer writes ([group][block of 16 tokens][k block][token],
 // the last block as narrow as its tokens): there a wave reads one contiguous piece per group and block, and the
 // few-token kernels, which are bound by this traffic from L2 where K is long, gain a third (48 tokens, 3584 x 18944:
 // 32 -> 22 us).  Chunk c of the packed axis meets chunk c % Cx of the row; an odd row's last chunk has one group only.
-template <int TM, int FORM>
+template <int TM, int FORM, bool BLOCKS>
 struct Acts {
     static constexpr int E = is_f16(FORM) ? 2 : 1;     // bytes of a value
+    static constexpr bool XCH = !BLOCKS && !is_f16(FORM);
+    const RowExchange exchange;
     __amdgpu_buffer_rsrc_t x;
     int voff[TM];
     int Cx, odd_last, step;     // step: bytes from group to group
-    __device__ __forceinline__ Acts(const void* __restrict__ xp, const Layout& L, int M, bool blocks, int m0, int lane)
-        : x(rsrc(xp, (int64_t)M * L.Kx * E)), Cx((int)L.Cx), odd_last((L.G & 1) ? (int)L.C - 1 : -1),
-          step(blocks ? M * 64 : 64 * E)
+    __device__ __forceinline__ Acts(const void* __restrict__ xp, const Layout& L, int M, int m0, int lane)
+        : exchange(lane), x(rsrc(xp, (int64_t)M * L.Kx * E)), Cx((int)L.Cx), odd_last((L.G & 1) ? (int)L.C - 1 : -1),
+          step(BLOCKS ? M * 64 : 64 * E)
     {
-        const int kb = lane >> 4;
+        const int kb = XCH ? lane & 3 : lane >> 4, m = XCH ? lane >> 2 : lane & 15;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
-            const int first = m0 + t * 16, left = M - first, width = left < 16 ? left : 16, m = lane & 15;
-            const int at = blocks ? first * 64 + (kb * width + m) * 16 : (first + m) * (int)L.Kx * E + kb * 16 * E;
+            const int first = m0 + t * 16, left = M - first, width = left < 16 ? left : 16;
+            const int at = BLOCKS ? first * 64 + (kb * width + m) * 16 : (first + m) * (int)L.Kx * E + kb * 16 * E;
             voff[t] = m < width ? at : kOutOfRange;      // (tokens past M: zeros, no traffic)
         }
     }
@@ -249,6 +263,15 @@ struct Acts {
                 a[0][t][e] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t] + e * 16, o0, 0);
                 a[1][t][e] = __builtin_amdgcn_raw_buffer_load_b128(x, voff[t] + e * 16, o1, 0);
             }
+    }
+    // what load brought -> the operands
+    __device__ __forceinline__ void arrange(ActRegs<TM, FORM>& a) const
+    {
+        if (!XCH) return;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < TM; ++t) exchange(a[h][t][0]);
     }
 };
 
@@ -302,9 +325,9 @@ struct Output {
     }
 };
 
-template <int TM, int NCH, int FORM, int MAXW>
+template <int TM, int NCH, int FORM, int MAXW, bool BLOCKS>
 __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                                const void* __restrict__ xq, bool blocks,
+                                                                const void* __restrict__ xq,
                                                                 const float* __restrict__ sx,
                                                                 const float* __restrict__ bias, float* __restrict__ y)
 {
@@ -322,7 +345,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
     const Output<TM> out(y, lds_sx, L, M, m0, ks, KS, lane);
     const float sx_own = out.fetch_sx(sx, M, m0, lane);
     const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
-    const Acts<TM, FORM> acts(xq, L, M, blocks, m0, lane);
+    const Acts<TM, FORM, BLOCKS> acts(xq, L, M, m0, lane);
     ActRegs<TM, FORM> a[NCH];
 #pragma unroll
     for (int u = 0; u < NCH; ++u) acts.load(a[u], c0 + u, u < own);
@@ -339,6 +362,8 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
         return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, ((int)t * kTileN + row) * 4, 0, 0));
     };
     float b = bias_of(tile);
+#pragma unroll
+    for (int u = 0; u < NCH; ++u) acts.arrange(a[u]);
 
     int buf = 0, turn = 0;
     do {   // (the grid has no more workgroups than there are row tiles)
@@ -373,9 +398,9 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
     } while (tile < L.T);
 }
 
-template <int TM, int DEPTH, int FORM, int MAXW>
+template <int TM, int DEPTH, int FORM, int MAXW, bool BLOCKS>
 __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
-                                                              const void* __restrict__ xq, bool blocks,
+                                                              const void* __restrict__ xq,
                                                               const float* __restrict__ sx,
                                                               const float* __restrict__ bias, float* __restrict__ y)
 {
@@ -395,7 +420,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __
     const float sx_own = out.fetch_sx(sx, M, m0, lane);
     const float b = __int_as_float(
         __builtin_amdgcn_raw_buffer_load_b32(rsrc(bias, bias ? L.N * 4 : 0), ((int)tile * kTileN + row) * 4, 0, 0));
-    const Acts<TM, FORM> acts(xq, L, M, blocks, m0, lane);
+    const Acts<TM, FORM, BLOCKS> acts(xq, L, M, m0, lane);
     const TileBuffers<FORM> weights(packed, L, tile);
     ActRegs<TM, FORM> a[DEPTH];
     WeightRegs<FORM> cur[DEPTH];
@@ -416,6 +441,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __
     do {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
+            acts.arrange(a[u]);
             contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);     // (past the wave's chunks everything is zero)
             const int next = c + u + DEPTH;
             cur[u] = weights.load(next < c1 ? next : C, lane, row);
@@ -482,9 +508,9 @@ FewPlan few_plan(const Layout& L, int tm, int form)
     return p;
 }
 
-template <int TM, int FORM>
-int launch_form(const uint8_t* packed, const Layout& L, int M, const void* xq, bool blocks, const float* sx, const float* bias,
-                float* y, hipStream_t st)
+template <int TM, int FORM, bool BLOCKS>
+int launch_form(const uint8_t* packed, const Layout& L, int M, const void* xq, const float* sx, const float* bias, float* y,
+                hipStream_t st)
 {
     const FewPlan p = few_plan(L, TM, FORM);
     const unsigned slices = (unsigned)((M + 16 * TM - 1) / (16 * TM));
@@ -497,17 +523,17 @@ int launch_form(const uint8_t* packed, const Layout& L, int M, const void* xq, b
         static thread_local int allowed[2] = {-1, -1};
         auto go = [&](auto kern, int& dev) -> int {
             if (int s = allow_large_lds(kern, smem, dev)) return s;
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid, slices), dim3(64 * p.ks), smem, st, packed, L, M, xq, blocks, sx, bias, y);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid, slices), dim3(64 * p.ks), smem, st, packed, L, M, xq, sx, bias, y);
             MNNQ_HIP_TRY(hipGetLastError());
             return MNNQ_OK;
         };
         if constexpr (resident_waves(TM, 4, FORM) != 0)
-            if (p.nch == 4) return go(few_resident_kernel<TM, 4, FORM, resident_waves(TM, 4, FORM)>, allowed[1]);
-        return go(few_resident_kernel<TM, 2, FORM, resident_waves(TM, 2, FORM)>, allowed[0]);
+            if (p.nch == 4) return go(few_resident_kernel<TM, 4, FORM, resident_waves(TM, 4, FORM), BLOCKS>, allowed[1]);
+        return go(few_resident_kernel<TM, 2, FORM, resident_waves(TM, 2, FORM), BLOCKS>, allowed[0]);
     }
     const size_t smem = (size_t)p.ks * TM * 64 * 16 + 256;
-    hipLaunchKernelGGL((few_stream_kernel<TM, stream_depth(TM, FORM), FORM, stream_waves(TM, FORM)>), dim3((unsigned)L.T, slices),
-                       dim3(64 * p.ks), smem, st, packed, L, M, xq, blocks, sx, bias, y);
+    hipLaunchKernelGGL((few_stream_kernel<TM, stream_depth(TM, FORM), FORM, stream_waves(TM, FORM), BLOCKS>),
+                       dim3((unsigned)L.T, slices), dim3(64 * p.ks), smem, st, packed, L, M, xq, sx, bias, y);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
 }
@@ -526,26 +552,34 @@ int form_of(const Layout& L, bool f16)
     return L.native8 ? kBytes : L.minf ? kMin : kZp;
 }
 
-template <int FORM>
-int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq, bool blocks, const float* sx, const float* bias,
-                  float* y, hipStream_t st)
+template <int FORM, bool BLOCKS>
+int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq, const float* sx, const float* bias, float* y,
+                  hipStream_t st)
 {
     switch (blocks_of(M)) {
-        case 1: return launch_form<1, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
-        case 2: return launch_form<2, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
-        case 3: return launch_form<3, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
-        default: return launch_form<4, FORM>(packed, L, M, xq, blocks, sx, bias, y, st);
+        case 1: return launch_form<1, FORM, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+        case 2: return launch_form<2, FORM, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+        case 3: return launch_form<3, FORM, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+        default: return launch_form<4, FORM, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
     }
 }
 
 }  // namespace
 
+template <bool BLOCKS>
+static int launch_int8(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, const float* sx, const float* bias,
+                       float* y, hipStream_t st)
+{
+    if (L.native8) return launch_tokens<kBytes, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+    if (L.minf) return launch_tokens<kMin, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+    return launch_tokens<kZp, BLOCKS>(packed, L, M, xq, sx, bias, y, st);
+}
+
 int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st)
 {
-    if (L.native8) return launch_tokens<kBytes>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
-    if (L.minf) return launch_tokens<kMin>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
-    return launch_tokens<kZp>(packed, L, (int)M, xq, blocks, sx, bias, y, st);
+    return blocks ? launch_int8<true>(packed, L, (int)M, xq, sx, bias, y, st)
+                  : launch_int8<false>(packed, L, (int)M, xq, sx, bias, y, st);
 }
 
 // fp16 activations.  Up to 16 tokens always; beyond, where the activation operands stay in registers (up to 32 tokens:
@@ -578,8 +612,8 @@ void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8])
 int launch_skinny_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,
                       hipStream_t st)
 {
-    if (L.minf) return launch_tokens<kMinF16>(packed, L, (int)M, x16, false, nullptr, bias, y, st);
-    return launch_tokens<kZpF16>(packed, L, (int)M, x16, false, nullptr, bias, y, st);
+    if (L.minf) return launch_tokens<kMinF16, false>(packed, L, (int)M, x16, nullptr, bias, y, st);
+    return launch_tokens<kZpF16, false>(packed, L, (int)M, x16, nullptr, bias, y, st);
 }
 
 }  // namespace mnnq

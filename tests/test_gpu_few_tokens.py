@@ -194,6 +194,8 @@ def test_k_split_tile_heights(form, M, N, K):
     B.mnnq_linear_prefill_fused(packed, N, K, dev(x), bias=dev(bias), out=out[:M], mode=mode)
     assert torch.isnan(out[M]).all()
     assert np.abs(out[:M].cpu().numpy() - y_o).max() <= 1e-5 * np.abs(y_o).max()
+    # int8 rows, whose pieces the kernel exchanges between its lanes: the same sums in the same order
+    assert torch.equal(B.mnnq_linear_prefill(packed, N, K, dev(xq), dev(sx), bias=dev(bias), mode=mode), out[:M])
     if form != "w8":        # fp16 activations: fp32 sums as the tiled kernel's, in another order
         x16 = dev(synth.activations_f16(M, K, 3302 + M))
         y16 = B.mnnq_linear_prefill_f16(packed, N, K, x16, mode=mode)
