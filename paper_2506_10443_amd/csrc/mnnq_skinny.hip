@@ -441,8 +441,12 @@ __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __
     do {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
-            acts.arrange(a[u]);
-            contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);     // (past the wave's chunks everything is zero)
+            // (past the wave's chunks nothing is contracted, but the loads go on - outside the buffers, so that they cost
+            // nothing: the waits stay counts)
+            if (u == 0 || c + u < c1) {
+                acts.arrange(a[u]);
+                contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);
+            }
             const int next = c + u + DEPTH;
             cur[u] = weights.load(next < c1 ? next : C, lane, row);
             acts.load(a[u], next, next < c1);
@@ -479,6 +483,17 @@ constexpr int stream_waves(int tm, int form) { return tm == 1 && !(form == kMinF
 // chunks in flight in the streaming form: what the registers hold without spilling
 constexpr int stream_depth(int tm, int form) { return is_f16(form) ? (tm == 1 ? 3 : tm <= 2 ? 4 : 2) : (tm <= 3 ? 4 : 3); }
 
+// Waves that share a row tile in the streaming form.  One block of tokens: the chunks a wave takes one after the other are
+// read ahead, further waves on the tile bring no more bytes in flight at once than that, and each adds its partial sums -
+// four, eight where half the CUs have no tile.  Two tokens with 4 / 8 / 16 waves: 4096 x 14336 int4 9.9 / 10.8 / 11.1 us,
+// float minimum 9.6 / 10.4 / 11.8, int8 nibble planes 16.4 / 16.9 / 19.2; 5120 x 13824 float minimum 15.4 / 18.0 / 21.5;
+// 1536 x 8960 (96 tiles) int4 7.2 / 6.5 / 7.6.  (The kernel stays built for sixteen: two to four workgroups on a CU.)
+int stream_split(const Layout& L, int tm, int form)
+{
+    if (tm > 1 || is_f16(form)) return stream_waves(tm, form);
+    return 2 * L.T < num_cus() ? 8 : 4;
+}
+
 FewPlan few_plan(const Layout& L, int tm, int form)
 {
     FewPlan p{};
@@ -492,7 +507,7 @@ FewPlan few_plan(const Layout& L, int tm, int form)
     p.resident = fits(nch);
     if (const char* e = debug_option(kDbgSkinnyStaged)) p.resident = p.resident && e[0] == '1';   // tests
     if (!p.resident) {
-        ks = stream_waves(tm, form);
+        ks = stream_split(L, tm, form);
         if (C < ks) ks = C;
     }
     if (const char* e = debug_option(kDbgDecodeKsplit)) {   // tests and tuning: force the split

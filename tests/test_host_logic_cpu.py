@@ -171,3 +171,12 @@ def test_few_token_kernels_run_with_the_waves_they_are_built_for(what, mode):
                         assert -(-chunks // waves) <= held
     finally:
         B.mnnq_debug_set("MNNQ_DECODE_KSPLIT", None)
+
+
+@pytest.mark.parametrize("mode", [B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT, B.MODE_W8_MIN_FLOAT, B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT])
+def test_few_tokens_of_long_rows_share_a_tile_among_few_waves(mode):
+    """One block of tokens, rows too long for the registers: four waves on a row tile, eight where tiles are few."""
+    for n, k, waves in ((4096, 14336, 4), (3584, 18944, 4), (2048, 8448, 4), (2032, 8448, 8), (1536, 8960, 8)):
+        for m in (2, 16):
+            assert B.mnnq_plan_debug(4, m, n, k, mode)[:4] == [2, 16, 16, waves]
+    assert B.mnnq_plan_debug(4, 17, 4096, 14336, mode)[3] == 8
