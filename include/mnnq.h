@@ -183,7 +183,8 @@ int mnnq_linear_prefill_fused(const void *packed, int64_t M, int64_t N, int64_t 
  *   mnnq_linear_prefill_planes: y [M, N] from those planes, the scales sx [M] and the packed weights;
  *     mode must carry MNNQ_WITH_MATRIX_PLANE and M must exceed 32 (MNNQ_ERR_UNSUPPORTED otherwise).
  * The result is that of mnnq_linear_prefill with a workspace, bit for bit, whenever that call takes
- * the fp6 GEMM as well (it leaves up to 64 tokens, 128 on small layers, to the few-token kernels). */
+ * the fp6 GEMM as well (it leaves up to 64 tokens of most layers, 128 of small ones, to the few-token
+ * kernels: what = 4 of mnnq_plan_debug). */
 size_t mnnq_act_planes_size(int64_t M, int64_t K, int group);
 int mnnq_act_planes(const int8_t *xq, int64_t M, int64_t K, int group, void *planes, size_t planes_bytes,
                     void *stream);

@@ -111,20 +111,6 @@ Layout layout_for(int64_t N, int64_t K, int mode, bool out16)
     return L;
 }
 
-// Up to this many tokens the few-token kernels beat the GEMMs where the call's own quantizer lays the codes out for them
-// (Qwen2-7B's down projection, 48 / 64 tokens: 24 / 28 us against 35 / 36 us tiled).  On int8 rows they lose a little
-// beyond 48 tokens (40 against 36 us), but the line is the same for both, so that the fused call stays bit for bit the
-// two calls.  Small layers stay with them up to 128 tokens in two slices: row tiles x chunks up to 7000 (128 tokens of
-// 2048 x 1536 7.7 against 11.3 us, of 1536 x 8960 - 6720 - 19 against 24 us; of 4608 x 3584 - 8064 - 18 against 15 us).
-constexpr int64_t kFewTokens = 64, kFewTokensSmall = 128, kSmallCells = 7000;
-
-bool few_tokens_wanted(const Layout& L, int64_t M)
-{
-    // (a forced tile or plan, tests and tuning: the tiled GEMMs)
-    return (M <= kFewTokens || (M <= kFewTokensSmall && L.T * L.C <= kSmallCells)) && !debug_option(kDbgNoSkinny) &&
-           (M <= 16 || (!debug_option(kDbgPrefillTile) && !debug_option(kDbgPrefill6Plan)));
-}
-
 // The four linear calls that exist with fp32 and with binary16 output; y points to the output array
 // of the requested kind (the kernels store through it according to Layout::out16).
 int decode_impl(const void* packed, int64_t N, int64_t K, int group, int mode, const int8_t* xq, const float* sx,
@@ -164,7 +150,7 @@ int prefill_impl(const void* packed, int64_t M, int64_t N, int64_t K, int group,
     }
     // A few tokens (batched or speculative decoding) are still memory-bound: one pass over the
     // weights in the GEMV's streaming order, all tokens at once in the matrix cores.
-    if (few_tokens_wanted(L, M))
+    if (skinny_wanted(L, M))
         return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, false, sx, bias, static_cast<float*>(y),
                              static_cast<hipStream_t>(stream));
     // With the matrix-core plane and room for the activations' planes: the GEMM on the fp6 matrix instructions.
@@ -273,7 +259,7 @@ int prefill_fused_impl(const void* packed, int64_t M, int64_t N, int64_t K, int 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Layout L = layout_for(N, K, mode, out16);
     if (quant_packed_possible(K) && prefill_fits(M, N, K, mode)) {
-        if (few_tokens_wanted(L, M)) {
+        if (skinny_wanted(L, M)) {
             if (int s = launch_quant_token_blocks(x, M, K, xq, sx, st)) return s;
             return launch_skinny(static_cast<const uint8_t*>(packed), L, M, xq, true, sx, bias, static_cast<float*>(y), st);
         }
@@ -522,7 +508,7 @@ int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mo
         if (slab <= 0) return MNNQ_ERR_UNSUPPORTED;
         const int64_t rows = slab < M ? slab : M;
         for (int i = 0; i < 8; ++i) out8[i] = 0;
-        if (f16 ? skinny_f16_wanted(L, rows) : few_tokens_wanted(L, rows)) {
+        if (f16 ? skinny_f16_wanted(L, rows) : skinny_wanted(L, rows)) {
             describe_skinny(L, rows, f16, out8);
         } else if (!f16 && prefill6_possible(L, rows)) {
             int32_t p[8];

@@ -256,6 +256,7 @@ size_t ksplit6_lds_bytes(int form);
 int launch_ksplit6(int form, const uint8_t* packed, const Layout& L, int64_t M, const void* planes, const float* sx,
                    const float* bias, float* y, hipStream_t st);
 // A few tokens sharing one pass over the weights; token_blocks: xq as launch_quant_token_blocks writes it.
+bool skinny_wanted(const Layout& L, int64_t M);
 int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,
                   const float* bias, float* y, hipStream_t st);
 // The same with fp16 activations.

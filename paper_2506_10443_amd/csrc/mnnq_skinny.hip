@@ -581,6 +581,43 @@ int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq,
 
 }  // namespace
 
+// int8 activations, from rows or token blocks (the same line for both, so that the fused call stays bit for bit the two calls).
+// Up to 16 tokens always.  Up to 64 tokens:
+//   * where the activations stay in registers, but for the tallest operands (49 tokens and more) on layers of very many row
+//     tiles, which the GEMMs take in few whole rounds: 64 tokens, few-token against the better GEMM, int4 20480 x 2048
+//     10.5 / 13, 28672 x 4096 23.2 / 22.4, 37888 x 3584 28.2 / 26.0 us; with a float minimum, twice the matrix instructions,
+//     already 14336 x 4096 18.3 / 15.1 (8192 x 2048 9.1 / 9.8); bytes, half the unpacking, 28672 x 4096 33.2 / 36.9;
+//   * where both operands stream, while the row tiles are one round of workgroups (a CU holds one): 33 tokens, few-token /
+//     K-split / tiled, int4 4096 x 14336 (256 tiles) 16.1 / 16.7 / 26.0, 5120 x 5120 (320) 17.9 / 8.4 / 16.6, 13824 x 5120
+//     (864) 34.4 / 13.6 / 18.5 us;
+//   * int8 nibble planes run twice the chunks here, which the tiled GEMM - the only other kernel - merges: what decides is
+//     the time of the rounds in us, fitted to 330 shapes (17 - 64 tokens; few-token / tiled, 33 tokens: 8192 x 8192 34 / 48,
+//     13824 x 5120 50 / 53, 28672 x 4096 75 / 46, 37888 x 3584 100 / 67).
+// Up to 128 tokens, in two slices, where the slices of all row tiles are one round of workgroups and the rows not too long
+// (row tiles x chunks up to 7000; 128 tokens, few-token / K-split / tiled: 2048 x 1536 (128 tiles) 4.7 / 5.3 / 8.5, 1104 x 4096
+// 7.7 / 7.3 / 14.4, 1536 x 8960 13.0 / 11.4 / 19.7, with the quantizer's call before 15.8 / 16.1; beyond one round 2560 x 2560
+// (160 tiles) 11.7 / 7.8 / 10.8, 3584 x 3584 13.6 / 8.9 / 13.2 us; nibble planes, tiled only, 2560 x 2560 17.4 / - / 29.3).
+bool skinny_wanted(const Layout& L, int64_t M)
+{
+    constexpr int64_t kFewTokens = 64, kTwoSlices = 128, kSmallCells = 7000;
+    if (debug_option(kDbgNoSkinny)) return false;
+    if (M <= 16) return true;
+    if (debug_option(kDbgPrefillTile) || debug_option(kDbgPrefill6Plan)) return false;   // tests and tuning: the tiled GEMMs
+    const int64_t cus = num_cus();
+    const bool planes8 = L.mode == MNNQ_W8_MIN_FLOAT && !L.native8;
+    if (M > kFewTokens) return M <= kTwoSlices && L.T * L.C <= kSmallCells && (planes8 || 2 * L.T <= cus);
+    if (debug_option(kDbgSkinnyStaged) || debug_option(kDbgDecodeKsplit)) return true;   // tests and tuning
+    const int tm = blocks_of(M), form = form_of(L, false);
+    if (few_plan(L, tm, form).resident) return tm < 4 || form == kBytes || L.T < (form == kMin && !planes8 ? 3 : 6) * cus;
+    if (!planes8) return L.T <= cus;
+    const float C = (float)L.Cx;
+    const int64_t tiles = (L.T + 7) / 8, rounds = (tiles + cus - 1) / cus;      // of 128 x 128
+    const bool halved = 2 * tiles <= cus && L.Cx >= 64 && !L.out16;             // (K split over two workgroups)
+    const float tiled = rounds == 1 ? 5.6f + (halved ? 0.6f : 1.2f) * C : (float)rounds * (3.4f + 1.07f * C);
+    const float few = (float)((L.T + cus - 1) / cus) * (4.4f + (0.033f + 0.0715f * (float)tm) * C);
+    return few <= tiled;
+}
+
 template <bool BLOCKS>
 static int launch_int8(const uint8_t* packed, const Layout& L, int M, const int8_t* xq, const float* sx, const float* bias,
                        float* y, hipStream_t st)

@@ -180,3 +180,23 @@ def test_few_tokens_of_long_rows_share_a_tile_among_few_waves(mode):
         for m in (2, 16):
             assert B.mnnq_plan_debug(4, m, n, k, mode)[:4] == [2, 16, 16, waves]
     assert B.mnnq_plan_debug(4, 17, 4096, 14336, mode)[3] == 8
+
+
+def test_few_token_kernels_where_they_are_the_faster_ones():
+    """Which layers leave the few-token kernels below 64 tokens, and which stay with them beyond: the shapes measured on
+    both sides of each line."""
+    few = lambda m, n, k, mode=B.MODE_W4_ZP_INT: B.mnnq_plan_debug(4, m, n, k, mode)[0] in (1, 2)
+    planes = B.MODE_W8_MIN_FLOAT
+    for mode in (B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT, B.MODE_W4_ZP_INT | B.WITH_MATRIX_PLANE, planes | B.NATIVE_8BIT):
+        assert all(few(16, n, k, mode) for n, k in ((13824, 5120), (37888, 3584)))
+        # both operands streamed: one round of workgroups and more
+        assert few(64, 4096, 14336, mode) and not few(17, 5120, 5120, mode) and not few(64, 13824, 5120, mode)
+        # two slices of tokens: one round and more
+        assert few(128, 2048, 1536, mode) and not few(65, 2560, 2560, mode) and not few(128, 3584, 3584, mode)
+        assert few(48, 37888, 3584, mode)
+    assert few(64, 20480, 2048) and not few(49, 28672, 4096) and few(64, 28672, 4096, planes | B.NATIVE_8BIT)
+    assert few(64, 8192, 2048, B.MODE_W4_MIN_FLOAT) and not few(49, 14336, 4096, B.MODE_W4_MIN_FLOAT)
+    # int8 nibble planes: twice the chunks, against the tiled GEMM that merges them
+    assert few(48, 8192, 8192, planes) and few(32, 13824, 5120, planes) and not few(48, 13824, 5120, planes)
+    assert not any(few(m, n, k, planes) for m in (17, 33, 64) for n, k in ((28672, 4096), (37888, 3584)))
+    assert few(128, 2560, 2560, planes)
