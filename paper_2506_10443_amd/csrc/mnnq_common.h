@@ -279,6 +279,21 @@ int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const 
 // Compute units of the current device (cached per thread and device).
 int num_cus();
 
+// Output tiles of a GEMM by XCD: workgroup b runs on XCD b % 8, and each XCD takes an even run of the tiles in column order,
+// so that a column of weights is fetched into one L2 (two where a run ends inside it) and the rules that count tiles per
+// CU hold.  Whole columns per XCD - 36 columns are five for four of them, four for the others - left a CU of the fuller
+// XCDs with a second tile where there was one per CU: fp16 activations, 1792 tokens of 4608 x 3584, 252 tiles, 119 us.
+constexpr int kXcdCount = 8;
+inline int64_t xcd_tile_grid(int64_t MT, int64_t NT) { return (MT * NT + kXcdCount - 1) / kXcdCount * kXcdCount; }
+__device__ __forceinline__ bool xcd_tile(int MT, int NT, int& tile_m, int& tile_n)
+{
+    const int tiles = MT * NT, run = (tiles + kXcdCount - 1) / kXcdCount;
+    const int t = (int)(blockIdx.x % kXcdCount) * run + (int)(blockIdx.x / kXcdCount);
+    tile_m = t % MT;
+    tile_n = t / MT;
+    return t < tiles;
+}
+
 // LDS of a workgroup on gfx950, and the amount a kernel may use without asking.
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 constexpr size_t kLdsDefault = 64 * 1024;
@@ -306,10 +321,11 @@ int allow_large_lds(Kernel kern, size_t bytes, int& allowed_dev)
 // decode: {waves per workgroup, waves per row tile, chunks held in registers, 1 if the wave loops with
 // a prefetch, LDS bytes, workgroups, row tiles per workgroup, 0}.
 void describe_prefill(const Layout& L, int64_t M, int32_t out[8]);
-// few tokens and K split: {family (mnnq_plan_debug, what = 4), tile tokens, tile weight rows, waves, waves the kernel is
-// built for, chunks held in registers}
+// few tokens, K split and fp16 tiles: {family (mnnq_plan_debug, what = 4), tile tokens, tile weight rows, waves, waves the
+// kernel is built for, chunks held in registers, workgroups (not for few tokens)}
 void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8]);
 void describe_ksplit(const Layout& L, int64_t M, bool f16, int32_t out[8]);
+void describe_prefill_f16(const Layout& L, int64_t M, int32_t out[8]);
 void describe_decode(const Layout& L, bool fused, int32_t out[8]);
 
 }  // namespace mnnq

@@ -125,10 +125,8 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     extern __shared__ __align__(16) float4 lds_sum[];   // [KS][T][64]
     const int lane = threadIdx.x & 63, row = lane & 15, kb = lane >> 4;
     const int ks = uniform(threadIdx.x >> 6);
-    // each XCD takes whole columns of tiles, so that a weight chunk is fetched into one L2 only
-    const int xcd = blockIdx.x % 8, seq = blockIdx.x / 8;
-    const int tile_m = seq % MT, tile_n = (seq / MT) * 8 + xcd;
-    if (tile_n >= NT) return;
+    int tile_m, tile_n;
+    if (!xcd_tile(MT, NT, tile_m, tile_n)) return;
     const int C = (int)L.C, m0 = tile_m * (16 * TM);
     const int c0 = C * ks / KS, c1 = C * (ks + 1) / KS;
     const int odd_last = (L.G & 1) ? C - 1 : -1;
@@ -345,7 +343,7 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, co
     auto kern = ksplit_kernel<FORM, KS, TM, BLOCKS>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
-    const int64_t grid = (int64_t)MT * ((NT + 7) / 8) * 8;
+    const int64_t grid = xcd_tile_grid(MT, NT);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * KS), smem, st, packed, L, (int)M, xq, sx, bias, y, MT, NT);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
@@ -447,6 +445,7 @@ void describe_ksplit(const Layout& L, int64_t M, bool f16, int32_t out[8])
     out[1] = 16 * tm;
     out[2] = 16 * TN;
     out[3] = out[4] = waves_of(L, M, tm);
+    out[6] = (int32_t)xcd_tile_grid((M + 16 * tm - 1) / (16 * tm), (L.T + TN - 1) / TN);
 }
 
 int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool blocks, const float* sx,

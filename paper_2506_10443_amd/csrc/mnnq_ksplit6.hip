@@ -66,11 +66,8 @@ __global__ __launch_bounds__(64 * KS) void ksplit6_kernel(const uint8_t* __restr
     constexpr int T = TM * TN, BLK = kPlaneBlockBytes;
     const int lane = threadIdx.x & 63;
     const int ks = uniform(threadIdx.x >> 6);
-    // XCD-aware order: workgroups are dealt to the eight XCDs round-robin; each XCD takes whole columns of tiles, so that
-    // a block of weights is fetched into one L2 only.
-    const int xcd = blockIdx.x % 8, seq = blockIdx.x / 8;
-    const int tile_m = seq % MT, tile_n = (seq / MT) * 8 + xcd;
-    if (tile_n >= NT) return;
+    int tile_m, tile_n;
+    if (!xcd_tile(MT, NT, tile_m, tile_n)) return;
     const int G = (int)L.Gx;
     const int g0 = G * ks / KS, g1 = G * (ks + 1) / KS;
 
@@ -224,7 +221,7 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const uint8_t* a6,
     auto kern = ksplit6_kernel<TM, TN, KS, DEPTH>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
-    const int64_t blocks = (int64_t)MT * ((NT + 7) / 8) * 8;
+    const int64_t blocks = xcd_tile_grid(MT, NT);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * KS), smem, st, packed + L.plane_off(), a6, L, M,
                        prefill6_row_tiles(M), sx, bias, y, MT, NT);
     MNNQ_HIP_TRY(hipGetLastError());

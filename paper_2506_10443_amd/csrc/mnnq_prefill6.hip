@@ -687,7 +687,7 @@ void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
     out[3] = 1;
     out[4] = p.waves;
     out[5] = (int32_t)p.lds;
-    out[6] = (int32_t)(MT * ((NT + 7) / 8) * 8);
+    out[6] = (int32_t)(plan >= 6 ? xcd_tile_grid(MT, NT) : MT * ((NT + 7) / 8) * 8);
     out[7] = plan >= 6 ? 7 : 6;   // operands in fp6: the K-split kernel, the tiled one
 }
 

@@ -133,13 +133,8 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 1 : 2) void prefill_f16_kernel(c
     const int K2 = (int)L.Kx * 2;                // bytes per activation row
     const int Gx = (int)L.Kx / 64;               // group g of the packed axis meets group g % Gx of the row
 
-    // Each XCD gets whole columns of output tiles, so that a weight block is fetched
-    // into one L2 only.
-    const int xcd = blockIdx.x % 8;
-    const int seq = blockIdx.x / 8;
-    const int tile_m = seq % MT;
-    const int tile_n = (seq / MT) * 8 + xcd;
-    if (tile_n >= NT) return;
+    int tile_m, tile_n;
+    if (!xcd_tile(MT, NT, tile_m, tile_n)) return;
     const int64_t m0 = (int64_t)tile_m * BM;
     const int rt0 = tile_n * NT16;
 
@@ -442,7 +437,7 @@ int launch_tiles_m(const uint8_t* packed, const Layout& L, int64_t M, const uint
             allowed_dev = dev;
         }
     }
-    const int64_t blocks = (int64_t)MT * ((NT + 7) / 8) * 8;
+    const int64_t blocks = xcd_tile_grid(MT, NT);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256 * KS), smem, st, packed, L, M, x16, rs, bias, y, MT, NT);
     MNNQ_HIP_TRY(hipGetLastError());
     return MNNQ_OK;
@@ -456,10 +451,13 @@ int launch_tiles(const uint8_t* packed, const Layout& L, int64_t M, const uint16
     return launch_tiles_m<BM, BN, false, KS>(packed, L, M, x16, rs, bias, y, st);
 }
 
-}  // namespace
+struct TilePlan {
+    bool big;      // 256 x 128, else 128 x 128
+    int ks;        // K parts
+};
 
-int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* rs,
-                       const float* bias, float* y, hipStream_t st)
+// rs: with a row factor
+TilePlan tile_plan(const Layout& L, int64_t M, bool rs)
 {
     // The tile by what the busiest CU has to do: 256 x 128 unpacks the weights for twice the rows, so that it costs as much as
     // 1.75 tiles of 128 x 128 instead of two, but leaves more of a last round empty.  Measured at K = 4096, 128-row against
@@ -479,6 +477,26 @@ int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const 
         if (e[0] == 's') big = false;
         if (e[0]) ks = (e[1] && e[2] == 'k') ? 2 : 1;
     }
+    return {big, ks};
+}
+
+}  // namespace
+
+void describe_prefill_f16(const Layout& L, int64_t M, int32_t out[8])
+{
+    const TilePlan p = tile_plan(L, M, false);
+    const int bm = p.big ? 256 : 128;
+    out[0] = 0;
+    out[1] = bm;
+    out[2] = 128;
+    out[3] = out[4] = 4 * p.ks;
+    out[6] = (int32_t)xcd_tile_grid((M + bm - 1) / bm, (L.N + 127) / 128);
+}
+
+int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* rs,
+                       const float* bias, float* y, hipStream_t st)
+{
+    const auto [big, ks] = tile_plan(L, M, rs != nullptr);
     if (big && ks == 2) return launch_tiles<256, 128, 2>(packed, L, M, x16, rs, bias, y, st);
     if (big) return launch_tiles<256, 128>(packed, L, M, x16, rs, bias, y, st);
     if (ks == 2) return launch_tiles<128, 128, 2>(packed, L, M, x16, rs, bias, y, st);

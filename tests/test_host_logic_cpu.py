@@ -200,3 +200,19 @@ def test_few_token_kernels_where_they_are_the_faster_ones():
     assert few(48, 8192, 8192, planes) and few(32, 13824, 5120, planes) and not few(48, 13824, 5120, planes)
     assert not any(few(m, n, k, planes) for m in (17, 33, 64) for n, k in ((28672, 4096), (37888, 3584)))
     assert few(128, 2560, 2560, planes)
+
+
+@pytest.mark.parametrize("what,mode,family", [(5, B.MODE_W4_ZP_INT, 0), (5, B.MODE_W4_ZP_INT, 3), (5, B.MODE_W8_MIN_FLOAT, 3),
+                                              (4, B.MODE_W4_MIN_FLOAT, 3), (4, B.MODE_W4_ZP_INT | B.WITH_MATRIX_PLANE, 7)])
+def test_tiles_are_dealt_evenly_to_the_xcds(what, mode, family):
+    """Columns of tiles that are no multiple of the eight XCDs: no more workgroups than tiles rounded up to eight (one set of
+    whole columns per XCD was up to 40 of 28 columns), since the rules of the dispatch count tiles per CU."""
+    met = 0
+    for m in (129, 333, 802, 1290, 1792):
+        for n, k in ((4608, 3584), (2560, 6400), (1136, 3712), (1040, 2688), (3440, 10496)):
+            f, tokens, rows, _, _, _, groups, _ = B.mnnq_plan_debug(what, m, n, k, mode)
+            if f == family:
+                met += 1
+                tiles = -(-m // tokens) * -(-n // rows)
+                assert tiles <= groups < tiles + 8
+    assert met
