@@ -583,10 +583,14 @@ int launch_tokens(const uint8_t* packed, const Layout& L, int M, const void* xq,
 
 // int8 activations, from rows or token blocks (the same line for both, so that the fused call stays bit for bit the two calls).
 // Up to 16 tokens always.  Up to 64 tokens:
-//   * where the activations stay in registers, but for the tallest operands (49 tokens and more) on layers of very many row
-//     tiles, which the GEMMs take in few whole rounds: 64 tokens, few-token against the better GEMM, int4 20480 x 2048
-//     10.5 / 13, 28672 x 4096 23.2 / 22.4, 37888 x 3584 28.2 / 26.0 us; with a float minimum, twice the matrix instructions,
-//     already 14336 x 4096 18.3 / 15.1 (8192 x 2048 9.1 / 9.8); bytes, half the unpacking, 28672 x 4096 33.2 / 36.9;
+//   * where the activations stay in registers, but for the tallest operands (49 tokens and more) on layers of many row tiles.
+//     64 tokens, the fused call, few-token / the GEMM behind it: int4 from six tiles per CU where a row takes three or five
+//     waves of four chunks, which leave a quarter of a CU's eight empty or more (28672 x 1152 16.2 / 14.5, x 2560
+//     23.3 / 21.2; four, six and seven waves 28672 x 2048 19.1 / 19.4, 24576 x 3072 22.7 / 23.5, 28672 x 3584
+//     26.2 / 28.5 us); with a float minimum, twice the matrix instructions, from three (37888 x 3584 39.4 / 38.5, 25424 x
+//     2304 27.1 / 21.1; 8192 x 2048 9.1 / 9.8); never in the byte form, half the unpacking (28672 x 4096 33.2 / 36.9), nor
+//     with the matrix-core plane, whose GEMM has tiles of 64 tokens for few row tiles only (28672 x 4096 27.6 / 32.6,
+//     37888 x 3584 33.7 / 49.7, 40960 x 2304 30.7 / 33.7 us);
 //   * where both operands stream, while the row tiles are one round of workgroups (a CU holds one): 33 tokens, few-token /
 //     K-split / tiled, int4 4096 x 14336 (256 tiles) 16.1 / 16.7 / 26.0, 5120 x 5120 (320) 17.9 / 8.4 / 16.6, 13824 x 5120
 //     (864) 34.4 / 13.6 / 18.5 us;
@@ -608,7 +612,12 @@ bool skinny_wanted(const Layout& L, int64_t M)
     if (M > kFewTokens) return M <= kTwoSlices && L.T * L.C <= kSmallCells && (planes8 || 2 * L.T <= cus);
     if (debug_option(kDbgSkinnyStaged) || debug_option(kDbgDecodeKsplit)) return true;   // tests and tuning
     const int tm = blocks_of(M), form = form_of(L, false);
-    if (few_plan(L, tm, form).resident) return tm < 4 || form == kBytes || L.T < (form == kMin && !planes8 ? 3 : 6) * cus;
+    const FewPlan plan = few_plan(L, tm, form);
+    if (plan.resident) {
+        if (tm < 4 || form == kBytes || L.plane) return true;
+        if (form == kMin) return L.T < (planes8 ? 6 : 3) * cus;
+        return L.T < 6 * cus || (plan.ks != 3 && plan.ks != 5);
+    }
     if (!planes8) return L.T <= cus;
     const float C = (float)L.Cx;
     const int64_t tiles = (L.T + 7) / 8, rounds = (tiles + cus - 1) / cus;      // of 128 x 128

@@ -194,7 +194,10 @@ def test_few_token_kernels_where_they_are_the_faster_ones():
         # two slices of tokens: one round and more
         assert few(128, 2048, 1536, mode) and not few(65, 2560, 2560, mode) and not few(128, 3584, 3584, mode)
         assert few(48, 37888, 3584, mode)
-    assert few(64, 20480, 2048) and not few(49, 28672, 4096) and few(64, 28672, 4096, planes | B.NATIVE_8BIT)
+    # 49 tokens and more: three or five waves for a row leave much of a CU empty; with the plane always
+    assert few(64, 20480, 2048) and few(64, 28672, 4096) and few(64, 37888, 3584) and few(64, 28672, 4096, planes | B.NATIVE_8BIT)
+    assert not few(49, 28672, 1152) and not few(49, 28672, 2560) and few(64, 20480, 2560)
+    assert all(few(m, n, k, B.MODE_W4_ZP_INT | B.WITH_MATRIX_PLANE) for m in (49, 64) for n, k in ((37888, 3584), (40960, 2304)))
     assert few(64, 8192, 2048, B.MODE_W4_MIN_FLOAT) and not few(49, 14336, 4096, B.MODE_W4_MIN_FLOAT)
     # int8 nibble planes: twice the chunks, against the tiled GEMM that merges them
     assert few(48, 8192, 8192, planes) and few(32, 13824, 5120, planes) and not few(48, 13824, 5120, planes)
