@@ -357,6 +357,8 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, co
 // 1 % (geometric mean) of the best of tm = 1 .. 4 and the tiled GEMM, and 12 % faster than tm = 4 alone up to three (fp16
 // activations: two) tiles per CU: 333 tokens of 4096 x 14336 65 -> 58 us (int8 bytes), 130 tokens of 1536 x 8960
 // 27 -> 19 us, 1500 tokens of 4096 x 14336 253 -> 206 us.
+// (With a float minimum and fp16 activations tm = 4 spills 21 registers of 256; at most three rows there is no faster: 441
+// shapes within 0.3 % in the geometric mean, 0.82 - 0.90 on short rows, 1.03 - 1.06 on long ones.)
 struct Height {
     int tm;
     float rounds;      // in rounds of tm = 4
@@ -379,11 +381,13 @@ Height tile_height(const Layout& L, int64_t M, int form)
 // first round weighs more than the next ones, with a CU's second workgroup beside it.
 float tiled_rounds(const Layout& L, int64_t M, int form)
 {
-    const int64_t tiles = (M + 127) / 128 * ((L.T + 7) / 8), cus = num_cus();
+    // (the int8 one deals whole columns of tiles to the XCDs)
+    const int64_t columns = (L.T + 7) / 8, cus = num_cus();
+    const int64_t tiles = (M + 127) / 128 * (is_f16(form) ? columns : (columns + kXcdCount - 1) / kXcdCount * kXcdCount);
     const float n = (float)((tiles + cus - 1) / cus);
     // (two tiles per CU run as one of 256 x 128, split: 1300 tokens of 3072 x 4096 66 us, in four rounds here 74 us)
     if (is_f16(form)) return n == 2.0f ? 3.8f : 1.8f * n + 0.4f;
-    return form == kBytes ? 3.1f * n + 1.0f : form == kMin ? 2.6f * n + 1.5f : 2.25f * n + 1.8f;
+    return form == kBytes ? 3.1f * n + 0.75f : form == kMin ? 2.6f * n + 1.5f : 2.25f * n + 1.8f;
 }
 
 int form_of(const Layout& L, bool f16)
@@ -428,13 +432,20 @@ int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const void* x
 // Where its rounds cost less than the tiled GEMM's: 1024 tokens of 6144 x 4096 in int8 bytes (six rounds against two) 68
 // against 76 us, 512 tokens of 17920 x 1536 (nine against three) 48 against 52 us; int4 57 against 60 and 41 against 39 us -
 // with the chip full, the tiled form's sharing of operands through LDS counts.
+//
+// A round costs as much again as two chunks of it, which the measured rounds (32 chunks) hold already: the exchange of the
+// partial sums.  Over 595 shapes of 65 - 2048 tokens, calls on int8 rows and fused ones, the choice costs 0.25 % against the
+// better of the two kernels at each shape, 8 % at most where the call is fused and 12 % on rows; without the round's own part
+// and with the byte form's constant at 1.0 it had been 0.53 % and 20 % (int8 bytes on rows, K-split / tiled, 377 tokens of
+// 17920 x 1536 41 / 34 us, 113 tokens of 28672 x 4096 55 / 49; int4 256 tokens of 15952 x 1664 24.3 / 20.3).
 bool ksplit8_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
     if (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8) return false;     // (nibble planes: the tiled GEMM merges them)
     const int64_t lim = kOutOfRange;                                 // 32-bit offsets
     const int form = form_of(L, false);
-    return tile_height(L, M, form).rounds <= tiled_rounds(L, M, form) && (M + 64) * L.Kx < lim &&
+    const float own = (1.0f + 2.0f / (float)L.C) / (1.0f + 2.0f / 32.0f);
+    return tile_height(L, M, form).rounds * own <= tiled_rounds(L, M, form) && (M + 64) * L.Kx < lim &&
            (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 2048 < lim;
 }
 

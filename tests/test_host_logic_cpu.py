@@ -219,3 +219,14 @@ def test_tiles_are_dealt_evenly_to_the_xcds(what, mode, family):
                 tiles = -(-m // tokens) * -(-n // rows)
                 assert tiles <= groups < tiles + 8
     assert met
+
+
+def test_k_split_int8_gemm_where_its_rounds_cost_less():
+    """Shapes measured on both sides of the line to the tiled GEMM: full rounds of many columns and short rows are the tiled
+    one's; long rows, and columns that the tiled GEMM deals unevenly to the XCDs, the K-split one's."""
+    ksplit = lambda m, n, k, mode=B.MODE_W4_ZP_INT: B.mnnq_plan_debug(4, m, n, k, mode)[0] == 3
+    w8 = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
+    assert not any(ksplit(m, n, k, w8) for m, n, k in ((113, 28672, 4096), (256, 28672, 4096), (377, 17920, 1536), (1617, 4096, 4096)))
+    assert not any(ksplit(m, n, k) for m, n, k in ((256, 15952, 1664), (356, 15952, 1664), (707, 5104, 1408)))
+    assert all(ksplit(m, n, k, w8) for m, n, k in ((784, 4096, 14336), (771, 4608, 3584), (529, 4000, 12672), (333, 4096, 4096)))
+    assert all(ksplit(m, n, k) for m, n, k in ((1125, 3584, 3584), (803, 4608, 3584), (1181, 4096, 14336), (333, 4096, 4096)))
