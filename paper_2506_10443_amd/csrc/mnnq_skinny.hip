@@ -504,8 +504,13 @@ FewPlan few_plan(const Layout& L, int tm, int form)
     if (L.T <= 2 * (int64_t)num_cus() && (C + 1) / 2 <= 8) nch = 2;
     if (!fits(nch) && fits(2)) nch = 2;
     int64_t ks = (C + nch - 1) / nch;
-    p.resident = fits(nch);
-    if (const char* e = debug_option(kDbgSkinnyStaged)) p.resident = p.resident && e[0] == '1';   // tests
+    // (One block of tokens, one row tile per workgroup and more than eight waves on it: resident operands serve one tile, and
+    // every wave adds its partial sums.  2 - 16 tokens, resident / streaming / the kernel before: 4096 x 4096 int8 nibble planes
+    // 10.0 / 8.7 / 9.3 us, 1728 x 4096 9.2 / 8.5 / 8.1; 4096 x 8192 float minimum 1.15 : 1 : 1.10, int4 1.10 : 1 : 1.25; from
+    // 4608 columns on - the second tile - the other way round, 0.93 : 1 and less.)
+    const bool one_tile = tm == 1 && !is_f16(form) && ks > 8 && L.T <= num_cus();
+    p.resident = fits(nch) && !one_tile;
+    if (const char* e = debug_option(kDbgSkinnyStaged)) p.resident = fits(nch) && e[0] == '1';   // tests
     if (!p.resident) {
         ks = stream_split(L, tm, form);
         if (C < ks) ks = C;

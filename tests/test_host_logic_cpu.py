@@ -180,6 +180,12 @@ def test_few_tokens_of_long_rows_share_a_tile_among_few_waves(mode):
         for m in (2, 16):
             assert B.mnnq_plan_debug(4, m, n, k, mode)[:4] == [2, 16, 16, waves]
     assert B.mnnq_plan_debug(4, 17, 4096, 14336, mode)[3] == 8
+    # rows that would fit the registers of more than eight waves, one tile per workgroup; with a second tile they stay there
+    plane8 = mode == B.MODE_W8_MIN_FLOAT
+    for n, k, waves in ((4096, 8192, 4), (3584, 6784, 4), (1536, 6784, 8)) if not plane8 else ((4096, 4096, 4), (1008, 3840, 8)):
+        assert B.mnnq_plan_debug(4, 2, n, k, mode)[:4] == [2, 16, 16, waves]
+    for n, k in ((4608, 8192), (4096, 4096), (4096, 3584)) if not plane8 else ((4608, 4096), (4096, 2048)):
+        assert B.mnnq_plan_debug(4, 2, n, k, mode)[0] == 1
 
 
 def test_few_token_kernels_where_they_are_the_faster_ones():
