@@ -201,8 +201,7 @@ int prefill_f16_impl(const void* packed, int64_t M, int64_t N, int64_t K, int gr
         return MNNQ_OK;
     }
     const Layout L = layout_for(N, K, mode, out16);
-    // (with a row factor the activations may be int8 codes: the tiled kernel adds the groups in the order of the tiled int8
-    // GEMM, whose result is then met bit for bit)
+    // (the few-token and K-split kernels have no row factor for fp16 activations)
     if (!row_scale && skinny_f16_wanted(L, M))
         return launch_skinny_f16(static_cast<const uint8_t*>(packed), L, M, x16, bias, static_cast<float*>(y),
                                  static_cast<hipStream_t>(stream));

@@ -456,8 +456,7 @@ struct TilePlan {
     int ks;        // K parts
 };
 
-// rs: with a row factor
-TilePlan tile_plan(const Layout& L, int64_t M, bool rs)
+TilePlan tile_plan(const Layout& L, int64_t M)
 {
     // The tile by what the busiest CU has to do: 256 x 128 unpacks the weights for twice the rows, so that it costs as much as
     // 1.75 tiles of 128 x 128 instead of two, but leaves more of a last round empty.  Measured at K = 4096, 128-row against
@@ -469,8 +468,8 @@ TilePlan tile_plan(const Layout& L, int64_t M, bool rs)
     // One tile per CU: the chunks are split over the two halves of an eight-wave workgroup, else half the wave slots are
     // empty.  Of 256-row tiles that fill a CU alone, two small ones are as fast on short rows: 4096 columns, 1536 tokens of
     // 1536 / 4096 / 14336 values 30.8 / 70.9 / 237 us in two small tiles, 32.1 / 67.6 / 219 us in one split tile (2048 tokens of
-    // 14336: 260 / 230).  (A row factor, see prefill_f16_impl, asks for the groups in order.)
-    if (big && per_cu_big == 1 && (L.C < 24 || rs)) big = false;
+    // 14336: 260 / 230; with a row factor, which the epilogue applies, 1536 tokens of 14336 values 240 / 224).
+    if (big && per_cu_big == 1 && L.C < 24) big = false;
     int ks = (big ? per_cu_big : per_cu_small) == 1 && L.C >= 4 ? 2 : 1;
     if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: "b"/"s" tile, third letter "k" = K parts
         if (e[0] == 'b') big = true;
@@ -484,7 +483,7 @@ TilePlan tile_plan(const Layout& L, int64_t M, bool rs)
 
 void describe_prefill_f16(const Layout& L, int64_t M, int32_t out[8])
 {
-    const TilePlan p = tile_plan(L, M, false);
+    const TilePlan p = tile_plan(L, M);
     const int bm = p.big ? 256 : 128;
     out[0] = 0;
     out[1] = bm;
@@ -496,7 +495,7 @@ void describe_prefill_f16(const Layout& L, int64_t M, int32_t out[8])
 int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* rs,
                        const float* bias, float* y, hipStream_t st)
 {
-    const auto [big, ks] = tile_plan(L, M, rs != nullptr);
+    const auto [big, ks] = tile_plan(L, M);
     if (big && ks == 2) return launch_tiles<256, 128, 2>(packed, L, M, x16, rs, bias, y, st);
     if (big) return launch_tiles<256, 128>(packed, L, M, x16, rs, bias, y, st);
     if (ks == 2) return launch_tiles<128, 128, 2>(packed, L, M, x16, rs, bias, y, st);

@@ -228,3 +228,6 @@ def test_fp16_tiles_by_tiles_per_cu(mode, M, N, K):
     assert torch.isnan(out[M]).all()                # nothing behind the last token
     assert (y.double() - exact).abs().max() <= 1e-5 * exact.abs().max()     # the layer's tolerance
     assert torch.equal(B.mnnq_linear_prefill_f16_o16(packed, N, K, x, bias=bias, mode=mode), y.half())
+    if B.mnnq_plan_debug(5, M, N, K, mode)[0] == 0:     # a row factor changes neither the tile nor the order of the sums
+        ones = torch.ones(M, device="cuda:0")
+        assert torch.equal(B.mnnq_linear_prefill_f16(packed, N, K, x, row_scale=ones, bias=bias, mode=mode), y)
