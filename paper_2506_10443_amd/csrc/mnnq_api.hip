@@ -78,9 +78,11 @@ size_t fused_prefill_ws_bytes(int64_t M, int64_t K)
 // activation planes (a multiple of 256 bytes); the fused call's codes and scales follow.
 size_t planes_ws_bytes(const Layout& L, int64_t M) { return prefill6_possible(L, M) ? prefill6_ws_bytes(M, L.Kx) : 0; }
 
-// Above this many bytes of packed weights quantizing the row once, in a kernel of its own (about
-// 4 us), beats quantizing it in every workgroup (measured: 75 MiB 16.4 us fused against 4.2 + 14.6 us,
-// 300 MiB 58 us against 4.2 + 45.7 us).
+// Above this many bytes of packed weights the row is quantized once, in a kernel of its own (2.3 us and the gap to the next
+// one), below it in every workgroup.  Where the line lies by bytes alone is a compromise: measured two kernels / one, int4
+// 28672 x 4096 (65 MiB) 16.4 / 16.6, 37888 x 3584 (75) 17.8 / 16.5, 100000 x 1536 (85) 19.3 / 20.9, 28672 x 8192 (129) 27.0 /
+// 36.3, 65536 x 3584 (129) 25.9 / 25.0, 152064 x 3584 (300) 50.4 / 48.1 us; float minimum 152064 x 3584 52.8 / 57.3; int8 bytes
+// 94 / 90.7 us.
 constexpr size_t kFusedTwoKernelBytes = (size_t)96 << 20;
 
 bool prefill_fits(int64_t M, int64_t N, int64_t K, int mode = MNNQ_W4_ZP_INT, int act_bytes = 1)

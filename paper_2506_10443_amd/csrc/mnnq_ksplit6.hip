@@ -4,10 +4,12 @@
 // The tiled GEMM gives a 128 x 128 output tile to a workgroup; 512 tokens of a 1536-wide layer are 48 such tiles on 256
 // CUs.  Here a wave owns a tile of 32 TM x 32 TN outputs and a part of K, and the KS waves of a workgroup share the tile:
 // four to eight times the parallelism per output.  No operand is shared between the waves of a workgroup (each meets its
-// own groups), so fragments go straight from L2 into registers, DEPTH groups ahead, with no LDS and no barrier in the
-// loop; the KS partial tiles are added through LDS in a fixed order at the end.  What bounds it is the vector memory pipe:
-// a group of a 64 x 64 tile is 9 KiB, 144 cycles at 64 bytes per cycle and CU, against about 100 cycles of matrix and
-// vector issue (four pairs of matrix instructions and 64 multiply-adds on four SIMDs).
+// own groups), so fragments go straight from L2 into registers, up to DEPTH groups ahead, with no LDS and no barrier in
+// the loop (a wave may leave it after any of the DEPTH stages: where those paths meet again, at the loop's head, the
+// 64 x 64 forms wait for all loads in flight, once per DEPTH groups); the KS partial tiles are added through LDS in a fixed
+// order at the end.  What bounds it is the vector memory pipe: a group of a 64 x 64 tile is 9 KiB, 144 cycles at 64 bytes
+// per cycle and CU, against about 100 cycles of matrix and vector issue (four pairs of matrix instructions and 64
+// multiply-adds on four SIMDs).
 #include "mnnq_common.h"
 
 namespace mnnq {
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64 * KS) void ksplit6_kernel(const uint8_t* __restr
         if (j == TN - 1)      // one load for the scales of up to two column tiles, one per half of the wave
             sc[u] = __builtin_amdgcn_raw_buffer_load_b32(rs_s, s_voff, uniform(g < g1 ? g * s_step + s_base : kOutOfRange), 0);
     };
-    // in the order of the loop's refills: the waits are counts
+    // in the order of the loop's refills: within an iteration the waits are counts
     auto refill = [&](int u, int t, int g) {     // after tile t of stage u's group
         const int i = t / TN, j = t % TN;
         if (j == TN - 1) load_a(u, i, g);
@@ -232,7 +234,7 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const uint8_t* a6,
 
 // Forms: 0 = 64 x 64 tiles of eight waves, 1 = 64 x 64 of four waves (two workgroups per CU), 2 = 64 x 32 of eight waves.
 // Groups in flight per wave: more did not help where the registers allow it (3584 x 18944, 128 tokens: two 44.3 us, three
-// 44.8 us), so the forms take what their registers leave at two waves per SIMD.
+// 44.8 us; each iteration's wait for all of them may be why), so the forms take what their registers leave at two waves per SIMD.
 size_t ksplit6_lds_bytes(int form) { return (size_t)(form == 0 ? 8 * 4 : form == 1 ? 4 * 4 : 8 * 2) * 4 * 64 * 16; }
 
 int launch_ksplit6(int form, const uint8_t* packed, const Layout& L, int64_t M, const void* planes, const float* sx,

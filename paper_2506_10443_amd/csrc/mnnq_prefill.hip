@@ -575,7 +575,8 @@ int launch_wide(const uint8_t* packed, const Layout& L, int64_t M, const int8_t*
     return launch_tiles_m<BM, 128, KS, false, false, false, 4>(packed, L, M, xq, sx, bias, y, nullptr, S, st);
 }
 
-// Tile, K-part and split choice.  A SIMD is full with four waves of the forms that need at most
+// Tile, K-part and split choice, for the shapes that the few-token kernels and the K-split GEMM leave (skinny_wanted,
+// ksplit8_wanted: rounds of many tiles, short rows; int8 nibble planes from 65 tokens) and for the accumulator dumps.  A SIMD is full with four waves of the forms that need at most
 // 128 registers (eight waves per K part: 128 x 32 or 64 x 32 outputs per wave), with two otherwise.
 //   * 256-row tiles share one B unpack between 8 MFMAs and are preferred when they
 //     alone give every CU two workgroups (of eight waves each);

@@ -109,7 +109,7 @@ def test_k_split_int8_gemm_matches_oracle(form, M, N, K):
 
 # fp16 activations: the few-token kernels (resident and streaming, both slices) and the K-split GEMM behind them
 F16_SHAPES = [(2, 16, 64), (15, 80, 1536), (16, 32, 8960), (17, 48, 4160), (33, 48, 1984), (40, 16 * 300, 2304), (64, 80, 2048),
-              (100, 48, 1536), (65, 48, 192), (130, 272, 1088), (3, 16 * 1100, 128), (200, 1040, 640), (129, 32, 8960)]
+              (100, 48, 1536), (65, 48, 192), (130, 272, 1088), (3, 16 * 1100, 128), (200, 1040, 640), (129, 32, 8960), (65, 16 * 520, 2048)]
 
 
 @pytest.mark.parametrize("M,N,K", F16_SHAPES)
@@ -175,14 +175,21 @@ def test_two_kernel_decode(K):
     assert torch.equal(y, B.mnnq_linear_decode(packed, 48, K, xq[0].contiguous(), sx))
 
 
-# one shape per tile height of the K-split kernel (16, 32, 48, 64 rows), ragged in rows and columns, with four and eight
-# waves, and more rounds than the limit of the 64-row tiles alone was
-@pytest.mark.parametrize("M,N,K", [(131, 1040, 320), (131, 2064, 320), (333, 4080, 192), (500, 4112, 192), (1100, 4096, 128)])
+# one shape per tile height of the K-split kernel (16, 32, 48, 64 rows) and number of waves, ragged in rows and columns, the
+# tall ones in one round and in two; and two shapes whose rounds are too short for it
+HEIGHTS = [(131, 1040, 320, 16, 8), (131, 2064, 320, 32, 8), (200, 4112, 320, 32, 4), (500, 1040, 320, 48, 8), (333, 4080, 192, 48, 4),
+           (200, 4080, 320, 64, 8), (500, 4080, 320, 64, 4), (500, 4112, 192, 0, 0), (1100, 4096, 128, 0, 0)]
+
+
+@pytest.mark.parametrize("M,N,K,height,waves", HEIGHTS)
 @pytest.mark.parametrize("form", ["w4", "w4min", "w8"])
-def test_k_split_tile_heights(form, M, N, K):
+def test_k_split_tile_heights(form, M, N, K, height, waves):
     mode, quant, linear = FORMS[form]
     if form == "w8":
         K = (K + 127) // 128 * 128
+    for what in (4,) if form == "w8" else (4, 5):       # the kernel that runs (5: with fp16 activations)
+        plan = B.mnnq_plan_debug(what, M, N, K, mode)
+        assert plan[:4] == [3, height, 64, waves] if height else plan[0] == 0
     print("K-split heights", form, M, N, K, flush=True)
     W, x = synth.weights(N, K, 3300 + M), synth.activations(M, K, 3301 + M)
     q, s, z = quant(W)

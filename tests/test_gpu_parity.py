@@ -347,7 +347,7 @@ def test_few_tokens_share_one_pass_over_the_weights(M, N, K):
     tol = TOL_A8 * np.abs(y_o).max()
     packed = B.mnnq_pack_weights(dev(W))
     xqd, sxd, bd = dev(xq), dev(sx), dev(bias)
-    for staged in ("0", "1"):        # activations straight from L2, or shared through LDS
+    for staged in ("0", "1"):        # both operands streamed, or the activations kept in registers
         B.mnnq_debug_set("MNNQ_SKINNY_STAGED", staged)
         for ks in ("", "1", "2", "4", "8"):
             if ks:

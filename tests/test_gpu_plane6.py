@@ -133,7 +133,7 @@ def test_prefill6_every_int8_code_bit_exact():
 
 def test_prefill6_bias_fused_and_fallbacks():
     M, N, K = 150, 512, 1536
-    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 0)       # (so few tiles would go to the int8 GEMM otherwise)
+    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 0)       # (so few tiles run the K-split kernel otherwise)
     W, x, q, s, z, xq, sx = make(N, K, M, 4400)
     bias = (0.5 * np.random.default_rng(4401).standard_normal(N)).astype(np.float32)
     _, y_o = oracle.linear_w4a8(xq, sx, q, s, z, bias=bias)
@@ -185,7 +185,7 @@ def test_few_output_tiles_take_the_k_split_kernel_unless_a_plan_is_forced():
 
 def test_act_planes_and_gemm_as_separate_calls():
     M, N, K = 300, 768, 1536
-    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 0)       # (so few tiles would go to the int8 GEMM otherwise)
+    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", 0)       # (so few tiles run the K-split kernel otherwise)
     W, x, q, s, z, xq, sx = make(N, K, M, 4500)
     _, y_o = oracle.linear_w4a8(xq, sx, q, s, z)
     packed = B.mnnq_pack_weights(dev(W), mode=MODE)

@@ -68,6 +68,8 @@ def test_decode_plan_fits_and_covers(model, name, M, N, K, mode):
 
 
 def test_documented_plans_of_the_qwen2_7b_block():
+    # (the tiled GEMM's; without the plane the call runs the K-split kernel for all but gate|up)
+    assert [B.mnnq_plan_debug(4, 1024, n, k)[0] for n, k in ((37888, 3584), (4608, 3584), (3584, 3584), (3584, 18944))] == [0, 3, 3, 3]
     plan = lambda n, k: B.mnnq_plan_debug(0, 1024, n, k)[:5]
     assert plan(37888, 3584) == [256, 128, 1, 1, 8]      # gate|up: two workgroups of eight waves per CU
     assert plan(4608, 3584) == [256, 128, 2, 1, 16]      # q|k|v: two K parts of eight waves
@@ -111,9 +113,11 @@ def test_plans_of_the_byte_form_of_int8_weights():
 
 
 def test_documented_plans_for_few_tokens():
-    """Batched decoding (17 .. 128 tokens): 64-row tiles, 64 columns wide unless there are very many,
+    """The tiled GEMM for 17 .. 128 tokens: 64-row tiles, 64 columns wide unless there are very many,
     the K range in more parts the fewer workgroups there are; very many tiles beyond 64 tokens take
-    128-row tiles."""
+    128-row tiles.  (Few tokens have kernels of their own, and few tiles the K-split one: it runs in this
+    range for short rows of many columns, or where those are switched off.)"""
+    assert B.mnnq_plan_debug(4, 128, 32768, 1536)[0] == 0 and B.mnnq_plan_debug(4, 64, 3584, 18944)[0] == 2
     plan = lambda m, n, k: B.mnnq_plan_debug(0, m, n, k)[:5]
     assert plan(64, 4608, 3584) == [64, 64, 4, 1, 16]        # q|k|v: 72 workgroups
     assert plan(64, 3584, 18944) == [64, 64, 4, 2, 16]       # down: long rows cut in two as well
