@@ -60,11 +60,12 @@ __device__ __forceinline__ uint32_t quant_group(const float4 v, float scale, flo
         zero = (int)fminf(fmaxf(zf, 0.0f), 255.0f);
         base = MAGIC;
     }
-    // clamped as floats, in which a NaN becomes the lower end
+    // clamped as floats, in one instruction: the median, with a NaN the smallest of the other two, i.e. code 0 (minimum and
+    // maximum instead: 37888 x 3584 with the plane 138.3 -> 139.7 us)
     uint32_t c[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        c[i] = (uint32_t)(__float_as_int(fminf(fmaxf(m[i], base), base + (float)MAX)) - __float_as_int(base));
+        c[i] = (uint32_t)(__float_as_int(__builtin_amdgcn_fmed3f(m[i], base, base + (float)MAX)) - __float_as_int(base));
     return c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
 }
 
