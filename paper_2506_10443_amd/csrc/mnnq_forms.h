@@ -1,0 +1,121 @@
+// Weight forms, their unpacking into matrix operands and the handling of int8 rows, shared by the few-token kernels
+// (mnnq_skinny.hip) and the GEMM with K split over the waves (mnnq_ksplit.hip).
+#pragma once
+
+#include "mnnq_common.h"
+
+namespace mnnq {
+
+namespace {
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+// Weights with an integer zero point or a float minimum, int8 weights as bytes; the first two with fp16 activations.
+enum Form { kZp = 0, kMin = 1, kBytes = 2, kZpF16 = 3, kMinF16 = 4 };
+constexpr bool is_f16(int form) { return form >= kZpF16; }
+constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
+inline int form_of(const Layout& L, bool f16)
+{
+    if (f16) return L.minf ? kMinF16 : kZpF16;
+    return L.native8 ? kBytes : L.minf ? kMin : kZp;
+}
+
+constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufFlags);
+}
+
+// A lane's part of one chunk of a row tile.
+template <int FORM>
+struct Weights {
+    v4i w[FORM == kBytes ? 2 : 1];   // .x,.y group 2c, .z,.w group 2c + 1; byte form: one register quad per group
+    v2f s;                           // scales of the lane's weight row for both groups
+    int z;                           // zero points of both groups of two weight rows, the lane's and its neighbour (kZp)
+    v2f mn;                          // group minima of both groups                    (kMin, kBytes)
+};
+
+// The B operands of a group: one register quad of int8, or two of halves.
+template <int FORM>
+struct Operand {
+    v4i q[is_f16(FORM) ? 2 : 1];
+};
+
+// q - z per byte for four codes in the bytes of v (c4 = 0x80 - z in every byte).
+__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
+
+// Eight codes (dword w) as halves q - z in natural order: a byte c under the high byte 0x64 is the half 1024 + c, and
+// subtracting the half 1024 + z (zb, twice) leaves c - z exactly (float minimum: 1024, the codes stay as they are).
+__device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
+{
+    const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
+    auto pair = [&](uint32_t v, uint32_t sel) {
+        return __builtin_bit_cast(int, __builtin_bit_cast(h2, __builtin_amdgcn_perm(0x64646464u, v, sel)) - zb);
+    };
+    return v4i{pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u)};
+}
+
+// Group h of a chunk.  zsel: the byte of the lane's row and first group in Weights::z, in every byte.
+template <int FORM>
+__device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, uint32_t zsel)
+{
+    Operand<FORM> o;
+    if (FORM == kBytes) {
+        o.q[0] = r.w[FORM == kBytes ? h : 0];
+        return o;
+    }
+    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
+    const uint32_t sel = h ? zsel + 0x01010101u : zsel;
+    if (is_f16(FORM)) {
+        // (bytes 1 and 3 of the selector pick 0x64)
+        const h2 zb = __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, (sel & 0x00ff00ffu) | 0x04000400u)
+                                                            : 0x64006400u);
+        o.q[0] = halves8(w0, zb);
+        o.q[is_f16(FORM) ? 1 : 0] = halves8(w1, zb);
+        return o;
+    }
+    const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
+    const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
+    if (FORM == kMin) {
+        o.q[0] = v4i{(int)n0, (int)n1, (int)n2, (int)n3};
+        return o;
+    }
+    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, sel);
+    o.q[0] = v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
+    return o;
+}
+
+__device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
+}
+
+// float(I) from a matrix instruction that accumulated on the bit pattern of 1.5 * 2^23: the register holds
+// 0x4B400000 + I, i.e. the float 12582912 + I (|I| < 2^22), and one exact subtraction - full rate, unlike a convert -
+// leaves I.
+constexpr int kMagicBits = 0x4B400000;
+__device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
+
+// Rows of int8 codes (calls that bring their codes).  Read in the operand's order - lane l: token l % 16, k block l / 16 -
+// four neighbouring lanes ask for 16 bytes of four tokens each, and the calls lost to the tiled GEMM wherever the token
+// blocks won; here they take 64 consecutive bytes of one token (lane l: token l / 4, k block l % 4), the two groups of a
+// chunk - one line - are requested together, and the operand's order is made in registers, through the LDS crossbar, a row
+// of tiles ahead (1024 tokens of 3584 x 18944 183 -> 141 us, 128 of 3584 x 3584 24.6 -> 13.6 us, int8 bytes 1024 tokens of
+// 3584 x 18944 216 -> 172 us; whole lines staged through LDS instead: the same within 2 %).
+struct RowExchange {
+    int from;       // byte address of the lane that holds this lane's piece
+    __device__ __forceinline__ explicit RowExchange(int lane) : from((4 * (lane & 15) + (lane >> 4)) * 4) {}
+    __device__ __forceinline__ void operator()(v4i& v) const
+    {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_ds_bpermute(from, v[d]);
+    }
+};
+
+}  // namespace
+
+}  // namespace mnnq

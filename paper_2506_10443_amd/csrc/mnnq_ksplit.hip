@@ -12,108 +12,17 @@
 //
 // Operand layout and arithmetic as in mnnq_skinny.hip (A: 16 tokens x 64 k, B: 64 k x 16 weight rows, D: lane l holds
 // weight row l % 16, tokens 4 (l / 16) + r).
-#include "mnnq_common.h"
+#include "mnnq_forms.h"
 
 namespace mnnq {
 
 namespace {
 
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-
-// Weights with an integer zero point or a float minimum, int8 weights as bytes; the first two with fp16 activations.
-enum Form { kZp = 0, kMin = 1, kBytes = 2, kZpF16 = 3, kMinF16 = 4 };
-constexpr bool is_f16(int form) { return form >= kZpF16; }
-constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
-
-constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
 constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer (ksplit8_wanted): loads give 0, stores are dropped
-constexpr int kMagicBits = 0x4B400000;    // 1.5 * 2^23: see from_magic in mnnq_skinny.hip
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufFlags);
-}
-__device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
-__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
 
 constexpr int TN = 4;   // 16 x 16 tiles of a wave: 16 TM tokens x 64 weight rows
-
-// One column tile of one chunk.
-template <int FORM>
-struct Weights {
-    v4i w[FORM == kBytes ? 2 : 1];
-    v2f s, mn;
-    int z;
-};
-
-// The B operands of a group: one register quad of int8, or two of halves (see halves8 in mnnq_skinny.hip).
-template <int FORM>
-struct Operand {
-    v4i q[is_f16(FORM) ? 2 : 1];
-};
-
-__device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
-{
-    const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
-    auto pair = [&](uint32_t v, uint32_t sel) {
-        return __builtin_bit_cast(int, __builtin_bit_cast(h2, __builtin_amdgcn_perm(0x64646464u, v, sel)) - zb);
-    };
-    return v4i{pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u)};
-}
-
-__device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
-}
-
-template <int FORM>
-__device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, uint32_t zsel)
-{
-    Operand<FORM> o;
-    if (FORM == kBytes) {
-        o.q[0] = r.w[FORM == kBytes ? h : 0];
-        return o;
-    }
-    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
-    const uint32_t sel = h ? zsel + 0x01010101u : zsel;      // the byte of the lane's row and group
-    if (is_f16(FORM)) {
-        const h2 zb = __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, (sel & 0x00ff00ffu) | 0x04000400u)
-                                                            : 0x64006400u);
-        o.q[0] = halves8(w0, zb);
-        o.q[is_f16(FORM) ? 1 : 0] = halves8(w1, zb);
-        return o;
-    }
-    const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
-    const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
-    if (FORM == kMin) {
-        o.q[0] = v4i{(int)n0, (int)n1, (int)n2, (int)n3};
-        return o;
-    }
-    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, sel);
-    o.q[0] = v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
-    return o;
-}
-
-// Rows of int8 codes (calls that bring their codes).  Read in the operand's order - lane l: token l % 16, k block l / 16 -
-// four neighbouring lanes ask for 16 bytes of four tokens each, and the calls lost to the tiled GEMM wherever the token
-// blocks won; here they take 64 consecutive bytes of one token (lane l: token l / 4, k block l % 4), the two groups of a
-// chunk - one line - are requested together, and the operand's order is made in registers, through the LDS crossbar, a row
-// of tiles ahead (1024 tokens of 3584 x 18944 183 -> 141 us, 128 of 3584 x 3584 24.6 -> 13.6 us, int8 bytes 1024 tokens of
-// 3584 x 18944 216 -> 172 us; whole lines staged through LDS instead: the same within 2 %).
-struct RowExchange {
-    int from;       // byte address of the lane that holds this lane's piece
-    __device__ __forceinline__ explicit RowExchange(int lane) : from((4 * (lane & 15) + (lane >> 4)) * 4) {}
-    __device__ __forceinline__ void operator()(v4i& v) const
-    {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_ds_bpermute(from, v[d]);
-    }
-};
 
 template <int FORM, int KS, int TM, bool BLOCKS>
 __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
@@ -388,12 +297,6 @@ float tiled_rounds(const Layout& L, int64_t M, int form)
     // (two tiles per CU run as one of 256 x 128, split: 1300 tokens of 3072 x 4096 66 us, in four rounds here 74 us)
     if (is_f16(form)) return n == 2.0f ? 3.8f : 1.8f * n + 0.4f;
     return form == kBytes ? 3.1f * n + 0.75f : form == kMin ? 2.6f * n + 1.5f : 2.25f * n + 1.8f;
-}
-
-int form_of(const Layout& L, bool f16)
-{
-    if (f16) return L.minf ? kMinF16 : kZpF16;
-    return L.native8 ? kBytes : L.minf ? kMin : kZp;
 }
 
 // Waves that share a tile: eight where there is one tile per CU, else four, and a CU holds two workgroups.

@@ -22,7 +22,7 @@
 //   A: lane l holds token l % 16, k block l / 16;  B: lane l holds weight row l % 16, the same k block - exactly the
 //   lane's 8 bytes of the chunk, unpacked (16 bytes in the byte form of int8 weights, as they are);
 //   D: lane l holds weight row l % 16, tokens 4 (l / 16) + r, r = 0..3.
-#include "mnnq_common.h"
+#include "mnnq_forms.h"
 
 #include <stdlib.h>
 
@@ -30,37 +30,11 @@ namespace mnnq {
 
 namespace {
 
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-
-// Weights with an integer zero point or a float minimum, int8 weights as bytes; the first two with fp16 activations.
-enum Form { kZp = 0, kMin = 1, kBytes = 2, kZpF16 = 3, kMinF16 = 4 };
-constexpr bool is_f16(int form) { return form >= kZpF16; }
-constexpr bool has_zero(int form) { return form == kZp || form == kZpF16; }
-
-template <int FORM>
-struct WeightRegs {
-    v4i w[FORM == kBytes ? 2 : 1];   // .x,.y group 2c, .z,.w group 2c + 1; byte form: one register quad per group
-    v2f s;                           // scales of the lane's weight row for both groups
-    int z;                           // zero points of both groups of two weight rows, the lane's and its neighbour (kZp)
-    v2f mn;                          // group minima of both groups                    (kMin, kBytes)
-};
-
 // Memory is read through buffer descriptors whose sizes are exact: a chunk that is not the wave's own, a row tile past
 // the matrix, a token past M or the missing half of an odd row lies outside and arrives as zeros without a branch and
 // without traffic.  (Plain loads in a loop that refills its registers are no alternative: the compiler moves a load
 // whose value crosses the back edge down to its use.)
-constexpr int kBufFlags = 0x00020000;     // raw buffer, 32-bit data format (gfx9 family)
 constexpr int kOutOfRange = 0x7ffffff0;   // a byte offset beyond every buffer
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, int64_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufFlags);
-}
 
 // The chunks of one row tile (an empty buffer past the last one).
 template <int FORM>
@@ -75,9 +49,9 @@ struct TileBuffers {
         s = rsrc(packed + L.scales_off() + first * 128, n * 128);
         z = rsrc(packed + L.zeros_off() + first * ZB, n * ZB);
     }
-    __device__ __forceinline__ WeightRegs<FORM> load(int c, int lane, int row) const   // c: chunk (uniform)
+    __device__ __forceinline__ Weights<FORM> load(int c, int lane, int row) const   // c: chunk (uniform)
     {
-        WeightRegs<FORM> r;
+        Weights<FORM> r;
         const int off = __builtin_amdgcn_readfirstlane(c);
         // (aux 2: the weights pass once and need not stay in the caches)
         r.w[0] = __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16, off * (FORM == kBytes ? 2048 : 1024), 2);
@@ -89,54 +63,6 @@ struct TileBuffers {
         return r;
     }
 };
-
-// q - z per byte for four codes in the bytes of v (c4 = 0x80 - z in every byte).
-__device__ __forceinline__ int sub_zero(uint32_t v, uint32_t c4) { return (int)((v + c4) ^ 0x80808080u); }
-
-template <int FORM>
-__device__ __forceinline__ v4i unpack_group(const WeightRegs<FORM>& r, int h, uint32_t zsel)
-{
-    if (FORM == kBytes) {
-        return r.w[FORM == kBytes ? h : 0];
-    }
-    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
-    const uint32_t n0 = w0 & 0x0f0f0f0fu, n1 = (w0 >> 4) & 0x0f0f0f0fu;
-    const uint32_t n2 = w1 & 0x0f0f0f0fu, n3 = (w1 >> 4) & 0x0f0f0f0fu;
-    if (FORM == kMin) return v4i{(int)n0, (int)n1, (int)n2, (int)n3};
-    // 0x80 - zero point in every byte; zsel picks the byte of the lane's row and first group
-    const uint32_t c4 = 0x80808080u - __builtin_amdgcn_perm(0u, (uint32_t)r.z, h ? zsel + 0x01010101u : zsel);
-    return v4i{sub_zero(n0, c4), sub_zero(n1, c4), sub_zero(n2, c4), sub_zero(n3, c4)};
-}
-
-// Eight codes (dword w) as halves q - z in natural order: a byte c under the high byte 0x64 is the half 1024 + c, and
-// subtracting the half 1024 + z (zb, twice) leaves c - z exactly (float minimum: 1024, the codes stay as they are).
-__device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
-{
-    const uint32_t lo = w & 0x0f0f0f0fu, hi = (w >> 4) & 0x0f0f0f0fu;
-    auto pair = [&](uint32_t v, uint32_t sel) {
-        return __builtin_bit_cast(int, __builtin_bit_cast(h2, __builtin_amdgcn_perm(0x64646464u, v, sel)) - zb);
-    };
-    return v4i{pair(lo, 0x04010400u), pair(lo, 0x04030402u), pair(hi, 0x04010400u), pair(hi, 0x04030402u)};
-}
-
-template <int FORM>
-__device__ __forceinline__ h2 half_zero(const WeightRegs<FORM>& r, int h, uint32_t zsel)
-{
-    // (bytes 1 and 3 of the selector pick 0x64)
-    const uint32_t sel = ((h ? zsel + 0x01010101u : zsel) & 0x00ff00ffu) | 0x04000400u;
-    return __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, sel) : 0x64006400u);
-}
-
-__device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
-}
-
-// float(I) from a matrix instruction that accumulated on the bit pattern of 1.5 * 2^23: the register holds
-// 0x4B400000 + I, i.e. the float 12582912 + I (|I| < 2^22), and one exact subtraction - full rate, unlike a convert -
-// leaves I.
-constexpr int kMagicBits = 0x4B400000;
-__device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
 
 // The vector side runs one group behind the matrix side: while a group's matrix instructions execute (a result is
 // readable 32 cycles after its issue, and at two waves per SIMD nothing else covers that), the results of the group
@@ -174,7 +100,7 @@ using ActRegs = v4i[2][TM][is_f16(FORM) ? 2 : 1];
 
 // One chunk: both groups of 16 weight rows against TM blocks of 16 tokens.
 template <int TM, int FORM>
-__device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const ActRegs<TM, FORM>& a, uint32_t zsel,
+__device__ __forceinline__ void contract(const Weights<FORM>& r, const ActRegs<TM, FORM>& a, uint32_t zsel,
                                          Pending<TM, FORM>& p, float (&acc)[TM][4])
 {
     const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
@@ -184,14 +110,8 @@ __device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const ActReg
     const v4i onesh = {0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        v4i b, b1;
-        if (is_f16(FORM)) {
-            const h2 zb = half_zero<FORM>(r, h, zsel);
-            b = halves8((uint32_t)(h ? r.w[0].z : r.w[0].x), zb);
-            b1 = halves8((uint32_t)(h ? r.w[0].w : r.w[0].y), zb);
-        } else {
-            b = unpack_group<FORM>(r, h, zsel);
-        }
+        const Operand<FORM> o = unpack<FORM>(r, h, zsel);
+        const v4i b = o.q[0], b1 = o.q[is_f16(FORM) ? 1 : 0];
         Pending<TM, FORM> n;
 #pragma unroll
         for (int t = 0; t < TM; ++t) {
@@ -213,18 +133,6 @@ __device__ __forceinline__ void contract(const WeightRegs<FORM>& r, const ActReg
         p = n;
     }
 }
-
-// Lanes of a load that brings rows of int8 codes: four in a row take 64 consecutive bytes of one token (lane l: token
-// l / 4, k block l % 4); the operand's order (token l % 16, k block l / 16) is made in registers, see mnnq_ksplit.hip.
-struct RowExchange {
-    int from;       // byte address of the lane that holds this lane's piece
-    __device__ __forceinline__ explicit RowExchange(int lane) : from((4 * (lane & 15) + (lane >> 4)) * 4) {}
-    __device__ __forceinline__ void operator()(v4i& v) const
-    {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) v[d] = __builtin_amdgcn_ds_bpermute(from, v[d]);
-    }
-};
 
 // The activations of one slice of tokens.  A operand of group g, token block t: 16 consecutive k of one token per lane,
 // from int8 rows or from the token blocks the fused call's quantizer writes ([group][block of 16 tokens][k block][token],
@@ -351,7 +259,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
     for (int u = 0; u < NCH; ++u) acts.load(a[u], c0 + u, u < own);
 
     int64_t tile = blockIdx.x;
-    WeightRegs<FORM> cur[NCH];
+    Weights<FORM> cur[NCH];
     const TileBuffers<FORM> first(packed, L, tile);
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
@@ -423,7 +331,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_stream_kernel(const uint8_t* __
     const Acts<TM, FORM, BLOCKS> acts(xq, L, M, m0, lane);
     const TileBuffers<FORM> weights(packed, L, tile);
     ActRegs<TM, FORM> a[DEPTH];
-    WeightRegs<FORM> cur[DEPTH];
+    Weights<FORM> cur[DEPTH];
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
         const int c = c0 + u;
@@ -564,12 +472,6 @@ int blocks_of(int64_t M)
     const int n = (int)(M + 15) / 16;
     const int slices = (n + 3) / 4;
     return (n + slices - 1) / slices;
-}
-
-int form_of(const Layout& L, bool f16)
-{
-    if (f16) return L.minf ? kMinF16 : kZpF16;
-    return L.native8 ? kBytes : L.minf ? kMin : kZp;
 }
 
 template <int FORM, bool BLOCKS>
