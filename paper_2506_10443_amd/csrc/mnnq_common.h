@@ -275,6 +275,13 @@ int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x1
 // rs: optional per-row factor applied to the fp32 sums before the bias (NULL = none).
 int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16,
                        const float* rs, const float* bias, float* y, hipStream_t st);
+// What the tiled GEMM with int4 zero-point weights, and the one with K split over waves, are expected to take (microseconds).
+float prefill_f16_us(const Layout& L, int64_t M);
+float ksplit_f16_us(const Layout& L, int64_t M);
+// The same on tiles of 128 tokens x 256, 192 or 128 columns (mnnq_prefill_f16w.hip): int4 weights with a zero point; ks: K parts
+// (1 or 2; of 128 columns 4).
+int launch_prefill_f16_wide(int columns, int ks, const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16,
+                            const float* rs, const float* bias, float* y, hipStream_t st);
 
 // Compute units of the current device (cached per thread and device).
 int num_cus();

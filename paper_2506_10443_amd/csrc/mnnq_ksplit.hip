@@ -370,15 +370,23 @@ int launch_ksplit8(const uint8_t* packed, const Layout& L, int64_t M, const int8
     return launch_form<kZp>(packed, L, M, xq, blocks, sx, bias, y, st);
 }
 
-// The same rule: 333 tokens of 4096 x 14336 (two rounds of 48 rows) 93 against 130 us tiled, 512 tokens (two of 64) 119
-// against 132 us; 700 tokens (three) 176 against 133 us.
+// fp16 activations: microseconds of a launch, from its rounds; over 8000 measured shapes of 17 - 2048 tokens, either form, nine
+// in ten are within 10 %.
+float ksplit_f16_us(const Layout& L, int64_t M)
+{
+    const float C = (float)L.C, rounds = tile_height(L, M, form_of(L, true)).rounds;
+    return L.minf ? 5.0f + (1.1f + 0.55f * C) * rounds : 4.7f + (1.0f + 0.515f * C) * rounds;
+}
+
+// Against the expected time of the wide tiles (float minimum: the rounds of 128 x 128 ones): 333 tokens of 4096 x 14336 (two
+// rounds of 48 rows) 93 against 120 us tiled, 512 tokens (two of 64) 119 against 119 us; 700 tokens (three) 176 against 115 us.
 bool ksplit_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgPrefillTile) || debug_option(kDbgNoSkinny)) return false;   // tests and tuning: the tiled GEMM
     const int64_t lim = kOutOfRange;                                 // 32-bit offsets
-    const int form = form_of(L, true);
-    return tile_height(L, M, form).rounds <= tiled_rounds(L, M, form) && (M + 64) * L.Kx * 2 < lim &&
-           (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 1024 < lim;
+    const bool faster = L.minf ? tile_height(L, M, kMinF16).rounds <= tiled_rounds(L, M, kMinF16)
+                               : ksplit_f16_us(L, M) <= 1.04f * prefill_f16_us(L, M);
+    return faster && (M + 64) * L.Kx * 2 < lim && (M + 64) * L.N * (L.out16 ? 2 : 4) < lim && TN * L.C * 1024 < lim;
 }
 
 int launch_ksplit_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* bias, float* y,

@@ -22,6 +22,8 @@
 // all-ones B operand yields the group sums of x in the D layout, i.e. for exactly the four
 // rows a lane holds.
 //
+// (int4 with a zero point runs on the wide tiles of mnnq_prefill_f16w.hip wherever those are the faster ones.)
+//
 // The structure is that of the int8 prefill kernel: operands reach LDS with
 // direct buffer loads, an A stage is one group (BM rows x 64 halves = 128 B per
 // row, 16-byte units XOR-swizzled by the row), a B chunk (two groups) is copied
@@ -149,7 +151,11 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 1 : 2) void prefill_f16_kernel(c
     int opaque_zero = 0;
     asm volatile("" : "+s"(opaque_zero));
 
-    const int a_voff = (lane >> 3) * K2 + (((lane & 7) ^ (lane >> 3)) << 4);
+    // Unit u = 2 kb + e (16 bytes) of a row lies at place (kb + 4 e) ^ (row % 8): the sixteen lanes that a 128-bit LDS read
+    // serves together - 0-3, 12-15 and 20-27 of every 32 - then touch every bank once.  With the units in their own order
+    // (place u ^ (row % 8)) every read took twice as long: 30.3 M conflict cycles in 28672 x 4096, 2048 tokens.
+    const int a_place = (lane & 7) ^ (lane >> 3);
+    const int a_voff = (lane >> 3) * K2 + ((2 * (a_place & 3) + (a_place >> 2)) << 4);
     const int b_voff = lane * 16;
     const int s_voff = (lane >> 5) * C * 128 + (lane & 31) * 4;
     const int z_voff = (lane >> 3) * C * 32 + (lane & 7) * 4;
@@ -158,8 +164,8 @@ __global__ __launch_bounds__(256 * KS, KS > 1 ? 1 : 2) void prefill_f16_kernel(c
 
     const int a_row_off = St::A_OFF + (wm * WM + col) * 128;   // + i * 2048 per m-tile
     const int a_sw = col & 7;
-    const int a_u0 = ((2 * kb) ^ a_sw) << 4;                    // unit of halves 16 kb .. 16 kb + 7
-    const int a_u1 = ((2 * kb + 1) ^ a_sw) << 4;                // unit of halves 16 kb + 8 .. 16 kb + 15
+    const int a_u0 = (kb ^ a_sw) << 4;                          // unit of halves 16 kb .. 16 kb + 7
+    const int a_u1 = ((kb + 4) ^ a_sw) << 4;                    // unit of halves 16 kb + 8 .. 16 kb + 15
     const int b_frag_off = St::B_OFF + wn * TN * 1024 + lane * 16;
     const int s_frag_off = St::S_OFF + wn * TN * 128 + col * 8;
     const int z_frag_off = St::Z_OFF + (MINF ? wn * TN * 128 + col * 8 : wn * TN * 32 + col * 2);
@@ -451,32 +457,75 @@ int launch_tiles(const uint8_t* packed, const Layout& L, int64_t M, const uint16
     return launch_tiles_m<BM, BN, false, KS>(packed, L, M, x16, rs, bias, y, st);
 }
 
+// Tile shapes.  The wide ones (mnnq_prefill_f16w.hip) take int4 weights with a zero point, the 256 x 128 one the other forms.
+enum Tile { k128x128, k256x128, k128x256, k128x192, k128x128parts };   // (parts: four K parts of two waves)
+
 struct TilePlan {
-    bool big;      // 256 x 128, else 128 x 128
+    Tile tile;
     int ks;        // K parts
+    float us;      // what the plan is expected to take
 };
+
+int64_t tiles_of(const Layout& L, int64_t M, Tile tile)
+{
+    const int64_t rows = tile == k256x128 ? 256 : 128, cols = tile == k128x256 ? 256 : tile == k128x192 ? 192 : 128;
+    return (M + rows - 1) / rows * ((L.N + cols - 1) / cols);
+}
+
+// The tile by what the busiest CU has to do, n tiles of C chunks: microseconds fitted to measured calls (24 shapes, 129 - 2048
+// tokens, K = 1536 - 18944).  Two workgroups share a CU; one alone takes about as long per chunk as the share of two plus the
+// last number.  Split in K, a tile alone on its CU has eight waves.  Measured, us, 128 x 128 / split / 128 x 256 / split /
+// 128 x 192 / split / four parts:
+//   2048 x 28672 x 4096 (14 / 7 / 10 per CU)   492 / 633 / 434 / 481 / 468 / 546 / -
+//   2048 x 6144 x 4096  (3 / 2 / 2)            110 / 134 / 117 / 129 / 97 / 110 / 132
+//   2048 x 4096 x 4096  (2 / 1 / 2)             74 /  84 /  73 /  65 / 84 /  97 / 83
+//   1024 x 6144 x 4096  (2 / 1 / 1)             69 /  81 /  70 /  59 / 58 /  52 / 78
+//   1024 x 4096 x 14336 (1 / 1 / 1)            167 / 136 / 223 / 177 / 180 / 148 / 119
+//   512 x 17920 x 1536  (3 / 2 / 2)             41 /  54 /  46 /  54 / 37 /  45 / 61
+TilePlan wide_plan(const Layout& L, int64_t M)
+{
+    const int64_t cus = num_cus();
+    const float C = (float)L.C;
+    auto per_cu = [&](Tile tile) { return (float)((tiles_of(L, M, tile) + cus - 1) / cus); };
+    const float n128 = per_cu(k128x128), n192 = per_cu(k128x192), n256 = per_cu(k128x256);
+    auto odd = [](float n) { return (float)((int)n & 1); };
+    TilePlan best{k128x128, 1, 5.2f + 1.03f * C * n128 + (n128 == 1.0f ? 0.4f * C : 0.0f)};
+    auto offer = [&](Tile tile, int ks, float us) {
+        if (us < 0.97f * best.us) best = TilePlan{tile, ks, us};
+    };
+    if (n128 == 1.0f && L.C >= 4) offer(k128x128, 2, 5.8f + 1.16f * C);
+    offer(k128x192, 1, 7.0f + C * (1.35f * n192 + 0.2f * odd(n192)));
+    if (n192 == 1.0f && L.C >= 4) offer(k128x192, 2, 7.0f + 1.25f * C);
+    offer(k128x256, 1, 10.0f + C * (1.7f * n256 + 0.25f * odd(n256)));
+    if (n256 == 1.0f && L.C >= 4) offer(k128x256, 2, 6.0f + 1.7f * C);
+    if (n128 == 1.0f && L.C >= 32) offer(k128x128parts, 4, 9.0f + 0.95f * C);
+    return best;
+}
+
+// Weights with a float minimum: 256 x 128 unpacks the weights for twice the rows, so that it costs as much as 1.75 tiles of
+// 128 x 128 instead of two, but leaves more of a last round empty; one 128-row tile per CU, or one of 256 rows with long rows,
+// is split over the two halves of an eight-wave workgroup (4096 columns, 1536 tokens of 1536 / 4096 / 14336 values
+// 30.8 / 70.9 / 237 us in two small tiles, 32.1 / 67.6 / 219 us in one split tile, int4 with a zero point).
+TilePlan minf_plan(const Layout& L, int64_t M)
+{
+    const int64_t cus = num_cus();
+    const int64_t small = (tiles_of(L, M, k128x128) + cus - 1) / cus, big = (tiles_of(L, M, k256x128) + cus - 1) / cus;
+    const bool take = 4 * small >= 7 * big && !(big == 1 && L.C < 24);
+    return {take ? k256x128 : k128x128, (take ? big : small) == 1 && L.C >= 4 ? 2 : 1, 0.0f};
+}
 
 TilePlan tile_plan(const Layout& L, int64_t M)
 {
-    // The tile by what the busiest CU has to do: 256 x 128 unpacks the weights for twice the rows, so that it costs as much as
-    // 1.75 tiles of 128 x 128 instead of two, but leaves more of a last round empty.  Measured at K = 4096, 128-row against
-    // 256-row tiles, in tiles per CU: 3 / 2 (6144 columns, 2048 tokens) 111 / 120 us, 4 / 2 (28672, 512) 141 / 122, 5 / 3
-    // (12288, 1300) 165 / 187, 6 / 3 (12288, 2048) 213 / 199, 10 / 6 (28672, 1300) 331 / 345, 14 / 7 (28672, 2048) 485 / 437.
-    const int64_t cus = num_cus(), nt = (L.N + 127) / 128;
-    const int64_t per_cu_small = ((M + 127) / 128 * nt + cus - 1) / cus, per_cu_big = ((M + 255) / 256 * nt + cus - 1) / cus;
-    bool big = 4 * per_cu_small >= 7 * per_cu_big;
-    // One tile per CU: the chunks are split over the two halves of an eight-wave workgroup, else half the wave slots are
-    // empty.  Of 256-row tiles that fill a CU alone, two small ones are as fast on short rows: 4096 columns, 1536 tokens of
-    // 1536 / 4096 / 14336 values 30.8 / 70.9 / 237 us in two small tiles, 32.1 / 67.6 / 219 us in one split tile (2048 tokens of
-    // 14336: 260 / 230; with a row factor, which the epilogue applies, 1536 tokens of 14336 values 240 / 224).
-    if (big && per_cu_big == 1 && L.C < 24) big = false;
-    int ks = (big ? per_cu_big : per_cu_small) == 1 && L.C >= 4 ? 2 : 1;
-    if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: "b"/"s" tile, third letter "k" = K parts
-        if (e[0] == 'b') big = true;
-        if (e[0] == 's') big = false;
-        if (e[0]) ks = (e[1] && e[2] == 'k') ? 2 : 1;
+    TilePlan p = L.minf ? minf_plan(L, M) : wide_plan(L, M);
+    if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: tile letter, third letter "k" = K parts
+        const Tile big = L.minf ? k256x128 : k128x256;
+        if (e[0] == 'b') p.tile = big;
+        if (e[0] == 's') p.tile = k128x128;
+        if (e[0] == 'c' && !L.minf) p.tile = k128x192;
+        if (e[0] == 'd' && !L.minf) p.tile = k128x128parts;
+        if (e[0]) p.ks = p.tile == k128x128parts ? 4 : (e[1] && e[2] == 'k') ? 2 : 1;
     }
-    return {big, ks};
+    return p;
 }
 
 }  // namespace
@@ -484,22 +533,30 @@ TilePlan tile_plan(const Layout& L, int64_t M)
 void describe_prefill_f16(const Layout& L, int64_t M, int32_t out[8])
 {
     const TilePlan p = tile_plan(L, M);
-    const int bm = p.big ? 256 : 128;
     out[0] = 0;
-    out[1] = bm;
-    out[2] = 128;
-    out[3] = out[4] = 4 * p.ks;
-    out[6] = (int32_t)xcd_tile_grid((M + bm - 1) / bm, (L.N + 127) / 128);
+    out[1] = p.tile == k256x128 ? 256 : 128;
+    out[2] = p.tile == k128x256 ? 256 : p.tile == k128x192 ? 192 : 128;
+    out[3] = out[4] = p.tile == k128x128parts ? 8 : 4 * p.ks;
+    out[6] = (int32_t)((tiles_of(L, M, p.tile) + kXcdCount - 1) / kXcdCount * kXcdCount);
 }
+
+float prefill_f16_us(const Layout& L, int64_t M) { return wide_plan(L, M).us; }
 
 int launch_prefill_f16(const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16, const float* rs,
                        const float* bias, float* y, hipStream_t st)
 {
-    const auto [big, ks] = tile_plan(L, M);
-    if (big && ks == 2) return launch_tiles<256, 128, 2>(packed, L, M, x16, rs, bias, y, st);
-    if (big) return launch_tiles<256, 128>(packed, L, M, x16, rs, bias, y, st);
-    if (ks == 2) return launch_tiles<128, 128, 2>(packed, L, M, x16, rs, bias, y, st);
-    return launch_tiles<128, 128>(packed, L, M, x16, rs, bias, y, st);
+    const TilePlan p = tile_plan(L, M);
+    switch (p.tile) {
+        case k128x256: return launch_prefill_f16_wide(256, p.ks, packed, L, M, x16, rs, bias, y, st);
+        case k128x192: return launch_prefill_f16_wide(192, p.ks, packed, L, M, x16, rs, bias, y, st);
+        case k128x128parts: return launch_prefill_f16_wide(128, p.ks, packed, L, M, x16, rs, bias, y, st);
+        case k256x128:
+            if (p.ks == 2) return launch_tiles_m<256, 128, true, 2>(packed, L, M, x16, rs, bias, y, st);
+            return launch_tiles_m<256, 128, true, 1>(packed, L, M, x16, rs, bias, y, st);
+        default:
+            if (p.ks == 2) return launch_tiles<128, 128, 2>(packed, L, M, x16, rs, bias, y, st);
+            return launch_tiles<128, 128>(packed, L, M, x16, rs, bias, y, st);
+    }
 }
 
 }  // namespace mnnq

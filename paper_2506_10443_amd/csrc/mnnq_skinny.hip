@@ -550,18 +550,22 @@ int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_
                   : launch_int8<false>(packed, L, (int)M, xq, sx, bias, y, st);
 }
 
-// fp16 activations.  Up to 16 tokens always; beyond, where the activation operands stay in registers (up to 32 tokens:
-// K <= 4096, up to 64: K <= 2048) or few row tiles read them again (measured, few-token / K-split / tiled: 32 tokens of
-// 28672 x 4096 22 / 31 / 42 us, 64 tokens of 4096 x 14336 56 / 63 / 129 us, of 4608 x 3584 35 / 20 / 36 us, 128 tokens of
-// 2048 x 1536 in two slices 8.6 / 12 / 19 us).
+// fp16 activations.  Up to 16 tokens always.  Up to 32 tokens by the time expected of either kernel, where the activation
+// operands stay in registers (K <= 4096): the GEMM with K split over waves takes whole rounds of 64-column tiles (few-token /
+// K-split, us: 32 tokens of 7040 x 1984 11.6 / 7.3, of 2320 x 5120 16.4 / 11.4, 24 of 16448 x 4096 - a second round - 17.9 / 23.2).
+// The line costs 1 % against the better of the two over 4700 shapes, 9 % at every shape before.  More tokens only on the
+// smallest layers (36 of 976 x 1280 6.6 / 8.1, 68 of 1152 x 1024 6.1 / 7.5; 48 of 1840 x 13248 40.5 / 22.9, 64 of
+// 1328 x 17024 65.7 / 28.8, 77 of 2800 x 2048 in two slices 14.3 / 7.2 us).
 bool skinny_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgNoSkinny) || debug_option(kDbgPrefillTile)) return false;   // tests and tuning: the tiled GEMM
     if (M <= 16) return true;
-    const bool resident = M <= 128 && few_plan(L, blocks_of(M), form_of(L, true)).resident;
-    if (M <= 32) return resident || L.T <= 2 * (int64_t)num_cus();
-    if (M <= 64) return resident || L.T <= num_cus();
-    return M <= 128 && resident && L.T * L.C <= 4096;
+    if (M > 128 || !few_plan(L, blocks_of(M), form_of(L, true)).resident) return false;
+    const int64_t cells = L.T * L.C;
+    if (M > 32) return L.C <= 10 && cells <= (M <= 48 ? 2000 : 600);
+    const float C = (float)L.C, tiles = (float)L.T / (float)num_cus();
+    const float few = L.minf ? 3.6f + 0.19f * C + tiles * (0.78f + 0.057f * C) : 4.2f + 0.16f * C + tiles * (0.7f + 0.044f * C);
+    return few <= ksplit_f16_us(L, M);
 }
 
 void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8])
