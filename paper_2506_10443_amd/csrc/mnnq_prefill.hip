@@ -148,15 +148,11 @@ __global__ __launch_bounds__(128 * WNW * KS, (ACC || KS > 1) ? 1 : 2) void prefi
     const int Cx = (int)L.Cx;   // chunk c of the packed axis meets chunk c % Cx of the activation row
     const int CL = W8 ? Cx : C; // chunks this kernel walks over (merged planes: those of the activation row)
 
-    // Workgroups are dealt to the 8 XCDs round-robin by their linear id.  Give each
-    // XCD whole columns of output tiles (one weight row block, all token blocks and
-    // K splits), so that a weight block is fetched into one L2 only.
-    const int xcd = blockIdx.x % 8;
-    const int seq = blockIdx.x / 8;
-    const int split = seq % S;
-    const int tile_m = (seq / S) % MT;
-    const int tile_n = (seq / (S * MT)) * 8 + xcd;
-    if (tile_n >= NT) return;
+    // Even runs of the output tiles in column order per XCD, all token blocks and K splits of a column together, so that a
+    // weight block is fetched into one L2, or two.
+    int tile_ms, tile_n;
+    if (!xcd_tile(MT * S, NT, tile_ms, tile_n)) return;
+    const int split = tile_ms % S, tile_m = tile_ms / S;
     const int wcb = CL * split / S, wce = CL * (split + 1) / S;   // this workgroup's chunks
     // ... of which each K part of the workgroup takes a contiguous share
     const int cb = wcb + (wce - wcb) * kh / KS, ce = wcb + (wce - wcb) * (kh + 1) / KS;
@@ -547,7 +543,7 @@ int launch_tiles_m(const uint8_t* packed, const Layout& L, int64_t M, const int8
                            reinterpret_cast<float4*>(y), n4);
         MNNQ_HIP_TRY(hipGetLastError());
     }
-    const int64_t blocks = (int64_t)MT * S * ((NT + 7) / 8) * 8;
+    const int64_t blocks = xcd_tile_grid((int64_t)MT * S, NT);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(128 * WNW * KS), smem, st, packed, L, M, xq, sx, bias, y, acc, MT,
                        NT, S);
     MNNQ_HIP_TRY(hipGetLastError());
@@ -628,7 +624,9 @@ TilePlan plan_tiles(const Layout& L, int64_t M)
     } else if (tiles(128) < 2 * cus) {
         // (float minimum form: the sixteen-wave 256-row form would spill; eight waves on 128-row tiles
         // measured 5 - 9 % faster than two K parts of four waves on 256-row tiles)
-        p.big = M > 128 && !L.minf;
+        // (256-row tiles with two K parts take a CU each: a second round of them, 337 tokens of 17488 x 4096 in 274 tiles,
+        // 105 us, took longer than the 411 tiles of 128 rows, two per CU)
+        p.big = M > 128 && !L.minf && tiles(256) <= cus;
         p.KS = p.big ? 2 : 1;
         p.wide = p.big || L.minf;
     } else {

@@ -211,13 +211,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void prefill6_kernel(
     static_assert(kFirst < 64, "six bits of vmcnt");
     constexpr int kWaitFirst = 0x0F70 | (kFirst & 15) | ((kFirst >> 4) << 14);
 
-    // Workgroups are dealt to the 8 XCDs round-robin by their linear id: each XCD gets whole columns
-    // of output tiles, so that a block of weights is fetched into one L2 only.
-    const int xcd = blockIdx.x % 8;
-    const int seq = blockIdx.x / 8;
-    const int tile_m = seq % MT;
-    const int tile_n = (seq / MT) * 8 + xcd;
-    if (tile_n >= NT) return;
+    int tile_m, tile_n;
+    if (!xcd_tile(MT, NT, tile_m, tile_n)) return;
     const int G = (int)L.Gx;
     const int gb = G * part / KS, ge = G * (part + 1) / KS;      // this part's groups
     const int n_iter = (G + KS - 1) / KS;                        // the longest share: every wave runs the same barriers
@@ -561,7 +556,7 @@ int launch6(const uint8_t* packed, const Layout& L, int64_t M, const uint8_t* a6
     auto kern = prefill6_kernel<BM, BN, WM, WN, KS, ACC, NS>;
     static thread_local int allowed_dev = -1;
     if (int s = allow_large_lds(kern, smem, allowed_dev)) return s;
-    const int64_t blocks = (int64_t)MT * ((NT + 7) / 8) * 8;
+    const int64_t blocks = xcd_tile_grid(MT, NT);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * WM * WN * KS), smem, st, packed + L.plane_off(), a6, L, M,
                        TMp, sx, bias, y, acc, MT, NT);
     MNNQ_HIP_TRY(hipGetLastError());
@@ -687,7 +682,7 @@ void describe_prefill6(const Layout& L, int64_t M, int32_t out[8])
     out[3] = 1;
     out[4] = p.waves;
     out[5] = (int32_t)p.lds;
-    out[6] = (int32_t)(plan >= 6 ? xcd_tile_grid(MT, NT) : MT * ((NT + 7) / 8) * 8);
+    out[6] = (int32_t)xcd_tile_grid(MT, NT);
     out[7] = plan >= 6 ? 7 : 6;   // operands in fp6: the K-split kernel, the tiled one
 }
 
