@@ -523,6 +523,8 @@ int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mo
             describe_ksplit(L, rows, f16, out8);
         } else if (f16) {
             describe_prefill_f16(L, rows, out8);
+        } else {
+            describe_prefill8_wide(L, rows, out8);
         }
     } else if (what == 0) {
         const int64_t slab = prefill_fits(M, N, K, mode) ? M : prefill_slab_rows(N, K, mode);

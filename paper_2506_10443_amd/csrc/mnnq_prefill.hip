@@ -722,8 +722,67 @@ void describe_prefill(const Layout& L, int64_t M, int32_t out[8])
     out[3] = r.S;
     out[4] = 2 * r.WNW * r.KS;                                   // waves per workgroup
     out[5] = (int32_t)prefill_lds_bytes(r, L.minf);
-    out[6] = (int32_t)(MT * r.S * ((NT + 7) / 8) * 8);           // workgroups
+    out[6] = (int32_t)xcd_tile_grid(MT * r.S, NT);           // workgroups
     out[7] = r.w8 ? (L.native8 ? 2 : 1) : 0;   // int8 weights: merged nibble planes / byte form
+}
+
+namespace {
+
+// More than one 128-row tile per CU: tiles of 128 x 128 (this file), 256 or 192 columns (mnnq_prefill8w.hip, whole or with two
+// K parts), by microseconds of a fused call fitted to 5600 measured ones (129 - 2048 tokens, three weight forms; nineteen in twenty
+// within 8 %).  Per form and tile: constant, per tile of the busiest CU, per chunk and tile, per chunk of an odd last tile; split:
+// constant, per chunk.  Measured, us, 128 x 128 / 256 / 192 columns: int8 bytes 1024 tokens of 37888 x 3584 300 / 250 / 272, 2048 of
+// 6144 x 4096 114 / 110 / 93, 333 of 28672 x 4096 115 / 110 / 92; float minimum 1024 of 37888 x 3584 258 / 231 / 252; int4 512 of
+// 28672 x 4096 106 / 93 / 111.
+struct Wide8Cost {
+    float s[4], x[4], c[4], xk[2], ck[2];
+};
+constexpr Wide8Cost kWide8Cost[3] = {
+    {{9.6f, -0.4f, 0.82f, 0.35f}, {8.8f, 2.7f, 1.28f, 0.39f}, {8.0f, 2.4f, 0.995f, 0.34f}, {14.1f, 1.29f}, {12.6f, 1.03f}},    // kZp
+    {{10.3f, -0.8f, 0.97f, 0.42f}, {10.2f, 2.6f, 1.54f, 0.46f}, {9.1f, 2.6f, 1.21f, 0.43f}, {16.3f, 1.52f}, {14.1f, 1.22f}},  // kMin
+    {{7.4f, 1.6f, 0.995f, 0.45f}, {9.0f, 3.8f, 1.53f, 0.48f}, {8.3f, 3.2f, 1.22f, 0.45f}, {15.9f, 1.58f}, {14.2f, 1.3f}},     // kBytes
+};
+
+struct Wide8Plan {
+    int columns, ks;      // 0 columns: not chosen here (few tiles, nibble planes, a forced tile)
+    float us;
+};
+
+Wide8Plan wide8_plan(const Layout& L, int64_t M)
+{
+    Wide8Plan best{0, 1, 0.0f};
+    if (M <= 128 || (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8)) return best;
+    const int64_t cus = num_cus(), rows = (M + 127) / 128;
+    auto per_cu = [&](int64_t cols) { return (int)((rows * ((L.N + cols - 1) / cols) + cus - 1) / cus); };
+    const int n128 = per_cu(128), n192 = per_cu(192), n256 = per_cu(256);
+    if (n128 == 1) return best;
+    const Wide8Cost& f = kWide8Cost[L.native8 ? 2 : L.minf ? 1 : 0];
+    const float C = (float)L.C;
+    auto whole = [&](const float (&k)[4], int n) { return k[0] + k[1] * (float)n + C * (k[2] * (float)n + k[3] * (float)(n & 1)); };
+    best = Wide8Plan{128, 1, whole(f.s, n128)};
+    auto offer = [&](int columns, int ks, float us) {
+        if (us < best.us) best = Wide8Plan{columns, ks, us};
+    };
+    offer(256, 1, whole(f.x, n256));
+    offer(192, 1, whole(f.c, n192));
+    if (n256 == 1 && L.C >= 4) offer(256, 2, f.xk[0] + f.xk[1] * C);
+    if (n192 == 1 && L.C >= 4) offer(192, 2, f.ck[0] + f.ck[1] * C);
+    return best;
+}
+
+}  // namespace
+
+float prefill8_us(const Layout& L, int64_t M) { return wide8_plan(L, M).us; }
+
+void describe_prefill8_wide(const Layout& L, int64_t M, int32_t out[8])
+{
+    const Wide8Plan p = wide8_plan(L, M);
+    if (p.columns == 0) return;
+    const int64_t NT = (L.N + p.columns - 1) / p.columns;
+    out[1] = 128;
+    out[2] = p.columns;
+    out[3] = out[4] = 4 * p.ks;
+    out[6] = (int32_t)xcd_tile_grid((M + 127) / 128, NT);
 }
 
 int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
@@ -732,6 +791,16 @@ int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8
     if (acc_debug) {
         if (M > 128) return launch_tiles<256, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
         return launch_tiles<128, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
+    }
+    const bool planes8 = L.mode == MNNQ_W8_MIN_FLOAT && !L.native8;
+    if (const char* e = debug_option(kDbgPrefillTile)) {      // tuning and tests: "x" / "c" = 256 / 192 columns
+        if ((e[0] == 'x' || e[0] == 'c') && !planes8)
+            return launch_prefill8_wide(e[0] == 'x' ? 256 : 192, e[1] && e[2] == 'k' ? 2 : 1, packed, L, M, xq, sx, bias, y, st);
+    } else {
+        const Wide8Plan p = wide8_plan(L, M);
+        if (p.columns > 128) return launch_prefill8_wide(p.columns, p.ks, packed, L, M, xq, sx, bias, y, st);
+        if (p.columns == 128 && L.native8) return launch_tiles_m<128, 128, 1, false, true, 2>(packed, L, M, xq, sx, bias, y, nullptr, 1, st);
+        if (p.columns == 128) return launch_tiles<128, 128, 1, false>(packed, L, M, xq, sx, bias, y, nullptr, 1, st);
     }
     const PrefillLaunch r = resolve_prefill(L, M);
 #define MNNQ_ARGS packed, L, M, xq, sx, bias, y, nullptr, r.S, st
