@@ -282,7 +282,8 @@ float ksplit_f16_us(const Layout& L, int64_t M);
 // (1 or 2; of 128 columns 4).
 int launch_prefill_f16_wide(int columns, int ks, const uint8_t* packed, const Layout& L, int64_t M, const uint16_t* x16,
                             const float* rs, const float* bias, float* y, hipStream_t st);
-// The int8 GEMM on tiles of 128 tokens x 256 or 192 columns (mnnq_prefill8w.hip), all forms but nibble planes; ks: K parts (1, 2).
+// The int8 GEMM on tiles of 128 tokens x 256 or 192 columns (mnnq_prefill8w.hip): int4 with a zero point, int8 bytes; ks: K
+// parts (1, 2).
 // prefill8_us: what the tiled int8 GEMM is expected to take where it has more than one tile per CU, else 0.
 float prefill8_us(const Layout& L, int64_t M);
 void describe_prefill8_wide(const Layout& L, int64_t M, int32_t out[8]);

@@ -60,7 +60,8 @@ __device__ __forceinline__ v4i halves8(uint32_t w, h2 zb)
 }
 
 // Group h of a chunk.  zsel: the byte of the lane's row and first group in Weights::z, in every byte.
-template <int FORM>
+// CENTERED (float minima with fp16 activations): codes less the middle of their range, see Centered.
+template <int FORM, bool CENTERED = false>
 __device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, uint32_t zsel)
 {
     Operand<FORM> o;
@@ -73,7 +74,7 @@ __device__ __forceinline__ Operand<FORM> unpack(const Weights<FORM>& r, int h, u
     if (is_f16(FORM)) {
         // (bytes 1 and 3 of the selector pick 0x64)
         const h2 zb = __builtin_bit_cast(h2, has_zero(FORM) ? __builtin_amdgcn_perm(0x64646464u, (uint32_t)r.z, (sel & 0x00ff00ffu) | 0x04000400u)
-                                                            : 0x64006400u);
+                                                            : CENTERED ? 0x64086408u : 0x64006400u);
         o.q[0] = halves8(w0, zb);
         o.q[is_f16(FORM) ? 1 : 0] = halves8(w1, zb);
         return o;
@@ -99,6 +100,38 @@ __device__ __forceinline__ v4f mfma_f16(v4i a, v4i b, v4f c)
 // leaves I.
 constexpr int kMagicBits = 0x4B400000;
 __device__ __forceinline__ float from_magic(int v) { return __int_as_float(v) - 12582912.0f; }
+
+// Float minima on the matrix cores (the GEMMs).  A group's term  scale * sum x q + min * sum x  is taken as
+//     scale * sum x (q - mid) + (min + mid * scale) * sum x,   mid = 8 of 4-bit codes (fp16 activations), 128 of bytes:
+// the second part is a contraction over the groups, one v_mfma_f32_16x16x4_f32 per tile and four groups (xs: lane l holds the sum
+// of token l % 16 in group l / 16 of the four; mn: the coefficient of weight row l % 16), and costs no vector instruction per
+// output.  Around the middle of the codes both parts are as small as the term itself; with q as it is they are large and of
+// opposite sign, four groups of one before the other, and the sums' error was 13 - 34 % larger than that of scale and minimum group by group.
+// A group whose codes are all 0 (a constant one: scale 1, whatever its value) is the minimum alone: its scale counts as 0, so
+// that nothing large cancels.  One more matrix instruction per column and group tells: with an all-ones operand it sums the
+// group's codes, in every lane of the column.
+template <int FORM>
+struct Centered {
+    static constexpr float mid = FORM == kMinF16 ? 8.0f : 128.0f;
+
+    float lanes;      // mid in the lanes of the group at hand, 0 in the others
+    __device__ __forceinline__ Centered(int group, int kb) : lanes(kb == group ? mid : 0.0f) {}
+
+    static __device__ __forceinline__ v4i column_sum(const Operand<FORM>& o)
+    {
+        const v4i one = is_f16(FORM) ? v4i{0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00} : v4i{0x01010101, 0x01010101, 0x01010101, 0x01010101};
+        if constexpr (is_f16(FORM))
+            return __builtin_bit_cast(v4i, mfma_f16(one, o.q[1], mfma_f16(one, o.q[0], v4f{0.0f, 0.0f, 0.0f, 0.0f})));
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(one, o.q[0], v4i{0, 0, 0, 0}, 0, 0, 0);
+    }
+    // s: the group's scale, mn: minimum -> coefficient, in the lanes of the group.
+    __device__ __forceinline__ void operator()(v4i sum, float& s, float& mn) const
+    {
+        const bool lowest = is_f16(FORM) ? __int_as_float(sum[0]) == -64.0f * mid : sum[0] == (int)(-64.0f * mid);
+        s *= lowest ? 0.0f : 1.0f;      // (an infinite scale stays a NaN)
+        mn = fmaf(lanes, s, mn);
+    }
+};
 
 // Rows of int8 codes (calls that bring their codes).  Read in the operand's order - lane l: token l % 16, k block l / 16 -
 // four neighbouring lanes ask for 16 bytes of four tokens each, and the calls lost to the tiled GEMM wherever the token

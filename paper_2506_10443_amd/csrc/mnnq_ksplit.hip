@@ -31,6 +31,9 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
                                                           float* __restrict__ y, int MT, int NT)
 {
     constexpr int T = TM * TN;
+    // the minima's part on the matrix cores (Centered), or with the scale on the vector ALU: unpacking centred 4-bit codes costs
+    // int8 activations more than it saves (1024 tokens of 3584 x 18944 170 / 167, 100 of 4096 x 14336 27.3 / 26.0 us)
+    constexpr bool CENTER = FORM == kBytes || FORM == kMinF16, PAIRS = FORM == kMin;
     extern __shared__ __align__(16) float4 lds_sum[];   // [KS][T][64]
     const int lane = threadIdx.x & 63, row = lane & 15, kb = lane >> 4;
     const int ks = uniform(threadIdx.x >> 6);
@@ -68,9 +71,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     v4i a[2][TM][E];
     // weights two chunks ahead (they come from HBM), activations one (from L2)
     Weights<FORM> w[2][TN];
-    // The minima's part of the sums, min[n,g] * xs[m,g], is a contraction over the groups: one v_mfma_f32_16x16x4_f32 per
-    // tile and two chunks.  Operands: lane l holds group l / 16 of the four for weight row (mn) and token (xs) l % 16.
-    float mn[TN], xs[TM];
+    float mn[TN], mn_next[TN], xs[TM];      // operands of the minima's part (Centered), the next two chunks' on their way
     auto load_a = [&](int h, int i, int c) {
         const int cx = c >= Cx ? c - Cx : c;
         const int off = uniform(c < c1 && (h == 0 || c != odd_last) ? (2 * cx + h) * x_step : kOutOfRange);
@@ -87,10 +88,12 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
         w[u][j].s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_s, row * 8, uniform(have ? cell * 128 : kOutOfRange), 0));
         if (has_zero(FORM))
             w[u][j].z = __builtin_amdgcn_raw_buffer_load_b32(rs_z, (row >> 1) * 4, uniform(have ? cell * ZB : kOutOfRange), 0);
+        if (PAIRS)
+            w[u][j].mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(rs_z, row * 8, uniform(have ? cell * ZB : kOutOfRange), 0));
     };
     auto load_min = [&](int j, int c) {      // (chunks past the wave's: zeros)
         const int off = c + (kb >> 1) < c1 ? (kb >> 1) * ZB + row * 8 + (kb & 1) * 4 : kOutOfRange;
-        mn[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_z, off, uniform((j * C + c) * ZB), 0));
+        mn_next[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_z, off, uniform((j * C + c) * ZB), 0));
     };
     // in the order of the loop's refills: the waits are counts
 #pragma unroll
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-    if (!has_zero(FORM)) {
+    if (CENTER) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) load_min(j, c0);
     }
@@ -124,9 +127,15 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
     const v4f zerof = {0.0f, 0.0f, 0.0f, 0.0f};
     int c = c0;
     do {
-      if (!has_zero(FORM)) {
+      if (CENTER) {
 #pragma unroll
           for (int i = 0; i < TM; ++i) xs[i] = 0.0f;
+          // (copies: the loads' registers stay where they are)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+              asm volatile("v_mov_b32 %0, %1" : "=v"(mn[j]) : "v"(mn_next[j]));
+              load_min(j, c + 2);
+          }
       }
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -134,10 +143,11 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             Operand<FORM> b[TN];
-            float s[TN];
+            float s[TN], pm[TN];
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                b[j] = unpack<FORM>(w[u][j], h, zsel);
+                b[j] = unpack<FORM, CENTER>(w[u][j], h, zsel);
+                if (PAIRS) pm[j] = h ? w[u][j].mn.y : w[u][j].mn.x;
                 s[j] = h ? w[u][j].s.y : w[u][j].s.x;
             }
             if (h == 1) {      // the second group is unpacked: the chunk's registers take the next chunk
@@ -145,39 +155,43 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
                 for (int j = 0; j < TN; ++j) {
                     // (copies: the refilled registers stay where they are)
                     asm volatile("v_mov_b32 %0, %1" : "=v"(s[j]) : "v"(w[u][j].s.y));
+                    if (PAIRS) asm volatile("v_mov_b32 %0, %1" : "=v"(pm[j]) : "v"(w[u][j].mn.y));
                     if (FORM != kBytes) load_codes(u, j, 0, c + u + 2);
                     load_params(u, j, c + u + 2);
                 }
             }
+            const Centered<FORM> center(2 * u + h, kb);
+            v4i sum[2];
+            float xf[2][4];
             if (XCH && h == 0) exchange(a[0][0][0]);
             v4i d[2];
-            v4i cbase = zero4;
 #pragma unroll
             for (int t = 0; t <= T; ++t) {
                 if (t < T) {
                     const int i = t / TN, j = t % TN;
                     constexpr int X = E - 1;
-                    if (!has_zero(FORM) && j == 0) {
-                        // sums of the group's activations, tokens in the lanes (all rows of the product are equal)
+                    if (PAIRS && j == 0) {      // sums of the group's activations, tokens in the rows
+                        const v4i x = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], ones, zero4, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) xf[i & 1][r] = (float)x[r];
+                    }
+                    if (CENTER && j == 0) {
+                        // ... tokens in the lanes (all rows of the product are equal)
                         if (is_f16(FORM)) {
                             const v4f x = mfma_f16(onesh, a[h][i][X], mfma_f16(onesh, a[h][i][0], zerof));
                             xs[i] = kb == 2 * u + h ? x[0] : xs[i];
                         } else {
                             const v4i x = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, a[h][i][0], zero4, 0, 0, 0);
                             xs[i] = kb == 2 * u + h ? (float)x[0] : xs[i];
-                            if (FORM == kBytes) {
-                                // byte form: the 128 that the bytes lack, which the accumulator starts from -
-                                // D + 128 xs as an integer (below 2^22); here tokens in the rows
-                                const v4i x4 = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], ones, zero4, 0, 0, 0);
-#pragma unroll
-                                for (int r = 0; r < 4; ++r) cbase[r] = (x4[r] << 7) + kMagicBits;
-                            }
                         }
                     }
                     if (is_f16(FORM))
                         d[t & 1] = __builtin_bit_cast(v4i, mfma_f16(a[h][i][X], b[j].q[X], mfma_f16(a[h][i][0], b[j].q[0], zerof)));
                     else
-                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], b[j].q[0], FORM == kBytes ? cbase : magic, 0, 0, 0);
+                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][i][0], b[j].q[0], magic, 0, 0, 0);
+                    if constexpr (CENTER) {
+                        if (i == 0) sum[j & 1] = Centered<FORM>::column_sum(b[j]);
+                    }
                     if (!XCH && j == TN - 1) load_a(h, i, c + u + 1);
                     if (XCH && h == 1 && j == TN - 1) {      // (both groups of a line)
                         load_a(0, i, c + u + 1);
@@ -190,22 +204,24 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (t > 0) {
-                    const int p = t - 1, j = p % TN;
+                    const int p = t - 1, i = p / TN, j = p % TN;
+                    if constexpr (CENTER) {
+                        if (p < TN) center(sum[j & 1], s[j], mn[j]);
+                    }
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const float v = is_f16(FORM) ? __int_as_float(d[p & 1][r]) : from_magic(d[p & 1][r]);
                         acc[p][r] = fmaf(s[j], v, acc[p][r]);
+                        if (PAIRS) acc[p][r] = fmaf(pm[j], xf[i & 1][r], acc[p][r]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
       }
-      if (!has_zero(FORM)) {
+      if (CENTER) {
 #pragma unroll
           for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[t / TN], mn[t % TN], acc[t], 0, 0, 0);
-#pragma unroll
-          for (int j = 0; j < TN; ++j) load_min(j, c + 2);
       }
       c += 2;
     } while (c < c1);
@@ -350,7 +366,7 @@ int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const void* x
 // with the chip full, the tiled form's sharing of operands through LDS counts.
 //
 // Where the tiled GEMM has more than one tile per CU both are weighed in microseconds (over 5600 shapes 0.25 % from the best of
-// all tiles in the mean, 1.4 % before: float minimum 342 tokens of 36688 x 1216 72 -> 45 us, 1053 of 14208 x 3136 156 -> 100 us).
+// all tiles in the mean, 1.4 % before: float minimum 342 tokens of 36688 x 1216 72 -> 49 us, 1053 of 14208 x 3136 156 -> 109 us).
 // Else a round costs as much again as two chunks of it, which the measured rounds (32 chunks) hold already: the exchange of the
 // partial sums.  Over 595 shapes of 65 - 2048 tokens, calls on int8 rows and fused ones, the choice costs 0.25 % against the
 // better of the two kernels at each shape, 8 % at most where the call is fused and 12 % on rows; without the round's own part
@@ -366,8 +382,8 @@ bool ksplit8_wanted(const Layout& L, int64_t M)
     bool faster;
     if (const float tiled = prefill8_us(L, M); tiled > 0.0f) {
         // microseconds against microseconds, on long rows with the margin that the fits leave
-        const float us = 0.14e-6f * (float)(M * L.Kx) + (form == kBytes ? 7.9f + (1.78f + 0.225f * C) * rounds
-                       : form == kMin ? 7.9f + (1.47f + 0.21f * C) * rounds : 8.1f + (1.34f + 0.198f * C) * rounds);
+        const float us = 0.14e-6f * (float)(M * L.Kx) + (form == kBytes ? 7.9f + (1.71f + 0.23f * C) * rounds
+                       : form == kMin ? 7.95f + (1.55f + 0.234f * C) * rounds : 8.1f + (1.34f + 0.198f * C) * rounds);
         faster = us <= tiled * (L.C >= 16 ? 1.045f : 1.0f);
     } else {
         const float own = (1.0f + 2.0f / C) / (1.0f + 2.0f / 32.0f);

@@ -731,16 +731,16 @@ namespace {
 // More than one 128-row tile per CU: tiles of 128 x 128 (this file), 256 or 192 columns (mnnq_prefill8w.hip, whole or with two
 // K parts), by microseconds of a fused call fitted to 5600 measured ones (129 - 2048 tokens, three weight forms; nineteen in twenty
 // within 8 %).  Per form and tile: constant, per tile of the busiest CU, per chunk and tile, per chunk of an odd last tile; split:
-// constant, per chunk.  Measured, us, 128 x 128 / 256 / 192 columns: int8 bytes 1024 tokens of 37888 x 3584 300 / 250 / 272, 2048 of
-// 6144 x 4096 114 / 110 / 93, 333 of 28672 x 4096 115 / 110 / 92; float minimum 1024 of 37888 x 3584 258 / 231 / 252; int4 512 of
-// 28672 x 4096 106 / 93 / 111.
+// constant, per chunk.  Measured, us, 128 x 128 / 256 / 192 columns: int8 bytes 1024 tokens of 37888 x 3584 302 / 255 / 277, 2048 of
+// 6144 x 4096 114 / 112 / 94, 333 of 28672 x 4096 113 / 112 / 93; int4 512 of 28672 x 4096 106 / 93 / 111.  (Float minima of 4-bit codes
+// 253 / 249 / 270, 96 / 114 / 94, 93 / 114 / 93: 128 x 128 always.)
 struct Wide8Cost {
     float s[4], x[4], c[4], xk[2], ck[2];
 };
 constexpr Wide8Cost kWide8Cost[3] = {
     {{9.6f, -0.4f, 0.82f, 0.35f}, {8.8f, 2.7f, 1.28f, 0.39f}, {8.0f, 2.4f, 0.995f, 0.34f}, {14.1f, 1.29f}, {12.6f, 1.03f}},    // kZp
-    {{10.3f, -0.8f, 0.97f, 0.42f}, {10.2f, 2.6f, 1.54f, 0.46f}, {9.1f, 2.6f, 1.21f, 0.43f}, {16.3f, 1.52f}, {14.1f, 1.22f}},  // kMin
-    {{7.4f, 1.6f, 0.995f, 0.45f}, {9.0f, 3.8f, 1.53f, 0.48f}, {8.3f, 3.2f, 1.22f, 0.45f}, {15.9f, 1.58f}, {14.2f, 1.3f}},     // kBytes
+    {{10.3f, -0.8f, 0.97f, 0.42f}, {}, {}, {}, {}},                                                                           // kMin
+    {{7.4f, 1.6f, 0.995f, 0.45f}, {9.4f, 3.2f, 1.6f, 0.5f}, {8.8f, 2.7f, 1.27f, 0.43f}, {16.1f, 1.58f}, {14.1f, 1.27f}},       // kBytes
 };
 
 struct Wide8Plan {
@@ -760,6 +760,7 @@ Wide8Plan wide8_plan(const Layout& L, int64_t M)
     const float C = (float)L.C;
     auto whole = [&](const float (&k)[4], int n) { return k[0] + k[1] * (float)n + C * (k[2] * (float)n + k[3] * (float)(n & 1)); };
     best = Wide8Plan{128, 1, whole(f.s, n128)};
+    if (L.minf && !L.native8) return best;
     auto offer = [&](int columns, int ks, float us) {
         if (us < best.us) best = Wide8Plan{columns, ks, us};
     };
@@ -792,9 +793,8 @@ int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8
         if (M > 128) return launch_tiles<256, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
         return launch_tiles<128, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
     }
-    const bool planes8 = L.mode == MNNQ_W8_MIN_FLOAT && !L.native8;
     if (const char* e = debug_option(kDbgPrefillTile)) {      // tuning and tests: "x" / "c" = 256 / 192 columns
-        if ((e[0] == 'x' || e[0] == 'c') && !planes8)
+        if ((e[0] == 'x' || e[0] == 'c') && (L.native8 || !L.minf))
             return launch_prefill8_wide(e[0] == 'x' ? 256 : 192, e[1] && e[2] == 'k' ? 2 : 1, packed, L, M, xq, sx, bias, y, st);
     } else {
         const Wide8Plan p = wide8_plan(L, M);

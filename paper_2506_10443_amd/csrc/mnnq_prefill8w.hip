@@ -1,5 +1,5 @@
 // Prefill GEMM on the int8 matrix instruction on wide tiles: 128 tokens x 256 or 192 columns per workgroup, for the
-// weight forms without a matrix-core plane (int4 with a zero point or a float minimum, int8 bytes).  Arithmetic and operand
+// weight forms without a matrix-core plane (int4 with a zero point, int8 bytes; a float minimum of 4-bit codes gained nothing).  Arithmetic and operand
 // order are those of mnnq_ksplit.hip.
 //
 // The waves of a workgroup share the tokens and own 16 TN columns each:
@@ -10,7 +10,8 @@
 //   * tiles are walked row by row, the operands of the next group unpacked beside the tiles of this one, the multiply-adds of a
 //     tile behind the matrix instruction of the next.
 // A tile and group costs eight instructions for the scale.  The minima's part, min[n,g] * (sum of the token's codes in g), is a
-// contraction over the groups on v_mfma_f32_16x16x4_f32, with one more matrix instruction per 16 tokens and group for the sums.
+// contraction over the groups on v_mfma_f32_16x16x4_f32 (Centered, mnnq_forms.h), with one more matrix instruction per 16 tokens and
+// group for the sums.
 #include "mnnq_forms.h"
 
 namespace mnnq {
@@ -30,12 +31,10 @@ constexpr int kStageBytes = 128 * 128;    // 128 rows of a chunk
 // vmcnt(n), the other counters left alone
 constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
-constexpr int kSumRing = 4, kSumBytes = 2 * 128 * 4;    // tokens' sums of a chunk's two groups
-
 template <int WAVES, int TM, int TN, int KS>
 struct Tile8 {
     static constexpr int NS = 3;
-    static constexpr int part_bytes = NS * kStageBytes + kSumRing * kSumBytes + 1024;
+    static constexpr int part_bytes = NS * kStageBytes;
     static constexpr int sum_bytes = KS > 1 ? WAVES * TM * TN * 4 * 64 * 4 : 0;      // one part's sums
     static constexpr int patch_bytes = WAVES * 16 * (16 * TN + 4) * 4;
     static constexpr int most(int a, int b) { return a > b ? a : b; }
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
     constexpr int NS = Cfg::NS, T = TM * TN;
     constexpr int NA = 16 / WAVES;                   // direct loads of a stage per wave
     constexpr int NU = has_zero(FORM) ? 1 : 2;       // chunks per turn of the loop: the minima go two at a time
-    constexpr int NW = (FORM == kBytes ? 3 : FORM == kMin ? 2 : 3) * TN;      // loads into registers per chunk, at least
+    constexpr int NW = 3 * TN;      // loads into registers per chunk, at least
     extern __shared__ __align__(16) uint8_t lds_all[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_id = uniform(tid >> 6);
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
     const int scales_off = (int)L.scales_off(), zeros_off = (int)L.zeros_off();
     const uint32_t zsel = (row & 1) * 0x02020202u;
     Weights<FORM> w[TN];
-    float mn[TN], xs[TM];
+    float mn[TN], mn_next[TN], xs[TM];      // operands of the minima's part (Centered), the next two chunks' on their way
     auto load_codes = [&](int j, int h, int c) {     // (the byte form: a kilobyte per group; else both groups with h = 0)
         const int off = uniform(c < ce ? ((rt0 + j) * C + c) * WB : kOutOfRange);
         w[j].w[FORM == kBytes ? h : 0] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, lane * 16 + h * 1024, off, 0);
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
     };
     auto load_min = [&](int j, int c) {              // of chunks c and c + 1
         const int off = c + (kb >> 1) < ce ? (kb >> 1) * ZB + row * 8 + (kb & 1) * 4 : kOutOfRange;
-        mn[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, off, uniform(zeros_off + ((rt0 + j) * C + c) * ZB), 0));
+        mn_next[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_w, off, uniform(zeros_off + ((rt0 + j) * C + c) * ZB), 0));
     };
 
     v4f acc[T];
@@ -111,44 +110,8 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
     const v4i zero4 = {0, 0, 0, 0};
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 
-    // Byte form: the tokens' sums of a group times 128, which the bytes lack and the accumulator starts from, as bit patterns of
-    // 1.5 * 2^23 + 128 xs: one matrix instruction with an all-ones operand per row of tiles, each wave for its share of the rows,
-    // a chunk ahead (its stage is visible by then).  (With a float minimum alone the sums of every wave's own are cheaper: 1024
-    // tokens of 37888 x 3584 231 us, shared 243; the byte form 270 and 255.)
-    constexpr bool SHARED = FORM == kBytes;
-    static_assert(!SHARED || TM % WAVES == 0, "whole rows of tiles per wave");
-    constexpr int kSumUnits = SHARED ? 2 * TM / WAVES : 0;      // (row of tiles, group) of a wave
-    auto sum_source = [&](int k, int slot) { return read_a(wave * (TM / WAVES) + k / 2, k % 2, slot); };
-    auto sum_slot = [&](int c) { return lds + NS * kStageBytes + (c & (kSumRing - 1)) * kSumBytes; };
-    auto make_sum = [&](int k, int c, v4i av) {
-        const int i = wave * (TM / WAVES) + k / 2, h = k % 2;
-        const v4i x = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, ones, zero4, 0, 0, 0);
-        v4i v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (x[r] << 7) + kMagicBits;
-        // (all columns are equal: the first one's lanes write it, the others to a spare kilobyte - a branch would end the block
-        // in which the compiler counts its waits)
-        const int at = NS * kStageBytes + (row == 0 ? (c & (kSumRing - 1)) * kSumBytes + h * 512 + (i * 16 + 4 * kb) * 4
-                                                    : kSumRing * kSumBytes + lane * 16);
-        *reinterpret_cast<v4i*>(lds + at) = v;
-    };
-    auto sums_of_rows = [&](int i, int h, int c) {       // tokens in the rows: four per lane
-        return *reinterpret_cast<const v4i*>(sum_slot(c) + h * 512 + (i * 16 + 4 * kb) * 4);
-    };
-    auto sum_operand = [&](int i, int c) {               // tokens in the lanes, group kb of chunks c and c + 1
-        const int v = *reinterpret_cast<const int*>(sum_slot(c + (kb >> 1)) + (kb & 1) * 512 + (i * 16 + row) * 4);
-        return fmaf(__int_as_float(v), 1.0f / 128, -12582912.0f / 128);      // (exact)
-    };
-
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s) issue_a(cb + s, s);
-    if (SHARED) {
-        __builtin_amdgcn_s_waitcnt(wait_vm(0));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int k = 0; k < kSumUnits; ++k) make_sum(k, cb, sum_source(k, 0));
-    }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         load_params(j, cb);
@@ -161,7 +124,7 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
     for (int j = 0; j < TN; ++j) {
         asm volatile("" : "+v"(w[j].w[0]), "+v"(w[j].s));
         if (FORM == kBytes) asm volatile("" : "+v"(w[j].w[FORM == kBytes ? 1 : 0]));
-        if (FORM != kZp) asm volatile("" : "+v"(mn[j]));
+        if (FORM != kZp) asm volatile("" : "+v"(mn_next[j]));
     }
     // operands of a group (the byte form takes the loaded registers as they are) and its scales
     Operand<FORM> b[2][FORM == kBytes ? 1 : TN];
@@ -175,17 +138,22 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
 
     int slot = 0;                                    // stage of the chunk being contracted
     for (int it = 0; it < n_iter; it += NU) {
-        if (FORM == kMin) {
+        if (!has_zero(FORM)) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) xs[i] = 0.0f;
+            // (copies: the loads' registers stay where they are)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                asm volatile("v_mov_b32 %0, %1" : "=v"(mn[j]) : "v"(mn_next[j]));
+                load_min(j, cb + it + 2);
+            }
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int c = cb + it + u;
-            // This wave's pieces of the chunk's stage - in the byte form, whose sums are made a chunk ahead, of the next one - have landed
-            // (in order behind them, at least: a chunk's weights, and but for the byte form a stage's loads), its reads of the stage
-            // before are done and its sums written.
-            __builtin_amdgcn_s_waitcnt(wait_vm(SHARED ? NW : NA + NW) & ~0x0F00);
+            // This wave's pieces of the chunk's stage have landed (in order behind them, at least: a stage's loads and a chunk's
+            // weights) and its reads of the stage before are done.
+            __builtin_amdgcn_s_waitcnt(wait_vm(NA + NW) & ~0x0F00);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             issue_a(c + NS - 1, slot == 0 ? NS - 1 : slot - 1);
@@ -193,9 +161,14 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
             a[0] = read_a(0, 0, slot);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                v4i d[2], source = zero4;
-                v4i cbase[2] = {magic, magic};
-                if (FORM == kBytes) cbase[0] = sums_of_rows(0, h, c);
+                auto operand = [&](int j) {
+                    Operand<FORM> o;
+                    o.q[0] = FORM == kBytes ? w[j].w[FORM == kBytes ? h : 0] : b[h][FORM == kBytes ? 0 : j].q[0];
+                    return o;
+                };
+                const Centered<FORM> center(2 * u + h, kb);
+                v4i sum[2];
+                v4i d[2];
 #pragma unroll
                 for (int t = 0; t <= T; ++t) {
                     if (t < T) {
@@ -206,22 +179,22 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
                             static_assert(TM % 2 == 0, "the first operand of the second group takes the free slot");
                         }
                         const v4i av = a[i & 1];
-                        if (FORM == kBytes && j == 0 && i + 1 < TM) cbase[(i + 1) & 1] = sums_of_rows(i + 1, h, c);
-                        if (h == 0 && i < kSumUnits) {
-                            if (j == 0) source = sum_source(i, slot == NS - 1 ? 0 : slot + 1);
-                            if (j == TN - 1) make_sum(i, c + 1, source);
-                        }
-                        if (FORM == kMin && j == 0) {    // tokens in the lanes; all rows of the product are equal
+                        if (!has_zero(FORM) && j == 0) {     // tokens in the lanes; all rows of the product are equal
                             const v4i x = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, av, zero4, 0, 0, 0);
                             xs[i] = kb == 2 * u + h ? (float)x[0] : xs[i];
                         }
-                        const v4i bv = FORM == kBytes ? w[j].w[FORM == kBytes ? h : 0] : b[h][FORM == kBytes ? 0 : j].q[0];
-                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bv, cbase[i & 1], 0, 0, 0);
+                        d[t & 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, operand(j).q[0], magic, 0, 0, 0);
+                        if constexpr (!has_zero(FORM)) {
+                            if (i == 0) sum[j & 1] = Centered<FORM>::column_sum(operand(j));
+                        }
                         if (FORM == kBytes && i == TM - 1) load_codes(j, h, c + 1);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                     if (t > 0) {
                         const int p = t - 1, i = p / TN, j = p % TN;
+                        if constexpr (!has_zero(FORM)) {
+                            if (i == 0) center(sum[j & 1], s[h][j], mn[j]);
+                        }
 #pragma unroll
                         for (int r = 0; r < 4; ++r) acc[p][r] = fmaf(s[h][j], from_magic(d[p & 1][r]), acc[p][r]);
                         // the next group's operands, a column in every second row of tiles
@@ -244,12 +217,9 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
         if (!has_zero(FORM)) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                if (SHARED) xs[i] = sum_operand(i, cb + it);
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[i * TN + j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[i], mn[j], acc[i * TN + j], 0, 0, 0);
             }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) load_min(j, cb + it + 2);
         }
     }
 
@@ -359,7 +329,6 @@ int launch_prefill8_wide(int columns, int ks, const uint8_t* packed, const Layou
                          const float* bias, float* y, hipStream_t st)
 {
     if (L.native8) return launch_form<kBytes>(columns, ks, packed, L, M, xq, sx, bias, y, st);
-    if (L.minf) return launch_form<kMin>(columns, ks, packed, L, M, xq, sx, bias, y, st);
     return launch_form<kZp>(columns, ks, packed, L, M, xq, sx, bias, y, st);
 }
 
