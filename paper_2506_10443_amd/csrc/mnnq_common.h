@@ -126,28 +126,26 @@ __device__ __forceinline__ void store_out(float* y, int64_t i, float v, bool out
 // Activation codes (Section 4.2, per-token symmetric int8): the definition is
 // clamp(rint(fl(x / scale)), -127, 127) with IEEE binary32 operations, but
 // a correctly rounded division per element is expensive (about ten vector
-// instructions).  r = x * fl(1 / scale) differs from fl(x / scale) by
+// instructions).  The exact product r = x * fl(1 / scale) differs from fl(x / scale) by
 // less than 3 * 2^-24 * 127.5 < 2.3e-5, so both round to the same integer unless
-// r is within that distance of a half-integer, i.e. unless |r - rint(r)| (exact:
-// the two are within 0.5 of each other) exceeds 0.5 - 6e-5; only then (about one
-// element in ten thousand) the division is done, for the four elements of a dword
+// r is within that distance of a half-integer, i.e. unless |r - rint(r)| exceeds
+// 0.5 - 6e-5 (a fused multiply-add gives it with one rounding of at most 2^-25); only then
+// (about one element in ten thousand) the division is done, for the four elements of a dword
 // together.  |r| <= 127 (1 + 2^-22) in this path, so rint(r) needs no clamp.
 // (lim is 0.5 - 6e-5 normally; negative - "always divide" - when 1 / scale is not
 // a normal number; the division path clamps as the definition does.)
-// rint(r) itself is taken from the sum r + 1.5 * 2^23 (round to nearest even happens in the
-// addition), which costs an add and a subtract instead of a rounding and a convert instruction
-// per element - converts run at a fraction of the rate of the other vector instructions.
-// Callers are compiled with -ffp-contract=off: x * inv - rint(x * inv) must be a
-// product rounded to binary32 and an exact subtraction.
+// rint(r) itself is taken from the fused sum x * fl(1 / scale) + 1.5 * 2^23 (round to nearest even
+// happens in it), not from a rounding and a convert instruction per element - converts run at a
+// fraction of the rate of the other vector instructions.
 __device__ __forceinline__ int quant4_fast(float4 v, float scale, float inv, float lim)
 {
     // Round to nearest even by adding 1.5 * 2^23: for |r| < 2^22 the sum is exactly 12582912 + rint(r),
     // and its bit pattern is 0x4B400000 + rint(r), i.e. the low byte already is the int8 code.
     constexpr float kMagic = 12582912.0f;
-    const float r0 = v.x * inv, r1 = v.y * inv, r2 = v.z * inv, r3 = v.w * inv;
-    float m0 = r0 + kMagic, m1 = r1 + kMagic, m2 = r2 + kMagic, m3 = r3 + kMagic;
-    const float d0 = fabsf(r0 - (m0 - kMagic)), d1 = fabsf(r1 - (m1 - kMagic));
-    const float d2 = fabsf(r2 - (m2 - kMagic)), d3 = fabsf(r3 - (m3 - kMagic));
+    float m0 = __builtin_fmaf(v.x, inv, kMagic), m1 = __builtin_fmaf(v.y, inv, kMagic);
+    float m2 = __builtin_fmaf(v.z, inv, kMagic), m3 = __builtin_fmaf(v.w, inv, kMagic);
+    const float d0 = fabsf(__builtin_fmaf(v.x, inv, kMagic - m0)), d1 = fabsf(__builtin_fmaf(v.y, inv, kMagic - m1));
+    const float d2 = fabsf(__builtin_fmaf(v.z, inv, kMagic - m2)), d3 = fabsf(__builtin_fmaf(v.w, inv, kMagic - m3));
     if (!(fmaxf(fmaxf(d0, d1), fmaxf(d2, d3)) <= lim)) {
         m0 = fminf(fmaxf(rintf(v.x / scale), -127.0f), 127.0f) + kMagic;
         m1 = fminf(fmaxf(rintf(v.y / scale), -127.0f), 127.0f) + kMagic;

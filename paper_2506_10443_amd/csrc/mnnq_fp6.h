@@ -6,23 +6,25 @@
 
 namespace mnnq {
 
-// fp6 packing.  c[0..7]: 32 six-bit codes, one per byte, code j in byte j % 4 of c[j / 4].
-// out[0..5]: the same codes at bits [6 j, 6 j + 6).
-__device__ __forceinline__ uint32_t pack24(uint32_t c)
+// fp6 packing.  c[0..7]: 32 six-bit codes, one per byte (bits 6 and 7 clear), code j in byte j % 4 of c[j / 4].
+// out[0..5]: the same codes at bits [6 j, 6 j + 6).  A dot product with 1 and 64 puts two codes side by side in one
+// instruction, and shift-or brings eight such pairs into three dwords: 17 instructions for 16 codes.
+__device__ __forceinline__ void pack_fp6_half(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t* out)
 {
-    return (c & 0x3fu) | ((c >> 2) & 0xfc0u) | ((c >> 4) & 0x3f000u) | ((c >> 6) & 0xfc0000u);
+    constexpr uint32_t kLow = 0x00004001u, kHigh = 0x40010000u;   // bytes 0 and 1, bytes 2 and 3
+    const uint32_t q0 = __builtin_amdgcn_udot4(c0, kLow, 0, false), q1 = __builtin_amdgcn_udot4(c0, kHigh, 0, false);
+    const uint32_t q2 = __builtin_amdgcn_udot4(c1, kLow, 0, false), q3 = __builtin_amdgcn_udot4(c1, kHigh, 0, false);
+    const uint32_t q4 = __builtin_amdgcn_udot4(c2, kLow, 0, false), q5 = __builtin_amdgcn_udot4(c2, kHigh, 0, false);
+    const uint32_t q6 = __builtin_amdgcn_udot4(c3, kLow, 0, false), q7 = __builtin_amdgcn_udot4(c3, kHigh, 0, false);
+    out[0] = (q2 << 24) | ((q1 << 12) | q0);
+    out[1] = (q5 << 28) | ((q4 << 16) | ((q3 << 4) | (q2 >> 8)));
+    out[2] = (q7 << 20) | ((q6 << 8) | (q5 >> 4));
 }
 
 __device__ __forceinline__ void pack_fp6(const uint32_t (&c)[8], uint32_t (&out)[6])
 {
-    const uint32_t p0 = pack24(c[0]), p1 = pack24(c[1]), p2 = pack24(c[2]), p3 = pack24(c[3]);
-    const uint32_t p4 = pack24(c[4]), p5 = pack24(c[5]), p6 = pack24(c[6]), p7 = pack24(c[7]);
-    out[0] = p0 | (p1 << 24);
-    out[1] = (p1 >> 8) | (p2 << 16);
-    out[2] = (p2 >> 16) | (p3 << 8);
-    out[3] = p4 | (p5 << 24);
-    out[4] = (p5 >> 8) | (p6 << 16);
-    out[5] = (p6 >> 16) | (p7 << 8);
+    pack_fp6_half(c[0], c[1], c[2], c[3], out);
+    pack_fp6_half(c[4], c[5], c[6], c[7], out + 3);
 }
 
 // Sign-magnitude six-bit codes of four small integers held as bytes 0x80 + v (|v| <= 15).
@@ -62,16 +64,17 @@ __device__ __forceinline__ void store_pair(uint8_t* pair, int lane, const uint32
 }
 
 // Four int8 activations (bytes) -> six-bit codes of their high and low parts: xq = s (16 hi + lo) with s = +-1,
-// hi = |xq| >> 4 (0..8), lo = |xq| & 15; the code of a part is its magnitude with the sign in bit 5, zero parts stay
-// all-zero codes.
+// hi = |xq| >> 4 (0..8), lo = |xq| & 15; the code of a part is its magnitude with the sign in bit 5.  (A zero part of
+// a negative value is -0, whose products add nothing.)
 __device__ __forceinline__ void split_act(uint32_t x, uint32_t& hi, uint32_t& lo)
 {
-    const uint32_t neg = (x >> 7) & 0x01010101u;              // 1 in the bytes with xq < 0
-    const uint32_t mag = (x ^ (neg * 255u)) + neg;            // |xq| (at most 128: no carry between bytes)
-    const uint32_t ml = mag & 0x0f0f0f0fu, mh = (mag >> 4) & 0x0f0f0f0fu;
-    const uint32_t nzl = ((ml + 0x0f0f0f0fu) >> 4) & 0x01010101u, nzh = ((mh + 0x0f0f0f0fu) >> 4) & 0x01010101u;
-    lo = ml | ((neg & nzl) << 5);
-    hi = mh | ((neg & nzh) << 5);
+    // 255 in the bytes with xq < 0: the permute's selectors 8..11 repeat the sign of bytes 1, 3 (of x) and 5, 7 (of
+    // x << 8, i.e. bytes 0 and 2 of x)
+    const uint32_t neg = __builtin_amdgcn_perm(x << 8, x, 0x090b080au);
+    const uint32_t mag = (x ^ neg) + (neg & 0x01010101u);     // |xq| (at most 128: no carry between bytes)
+    const uint32_t sign = neg & 0x20202020u;
+    lo = (mag & 0x0f0f0f0fu) | sign;
+    hi = ((mag >> 4) & 0x0f0f0f0fu) | sign;
 }
 
 }  // namespace mnnq
