@@ -78,13 +78,6 @@ size_t fused_prefill_ws_bytes(int64_t M, int64_t K)
 // activation planes (a multiple of 256 bytes); the fused call's codes and scales follow.
 size_t planes_ws_bytes(const Layout& L, int64_t M) { return prefill6_possible(L, M) ? prefill6_ws_bytes(M, L.Kx) : 0; }
 
-// Above this many bytes of packed weights the row is quantized once, in a kernel of its own (2.3 us and the gap to the next
-// one), below it in every workgroup.  Where the line lies by bytes alone is a compromise: measured two kernels / one, int4
-// 28672 x 4096 (65 MiB) 16.4 / 16.6, 37888 x 3584 (75) 17.8 / 16.5, 100000 x 1536 (85) 19.3 / 20.9, 28672 x 8192 (129) 27.0 /
-// 36.3, 65536 x 3584 (129) 25.9 / 25.0, 152064 x 3584 (300) 50.4 / 48.1 us; float minimum 152064 x 3584 52.8 / 57.3; int8 bytes
-// 94 / 90.7 us.
-constexpr size_t kFusedTwoKernelBytes = (size_t)96 << 20;
-
 bool prefill_fits(int64_t M, int64_t N, int64_t K, int mode = MNNQ_W4_ZP_INT, int act_bytes = 1)
 {
     const int64_t lim = ((int64_t)1 << 31) - 1;
@@ -225,9 +218,7 @@ int decode_fused_impl(const void* packed, int64_t N, int64_t K, int group, int m
         return MNNQ_ERR_ALIGN;
     const Layout L = layout_for(N, K, mode, out16);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    size_t two_kernel_bytes = kFusedTwoKernelBytes;
-    if (const char* e = debug_option(kDbgFusedTwoKernelMib)) two_kernel_bytes = (size_t)atoll(e) << 20;   // tuning only
-    if (workspace && workspace_bytes >= fused_ws_bytes(K) && L.total() > two_kernel_bytes) {
+    if (workspace && workspace_bytes >= fused_ws_bytes(K) && decode_fused_splits(L)) {
         int8_t* xq = static_cast<int8_t*>(workspace);
         float* sx = reinterpret_cast<float*>(xq + (K + 127) / 128 * 128);
         // (a block of one token is a plain row: 3584 values 4.9 -> 2.5 us against the kernel that splits rows, which long

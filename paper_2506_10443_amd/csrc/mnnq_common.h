@@ -231,6 +231,7 @@ int launch_quant_token_blocks(const float* x, int64_t M, int64_t K, int8_t* xq, 
 int launch_quant_planes(const float* x, int64_t M, int64_t K, int TMp, void* planes, float* sx, hipStream_t st);
 int launch_decode(const uint8_t* packed, const Layout& L, const int8_t* xq, const float* sx,
                   const float* bias, float* y, hipStream_t st);
+bool decode_fused_splits(const Layout& L);   // the quantizer of a one-token fused call in a kernel of its own
 int launch_decode_fused(const uint8_t* packed, const Layout& L, const float* x, const float* bias, float* y,
                         hipStream_t st);
 int launch_decode_acc(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq,

@@ -1,0 +1,32 @@
+"""The fused one-token call on both sides of the lines of its rule: quantizer in every workgroup, or once in front."""
+import pytest
+import torch
+
+from paper_2506_10443_amd import binding as B
+from paper_2506_10443_amd import synth
+
+pytestmark = pytest.mark.gpu
+W8N = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
+
+# sixteen waves per row tile: one round of workgroups and one more tile (256 CUs); the 40 MiB line of int4 weights; exact
+# configurations and int8 bytes stay in one kernel beyond it
+ROUTES = [(4096, 8320, B.MODE_W4_ZP_INT, False), (4112, 8320, B.MODE_W4_ZP_INT, True), (4096, 7296, W8N, False), (4112, 7296, W8N, True),
+          (4112, 14464, W8N, True), (33024, 1856, B.MODE_W4_ZP_INT, False), (40976, 1856, B.MODE_W4_ZP_INT, True),
+          (40976, 1856, B.MODE_W4_MIN_FLOAT, True), (21504, 3584, B.MODE_W4_MIN_FLOAT, False), (52000, 3584, B.MODE_W4_ZP_INT, False),
+          (38000, 3072, W8N, False)]
+
+
+@pytest.mark.parametrize("N,K,mode,two", ROUTES)
+def test_fused_decode_route(N, K, mode, two):
+    print("fused decode route", N, K, mode, flush=True)
+    x = torch.from_numpy(synth.activations(1, K, 5)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    packed = B.mnnq_pack_weights(torch.randn((N, K), generator=gen, device="cuda").mul_(0.02), mode=mode)
+    xq, sx, _ = B.mnnq_quant_act(x)
+    want = B.mnnq_linear_decode(packed, N, K, xq[0].contiguous(), sx, mode=mode)
+    ws = torch.zeros(B.mnnq_workspace_size(1, N, K, 64, mode), dtype=torch.uint8, device="cuda")
+    out = B.mnnq_linear_decode_fused(packed, N, K, x[0].contiguous(), workspace=ws, mode=mode)
+    # the same codes and group products; the sums over K may be taken in another order (fp32, bounded as everywhere)
+    assert (out - want).abs().max() <= 1e-5 * want.abs().max()
+    # the codes are in the workspace if, and only if, the quantizer ran on its own
+    assert torch.equal(ws[:K].view(torch.int8), xq[0] if two else torch.zeros_like(xq[0]))
