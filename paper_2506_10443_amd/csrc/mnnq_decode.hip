@@ -707,20 +707,22 @@ int dispatch(const uint8_t* packed, const Layout& L, int64_t M, const void* xin,
 //     0.92 on average; more of them - a second round, with a second quantization behind the first - 1.05 - 1.28;
 //   int8 bytes: up to four waves per tile 0.96 - 0.98 at 64 MiB as at 600 (152064 x 3584 90.0 -> 87.4 us), eight 0.99 at
 //     80 - 96 MiB, 1.03 - 1.06 beyond;
-//   int4: 0.93 at 24 - 32 MiB, 0.99 at 32 - 40, 1.03 at 40 - 48, 1.09 at 64 - 80, 1.13 at 80 - 96, 1.17 - 1.29 beyond (28672 x
-//     8192 36.3 -> 27.0 us); with exact configurations 0.94 at 64 - 80 MiB, 1.01 - 1.07 beyond 96, but 0.93 - 0.97 at every
-//     size with seven chunks a wave and integer zero points (124192 x 3584 41.0 -> 39.6 us).
+//   int4, eight waves per tile: 1.02 at 32 - 40 MiB, 1.06 at 40 - 48, 1.08 at 48 - 56, 1.18 at 80 - 96, 1.23 - 1.34 beyond; up to
+//     four: 0.99 at 32 - 40 MiB, 1.02 at 40 - 48, 1.04 at 48 - 56, 1.07 at 56 - 64, 1.09 at 64 - 80, 1.17 beyond 96 (between other
+//     kernels the second launch costs 0.3 us more than in a loop of one call: the lines lie where no shape loses); with exact
+//     configurations 0.94 at 64 - 80 MiB, 1.01 - 1.07 beyond 96, but 0.93 - 0.97 at every size with seven chunks a wave and integer
+//     zero points (124192 x 3584 41.0 -> 39.6 us).
 // Nibble planes, whose rows are twice as long in the buffer as in the quantizer, keep a line of 96 MiB for all.
 bool decode_fused_splits(const Layout& L)
 {
     if (const char* e = debug_option(kDbgFusedTwoKernelMib)) return L.total() > (size_t)atoll(e) << 20;   // tests and tuning
-    constexpr size_t kLine = (size_t)40 << 20, kHiddenLine = (size_t)96 << 20;
+    constexpr size_t kLine8 = (size_t)48 << 20, kLine = (size_t)64 << 20, kHiddenLine = (size_t)96 << 20;
     const DecodeCfg c = L.native8 ? decode8_config(L, true) : decode_config(L, true);
     if (L.K != L.Kx) return L.total() > kHiddenLine;
     if (c.ks == 16) return L.T > num_cus();
     if (L.native8) return c.ks == 8 && L.total() > kHiddenLine;
     if (c.ks < 8 && c.early) return (L.minf || c.unroll != 7) && L.total() > kHiddenLine;
-    return L.total() > kLine;
+    return L.total() > (c.ks == 8 ? kLine8 : kLine);
 }
 
 void describe_decode(const Layout& L, bool fused, int32_t out[8])

@@ -8,11 +8,11 @@ from paper_2506_10443_amd import synth
 pytestmark = pytest.mark.gpu
 W8N = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
 
-# sixteen waves per row tile: one round of workgroups and one more tile (256 CUs); the 40 MiB line of int4 weights; exact
+# sixteen waves per row tile: one round of workgroups and one more tile (256 CUs); the 64 MiB line of int4 weights (48 for eight waves); exact
 # configurations and int8 bytes stay in one kernel beyond it
 ROUTES = [(4096, 8320, B.MODE_W4_ZP_INT, False), (4112, 8320, B.MODE_W4_ZP_INT, True), (4096, 7296, W8N, False), (4112, 7296, W8N, True),
-          (4112, 14464, W8N, True), (33024, 1856, B.MODE_W4_ZP_INT, False), (40976, 1856, B.MODE_W4_ZP_INT, True),
-          (40976, 1856, B.MODE_W4_MIN_FLOAT, True), (21504, 3584, B.MODE_W4_MIN_FLOAT, False), (52000, 3584, B.MODE_W4_ZP_INT, False),
+          (4112, 14464, W8N, True), (33024, 1856, B.MODE_W4_ZP_INT, False), (62000, 1856, B.MODE_W4_ZP_INT, True),
+          (62000, 1856, B.MODE_W4_MIN_FLOAT, True), (8192, 8064, B.MODE_W4_ZP_INT, False), (16384, 6080, B.MODE_W4_ZP_INT, True), (21504, 3584, B.MODE_W4_MIN_FLOAT, False), (52000, 3584, B.MODE_W4_ZP_INT, False),
           (38000, 3072, W8N, False)]
 
 
