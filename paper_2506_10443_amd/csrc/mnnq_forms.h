@@ -1,5 +1,6 @@
 // Weight forms, their unpacking into matrix operands and the handling of int8 rows, shared by the few-token kernels
-// (mnnq_skinny.hip) and the GEMM with K split over the waves (mnnq_ksplit.hip).
+// (mnnq_skinny.hip), the GEMM with K split over the waves (mnnq_ksplit.hip) and the wide tiles (mnnq_prefill8w.hip,
+// mnnq_prefill_f16w.hip).
 #pragma once
 
 #include "mnnq_common.h"
@@ -132,6 +133,69 @@ struct Centered {
         mn = fmaf(lanes, s, mn);
     }
 };
+
+// A lane's four results of a 16 x 16 tile, y[m + r][n] = f[r] * scale[r] + shift, as fp32 or binary16; rows past M lie past the
+// end of y, columns past N are sent there.
+__device__ __forceinline__ void store_tile(__amdgpu_buffer_rsrc_t rs_y, const Layout& L, int m, int n, v4f f, const float (&scale)[4],
+                                           float shift)
+{
+    const int N = (int)L.N;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float o = fmaf(f[r], scale[r], shift);
+        const int at = n < N ? ((m + r) * N + n) * (L.out16 ? 2 : 4) : 0x7fff0000;
+        if (L.out16) {
+            const _Float16 q = (_Float16)o;
+            __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, q), rs_y, at, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(o), rs_y, at, 0, 0);
+        }
+    }
+}
+
+// Centred sums of a weight row cannot express a group whose scale or minimum is infinite or NaN, or whose coefficient overflows
+// (imported parameters; the quantizer makes none): infinity around the middle of the codes and infinity times the
+// activations' sum meet as NaN, and the zeros of the other groups' lanes do as well.  The row's sums are then not finite for any
+// token, so that one token per tile tells and the loops need no check; a wave that sees it computes its tiles again, one by one,
+// with the codes as they are: scale * (sum x q) + minimum * (sum x), group by group.
+// first: cell (chunk of a row tile) that the tile's weights start at; load_a(c, h): the A operand of group h of chunk c.
+template <int FORM, typename LoadA>
+__device__ __forceinline__ v4f tile_by_definition(__amdgpu_buffer_rsrc_t packed, const Layout& L, int lane, int first, LoadA load_a)
+{
+    constexpr int WB = FORM == kBytes ? 2048 : 1024, X = is_f16(FORM) ? 1 : 0;
+    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101}, onesh = {0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00};
+    const v4i zero4 = {0, 0, 0, 0};
+    const v4f zerof = {0.0f, 0.0f, 0.0f, 0.0f};
+    v4f y = zerof;
+#pragma unroll 1
+    for (int c = 0; c < (int)L.C; ++c) {
+        const int at = (lane & 15) * 8;
+        Weights<FORM> w;
+#pragma unroll
+        for (int h = 0; h < (FORM == kBytes ? 2 : 1); ++h)
+            w.w[h] = __builtin_amdgcn_raw_buffer_load_b128(packed, lane * 16 + h * 1024, (first + c) * WB, 0);
+        w.s = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(packed, at, (int)L.scales_off() + (first + c) * 128, 0));
+        w.mn = __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(packed, at, (int)L.zeros_off() + (first + c) * 128, 0));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const Operand<FORM> a = load_a(c, h), b = unpack<FORM>(w, h, 0);
+            v4f d, x;
+            if constexpr (is_f16(FORM)) {
+                d = mfma_f16(a.q[X], b.q[X], mfma_f16(a.q[0], b.q[0], zerof));
+                x = mfma_f16(a.q[X], onesh, mfma_f16(a.q[0], onesh, zerof));
+            } else {
+                const v4i di = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.q[0], b.q[0], zero4, 0, 0, 0);
+                const v4i xi = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.q[0], ones, zero4, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) d[r] = (float)(di[r] + xi[r] * (FORM == kBytes ? 128 : 0)), x[r] = (float)xi[r];
+            }
+            const float s = h ? w.s.y : w.s.x, mn = h ? w.mn.y : w.mn.x;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] = fmaf(mn, x[r], fmaf(s, d[r], y[r]));
+        }
+    }
+    return y;
+}
 
 // Rows of int8 codes (calls that bring their codes).  Read in the operand's order - lane l: token l % 16, k block l / 16 -
 // four neighbouring lanes ask for 16 bytes of four tokens each, and the calls lost to the tiled GEMM wherever the token

@@ -225,14 +225,12 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
       }
       c += 2;
     } while (c < c1);
-
     // Sum over the waves in a fixed order, the tiles dealt to the waves; their scales and biases are requested before the
     // exchange, which their latency would follow.
     constexpr int NP = (T + KS - 1) / KS;
     const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, (int64_t)M * 4);
     const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
     const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, (int64_t)M * L.N * (L.out16 ? 2 : 4));
-    const int N = (int)L.N;
     float bn[NP], sm[NP][4];
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
@@ -241,13 +239,14 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
 #pragma unroll
         for (int r = 0; r < 4; ++r) sm[k][r] = sx ? __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0)) : 1.0f;
     }
+    uint64_t bad = 0;      // (CENTER) lanes with a sum that is not finite
 #pragma unroll
     for (int t = 0; t < T; ++t)
         lds_sum[(ks * T + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const int t = ks + k * KS, m = m0 + (t / TN) * 16 + 4 * kb, n = (t0 + t % TN) * 16 + row;
+        const int t = ks + k * KS;
         if (T % KS != 0 && t >= T) break;
         float4 v = lds_sum[t * 64 + lane];
 #pragma unroll
@@ -255,17 +254,41 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
             const float4 o = lds_sum[(p * T + t) * 64 + lane];
             v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
         }
-        const float f[4] = {v.x, v.y, v.z, v.w};
+        store_tile(rs_y, L, m0 + (t / TN) * 16 + 4 * kb, (t0 + t % TN) * 16 + row, v4f{v.x, v.y, v.z, v.w}, sm[k], bn[k]);
+        if (CENTER) bad |= t % TN < live ? __ballot(v.x * 0.0f != 0.0f) : 0;
+    }
+    if constexpr (CENTER) {
+        if (__builtin_expect(bad == 0, 1)) return;
+        // Groups that centred sums cannot express: the wave's tiles again by the definition.  Behind everything else, with the
+        // buffers described anew, so that neither registers nor instruction fetches of the usual way pay for it (inside the
+        // loop over the tiles 0.7 us of 17).
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): the stores above are done
+        const uint8_t* wp = packed;
+        const void* xp = xq;
+        int l = lane;
+        asm volatile("" : "+s"(wp), "+s"(xp), "+v"(l));
+        const int row = l & 15, kb = l >> 4;
+        const __amdgpu_buffer_rsrc_t rx = rsrc(xp, (int64_t)M * L.Kx * E), rw = rsrc(wp, (int64_t)L.total());
+#pragma unroll 1
+        for (int t = ks; t < T; t += KS) {
+            if (t % TN >= live) continue;
+            const int first = m0 + (t / TN) * 16, left = M - first, width = left < 16 ? left : 16;
+            const int voff = row < width ? (BLOCKS ? first * 64 + (kb * width + row) * 16 : (first + row) * (int)L.Kx * E + kb * 16 * E)
+                                         : kOutOfRange;
+            const auto operand_a = [&](int cc, int h) {
+                const int off = uniform(h == 0 || cc != odd_last ? (2 * (cc >= Cx ? cc - Cx : cc) + h) * x_step : kOutOfRange);
+                Operand<FORM> o;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float o = fmaf(f[r], sm[k][r], bn[k]);
-            const int at = n < N ? ((m + r) * N + n) * (L.out16 ? 2 : 4) : kOutOfRange;   // rows past M: past the end of y
-            if (L.out16) {
-                const _Float16 q = (_Float16)o;
-                __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, q), rs_y, at, 0, 0);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(o), rs_y, at, 0, 0);
-            }
+                for (int e = 0; e < E; ++e) o.q[e] = __builtin_amdgcn_raw_buffer_load_b128(rx, voff + e * 16, off, 0);
+                return o;
+            };
+            const int cell = uniform((t0 + t % TN) * C);
+            const v4f f = tile_by_definition<FORM>(rw, L, l, cell, operand_a);
+            const int m = first + 4 * kb, n = (t0 + t % TN) * 16 + row;
+            float scale[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) scale[r] = sx ? __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (m + r) * 4, 0, 0)) : 1.0f;
+            store_tile(rs_y, L, m, n, f, scale, __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, n * 4, 0, 0)));
         }
     }
 }

@@ -295,6 +295,29 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
             }
         }
     }
+    if constexpr (!has_zero(FORM)) {
+        float probe = 0.0f;      // NaN: a column's sums are not finite
+#pragma unroll
+        for (int j = 0; j < TN; ++j) probe = rt0 + j < (int)L.T ? fmaf(acc[j][0], 0.0f, probe) : probe;
+        if (__builtin_expect(__ballot(probe != 0.0f) == 0, 1)) return;
+        __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the stores above are done
+#pragma unroll 1
+        for (int t = 0; t < TM * TN; ++t) {          // (rows past M: past the ends of the buffers)
+            const int rt = rt0 + t % TN, first = m0 + (t / TN) * 16;
+            if (rt >= (int)L.T) continue;
+            const auto operand_a = [&](int c, int h) {
+                Operand<FORM> o;
+                o.q[0] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, (first + row) * K + kb * 16, uniform(c * 128 + h * 64), 0);
+                return o;
+            };
+            const v4f f = tile_by_definition<FORM>(rs_w, L, lane, uniform(rt * C), operand_a);
+            float scale[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) scale[r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, (first + 4 * kb + r) * 4, 0, 0));
+            store_tile(rs_y, L, first + 4 * kb, rt * 16 + row, f, scale,
+                       __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, (rt * 16 + row) * 4, 0, 0)));
+        }
+    }
 }
 
 template <int FORM, int WAVES, int TM, int TN, int KS>
