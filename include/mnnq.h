@@ -293,10 +293,10 @@ int mnnq_debug_set(const char *key, const char *value);
  *           prefetch, LDS bytes per workgroup, workgroups, row tiles per workgroup, 1 if the activation
  *           row is requested ahead of the weights and handled while they arrive}.
  * what = 4: the kernel behind mnnq_linear_prefill_fused given mnnq_workspace_size bytes, what = 5: behind
- *           mnnq_linear_prefill_f16 without row_scale; out8 = {0 tiled (int8: see what = 0), 1 few tokens with the activations
+ *           mnnq_linear_prefill_f16 without row_scale; out8 = {0 tiled, 1 few tokens with the activations
  *           in registers, 2 few tokens streaming both operands, 3 K split over the waves, 6 tiled fp6, 7 fp6 with K
- *           split; and but for int8 tiles where they are at most one per CU (all 0): tokens and weight rows of a workgroup's tile, its waves, the most waves that
- *           kernel is built for, chunks a wave holds in registers (form 1), workgroups (not forms 1 and 2), 0}.
+ *           split; tokens and weight rows of a workgroup's tile, its waves, the most waves that kernel is built for, chunks a
+ *           wave holds in registers (form 1), workgroups (not forms 1 and 2), 0}.
  * out8: HOST pointer to 8 int32.  Same shape / mode errors as the calls themselves. */
 int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mode, int32_t *out8);
 

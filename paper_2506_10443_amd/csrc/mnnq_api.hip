@@ -515,7 +515,12 @@ int mnnq_plan_debug(int what, int64_t M, int64_t N, int64_t K, int group, int mo
         } else if (f16) {
             describe_prefill_f16(L, rows, out8);
         } else {
-            describe_prefill8_wide(L, rows, out8);
+            int32_t p[8];
+            describe_prefill(L, rows, p);
+            out8[1] = p[0];
+            out8[2] = p[1];
+            out8[3] = out8[4] = p[4];
+            out8[6] = p[6];
         }
     } else if (what == 0) {
         const int64_t slab = prefill_fits(M, N, K, mode) ? M : prefill_slab_rows(N, K, mode);

@@ -285,7 +285,7 @@ int launch_prefill_f16_wide(int columns, int ks, const uint8_t* packed, const La
 // parts (1, 2).
 // prefill8_us: what the tiled int8 GEMM is expected to take where it has more than one tile per CU, else 0.
 float prefill8_us(const Layout& L, int64_t M);
-void describe_prefill8_wide(const Layout& L, int64_t M, int32_t out[8]);
+size_t prefill8_wide_lds_bytes(int columns, int ks);
 int launch_prefill8_wide(int columns, int ks, const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                          const float* bias, float* y, hipStream_t st);
 

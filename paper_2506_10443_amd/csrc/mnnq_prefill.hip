@@ -665,14 +665,15 @@ int num_cus()
 namespace {
 
 // What launch_prefill starts for a shape: tile rows, K parts inside the workgroup, K split over
-// workgroups, waves along N per K part (2 x WNW waves each), merged nibble planes of int8 weights.
+// workgroups, waves along N per K part (2 x WNW waves each), merged nibble planes of int8 weights or their byte form,
+// tile columns (more than 128: mnnq_prefill8w.hip, four waves per K part).
 struct PrefillLaunch {
     int BM, KS, S, WNW;
     bool w8;
     int BN;
 };
 
-PrefillLaunch resolve_prefill(const Layout& L, int64_t M)
+PrefillLaunch resolve_few_tiles(const Layout& L, int64_t M)
 {
     TilePlan p = plan_tiles(L, M);
     if (L.out16) p.S = 1;   // the split over two workgroups adds fp32 partial sums in the output array
@@ -699,34 +700,6 @@ PrefillLaunch resolve_prefill(const Layout& L, int64_t M)
         r.WNW = 4;   // (256 rows, two K parts, float minimum form: would spill registers)
     return r;
 }
-
-static_assert(Lds<256, 128, false>::BYTES == 2 * 256 * 128 + 8 * 1024 + 8 * 128 + 8 * 32, "prefill_lds_bytes");
-static_assert(Lds<128, 128, true, true>::BYTES == 2 * 128 * 128 + 16 * 1024 + 8 * 128 + 8 * 128, "prefill_lds_bytes");
-static_assert(Lds<64, 64, false>::BYTES == 2 * 64 * 128 + 4 * 1024 + 4 * 128 + 8 * 32, "prefill_lds_bytes");
-
-size_t prefill_lds_bytes(const PrefillLaunch& r, bool minf)
-{
-    const int nt16 = r.BN / 16;
-    return (size_t)r.KS * (2 * r.BM * 128 + nt16 * 1024 * (r.w8 ? 2 : 1) + nt16 * 128 + (minf ? nt16 * 128 : 8 * 32));
-}
-
-}  // namespace
-
-void describe_prefill(const Layout& L, int64_t M, int32_t out[8])
-{
-    const PrefillLaunch r = resolve_prefill(L, M);
-    const int64_t MT = (M + r.BM - 1) / r.BM, NT = (L.N + r.BN - 1) / r.BN;
-    out[0] = r.BM;
-    out[1] = r.BN;
-    out[2] = r.KS;
-    out[3] = r.S;
-    out[4] = 2 * r.WNW * r.KS;                                   // waves per workgroup
-    out[5] = (int32_t)prefill_lds_bytes(r, L.minf);
-    out[6] = (int32_t)xcd_tile_grid(MT * r.S, NT);           // workgroups
-    out[7] = r.w8 ? (L.native8 ? 2 : 1) : 0;   // int8 weights: merged nibble planes / byte form
-}
-
-namespace {
 
 // More than one 128-row tile per CU: tiles of 128 x 128 (this file), 256 or 192 columns (mnnq_prefill8w.hip, whole or with two
 // K parts), by microseconds of a fused call fitted to 5600 measured ones (129 - 2048 tokens, three weight forms; nineteen in twenty
@@ -771,20 +744,46 @@ Wide8Plan wide8_plan(const Layout& L, int64_t M)
     return best;
 }
 
+// The one place that decides: launch_prefill starts what this says, the plan view shows it.
+PrefillLaunch resolve_prefill(const Layout& L, int64_t M)
+{
+    if (const char* e = debug_option(kDbgPrefillTile)) {      // tuning and tests: "x" / "c" = 256 / 192 columns
+        if ((e[0] == 'x' || e[0] == 'c') && (L.native8 || !L.minf))
+            return {128, e[1] && e[2] == 'k' ? 2 : 1, 1, 2, L.native8, e[0] == 'x' ? 256 : 192};
+    } else if (const Wide8Plan p = wide8_plan(L, M); p.columns) {
+        return {128, p.ks, 1, 2, L.native8, p.columns};
+    }
+    return resolve_few_tiles(L, M);
+}
+
+static_assert(Lds<256, 128, false>::BYTES == 2 * 256 * 128 + 8 * 1024 + 8 * 128 + 8 * 32, "prefill_lds_bytes");
+static_assert(Lds<128, 128, true, true>::BYTES == 2 * 128 * 128 + 16 * 1024 + 8 * 128 + 8 * 128, "prefill_lds_bytes");
+static_assert(Lds<64, 64, false>::BYTES == 2 * 64 * 128 + 4 * 1024 + 4 * 128 + 8 * 32, "prefill_lds_bytes");
+
+size_t prefill_lds_bytes(const PrefillLaunch& r, bool minf)
+{
+    const int nt16 = r.BN / 16;
+    if (r.BN > 128) return prefill8_wide_lds_bytes(r.BN, r.KS);
+    return (size_t)r.KS * (2 * r.BM * 128 + nt16 * 1024 * (r.w8 ? 2 : 1) + nt16 * 128 + (minf ? nt16 * 128 : 8 * 32));
+}
+
 }  // namespace
 
-float prefill8_us(const Layout& L, int64_t M) { return wide8_plan(L, M).us; }
-
-void describe_prefill8_wide(const Layout& L, int64_t M, int32_t out[8])
+void describe_prefill(const Layout& L, int64_t M, int32_t out[8])
 {
-    const Wide8Plan p = wide8_plan(L, M);
-    if (p.columns == 0) return;
-    const int64_t NT = (L.N + p.columns - 1) / p.columns;
-    out[1] = 128;
-    out[2] = p.columns;
-    out[3] = out[4] = 4 * p.ks;
-    out[6] = (int32_t)xcd_tile_grid((M + 127) / 128, NT);
+    const PrefillLaunch r = resolve_prefill(L, M);
+    const int64_t MT = (M + r.BM - 1) / r.BM, NT = (L.N + r.BN - 1) / r.BN;
+    out[0] = r.BM;
+    out[1] = r.BN;
+    out[2] = r.KS;
+    out[3] = r.S;
+    out[4] = 2 * r.WNW * r.KS;                                   // waves per workgroup
+    out[5] = (int32_t)prefill_lds_bytes(r, L.minf);
+    out[6] = (int32_t)xcd_tile_grid(MT * r.S, NT);           // workgroups
+    out[7] = r.w8 ? (L.native8 ? 2 : 1) : 0;   // int8 weights: merged nibble planes / byte form
 }
+
+float prefill8_us(const Layout& L, int64_t M) { return wide8_plan(L, M).us; }
 
 int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                    const float* bias, float* y, int32_t* acc_debug, hipStream_t st)
@@ -793,16 +792,8 @@ int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8
         if (M > 128) return launch_tiles<256, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
         return launch_tiles<128, 128, 1, true>(packed, L, M, xq, sx, bias, y, acc_debug, 1, st);
     }
-    if (const char* e = debug_option(kDbgPrefillTile)) {      // tuning and tests: "x" / "c" = 256 / 192 columns
-        if ((e[0] == 'x' || e[0] == 'c') && (L.native8 || !L.minf))
-            return launch_prefill8_wide(e[0] == 'x' ? 256 : 192, e[1] && e[2] == 'k' ? 2 : 1, packed, L, M, xq, sx, bias, y, st);
-    } else {
-        const Wide8Plan p = wide8_plan(L, M);
-        if (p.columns > 128) return launch_prefill8_wide(p.columns, p.ks, packed, L, M, xq, sx, bias, y, st);
-        if (p.columns == 128 && L.native8) return launch_tiles_m<128, 128, 1, false, true, 2>(packed, L, M, xq, sx, bias, y, nullptr, 1, st);
-        if (p.columns == 128) return launch_tiles<128, 128, 1, false>(packed, L, M, xq, sx, bias, y, nullptr, 1, st);
-    }
     const PrefillLaunch r = resolve_prefill(L, M);
+    if (r.BN > 128) return launch_prefill8_wide(r.BN, r.KS, packed, L, M, xq, sx, bias, y, st);
 #define MNNQ_ARGS packed, L, M, xq, sx, bias, y, nullptr, r.S, st
     if (r.w8 && L.native8) {   // byte form: the chunk's two kilobytes are the two groups' operands
         if (r.KS == 2 && r.WNW == 4) return launch_tiles_m<128, 128, 2, false, true, 2, 4>(MNNQ_ARGS);

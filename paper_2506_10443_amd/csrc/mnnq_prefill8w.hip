@@ -348,6 +348,12 @@ int launch_form(int columns, int ks, const uint8_t* packed, const Layout& L, int
 
 }  // namespace
 
+size_t prefill8_wide_lds_bytes(int columns, int ks)
+{
+    if (columns == 192) return ks == 2 ? Tile8<4, 8, 3, 2>::lds_bytes : Tile8<4, 8, 3, 1>::lds_bytes;
+    return ks == 2 ? Tile8<4, 8, 4, 2>::lds_bytes : Tile8<4, 8, 4, 1>::lds_bytes;
+}
+
 int launch_prefill8_wide(int columns, int ks, const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                          const float* bias, float* y, hipStream_t st)
 {

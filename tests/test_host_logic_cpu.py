@@ -36,7 +36,7 @@ def shapes():
 def test_prefill_plan_fits_and_covers(model, name, M, N, K, mode):
     for m in sorted({M, 17, 100, 129, 300}):
         bm, bn, ks, s, waves, lds, wgs, merged = B.mnnq_plan_debug(0, m, N, K, mode)
-        assert (bm, bn) in ((64, 64), (64, 128), (128, 128), (256, 128)) and ks in (1, 2, 4) and s in (1, 2)
+        assert (bm, bn) in ((64, 64), (64, 128), (128, 128), (256, 128), (128, 256), (128, 192)) and ks in (1, 2, 4) and s in (1, 2)
         assert (bm == 64) == (m <= 128 and not merged and not (m > 64 and -(-N // 128) >= 1024))
         assert ks < 4 or bm == 64
         assert waves in (4, 8, 16) and waves * 64 <= 1024 and waves % ks == 0
@@ -71,8 +71,8 @@ def test_documented_plans_of_the_qwen2_7b_block():
     # (the tiled GEMM's; without the plane the call runs the K-split kernel for all but gate|up)
     assert [B.mnnq_plan_debug(4, 1024, n, k)[0] for n, k in ((37888, 3584), (4608, 3584), (3584, 3584), (3584, 18944))] == [0, 3, 3, 3]
     plan = lambda n, k: B.mnnq_plan_debug(0, 1024, n, k)[:5]
-    assert plan(37888, 3584) == [256, 128, 1, 1, 8]      # gate|up: two workgroups of eight waves per CU
-    assert plan(4608, 3584) == [256, 128, 2, 1, 16]      # q|k|v: two K parts of eight waves
+    assert plan(37888, 3584) == [128, 256, 1, 1, 4]      # gate|up: two workgroups of four waves per CU
+    assert plan(4608, 3584) == [128, 192, 2, 1, 8]       # q|k|v: two K parts of four waves
     assert plan(3584, 3584) == [128, 128, 2, 1, 16]      # o
     assert plan(3584, 18944) == [128, 128, 2, 1, 16]     # down
     assert B.mnnq_plan_debug(1, 1, 37888, 3584)[:4] == [4, 4, 7, 0]      # GEMV: four waves per row tile, 7 chunks each
@@ -91,7 +91,7 @@ def test_documented_plans_of_the_qwen2_7b_block():
 
 def test_plans_of_the_byte_form_of_int8_weights():
     """mode MNNQ_W8_MIN_FLOAT | MNNQ_NATIVE_8BIT: the GEMV keeps seven chunks of two kilobytes per wave in
-    registers (a rolling window beyond sixteen waves per row tile), the GEMM runs 128 x 128 tiles."""
+    registers (a rolling window beyond sixteen waves per row tile), the GEMM runs tiles of 128 tokens."""
     NB = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
     for model, name, M, N, K in shapes():
         if K % 128:
@@ -106,10 +106,35 @@ def test_plans_of_the_byte_form_of_int8_weights():
                                    ((8, 1), (8, 2), (8, 4), (8, 8), (16, 16)))
             assert lds <= LDS_GEMV and wgs * tiles_per_wg >= N // 16
         bm, bn, kparts, s, w, lds, wgs, form = B.mnnq_plan_debug(0, M, N, K, NB)
-        assert (bm, bn, form) == (128, 128, 2) and kparts in (1, 2) and lds <= LDS_GEMM
-        assert wgs >= -(-M // 128) * s * -(-N // 128)
+        assert bm == 128 and bn in (128, 192, 256) and form == 2 and kparts in (1, 2) and lds <= LDS_GEMM
+        assert bn == 128 or w == 4 * kparts         # (the wide tiles: four waves of 16 tokens x bn / 4 columns per part)
+        assert wgs >= -(-M // 128) * s * -(-N // bn)
     assert B.mnnq_plan_debug(1, 1, 152064, 3584, NB)[:4] == [4, 4, 7, 0]     # LM head: 28 chunks on four waves
     assert B.mnnq_plan_debug(1, 1, 3584, 18944, NB)[:4] == [16, 16, 7, 1]    # down: 148 chunks, a window of seven
+
+
+@pytest.mark.parametrize("mode", [B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT, B.MODE_W8_MIN_FLOAT, B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT])
+def test_both_plan_views_show_the_tiled_kernel_that_runs(mode):
+    """Where the fused call takes the tiled GEMM, what = 4 and what = 0 name the same tile, waves and workgroups, and a forced
+    tile is what both show; every tile and K split is seen."""
+    seen = set()
+    for m in (65, 129, 200, 333, 512, 1024, 2048):
+        for n, k in ((37888, 3584), (28672, 4096), (17920, 1536), (6144, 4096), (4608, 3584), (4096, 14336), (11264, 1536), (32768, 1536), (152064, 3584)):
+            family, bm, bn, waves, _, _, groups, _ = B.mnnq_plan_debug(4, m, n, k, mode)
+            t = B.mnnq_plan_debug(0, m, n, k, mode)
+            assert t[5] <= LDS_GEMM and t[6] >= -(-m // t[0]) * t[3] * -(-n // t[1])
+            seen.add(tuple(t[:3]))
+            if family == 0:
+                assert (bm, bn, waves, groups) == (t[0], t[1], t[4], t[6])
+    if mode in (B.MODE_W4_ZP_INT, B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT):
+        assert {(128, 256, 1), (128, 192, 1), (128, 256, 2), (128, 192, 2)} <= seen
+        try:
+            for tile, columns, parts in (("x1", 256, 1), ("x1k", 256, 2), ("c1", 192, 1), ("c1k", 192, 2)):
+                B.mnnq_debug_set("MNNQ_PREFILL_TILE", tile)
+                assert B.mnnq_plan_debug(0, 1024, 37888, 3584, mode)[:5] == [128, columns, parts, 1, 4 * parts]
+                assert B.mnnq_plan_debug(4, 1024, 37888, 3584, mode)[:4] == [0, 128, columns, 4 * parts]
+        finally:
+            B.mnnq_debug_set("MNNQ_PREFILL_TILE", None)
 
 
 def test_documented_plans_for_few_tokens():
