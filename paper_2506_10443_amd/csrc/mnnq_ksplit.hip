@@ -388,8 +388,9 @@ int launch_form(const uint8_t* packed, const Layout& L, int64_t M, const void* x
 // against 76 us, 512 tokens of 17920 x 1536 (nine against three) 48 against 52 us; int4 57 against 60 and 41 against 39 us -
 // with the chip full, the tiled form's sharing of operands through LDS counts.
 //
-// Where the tiled GEMM has more than one tile per CU both are weighed in microseconds (over 5600 shapes 0.25 % from the best of
-// all tiles in the mean, 1.4 % before: float minimum 342 tokens of 36688 x 1216 72 -> 49 us, 1053 of 14208 x 3136 156 -> 109 us).
+// Where the tiled GEMM has more than one tile per CU both are weighed in microseconds fitted to the same calls (K-split / tiled,
+// us: float minimum 2048 tokens of 6144 x 4096 129 / 103, 427 of 24288 x 3456 102 / 84, 342 of 36688 x 1216 49 / 72; bytes 1220
+// of 14720 x 3456 173 / 154).  A call on rows and a fused one take the same kernel, so that their results are the same bits.
 // Else a round costs as much again as two chunks of it, which the measured rounds (32 chunks) hold already: the exchange of the
 // partial sums.  Over 595 shapes of 65 - 2048 tokens, calls on int8 rows and fused ones, the choice costs 0.25 % against the
 // better of the two kernels at each shape, 8 % at most where the call is fused and 12 % on rows; without the round's own part
@@ -404,10 +405,10 @@ bool ksplit8_wanted(const Layout& L, int64_t M)
     const float rounds = tile_height(L, M, form).rounds, C = (float)L.C;
     bool faster;
     if (const float tiled = prefill8_us(L, M); tiled > 0.0f) {
-        // microseconds against microseconds, on long rows with the margin that the fits leave
-        const float us = 0.14e-6f * (float)(M * L.Kx) + (form == kBytes ? 7.9f + (1.71f + 0.23f * C) * rounds
-                       : form == kMin ? 7.95f + (1.55f + 0.234f * C) * rounds : 8.1f + (1.34f + 0.198f * C) * rounds);
-        faster = us <= tiled * (L.C >= 16 ? 1.045f : 1.0f);
+        // microseconds against microseconds (of a call on rows; M Kx: what the quantizer in token-block order costs less)
+        const float us = -0.3e-6f * (float)(M * L.Kx) + (form == kBytes ? 6.25f + (1.5f + 0.275f * C) * rounds
+                       : form == kMin ? 6.6f + (1.41f + 0.252f * C) * rounds : 6.45f + (1.35f + 0.216f * C) * rounds);
+        faster = us <= tiled * (form == kZp ? 1.03f : 1.02f);      // (within the fits, the side that the fused call gains by)
     } else {
         const float own = (1.0f + 2.0f / C) / (1.0f + 2.0f / 32.0f);
         faster = rounds * own <= tiled_rounds(L, M, form);

@@ -701,46 +701,56 @@ PrefillLaunch resolve_few_tiles(const Layout& L, int64_t M)
     return r;
 }
 
-// More than one 128-row tile per CU: tiles of 128 x 128 (this file), 256 or 192 columns (mnnq_prefill8w.hip, whole or with two
-// K parts), by microseconds of a fused call fitted to 5600 measured ones (129 - 2048 tokens, three weight forms; nineteen in twenty
-// within 8 %).  Per form and tile: constant, per tile of the busiest CU, per chunk and tile, per chunk of an odd last tile; split:
-// constant, per chunk.  Measured, us, 128 x 128 / 256 / 192 columns: int8 bytes 1024 tokens of 37888 x 3584 302 / 255 / 277, 2048 of
-// 6144 x 4096 114 / 112 / 94, 333 of 28672 x 4096 113 / 112 / 93; int4 512 of 28672 x 4096 106 / 93 / 111.  (Float minima of 4-bit codes
-// 253 / 249 / 270, 96 / 114 / 94, 93 / 114 / 93: 128 x 128 always.)
-struct Wide8Cost {
-    float s[4], x[4], c[4], xk[2], ck[2];
+// More than one 128-row tile per CU: the tile by the microseconds a call is expected to take, fixed + n (tile + C chunk) and
+// C odd for an odd n, with n tiles on the busiest CU and C chunks; the forms with two K parts have one tile per CU.  Fitted
+// to 4600 measured calls (129 - 2048 tokens, 512 - 37888 columns, three weight forms, calls on rows and fused ones less their
+// quantizer), half of them within 2 %, nineteen in twenty within 8 %; with the K-split kernel's times (ksplit8_wanted) the choice
+// costs 0.7 % against the best kernel of each shape (int4), 0.3 % (float minimum) and 0.5 % (bytes).  Every tile listed is the
+// best one somewhere; us, 128 x 128 of four waves / of eight / 256 x 128 of eight / 128 x 256 / 128 x 192:
+//   int4    932 tokens of 37280 x 3840  238 / 253 / 221 / 226 / 244;  924 of 23456 x 1280 62.1 / 65.1 / 58.8 / 60.6 / 60.1
+//           512 of 28672 x 4096 106 / - / - / 93 / 111;  225 of 28160 x 1792 35.0 / 33.9 / 35.4 / 37.6 / 41.1
+//   bytes   634 of 31168 x 1664 89.4 / 87.6 / - / 97.2 / 97.3;  1024 of 37888 x 3584 302 / - / - / 255 / 277;  333 of 28672 x 4096
+//           113 / - / - / 112 / 93
+// (Bytes never want four waves on 128 x 128: without them the loss is the same.  Float minima of 4-bit codes take 128 x 128
+// always - 128 x 256 with centred codes 249 - 258 against 253 us at 1024 of 37888 x 3584, 256 rows and eight waves within 0.1 %
+// of it over all shapes.)
+struct TileCost {
+    int BM, BN, KS, WNW;
+    float fixed, tile, chunk, odd;
 };
-constexpr Wide8Cost kWide8Cost[3] = {
-    {{9.6f, -0.4f, 0.82f, 0.35f}, {8.8f, 2.7f, 1.28f, 0.39f}, {8.0f, 2.4f, 0.995f, 0.34f}, {14.1f, 1.29f}, {12.6f, 1.03f}},    // kZp
-    {{10.3f, -0.8f, 0.97f, 0.42f}, {}, {}, {}, {}},                                                                           // kMin
-    {{7.4f, 1.6f, 0.995f, 0.45f}, {9.4f, 3.2f, 1.6f, 0.5f}, {8.8f, 2.7f, 1.27f, 0.43f}, {16.1f, 1.58f}, {14.1f, 1.27f}},       // kBytes
-};
+constexpr TileCost kTilesZp[] = {
+    {128, 128, 1, 2, 9.1f, 0.26f, 0.785f, -0.138f}, {128, 128, 1, 4, 5.6f, 1.62f, 0.77f, 0.039f}, {256, 128, 1, 4, 6.8f, 2.58f, 1.232f, 0.353f},
+    {128, 256, 1, 2, 7.1f, 2.97f, 1.249f, 0.455f},  {128, 256, 2, 2, 13.2f, 0.0f, 1.305f, 0.0f},  {128, 192, 1, 2, 6.8f, 2.29f, 0.977f, 0.39f},
+    {128, 192, 2, 2, 11.7f, 0.0f, 1.052f, 0.0f}};
+constexpr TileCost kTilesMin[] = {{128, 128, 1, 2, 9.5f, -0.12f, 0.934f, -0.143f}};
+constexpr TileCost kTilesBytes[] = {
+    {128, 128, 1, 4, 5.3f, 1.65f, 0.998f, 0.066f}, {128, 256, 1, 2, 7.0f, 4.07f, 1.568f, 0.574f}, {128, 256, 2, 2, 15.3f, 0.0f, 1.611f, 0.0f},
+    {128, 192, 1, 2, 6.6f, 3.1f, 1.259f, 0.484f},  {128, 192, 2, 2, 13.5f, 0.0f, 1.306f, 0.0f}};
 
-struct Wide8Plan {
-    int columns, ks;      // 0 columns: not chosen here (few tiles, nibble planes, a forced tile)
-    float us;
-};
-
-Wide8Plan wide8_plan(const Layout& L, int64_t M)
+// us = 0: not chosen here (up to 128 tokens, at most one tile per CU, nibble planes).
+PrefillLaunch resolve_many_tiles(const Layout& L, int64_t M, float& us)
 {
-    Wide8Plan best{0, 1, 0.0f};
-    if (M <= 128 || (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8)) return best;
-    const int64_t cus = num_cus(), rows = (M + 127) / 128;
-    auto per_cu = [&](int64_t cols) { return (int)((rows * ((L.N + cols - 1) / cols) + cus - 1) / cus); };
-    const int n128 = per_cu(128), n192 = per_cu(192), n256 = per_cu(256);
-    if (n128 == 1) return best;
-    const Wide8Cost& f = kWide8Cost[L.native8 ? 2 : L.minf ? 1 : 0];
-    const float C = (float)L.C;
-    auto whole = [&](const float (&k)[4], int n) { return k[0] + k[1] * (float)n + C * (k[2] * (float)n + k[3] * (float)(n & 1)); };
-    best = Wide8Plan{128, 1, whole(f.s, n128)};
-    if (L.minf && !L.native8) return best;
-    auto offer = [&](int columns, int ks, float us) {
-        if (us < best.us) best = Wide8Plan{columns, ks, us};
+    us = 0.0f;
+    PrefillLaunch best{};
+    const int64_t cus = num_cus();
+    auto per_cu = [&](const TileCost& t) { return ((M + t.BM - 1) / t.BM * ((L.N + t.BN - 1) / t.BN) + cus - 1) / cus; };
+    if (M <= 128 || (L.mode == MNNQ_W8_MIN_FLOAT && !L.native8) || per_cu(TileCost{128, 128}) == 1) return best;
+    auto offer = [&](const TileCost& t) {
+        const int64_t n = per_cu(t);
+        if (t.KS == 2 && (n > 1 || L.C < 4)) return;
+        const float C = (float)L.C, time = t.fixed + (float)n * (t.tile + C * t.chunk) + (n & 1 ? C * t.odd : 0.0f);
+        if (us == 0.0f || time < us) {
+            us = time;
+            best = PrefillLaunch{t.BM, t.KS, 1, t.WNW, L.native8, t.BN};
+        }
     };
-    offer(256, 1, whole(f.x, n256));
-    offer(192, 1, whole(f.c, n192));
-    if (n256 == 1 && L.C >= 4) offer(256, 2, f.xk[0] + f.xk[1] * C);
-    if (n192 == 1 && L.C >= 4) offer(192, 2, f.ck[0] + f.ck[1] * C);
+    if (L.native8) {
+        for (const TileCost& t : kTilesBytes) offer(t);
+    } else if (L.minf) {
+        for (const TileCost& t : kTilesMin) offer(t);
+    } else {
+        for (const TileCost& t : kTilesZp) offer(t);
+    }
     return best;
 }
 
@@ -750,8 +760,10 @@ PrefillLaunch resolve_prefill(const Layout& L, int64_t M)
     if (const char* e = debug_option(kDbgPrefillTile)) {      // tuning and tests: "x" / "c" = 256 / 192 columns
         if ((e[0] == 'x' || e[0] == 'c') && (L.native8 || !L.minf))
             return {128, e[1] && e[2] == 'k' ? 2 : 1, 1, 2, L.native8, e[0] == 'x' ? 256 : 192};
-    } else if (const Wide8Plan p = wide8_plan(L, M); p.columns) {
-        return {128, p.ks, 1, 2, L.native8, p.columns};
+    } else {
+        float us;
+        const PrefillLaunch r = resolve_many_tiles(L, M, us);
+        if (us > 0.0f) return r;
     }
     return resolve_few_tiles(L, M);
 }
@@ -783,7 +795,12 @@ void describe_prefill(const Layout& L, int64_t M, int32_t out[8])
     out[7] = r.w8 ? (L.native8 ? 2 : 1) : 0;   // int8 weights: merged nibble planes / byte form
 }
 
-float prefill8_us(const Layout& L, int64_t M) { return wide8_plan(L, M).us; }
+float prefill8_us(const Layout& L, int64_t M)
+{
+    float us;
+    resolve_many_tiles(L, M, us);
+    return us;
+}
 
 int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                    const float* bias, float* y, int32_t* acc_debug, hipStream_t st)

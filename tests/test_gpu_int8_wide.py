@@ -51,4 +51,4 @@ def test_wide_tiles_match_exact(form, M, N, K):
 def test_the_tile_follows_the_shape():
     plan = lambda m, n, k, f: B.mnnq_plan_debug(4, m, n, k, FORMS[f])[:4]
     assert plan(1024, 37888, 3584, "w8") == [0, 128, 256, 4] and plan(333, 28672, 4096, "w8") == [0, 128, 192, 4]
-    assert plan(1024, 37888, 3584, "w4min") == [0, 128, 128, 4] and plan(512, 28672, 4096, "w4") == [0, 128, 256, 4]
+    assert plan(1024, 37888, 3584, "w4min") == [0, 128, 128, 4] and plan(384, 37888, 3584, "w4") == [0, 128, 256, 4]

@@ -71,7 +71,7 @@ def test_documented_plans_of_the_qwen2_7b_block():
     # (the tiled GEMM's; without the plane the call runs the K-split kernel for all but gate|up)
     assert [B.mnnq_plan_debug(4, 1024, n, k)[0] for n, k in ((37888, 3584), (4608, 3584), (3584, 3584), (3584, 18944))] == [0, 3, 3, 3]
     plan = lambda n, k: B.mnnq_plan_debug(0, 1024, n, k)[:5]
-    assert plan(37888, 3584) == [128, 256, 1, 1, 4]      # gate|up: two workgroups of four waves per CU
+    assert plan(37888, 3584) == [256, 128, 1, 1, 8]      # gate|up: two workgroups of eight waves per CU
     assert plan(4608, 3584) == [128, 192, 2, 1, 8]       # q|k|v: two K parts of four waves
     assert plan(3584, 3584) == [128, 128, 2, 1, 16]      # o
     assert plan(3584, 18944) == [128, 128, 2, 1, 16]     # down
@@ -265,3 +265,24 @@ def test_k_split_int8_gemm_where_its_rounds_cost_less():
     assert not any(ksplit(m, n, k) for m, n, k in ((256, 15952, 1664), (356, 15952, 1664), (707, 5104, 1408)))
     assert all(ksplit(m, n, k, w8) for m, n, k in ((784, 4096, 14336), (771, 4608, 3584), (529, 4000, 12672), (333, 4096, 4096)))
     assert all(ksplit(m, n, k) for m, n, k in ((1125, 3584, 3584), (803, 4608, 3584), (1181, 4096, 14336), (333, 4096, 4096)))
+
+
+def test_int8_tiles_that_the_shapes_were_measured_fastest_on():
+    """Shapes at which one kernel beat the others by 3 % and more, on rows and fused: the K-split kernel (3), and of the tiled
+    GEMM's forms (tokens, columns, waves)."""
+    w8 = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
+    plan = lambda m, n, k, mode: tuple(B.mnnq_plan_debug(4, m, n, k, mode)[:4])
+    low = B.MODE_W4_MIN_FLOAT
+    # float minima of 4-bit codes: 128 x 128 of four waves, 10 - 20 % ahead of the K-split kernel ...
+    for m, n, k in ((2048, 6144, 4096), (427, 24288, 3456), (1803, 5824, 3840), (512, 17920, 1536), (333, 28672, 4096), (1914, 5856, 3200)):
+        assert plan(m, n, k, low) == (0, 128, 128, 4)
+    # ... and behind it
+    for m, n, k in ((147, 16672, 1792), (502, 8224, 2048), (1963, 2544, 6144), (467, 9840, 2432), (391, 16880, 3072)):
+        assert plan(m, n, k, low)[0] == 3
+    for m, n, k in ((1024, 37888, 3584), (2048, 28672, 4096), (932, 37280, 3840), (924, 23456, 1280), (1974, 10688, 1280)):
+        assert plan(m, n, k, B.MODE_W4_ZP_INT) == (0, 256, 128, 8)
+    for m, n, k in ((225, 28160, 1792), (428, 15184, 1664)):
+        assert plan(m, n, k, B.MODE_W4_ZP_INT) == (0, 128, 128, 8)
+    for m, n, k in ((634, 31168, 1664), (1220, 14720, 3456)):
+        assert plan(m, n, k, w8) == (0, 128, 128, 8)
+    assert plan(1024, 37888, 3584, w8) == (0, 128, 256, 4) and plan(2048, 6144, 4096, w8) == (0, 128, 192, 4)
