@@ -273,9 +273,11 @@ int mnnq_linear_acc_debug_planes(const void *packed, int64_t M, int64_t N, int64
 /* Tests and tuning: overrides of the launch plans, which otherwise follow from the shapes alone (the
  * library never reads the environment).  key: one of MNNQ_DECODE_KSPLIT (waves per row tile of the GEMV:
  * 1, 2, 4, 8, 16), MNNQ_DECODE_WAVES (4, 8, 16), MNNQ_DECODE_EARLY (0/1), MNNQ_PREFILL_TILE (tile letter,
- * K split digit, k/q), MNNQ_NO_SKINNY, MNNQ_SKINNY_STAGED (0/1), MNNQ_W8_PLANES (1), MNNQ_FUSED_TWO_KERNEL_MIB,
- * MNNQ_PREFILL6_PLAN (0..8: tile plan of the fp6 GEMM), MNNQ_PREFILL6_STAGES (2..4: depth of its LDS rings);
- * value: a string of at most 15 characters, or NULL to clear the override.  Applies to all later calls of the process; not thread safe.  MNNQ_ERR_UNSUPPORTED
+ * K split digit, k/q; int8 GEMM: s, v 128 x 128 of four, eight waves, w 256 x 128, t, n 64 x 128, 64 x 64, x, c 128 x 256,
+ * 128 x 192; fp16: b 256 wide or high, s, c, d; a tile that the weight form has no kernel for runs as s),
+ * MNNQ_NO_SKINNY, MNNQ_SKINNY_STAGED (0/1), MNNQ_W8_PLANES (1), MNNQ_FUSED_TWO_KERNEL_MIB, MNNQ_PREFILL6_PLAN (0..8: tile plan
+ * of the fp6 GEMM), MNNQ_PREFILL6_STAGES (2..4: depth of its LDS rings); value: a string of at most 15 characters, or NULL to
+ * clear the override.  Applies to all later calls of the process; not thread safe.  MNNQ_ERR_UNSUPPORTED
  * for an unknown key. */
 int mnnq_debug_set(const char *key, const char *value);
 

@@ -559,43 +559,37 @@ int launch_tiles(const uint8_t* packed, const Layout& L, int64_t M, const int8_t
     return launch_tiles_m<BM, BN, KS, ACC, false>(packed, L, M, xq, sx, bias, y, acc, S, st);
 }
 
-// Eight waves per K part (128 x 32 or 64 x 32 outputs per wave).
+// Eight waves per K part (128 x 32 or 64 x 32 outputs per wave); float minima: two K parts only.
 template <int BM, int KS>
 int launch_wide(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                 const float* bias, float* y, int S, hipStream_t st)
 {
-    if (L.minf) {
-        if constexpr (BM == 256 && KS == 2) return MNNQ_ERR_UNSUPPORTED;   // not built: see launch_prefill
-        else return launch_tiles_m<BM, 128, KS, false, true, false, 4>(packed, L, M, xq, sx, bias, y, nullptr, S, st);
+    if constexpr (KS == 2) {
+        if (L.minf) return launch_tiles_m<BM, 128, KS, false, true, false, 4>(packed, L, M, xq, sx, bias, y, nullptr, S, st);
     }
     return launch_tiles_m<BM, 128, KS, false, false, false, 4>(packed, L, M, xq, sx, bias, y, nullptr, S, st);
 }
 
-// Tile, K-part and split choice, for the shapes that the few-token kernels and the K-split GEMM leave (skinny_wanted,
-// ksplit8_wanted: rounds of many tiles, short rows; int8 nibble planes from 65 tokens) and for the accumulator dumps.  A SIMD is full with four waves of the forms that need at most
-// 128 registers (eight waves per K part: 128 x 32 or 64 x 32 outputs per wave), with two otherwise.
-//   * 256-row tiles share one B unpack between 8 MFMAs and are preferred when they
-//     alone give every CU two workgroups (of eight waves each);
-//   * with at most one 128-row tile per CU, the tile's K range is split inside the
-//     workgroup (two K parts of eight waves), which fills the SIMDs without any traffic
-//     through memory;
-//   * in between (more 128-row tiles than CUs, fewer than two each) a second round of
-//     workgroups would run on a few CUs only; 256-row tiles with the same K split inside the
-//     workgroup use fewer CUs but use them fully;
-//   * a split of K over two workgroups (S = 2, fp32 atomics onto a zeroed y) is left
-//     for long rows with so few tiles that most CUs would idle.
+// Tile, K-part and split choice for what resolve_many_tiles leaves: up to 128 tokens, at most one 128-row tile per CU, and int8
+// nibble planes (whose tile is fixed, see resolve_few_tiles) - of these, what the few-token and the K-split kernels do not take.
+// A SIMD is full with four waves of the forms that need at most 128 registers (eight waves per K part: 64 x 32 outputs per
+// wave), with two otherwise.
+//   * with at most one 128-row tile per CU, the tile's K range is split inside the workgroup (two K parts of eight waves),
+//     which fills the SIMDs without any traffic through memory;
+//   * a split of K over two workgroups (S = 2, fp32 atomics onto a zeroed y) is left for long rows with so few tiles that
+//     most CUs would idle.
 struct TilePlan {
-    bool big;
     int KS;
     int S;
-    bool wide;   // 256-row tile worked on by eight waves (128 x 32 outputs each), two workgroups per CU
+    bool big;    // 256-row tile (forced only)
+    bool wide;   // eight waves per K part
     bool tiny;   // 64-row tile (few tokens): the call is bound by the weight stream, not by the MFMAs
     bool narrow; // ... of 64 columns: twice the workgroups for layers with few output columns
 };
 
 TilePlan plan_tiles(const Layout& L, int64_t M)
 {
-    TilePlan p{true, 1, 1, false, false, false};
+    TilePlan p{1, 1, false, false, false, false};
     const int64_t cus = num_cus();
     auto tiles = [&](int bm) { return ((M + bm - 1) / bm) * ((L.N + 127) / 128); };
     if (M <= 128 && L.mode != MNNQ_W8_MIN_FLOAT && !(M > 64 && tiles(128) >= 4 * cus)) {
@@ -603,8 +597,7 @@ TilePlan plan_tiles(const Layout& L, int64_t M)
         // per chunk.  Such a call is bound by stalls, not by the MFMAs, and runs the faster the more
         // waves a CU holds: 64-column tiles (twice the workgroups, of 21 KiB of LDS each) unless there
         // are very many tiles, the K range in 1, 2 or 4 parts of four waves, and long rows also cut in
-        // two.  (Beyond 64 tokens and with that many tiles, 128-row tiles are faster: the plans below.)
-        p.big = false;
+        // two.  (Beyond 64 tokens and with that many tiles, 128-row tiles of four waves are faster.)
         p.tiny = true;
         int64_t t = tiles(64);
         if (t < 4 * cus) {
@@ -613,35 +606,22 @@ TilePlan plan_tiles(const Layout& L, int64_t M)
         }
         p.KS = t >= 4 * cus ? 1 : (2 * t >= cus ? 2 : 4);
         if (4 * t <= cus && L.C >= 64) p.S = 2;
-    } else if (M > 128 && tiles(256) >= 2 * cus) {
-        p.big = true;
-        p.wide = !L.minf;   // the float minimum form needs more registers than four waves per SIMD leave
     } else if (tiles(128) <= cus) {
-        p.big = false;
         p.KS = 2;
         p.wide = true;      // sixteen waves: two K parts of eight
         if (tiles(128) * 2 <= cus && L.C >= 64) p.S = 2;
-    } else if (tiles(128) < 2 * cus) {
-        // (float minimum form: the sixteen-wave 256-row form would spill; eight waves on 128-row tiles
-        // measured 5 - 9 % faster than two K parts of four waves on 256-row tiles)
-        // (256-row tiles with two K parts take a CU each: a second round of them, 337 tokens of 17488 x 4096 in 274 tiles,
-        // 105 us, took longer than the 411 tiles of 128 rows, two per CU)
-        p.big = M > 128 && !L.minf && tiles(256) <= cus;
-        p.KS = p.big ? 2 : 1;
-        p.wide = p.big || L.minf;
-    } else {
-        p.big = false;
     }
-    if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: "b"/"s", split digit, "k" = K parts
-        if (e[0] == 'b' || e[0] == 'w') p.big = true;
-        if (e[0] == 's' || e[0] == 'v' || e[0] == 't' || e[0] == 'n') p.big = false;
-        p.wide = (e[0] == 'w' || e[0] == 'v');     // "w"/"v" = "b"/"s" worked on by twice the waves
-        p.tiny = (e[0] == 't' || e[0] == 'n') && L.mode != MNNQ_W8_MIN_FLOAT;   // "t" = 64-row tile; "k" / "q" = 2 / 4 K parts
+    if (const char* e = debug_option(kDbgPrefillTile)) {   // tuning and tests: tile letter, split digit, "k" / "q" = 2 / 4 K parts
+        p.wide = (e[0] == 'w' || e[0] == 'v');                                   // "s" 128 x 128 of four waves, "v" of eight
+        p.tiny = (e[0] == 't' || e[0] == 'n') && L.mode != MNNQ_W8_MIN_FLOAT;   // "t" = 64-row tile
         p.narrow = p.tiny && e[0] == 'n';                                        // "n" = 64 x 64 tile
         if (e[0] && (e[1] == '1' || e[1] == '2' || e[1] == '4')) {
             p.S = e[1] - '0';
             p.KS = (e[2] == 'k') ? 2 : ((e[2] == 'q' && p.tiny) ? 4 : 1);
         }
+        if (p.KS == 4 && !p.tiny) p.KS = 2;
+        // "w" = 256 x 128 of eight waves: int4 with a zero point, one K part
+        p.big = e[0] == 'w' && !L.minf && p.KS == 1;
     }
     return p;
 }
@@ -686,7 +666,7 @@ PrefillLaunch resolve_few_tiles(const Layout& L, int64_t M)
         r.w8 = true;
         r.BM = 128;
         const int64_t tiles128 = ((M + 127) / 128) * ((L.N + 127) / 128), cus = num_cus();
-        if (!forced_plan) {   // the plan above counted 256-row tiles too
+        if (!forced_plan) {
             r.KS = tiles128 <= cus ? 2 : 1;
             r.WNW = tiles128 < 2 * cus ? 4 : 2;     // few tiles: twice the waves on each
         } else {
@@ -695,9 +675,8 @@ PrefillLaunch resolve_few_tiles(const Layout& L, int64_t M)
         if (r.S > 1 && L.Cx < 64) r.S = 1;
         return r;
     }
-    // twice the waves per tile; the combinations not listed run in the four-wave form
-    if (p.wide && ((r.BM == 256 && r.KS == 1) || (r.BM == 256 && r.KS == 2 && !L.minf) || r.BM == 128))
-        r.WNW = 4;   // (256 rows, two K parts, float minimum form: would spill registers)
+    // twice the waves per tile (float minima with one K part run in the four-wave form)
+    if (p.wide && (!L.minf || r.KS == 2)) r.WNW = 4;
     return r;
 }
 
@@ -825,8 +804,7 @@ int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8
         return launch_tiles_m<128, 128, 1, false, true, true>(MNNQ_ARGS);
     }
     if (r.WNW == 4) {
-        if (r.BM == 256 && r.KS == 1) return launch_wide<256, 1>(packed, L, M, xq, sx, bias, y, r.S, st);
-        if (r.BM == 256) return launch_wide<256, 2>(packed, L, M, xq, sx, bias, y, r.S, st);
+        if (r.BM == 256) return launch_wide<256, 1>(packed, L, M, xq, sx, bias, y, r.S, st);
         if (r.KS == 2) return launch_wide<128, 2>(packed, L, M, xq, sx, bias, y, r.S, st);
         return launch_wide<128, 1>(packed, L, M, xq, sx, bias, y, r.S, st);
     }
@@ -840,8 +818,6 @@ int launch_prefill(const uint8_t* packed, const Layout& L, int64_t M, const int8
         if (r.KS == 2) return launch_tiles<64, 128, 2, false>(MNNQ_ARGS);
         return launch_tiles<64, 128, 1, false>(MNNQ_ARGS);
     }
-    if (r.BM == 256 && r.KS == 2) return launch_tiles<256, 128, 2, false>(MNNQ_ARGS);
-    if (r.BM == 256) return launch_tiles<256, 128, 1, false>(MNNQ_ARGS);
     if (r.KS == 2) return launch_tiles<128, 128, 2, false>(MNNQ_ARGS);
     return launch_tiles<128, 128, 1, false>(MNNQ_ARGS);
 #undef MNNQ_ARGS
