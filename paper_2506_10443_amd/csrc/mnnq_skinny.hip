@@ -550,22 +550,33 @@ int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_
                   : launch_int8<false>(packed, L, (int)M, xq, sx, bias, y, st);
 }
 
-// fp16 activations.  Up to 16 tokens always.  Up to 32 tokens by the time expected of either kernel, where the activation
-// operands stay in registers (K <= 4096): the GEMM with K split over waves takes whole rounds of 64-column tiles (few-token /
-// K-split, us: 32 tokens of 7040 x 1984 11.6 / 7.3, of 2320 x 5120 16.4 / 11.4, 24 of 16448 x 4096 - a second round - 17.9 / 23.2).
-// The line costs 1 % against the better of the two over 4700 shapes, 9 % at every shape before.  More tokens only on the
-// smallest layers (36 of 976 x 1280 6.6 / 8.1, 68 of 1152 x 1024 6.1 / 7.5; 48 of 1840 x 13248 40.5 / 22.9, 64 of
-// 1328 x 17024 65.7 / 28.8, 77 of 2800 x 2048 in two slices 14.3 / 7.2 us).
+// fp16 activations.  Up to 16 tokens always.  Up to 64 by the time expected of either kernel, where the activation operands
+// stay in registers: the few-token kernel takes fixed + chunk C + n (tile + tile_chunk C) with n row tiles on the busiest CU, the
+// GEMM with K split over waves whole rounds of 64-column tiles (its formula, fitted up to 2048 tokens, is 10 % short here; us,
+// few-token / K-split: int4 32 tokens of 7040 x 1984 11.6 / 7.3, 24 of 16448 x 4096 - a second round - 17.9 / 23.2, 56 of
+// 19264 x 1664 16.9 / 20.3; float minimum 54 of 10480 x 1088 12.7 / 15.9, 24 of 36224 x 3840 32.0 / 37.7, 42 of 31888 x 1152
+// 20.0 / 16.5).  Over 3000 shapes of 17 - 64 tokens that costs 0.3 % (int4) and 0.6 % (float minimum) against the better kernel;
+// the time of 32 tokens and a limit on the cells beyond, fitted to int4, had cost 1.1 %, up to 29 % on float minima of short rows.
+// Where the operands are streamed the K-split kernel wins but for float minima of at most one row tile per CU (1.01 - 1.09
+// : 1, 45 of 189 shapes the other way).  More tokens only on the smallest layers (68 of 1152 x 1024 6.1 / 7.5, 77 of 2800 x 2048 in
+// two slices 14.3 / 7.2 us).
+struct FewCost {
+    float fixed, chunk, tile, tile_chunk;
+};
+constexpr FewCost kFewF16[2][3] = {      // [float minimum][blocks of 16 tokens, from two on]
+    {{2.53f, 0.202f, 1.21f, 0.029f}, {2.62f, 0.327f, 1.19f, 0.023f}, {2.49f, 0.428f, 1.37f, 0.025f}},
+    {{2.48f, 0.212f, 1.18f, 0.046f}, {2.15f, 0.355f, 1.52f, 0.024f}, {2.27f, 0.42f, 1.8f, 0.02f}}};
+
 bool skinny_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgNoSkinny) || debug_option(kDbgPrefillTile)) return false;   // tests and tuning: the tiled GEMM
     if (M <= 16) return true;
     if (M > 128 || !few_plan(L, blocks_of(M), form_of(L, true)).resident) return false;
-    const int64_t cells = L.T * L.C;
-    if (M > 32) return L.C <= 10 && cells <= (M <= 48 ? 2000 : 600);
-    const float C = (float)L.C, tiles = (float)L.T / (float)num_cus();
-    const float few = L.minf ? 3.6f + 0.19f * C + tiles * (0.78f + 0.057f * C) : 4.2f + 0.16f * C + tiles * (0.7f + 0.044f * C);
-    return few <= ksplit_f16_us(L, M);
+    if (M > 64) return L.C <= 10 && L.T * L.C <= 600;
+    const int64_t cus = num_cus();
+    const FewCost& f = kFewF16[L.minf ? 1 : 0][blocks_of(M) - 2];
+    const float C = (float)L.C, n = (float)((L.T + cus - 1) / cus);
+    return f.fixed + f.chunk * C + n * (f.tile + f.tile_chunk * C) <= 1.1f * ksplit_f16_us(L, M);
 }
 
 void describe_skinny(const Layout& L, int64_t M, bool f16, int32_t out[8])

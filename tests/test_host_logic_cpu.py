@@ -286,3 +286,16 @@ def test_int8_tiles_that_the_shapes_were_measured_fastest_on():
     for m, n, k in ((634, 31168, 1664), (1220, 14720, 3456)):
         assert plan(m, n, k, w8) == (0, 128, 128, 8)
     assert plan(1024, 37888, 3584, w8) == (0, 128, 256, 4) and plan(2048, 6144, 4096, w8) == (0, 128, 192, 4)
+
+
+def test_fp16_activations_of_17_to_64_tokens_take_the_faster_kernel():
+    """Shapes at which the few-token kernel (families 1, 2) or the K-split one (3) was measured 7 % and more ahead."""
+    plan = lambda m, n, k, mode: B.mnnq_plan_debug(5, m, n, k, mode)[0]
+    for m, n, k in ((56, 19264, 1664), (58, 21632, 1920), (59, 17360, 1536), (43, 19536, 1664), (25, 4016, 2176), (24, 16448, 4096), (18, 4000, 1408)):
+        assert plan(m, n, k, B.MODE_W4_ZP_INT) in (1, 2)
+    for m, n, k in ((32, 14432, 1792), (24, 5824, 1792), (46, 1008, 1792), (62, 1296, 1024), (32, 7040, 1984), (64, 1328, 17024)):
+        assert plan(m, n, k, B.MODE_W4_ZP_INT) == 3
+    for m, n, k in ((54, 10480, 1088), (53, 9152, 1664), (24, 36224, 3840), (23, 992, 1280), (36, 1040, 1280), (48, 18608, 1280)):
+        assert plan(m, n, k, B.MODE_W4_MIN_FLOAT) in (1, 2)
+    for m, n, k in ((42, 31888, 1152), (42, 2416, 2048), (20, 14736, 2688), (49, 1616, 1536), (64, 1760, 8320)):
+        assert plan(m, n, k, B.MODE_W4_MIN_FLOAT) == 3
