@@ -697,21 +697,51 @@ int dispatch(const uint8_t* packed, const Layout& L, int64_t M, const void* xin,
     return MNNQ_ERR_UNSUPPORTED;
 }
 
+// Workgroups of a fused kernel that a CU holds (by its registers: a row of at most 32 chunks takes 6 KB of LDS), asked of the
+// runtime once per kernel, device and thread; 0 if the configuration is not one of decode_config's own.
+template <int KSPLIT, int UNROLL, bool MINF>
+int fused_workgroups(size_t lds)
+{
+    static thread_local int asked_dev = -1, held = 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (dev != asked_dev) {
+        auto kern = decode_kernel<8, KSPLIT, UNROLL, kFused, false, MINF, true>;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&held, kern, 8 * 64, lds) != hipSuccess) held = 0;
+        asked_dev = dev;
+    }
+    return held;
+}
+
+int fused_workgroups_per_cu(const Layout& L, const DecodeCfg& c)
+{
+    if (c.waves != 8 || c.prefetch || !c.early) return 0;
+    const size_t lds = decode_lds_bytes(L, c, true);
+#define MNNQ_HELD(K, U) \
+    if (c.ks == K && c.unroll == U) return L.minf ? fused_workgroups<K, U, true>(lds) : fused_workgroups<K, U, false>(lds);
+    MNNQ_HELD(1, 8) MNNQ_HELD(2, 8) MNNQ_HELD(4, 8) MNNQ_HELD(4, 7)
+#undef MNNQ_HELD
+    return 0;
+}
+
 }  // namespace
 
 // The fused call quantizes the row in every workgroup of one kernel, or once in a kernel of its own (2.3 us and the gap to
-// the next one).  What every workgroup pays grows with the row and with their number; the exact configurations of int4
-// weights and the byte form, whose lanes wait for the memory anyway, hide most of it under the weight stream.  Measured,
-// one kernel / two over 25 000 drawn calls:
-//   sixteen waves per row tile (rows beyond 8192 columns; bytes beyond 7168): at most one workgroup per CU 0.77 - 1.08,
-//     0.92 on average; more of them - a second round, with a second quantization behind the first - 1.05 - 1.28;
+// the next one).  What every workgroup pays grows with the row and with their number; while one workgroup of a CU quantizes, the
+// others stream weights, so that with three of them on a CU it costs nothing, and with two it does.  Measured, one kernel / two
+// over 25 000 drawn calls:
+//   sixteen waves per row tile (rows beyond 8192 columns; bytes beyond 7168): at most one workgroup per CU 0.77 - 1.02
+//     (up to 20480 columns 0.83 - 1.02, from 28672 to 126976 0.76 - 0.93), but float minima of 16512 - 20480 columns and 2816 - 4096
+//     rows 0.99 - 1.11: their kernel of twelve chunks a wave spills seven registers; more workgroups - a second round, with a
+//     second quantization behind the first - 1.02 - 1.28 up to 49152 columns;
 //   int8 bytes: up to four waves per tile 0.96 - 0.98 at 64 MiB as at 600 (152064 x 3584 90.0 -> 87.4 us), eight 0.99 at
 //     80 - 96 MiB, 1.03 - 1.06 beyond;
 //   int4, eight waves per tile: 1.02 at 32 - 40 MiB, 1.06 at 40 - 48, 1.08 at 48 - 56, 1.18 at 80 - 96, 1.23 - 1.34 beyond; up to
 //     four: 0.99 at 32 - 40 MiB, 1.02 at 40 - 48, 1.04 at 48 - 56, 1.07 at 56 - 64, 1.09 at 64 - 80, 1.17 beyond 96 (between other
-//     kernels the second launch costs 0.3 us more than in a loop of one call: the lines lie where no shape loses); with exact
-//     configurations 0.94 at 64 - 80 MiB, 1.01 - 1.07 beyond 96, but 0.93 - 0.97 at every size with seven chunks a wave and integer
-//     zero points (124192 x 3584 41.0 -> 39.6 us).
+//     kernels the second launch costs 0.3 us more than in a loop of one call: the lines lie where no shape loses);
+//   int4, every wave's registers exactly filled: 0.94 at 64 - 80 MiB, 0.97 - 1.11 beyond 96 with two workgroups per CU (eight chunks a
+//     wave, 96 registers; float minima, 88 - 96), 0.91 - 0.97 at every size with three (seven chunks and zero points, 76: 124192 x
+//     3584 41.0 -> 39.6 us; the same kernel held to two workgroups by its LDS takes 0.99 - 1.08).
 // Nibble planes, whose rows are twice as long in the buffer as in the quantizer, keep a line of 96 MiB for all.
 bool decode_fused_splits(const Layout& L)
 {
@@ -721,7 +751,7 @@ bool decode_fused_splits(const Layout& L)
     if (L.K != L.Kx) return L.total() > kHiddenLine;
     if (c.ks == 16) return L.T > num_cus();
     if (L.native8) return c.ks == 8 && L.total() > kHiddenLine;
-    if (c.ks < 8 && c.early) return (L.minf || c.unroll != 7) && L.total() > kHiddenLine;
+    if (c.ks < 8 && c.early) return L.total() > kHiddenLine && fused_workgroups_per_cu(L, c) < 3;
     return L.total() > (c.ks == 8 ? kLine8 : kLine);
 }
 

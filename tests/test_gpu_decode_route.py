@@ -8,12 +8,14 @@ from paper_2506_10443_amd import synth
 pytestmark = pytest.mark.gpu
 W8N = B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT
 
-# sixteen waves per row tile: one round of workgroups and one more tile (256 CUs); the 64 MiB line of int4 weights (48 for eight waves); exact
-# configurations and int8 bytes stay in one kernel beyond it
+# sixteen waves per row tile: one round of workgroups and one more tile (256 CUs), very long rows too; the 64 MiB line of int4 weights
+# (48 for eight waves); int8 bytes stay in one kernel beyond it, and so do waves whose registers are exactly filled: up to 96 MiB, and
+# at every size where a CU holds three workgroups of the kernel (28 chunks and zero points), not where it holds two
 ROUTES = [(4096, 8320, B.MODE_W4_ZP_INT, False), (4112, 8320, B.MODE_W4_ZP_INT, True), (4096, 7296, W8N, False), (4112, 7296, W8N, True),
           (4112, 14464, W8N, True), (33024, 1856, B.MODE_W4_ZP_INT, False), (62000, 1856, B.MODE_W4_ZP_INT, True),
           (62000, 1856, B.MODE_W4_MIN_FLOAT, True), (8192, 8064, B.MODE_W4_ZP_INT, False), (16384, 6080, B.MODE_W4_ZP_INT, True), (21504, 3584, B.MODE_W4_MIN_FLOAT, False), (52000, 3584, B.MODE_W4_ZP_INT, False),
-          (38000, 3072, W8N, False)]
+          (38000, 3072, W8N, False), (52000, 3520, B.MODE_W4_ZP_INT, False), (52000, 3584, B.MODE_W4_MIN_FLOAT, True),
+          (48000, 4096, B.MODE_W4_ZP_INT, True), (40000, 4096, B.MODE_W4_ZP_INT, False), (1024, 65536, B.MODE_W4_MIN_FLOAT, False)]
 
 
 @pytest.mark.parametrize("N,K,mode,two", ROUTES)
@@ -26,7 +28,15 @@ def test_fused_decode_route(N, K, mode, two):
     want = B.mnnq_linear_decode(packed, N, K, xq[0].contiguous(), sx, mode=mode)
     ws = torch.zeros(B.mnnq_workspace_size(1, N, K, 64, mode), dtype=torch.uint8, device="cuda")
     out = B.mnnq_linear_decode_fused(packed, N, K, x[0].contiguous(), workspace=ws, mode=mode)
-    # the same codes and group products; the sums over K may be taken in another order (fp32, bounded as everywhere)
-    assert (out - want).abs().max() <= 1e-5 * want.abs().max()
     # the codes are in the workspace if, and only if, the quantizer ran on its own
     assert torch.equal(ws[:K].view(torch.int8), xq[0] if two else torch.zeros_like(xq[0]))
+    # the same codes, the same waves per row tile and the same order of the sums: bits, on the route that was taken and on the other
+    assert torch.equal(out, want)
+    B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", 100000 if two else 0)
+    try:
+        ws.zero_()
+        other = B.mnnq_linear_decode_fused(packed, N, K, x[0].contiguous(), workspace=ws, mode=mode)
+        assert torch.equal(ws[:K].view(torch.int8), torch.zeros_like(xq[0]) if two else xq[0])
+    finally:
+        B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", None)
+    assert torch.equal(other, want)

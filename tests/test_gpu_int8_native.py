@@ -180,5 +180,12 @@ def test_full_size_lm_head_decode():
     y = host(B.mnnq_linear_decode(packed, N, K, dev(xq_o[0]), dev(sx_o), mode=W8N))
     assert np.abs(y - y_o[0]).max() <= TOL * np.abs(y_o).max()
     ws = torch.empty(B.mnnq_workspace_size(1, N, K, 64, W8N), dtype=torch.uint8, device="cuda:0")
-    yf = host(B.mnnq_linear_decode_fused(packed, N, K, dev(x[0]), workspace=ws, mode=W8N))
-    assert np.array_equal(yf, y)      # beyond 96 MiB the fused call runs the quantizer as a kernel of its own
+    for mib in (None, "0", "100000"):      # the route it takes, the quantizer as a kernel of its own, and in every workgroup
+        B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", mib)
+        try:
+            ws.zero_()
+            yf = host(B.mnnq_linear_decode_fused(packed, N, K, dev(x[0]), workspace=ws, mode=W8N))
+        finally:
+            B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", None)
+        assert np.array_equal(yf, y)
+        assert np.array_equal(host(ws[:K].view(torch.int8)), xq_o[0] if mib == "0" else np.zeros(K, np.int8))
