@@ -8,12 +8,14 @@ from paper_2506_10443_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 # one group; an odd number of groups (a padding group, whose activations would be the next token's); fewer chunks than K parts;
-# one row tile; columns and tokens one past a tile, one short of it; more tiles than a round
-SHAPES = [(128, 256, 64), (129, 16, 192), (127, 272, 320), (257, 208, 448), (300, 784, 1088), (17, 528, 2176), (1030, 1040, 384)]
+# one row tile; columns and tokens one past a tile, one short of it; an odd number of rows of tiles; more than two workgroups per
+# CU of 256 CUs, ragged in both directions
+SHAPES = [(128, 256, 64), (129, 16, 192), (127, 272, 320), (257, 208, 448), (300, 784, 1088), (17, 528, 2176), (1030, 1040, 384),
+          (1030, 14864, 384)]
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
-@pytest.mark.parametrize("tile", ["b1", "b1k", "c1", "c1k", "d1"])
+@pytest.mark.parametrize("tile", ["b1", "b1k", "c1", "c1k", "d1", None])      # (None: the kernel that the shape takes)
 def test_wide_tiles_match_exact(tile, M, N, K):
     print("fp16 wide", tile, M, N, K, flush=True)
     gen = torch.Generator(device="cuda:0").manual_seed(M + N + K)
@@ -27,7 +29,7 @@ def test_wide_tiles_match_exact(tile, M, N, K):
     x_inf = x.clone()
     x_inf[M // 2] = float("inf")          # infinities stay in their own token's row
     B.mnnq_debug_set("MNNQ_PREFILL_TILE", tile)
-    B.mnnq_debug_set("MNNQ_NO_SKINNY", 1)
+    B.mnnq_debug_set("MNNQ_NO_SKINNY", None if tile is None else 1)
     try:
         y = B.mnnq_linear_prefill_f16(packed, N, K, x, bias=bias, out=out[:M])
         half = B.mnnq_linear_prefill_f16_o16(packed, N, K, x, bias=bias)

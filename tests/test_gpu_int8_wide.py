@@ -1,6 +1,6 @@
-"""The int8 GEMM on tiles of 128 tokens x 256 and 192 columns: every tile and K split (a float minimum
-of 4-bit codes: the 128 x 128 tile), at the edges of tokens,
-columns and chunks, against the product in float64 of the stored codes."""
+"""The int8 GEMM on tiles of 128 tokens x 256 and 192 columns, 256 x 128 and 128 x 128 of eight waves: every tile and K split that
+a weight form has, at the edges of tokens, columns and chunks and with a second round of workgroups, against the product in
+float64 of the stored codes."""
 import pytest
 import torch
 
@@ -9,9 +9,11 @@ from paper_2506_10443_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 FORMS = {"w4": B.MODE_W4_ZP_INT, "w4min": B.MODE_W4_MIN_FLOAT, "w8": B.MODE_W8_MIN_FLOAT | B.NATIVE_8BIT}
+TILES = {"w4": ("x1", "x1k", "c1", "c1k", "w1", "v1"), "w4min": ("s1", "s1k", "v1k"), "w8": ("x1", "x1k", "c1", "c1k", "s1", "v1")}
 # one chunk, and an odd number of chunks (the minima go two chunks at a time); one row tile; one past a tile and one short of it;
-# K split into unequal parts; more tiles than a round
-SHAPES = [(128, 256, 128), (17, 16, 384), (129, 272, 640), (255, 208, 1152), (300, 784, 1152), (1030, 1040, 384)]
+# K split into unequal parts; many tiles of an odd number of rows; and more than two workgroups per CU of 256 CUs - 531 tiles of
+# 128 x 256, 295 of 256 x 128, two on a CU at a time - ragged in both directions
+SHAPES = [(128, 256, 128), (17, 16, 384), (129, 272, 640), (255, 208, 1152), (300, 784, 1152), (1030, 1040, 384), (1030, 14864, 384)]
 HALF_CHUNK = [(130, 272, 192), (77, 16, 320), (128, 256, 64)]      # an odd number of groups (4-bit codes only)
 
 
@@ -33,10 +35,10 @@ def test_wide_tiles_match_exact(form, M, N, K):
     q, s, z = q.view(N, K // 64, 64), s[:, :, None], z[:, :, None]
     w = ((q - z) * s if form == "w4" else q * s + z).view(N, K)
     exact = (xq.double() @ w.t()) * sx.double()[:, None] + bias.double()
-    for tile in ("x1", "x1k", "c1", "c1k"):
+    for tile in TILES[form] + (None,):      # (None: the kernel that the shape takes)
         out = torch.full((M + 1, N), float("nan"), device="cuda:0")
         B.mnnq_debug_set("MNNQ_PREFILL_TILE", tile)
-        B.mnnq_debug_set("MNNQ_NO_SKINNY", 1)
+        B.mnnq_debug_set("MNNQ_NO_SKINNY", None if tile is None else 1)
         try:
             y = B.mnnq_linear_prefill(packed, N, K, xq, sx, bias=bias, out=out[:M], mode=mode)
             half = B.mnnq_linear_prefill_o16(packed, N, K, xq, sx, bias=bias, mode=mode)
