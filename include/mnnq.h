@@ -62,8 +62,7 @@ typedef enum {
      * (row, group): fp32 step and fp32 min (3 bytes more than a zero point).
      *   y[m,n] = sx[m] * sum_g (step[n,g] * A[m,n,g] + min[n,g] * xs[m,g]) (+ bias[n]),
      *   A = sum_{k in g} xq[m,k] * q[n,k],  xs[m,g] = sum_{k in g} xq[m,k].
-     * Supported by the pack / unpack / import calls and the W4A8 linear calls;
-     * the fp16-activation calls return MNNQ_ERR_UNSUPPORTED for it. */
+     * Supported by the same calls as MNNQ_W4_ZP_INT. */
     MNNQ_W4_MIN_FLOAT = 1,
     /* int8 weights (Section 4.2: parameters are quantized to int4 or int8, the LM
      * head preferably to int8): Eq. 1 with clip range 0..255 and a float minimum,

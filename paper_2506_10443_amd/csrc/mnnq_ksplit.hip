@@ -318,7 +318,7 @@ int launch(const uint8_t* packed, const Layout& L, int64_t M, const void* xq, co
 // 1 % (geometric mean) of the best of tm = 1 .. 4 and the tiled GEMM, and 12 % faster than tm = 4 alone up to three (fp16
 // activations: two) tiles per CU: 333 tokens of 4096 x 14336 65 -> 58 us (int8 bytes), 130 tokens of 1536 x 8960
 // 27 -> 19 us, 1500 tokens of 4096 x 14336 253 -> 206 us.
-// (With a float minimum and fp16 activations tm = 4 spills ten registers of 256; at most three rows there is no faster: 441
+// (With a float minimum and fp16 activations tm = 4 spills 17 registers of 256; at most three rows there is no faster: 441
 // shapes within 0.3 % in the geometric mean, 0.82 - 0.90 on short rows, 1.03 - 1.06 on long ones.)
 struct Height {
     int tm;
@@ -342,7 +342,8 @@ Height tile_height(const Layout& L, int64_t M, int form)
 // first round weighs more than the next ones, with a CU's second workgroup beside it.
 float tiled_rounds(const Layout& L, int64_t M, int form)
 {
-    // (int8: whole columns per XCD, as the fit saw them; this side is asked up to one tile per CU)
+    // (int8: whole columns per XCD, as the fit saw them and as the tiles were dealt then; this side is asked up to one tile per CU,
+    // and for 65 - 128 tokens of any number of columns)
     const int64_t columns = (L.T + 7) / 8, cus = num_cus();
     const int64_t tiles = (M + 127) / 128 * (is_f16(form) ? columns : (columns + kXcdCount - 1) / kXcdCount * kXcdCount);
     const float n = (float)((tiles + cus - 1) / cus);
