@@ -12,15 +12,13 @@
 // A tile and group costs eight instructions for the scale.  The minima's part, min[n,g] * (sum of the token's codes in g), is a
 // contraction over the groups on v_mfma_f32_16x16x4_f32 (Centered, mnnq_forms.h), with one more matrix instruction per 16 tokens and
 // group for the sums.
-#include "mnnq_forms.h"
+#include "mnnq_wide.h"
 
 namespace mnnq {
 
 namespace {
 
 #define MNNQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-
-typedef int v2i __attribute__((ext_vector_type(2)));
 
 constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer: loads give 0
 
@@ -35,10 +33,9 @@ template <int WAVES, int TM, int TN, int KS>
 struct Tile8 {
     static constexpr int NS = 3;
     static constexpr int part_bytes = NS * kStageBytes;
-    static constexpr int sum_bytes = KS > 1 ? WAVES * TM * TN * 4 * 64 * 4 : 0;      // one part's sums
-    static constexpr int patch_bytes = WAVES * 16 * (16 * TN + 4) * 4;
+    using Out = WideOut<WAVES, TM, TN, KS>;
     static constexpr int most(int a, int b) { return a > b ? a : b; }
-    static constexpr int lds_bytes = most(KS * part_bytes, most(sum_bytes, patch_bytes));
+    static constexpr int lds_bytes = most(KS * part_bytes, most(Out::sum_bytes, Out::patch_bytes));
 };
 
 template <int FORM, int WAVES, int TM, int TN, int KS>
@@ -223,84 +220,16 @@ __global__ __launch_bounds__(64 * WAVES * KS, KS > 1 ? 1 : 2) void prefill8_wide
         }
     }
 
-    if (KS > 1) {
-        // A part > 0 leaves its sums in LDS (one conflict-free float per lane and accumulator), part 0 adds them, in order.
-        float* red = reinterpret_cast<float*>(lds_all) + wave * (TM * TN * 4 * 64) + lane;
-#pragma unroll
-        for (int p = 1; p < KS; ++p) {
-            __syncthreads();                         // the stages are dead, the previous part's sums are read
-            if (part == p) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) red[((i * TN + j) * 4 + r) * 64] = acc[i * TN + j][r];
-            }
-            __syncthreads();
-            if (part == 0) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[i * TN + j][r] += red[((i * TN + j) * 4 + r) * 64];
-            }
-        }
-        __syncthreads();                             // LDS is free for the output
-        if (part != 0) return;
-    } else {
-        __syncthreads();                             // (a load past the end may still be writing to a stage)
-    }
-
-    // y = acc * sx[m] + bias[n].  Rows past M fall outside the buffers (loads give 0, stores are dropped), a NULL bias is an
-    // empty buffer.  The 16 x 64 block of a row of tiles goes through a private LDS patch (rows padded by 4 floats) and
-    // leaves as 128-bit stores of whole row segments; LDS operations of a wave complete in order.
-    const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, M * 4);
-    const __amdgpu_buffer_rsrc_t rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
-    const int out_size = L.out16 ? 2 : 4, row_bytes = (int)L.N * out_size, y_bytes = (int)(uint32_t)(M * L.N * out_size);
-    const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, (uint32_t)y_bytes);
-    float bj[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bj[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, row * 4, (rt0 + j) * 64, 0));
-    constexpr int RS = 16 * TN + 4;
-    float* patch = reinterpret_cast<float*>(lds_all) + wave * (16 * RS);
-    float* wr = patch + (kb * 4) * RS + row;
-    // sixteen rows of 4 TN units of 16 bytes (four values), TN units per lane; units past N are sent out of range
-    int rd[TN], y_voff[TN];
-#pragma unroll
-    for (int p = 0; p < TN; ++p) {
-        const int u = p * 64 + lane, ur = u / (4 * TN), uc = u % (4 * TN);
-        rd[p] = ur * RS + uc * 4;
-        y_voff[p] = rt0 + (uc >> 2) < (int)L.T ? ur * row_bytes + uc * 4 * out_size : y_bytes;
-    }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        float f[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) f[r] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_sx, kb * 16, (m0 + i * 16 + r) * 4, 0));
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) wr[r * RS + j * 16] = fmaf(acc[i * TN + j][r], f[r], bj[j]);
-#pragma unroll
-        for (int p = 0; p < TN; ++p) {
-            const float4 v = *reinterpret_cast<const float4*>(patch + rd[p]);
-            const int at = (m0 + i * 16) * row_bytes + rt0 * 16 * out_size;
-            if (L.out16) {
-                const v2i o = {__builtin_bit_cast(int, h2{(_Float16)v.x, (_Float16)v.y}), __builtin_bit_cast(int, h2{(_Float16)v.z, (_Float16)v.w})};
-                __builtin_amdgcn_raw_buffer_store_b64(o, rs_y, y_voff[p], at, 0);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), rs_y, y_voff[p], at, 0);
-            }
-        }
-    }
+    if (!sum_parts<TM, TN, KS>(lds_all, wave, part, lane, acc)) return;
+    store_wide<TM, TN>(lds_all, wave, lane, L, M, m0, rt0, sx, bias, y, acc);
     if constexpr (!has_zero(FORM)) {
         float probe = 0.0f;      // NaN: a column's sums are not finite
 #pragma unroll
         for (int j = 0; j < TN; ++j) probe = rt0 + j < (int)L.T ? fmaf(acc[j][0], 0.0f, probe) : probe;
         if (__builtin_expect(__ballot(probe != 0.0f) == 0, 1)) return;
         __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0): the stores above are done
+        const __amdgpu_buffer_rsrc_t rs_sx = rsrc(sx, M * 4), rs_bias = rsrc(bias, bias ? L.N * 4 : 0);
+        const __amdgpu_buffer_rsrc_t rs_y = rsrc(y, M * L.N * (L.out16 ? 2 : 4));
 #pragma unroll 1
         for (int t = 0; t < TM * TN; ++t) {          // (rows past M: past the ends of the buffers)
             const int rt = rt0 + t % TN, first = m0 + (t / TN) * 16;
