@@ -296,7 +296,9 @@ int num_cus();
 // so that a column of weights is fetched into one L2 (two where a run ends inside it) and the rules that count tiles per
 // CU hold.  Whole columns per XCD - 36 columns are five for four of them, four for the others - left a CU of the fuller
 // XCDs with a second tile where there was one per CU: fp16 activations, 1792 tokens of 4608 x 3584, 252 tiles, 119 us; fp6,
-// 1328 tokens of 2256 x 5504, 198 tiles, 76 us.
+// 1328 tokens of 2256 x 5504, 198 tiles, 63 against 35 us.  Where whole columns cost no round they fetch less (1024 tokens of 37888 x 3584
+// in fp6 268 against 305 MB) but are no faster: 187.2 / 186.4 us there, 2048 x 28672 x 4096 304.1 / 303.0, 1.006 : 1 over 85 fp6 shapes
+// and 1.001 : 1 over 107 int8 ones, so that there is one way.
 constexpr int kXcdCount = 8;
 inline int64_t xcd_tile_grid(int64_t MT, int64_t NT) { return (MT * NT + kXcdCount - 1) / kXcdCount * kXcdCount; }
 __device__ __forceinline__ bool xcd_tile(int MT, int NT, int& tile_m, int& tile_n)
