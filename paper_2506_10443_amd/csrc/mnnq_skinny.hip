@@ -557,8 +557,9 @@ int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_
 // 19264 x 1664 16.9 / 20.3; float minimum 54 of 10480 x 1088 12.7 / 15.9, 24 of 36224 x 3840 32.0 / 37.7, 42 of 31888 x 1152
 // 20.0 / 16.5).  Over 3000 shapes of 17 - 64 tokens that costs 0.3 % (int4) and 0.6 % (float minimum) against the better kernel;
 // the time of 32 tokens and a limit on the cells beyond, fitted to int4, had cost 1.1 %, up to 29 % on float minima of short rows.
-// Where the operands are streamed the K-split kernel wins but for float minima of at most one row tile per CU (1.01 - 1.09
-// : 1, 45 of 189 shapes the other way).  More tokens only on the smallest layers (68 of 1152 x 1024 6.1 / 7.5, 77 of 2800 x 2048 in
+// Where the operands are streamed the K-split kernel wins (few-token : K-split at one row tile per CU, by tokens: int4 17
+// 0.93, 18 1.03, 22 1.09; float minima 17 0.90, 18 0.96, 19 0.99, 20 1.01, 24 1.08, 32 1.18; at more tiles 1.7 - 3) but for the first of a second block of
+// tokens, whose 16-row tiles there are nearly empty.  More tokens only on the smallest layers (68 of 1152 x 1024 6.1 / 7.5, 77 of 2800 x 2048 in
 // two slices 14.3 / 7.2 us).
 struct FewCost {
     float fixed, chunk, tile, tile_chunk;
@@ -571,9 +572,10 @@ bool skinny_f16_wanted(const Layout& L, int64_t M)
 {
     if (debug_option(kDbgNoSkinny) || debug_option(kDbgPrefillTile)) return false;   // tests and tuning: the tiled GEMM
     if (M <= 16) return true;
-    if (M > 128 || !few_plan(L, blocks_of(M), form_of(L, true)).resident) return false;
-    if (M > 64) return L.C <= 10 && L.T * L.C <= 600;
     const int64_t cus = num_cus();
+    if (M > 128) return false;
+    if (!few_plan(L, blocks_of(M), form_of(L, true)).resident) return M <= (L.minf ? 19 : 17) && L.T <= cus;
+    if (M > 64) return L.C <= 10 && L.T * L.C <= 600;
     const FewCost& f = kFewF16[L.minf ? 1 : 0][blocks_of(M) - 2];
     const float C = (float)L.C, n = (float)((L.T + cus - 1) / cus);
     return f.fixed + f.chunk * C + n * (f.tile + f.tile_chunk * C) <= 1.1f * ksplit_f16_us(L, M);

@@ -297,5 +297,8 @@ def test_fp16_activations_of_17_to_64_tokens_take_the_faster_kernel():
         assert plan(m, n, k, B.MODE_W4_ZP_INT) == 3
     for m, n, k in ((54, 10480, 1088), (53, 9152, 1664), (24, 36224, 3840), (23, 992, 1280), (36, 1040, 1280), (48, 18608, 1280)):
         assert plan(m, n, k, B.MODE_W4_MIN_FLOAT) in (1, 2)
+    # rows too long for the registers: the first tokens of a second block, whose 16-row tiles are nearly empty
+    for m, n, k, mode in ((17, 3600, 11776, B.MODE_W4_MIN_FLOAT), (18, 3584, 15616, B.MODE_W4_MIN_FLOAT), (18, 2064, 13568, B.MODE_W8_MIN_FLOAT)):
+        assert plan(m, n, k, mode) == 2 and plan(m + 6, n, k, mode) == 3 and plan(m, n + 4096, k, mode) == 3
     for m, n, k in ((42, 31888, 1152), (42, 2416, 2048), (20, 14736, 2688), (49, 1616, 1536), (64, 1760, 8320)):
         assert plan(m, n, k, B.MODE_W4_MIN_FLOAT) == 3
