@@ -80,7 +80,7 @@ size_t planes_ws_bytes(const Layout& L, int64_t M) { return prefill6_possible(L,
 
 bool prefill_fits(int64_t M, int64_t N, int64_t K, int mode = MNNQ_W4_ZP_INT, int act_bytes = 1)
 {
-    const int64_t lim = ((int64_t)1 << 31) - 1;
+    const int64_t lim = kMaxBufferBytes;
     // 32-bit byte offsets: activation rows of a whole tile, the packed weights, the output.
     return M <= ((int64_t)1 << 24) && (M + 256) * K * act_bytes <= lim &&
            (int64_t)make_layout(N, K, mode).total() <= lim && (M + 256) * N * 4 <= lim;
@@ -91,7 +91,7 @@ bool prefill_fits(int64_t M, int64_t N, int64_t K, int mode = MNNQ_W4_ZP_INT, in
 // matrix or a single slab is out of reach of the 32-bit offsets.
 int64_t prefill_slab_rows(int64_t N, int64_t K, int mode, int act_bytes = 1)
 {
-    const int64_t lim = ((int64_t)1 << 31) - 1;
+    const int64_t lim = kMaxBufferBytes;
     if ((int64_t)make_layout(N, K, mode).total() > lim) return 0;
     int64_t rows = lim / (K * act_bytes) < lim / (N * 4) ? lim / (K * act_bytes) : lim / (N * 4);
     rows = (rows - 256) / 256 * 256;

@@ -289,6 +289,9 @@ size_t prefill8_wide_lds_bytes(int columns, int ks);
 int launch_prefill8_wide(int columns, int ks, const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, const float* sx,
                          const float* bias, float* y, hipStream_t st);
 
+// The largest operand of a prefill call (32-bit byte offsets; operands are multiples of 16 bytes).
+constexpr int64_t kMaxBufferBytes = ((int64_t)1 << 31) - 1;
+
 // Compute units of the current device (cached per thread and device).
 int num_cus();
 

@@ -20,7 +20,8 @@ namespace {
 
 #define MNNQ_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
-constexpr int kOutOfRange = 0x7fff0000;   // a byte offset beyond every buffer: loads give 0
+constexpr int kOutOfRange = 0x7ffffff0;   // a byte offset beyond every buffer: loads give 0
+static_assert((int64_t)kOutOfRange >= kMaxBufferBytes / 16 * 16, "beyond every buffer that the calls accept");
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
