@@ -14,7 +14,7 @@ LIB_DIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIB_DIR, "libmnnq.so")
 
 SOURCES = ["mnnq_api.hip", "mnnq_pack.hip", "mnnq_quant_act.hip", "mnnq_decode.hip",
-           "mnnq_prefill.hip", "mnnq_prefill6.hip", "mnnq_ksplit6.hip", "mnnq_ksplit.hip", "mnnq_prefill_f16.hip", "mnnq_prefill_f16w.hip", "mnnq_prefill8w.hip", "mnnq_f16.hip", "mnnq_skinny.hip"]
+           "mnnq_prefill.hip", "mnnq_prefill6.hip", "mnnq_prefill6w.hip", "mnnq_ksplit6.hip", "mnnq_ksplit.hip", "mnnq_prefill_f16.hip", "mnnq_prefill_f16w.hip", "mnnq_prefill8w.hip", "mnnq_f16.hip", "mnnq_skinny.hip"]
 # measurement helpers of bench.py: a library of their own, not part of the product's C-ABI
 BENCH_SOURCES = ["bench_kernels.hip"]
 BENCH_LIB = os.path.join(LIB_DIR, "libmnnq_bench.so")
@@ -24,7 +24,7 @@ NATIVE = os.path.join(HERE, "_native.so")
 # The quantizers are fixed sequences of IEEE binary32 operations: no contraction.
 STRICT_FP = {"mnnq_pack.hip", "mnnq_quant_act.hip", "mnnq_decode.hip"}
 # MFMA results stay in architectural VGPRs so that the VALU epilogue reads them directly.
-MFMA_VGPR = {"mnnq_prefill.hip", "mnnq_prefill6.hip", "mnnq_ksplit6.hip", "mnnq_ksplit.hip", "mnnq_prefill_f16.hip", "mnnq_prefill_f16w.hip", "mnnq_prefill8w.hip", "mnnq_skinny.hip", "bench_kernels.hip"}
+MFMA_VGPR = {"mnnq_prefill.hip", "mnnq_prefill6.hip", "mnnq_prefill6w.hip", "mnnq_ksplit6.hip", "mnnq_ksplit.hip", "mnnq_prefill_f16.hip", "mnnq_prefill_f16w.hip", "mnnq_prefill8w.hip", "mnnq_skinny.hip", "bench_kernels.hip"}
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
           "-fhip-fp32-correctly-rounded-divide-sqrt",

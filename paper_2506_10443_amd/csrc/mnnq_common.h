@@ -254,6 +254,10 @@ int prefill6_row_tiles(int64_t M);
 size_t ksplit6_lds_bytes(int form);
 int launch_ksplit6(int form, const uint8_t* packed, const Layout& L, int64_t M, const void* planes, const float* sx,
                    const float* bias, float* y, hipStream_t st);
+// The same product on tiles of 64 tokens x 384 columns whose waves share the tokens (mnnq_prefill6w.hip); ks: K parts (1, 2).
+size_t prefill6_wide_lds_bytes(int ks);
+int launch_prefill6_wide(int ks, const uint8_t* packed, const Layout& L, int64_t M, const void* planes, const float* sx,
+                         const float* bias, float* y, hipStream_t st);
 // A few tokens sharing one pass over the weights; token_blocks: xq as launch_quant_token_blocks writes it.
 bool skinny_wanted(const Layout& L, int64_t M);
 int launch_skinny(const uint8_t* packed, const Layout& L, int64_t M, const int8_t* xq, bool token_blocks, const float* sx,

@@ -567,7 +567,7 @@ int tmp_tiles(int64_t M) { return (int)(((M + 31) / 32 + kPlaneTilePad - 1) / kP
 
 // Tile plans (all waves own 64 rows): 0 = 128 x 128 tiles of four waves (two workgroups per CU),
 // 1 = 128 x 128 with the K range in two parts (eight waves), 2 = 128 x 256 of four waves (64 x 128
-// outputs per wave, two workgroups per CU), 3 = 128 x 256 with two K parts, 4 = 256 x 256 of eight waves,
+// outputs per wave, two workgroups per CU), 3, 4 = 64 x 384 with two and with one K part (mnnq_prefill6w.hip),
 // 5 = 128 x 320 of four waves (64 x 160 outputs per wave, the column-major loop, two workgroups per CU);
 // the K-split kernel (mnnq_ksplit6.hip): 6 = 64 x 64 tiles of eight waves, 7 = 64 x 64 of four waves (two workgroups
 // per CU), 8 = 64 x 32 of eight waves.
@@ -594,6 +594,13 @@ int choose_tiled6(const Layout& L, int64_t M)
                             : t < 2 * cus ? full : half + (full - half) * (double)(rest - cus) / (double)cus;
         return (double)(t / (2 * cus)) * full + last;
     };
+    // More than one 128 x 128 tile per CU, but one 64 x 384 tile: a CU has three quarters of two such tiles to contract rather than both.
+    // On 73 shapes of 119 - 2048 tokens, K 1088 - 16320, weights from HBM, 0.91 of the time of 128 x 128 tiles in the mean, three of
+    // them slower by up to 3 % (259 - 272 tiles of 128 x 128, few groups); us, 128 x 128 / 64 x 384 with one / with two K parts: 1024
+    // tokens of 4608 x 3584 38.5 / 35.5 / 35.3, of 6144 x 1152 19.4 / 17.6 / 19.4; 256 of 17264 x 2944 36.1 / 30.6 / 31.4; 2048 of
+    // 3024 x 6848 76.7 / 65.2 / 64.3; 1990 of 2672 x 12352 117.0 / 103.1 / 98.7.  Two K parts (eight waves on the CU rather than four) are
+    // 1.05 of one part below 2500 columns of K, even around 4096, 0.96 above 4500.
+    if (tiles6(L, M, 64, 384) <= cus) return L.Gx >= 64 ? 3 : 4;
     const double c0 = cost(128, 27, 42), c2 = cost(256, 49, 68), c5 = cost(320, 54, 88);
     if (c5 < c2 && c5 < 0.97 * c0) return 5;
     return c2 < 0.97 * c0 ? 2 : 0;
@@ -633,7 +640,7 @@ int choose_stages6(int plan, const Layout& L, int64_t M)
         const int v = e[0] - '0';
         if (v >= 2 && v <= 4) ns = v;
     }
-    if (plan >= 4 || (plan >= 2 && ns > 3)) ns = 2;   // what fits the LDS: 4 for the 128 x 128 tiles, 3 for 128 x 256
+    if (plan >= 3 || (plan == 2 && ns > 3)) ns = 2;   // what fits the LDS: 4 for the 128 x 128 tiles, 3 for 128 x 256
     return ns;
 }
 
@@ -648,8 +655,8 @@ Plan6Info plan6_info(int plan, const Layout& L, int64_t M)
     switch (plan) {
         case 1: return {128, 128, 2, 8, ns == 4 ? lds_bytes6<128, 128, 2, 4>() : ns == 3 ? lds_bytes6<128, 128, 2, 3>() : lds_bytes6<128, 128, 2>()};
         case 2: return {128, 256, 1, 4, ns == 3 ? lds_bytes6<128, 256, 1, 3>() : lds_bytes6<128, 256, 1>()};
-        case 3: return {128, 256, 2, 8, ns == 3 ? lds_bytes6<128, 256, 2, 3>() : lds_bytes6<128, 256, 2>()};
-        case 4: return {256, 256, 1, 8, lds_bytes6<256, 256, 1>()};
+        case 3: return {64, 384, 2, 8, prefill6_wide_lds_bytes(2)};
+        case 4: return {64, 384, 1, 4, prefill6_wide_lds_bytes(1)};
         case 5: return {128, 320, 1, 4, lds_bytes6<128, 320, 1>()};
         case 6: return {64, 64, 8, 8, ksplit6_lds_bytes(0)};
         case 7: return {64, 64, 4, 4, ksplit6_lds_bytes(1)};
@@ -722,14 +729,13 @@ int launch_prefill6(const uint8_t* packed, const Layout& L, int64_t M, const voi
         if (plan == 0) return launch6<128, 128, 2, 2, 1, false, 3>(MNNQ_ARGS6);
         if (plan == 1) return launch6<128, 128, 2, 2, 2, false, 3>(MNNQ_ARGS6);
         if (plan == 2) return launch6<128, 256, 2, 2, 1, false, 3>(MNNQ_ARGS6);
-        if (plan == 3) return launch6<128, 256, 2, 2, 2, false, 3>(MNNQ_ARGS6);
     }
 #undef MNNQ_ARGS6
     switch (plan) {
         case 1: return launch6<128, 128, 2, 2, 2, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
         case 2: return launch6<128, 256, 2, 2, 1, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
-        case 3: return launch6<128, 256, 2, 2, 2, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
-        case 4: return launch6<256, 256, 4, 2, 1, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
+        case 3: return launch_prefill6_wide(2, packed, L, M, planes, sx, bias, y, st);
+        case 4: return launch_prefill6_wide(1, packed, L, M, planes, sx, bias, y, st);
         case 5: return launch6<128, 320, 2, 2, 1, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
         default: return launch6<128, 128, 2, 2, 1, false>(packed, L, M, a6, TMp, sx, bias, y, nullptr, st);
     }

@@ -80,6 +80,34 @@ def test_prefill6_every_plan(plan, M, N, K):
     assert np.array_equal(y, y2)
 
 
+@pytest.mark.parametrize("plan", [3, 4])
+@pytest.mark.parametrize("M,N,K", [(33, 368, 128), (64, 384, 192), (65, 400, 256), (97, 768, 320), (128, 784, 64), (193, 80, 1088)])
+def test_prefill6_wide_tile_edges(plan, M, N, K):
+    """Tiles of 64 x 384 whose waves share the tokens, in two and in one K part: around a tile's rows and columns, odd numbers of
+    groups (half a chunk) and of chunks (uneven parts), fewer chunks than the ring holds; fp32 and binary16 results."""
+    note("prefill6 wide plan", plan, "M", M, "N", N, "K", K)
+    W, x, q, s, z, xq, sx = make(N, K, M, 4270 + plan, special=True)
+    _, y_o = oracle.linear_w4a8(xq, sx, q, s, z)
+    packed = B.mnnq_pack_weights(dev(W), mode=MODE)
+    ws = torch.empty(B.mnnq_workspace_size(M, N, K, 64, MODE), dtype=torch.uint8, device="cuda:0")
+    B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", plan)
+    guard = torch.full((M + 1, N), 7.5, dtype=torch.float32, device="cuda:0")
+    y = B.mnnq_linear_prefill(packed, N, K, dev(xq), dev(sx), mode=MODE, workspace=ws, out=guard[:M])
+    assert np.abs(y.cpu().numpy() - y_o).max() <= TOL_A8 * np.abs(y_o).max()
+    assert bool((guard[M] == 7.5).all())                       # nothing behind the last row
+    yf = B.mnnq_linear_prefill_fused(packed, N, K, dev(x), mode=MODE, workspace=ws)
+    y16 = B.mnnq_linear_prefill_fused_o16(packed, N, K, dev(x), mode=MODE, workspace=ws)
+    assert torch.equal(y16, yf.half())
+
+
+def test_one_wide_tile_per_cu_takes_the_wide_tiles():
+    """More 128 x 128 tiles than CUs (256), at most as many 64 x 384 ones; two K parts from 64 groups on."""
+    tile = lambda M, N, K: B.mnnq_plan_debug(0, M, N, K, mode=MODE)[:3]
+    assert tile(1024, 4608, 3584) == [64, 384, 1] and tile(1024, 4608, 4096) == [64, 384, 2]
+    assert tile(1024, 6144, 1152) == [64, 384, 1]              # 256 wide tiles
+    assert tile(1024, 6160, 1152)[0] == 128                    # 272 of them
+
+
 @pytest.mark.parametrize("M,N,K", [(200, 400 - 400 % 16, 1536), (129, 592, 448), (40, 48, 64)])
 def test_prefill6_deeper_rings(M, N, K):
     """Three and four stages in the LDS rings (MNNQ_PREFILL6_STAGES) for the plans that have them."""
