@@ -98,10 +98,33 @@ struct Pending {
 template <int TM, int FORM>
 using ActRegs = v4i[2][TM][is_f16(FORM) ? 2 : 1];
 
-// One chunk: both groups of 16 weight rows against TM blocks of 16 tokens.
+// Resident int4 chunks: the codes enter the matrix instruction as q - z + 64 (positive bytes, one addition each; q - z takes an
+// addition and an exclusive or), and its accumulator starts at the pattern of 1.5 * 2^23 less 64 times the sum of the token's group,
+// which leaves the same integers.  The starts come from one matrix instruction per group when the activations arrive and stay in
+// registers for all row tiles.
+constexpr int kShift = 64;
+template <int TM>
+using Starts = v4i[2][TM];
+
+__device__ __forceinline__ v4i shifted_start(v4i a)
+{
+    const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
+    constexpr int minus = (int)(0x01010101u * (256 - kShift));
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, v4i{minus, minus, minus, minus}, magic, 0, 0, 0);
+}
+
+__device__ __forceinline__ v4i unpack_shifted(const Weights<kZp>& r, int h, uint32_t zsel)
+{
+    const uint32_t w0 = (uint32_t)(h ? r.w[0].z : r.w[0].x), w1 = (uint32_t)(h ? r.w[0].w : r.w[0].y);
+    const uint32_t c4 = 0x01010101u * kShift - __builtin_amdgcn_perm(0u, (uint32_t)r.z, h ? zsel + 0x01010101u : zsel);
+    return v4i{(int)((w0 & 0x0f0f0f0fu) + c4), (int)(((w0 >> 4) & 0x0f0f0f0fu) + c4), (int)((w1 & 0x0f0f0f0fu) + c4),
+               (int)(((w1 >> 4) & 0x0f0f0f0fu) + c4)};
+}
+
+// One chunk: both groups of 16 weight rows against TM blocks of 16 tokens.  start: of shifted codes, or NULL.
 template <int TM, int FORM>
 __device__ __forceinline__ void contract(const Weights<FORM>& r, const ActRegs<TM, FORM>& a, uint32_t zsel,
-                                         Pending<TM, FORM>& p, float (&acc)[TM][4])
+                                         Pending<TM, FORM>& p, float (&acc)[TM][4], const Starts<TM>* start = nullptr)
 {
     const v4i magic = {kMagicBits, kMagicBits, kMagicBits, kMagicBits};
     const v4i zero = {0, 0, 0, 0};
@@ -110,7 +133,9 @@ __device__ __forceinline__ void contract(const Weights<FORM>& r, const ActRegs<T
     const v4i onesh = {0x3c003c00, 0x3c003c00, 0x3c003c00, 0x3c003c00};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const Operand<FORM> o = unpack<FORM>(r, h, zsel);
+        Operand<FORM> o;
+        if constexpr (FORM == kZp) o.q[0] = start ? unpack_shifted(r, h, zsel) : unpack<FORM>(r, h, zsel).q[0];
+        else o = unpack<FORM>(r, h, zsel);
         const v4i b = o.q[0], b1 = o.q[is_f16(FORM) ? 1 : 0];
         Pending<TM, FORM> n;
 #pragma unroll
@@ -121,7 +146,7 @@ __device__ __forceinline__ void contract(const Weights<FORM>& r, const ActRegs<T
                 n.d[t] = __builtin_bit_cast(v4i, mfma_f16(a[h][t][X], b1, mfma_f16(a[h][t][0], b, zerof)));
                 if (!has_zero(FORM)) n.xs[tx] = __builtin_bit_cast(v4i, mfma_f16(a[h][t][X], onesh, mfma_f16(a[h][t][0], onesh, zerof)));
             } else {
-                n.d[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t][0], b, FORM == kBytes ? zero : magic, 0, 0, 0);
+                n.d[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t][0], b, FORM == kBytes ? zero : start ? (*start)[h][t] : magic, 0, 0, 0);
                 if (!has_zero(FORM)) n.xs[tx] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[h][t][0], ones, zero, 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -233,6 +258,15 @@ struct Output {
     }
 };
 
+// Chunks of a wave with shifted codes: as many as the registers hold starts of (8 TM each) without spilling.  A row tile is 179 vector
+// instructions of a wave instead of 214 (one block of tokens, four chunks), 243 instead of 275 (two), 325 instead of 341 (three); 24 tokens of
+// 28672 x 4096 19.5 -> 19.2 us, 40 of 37888 x 3584 26.2 -> 25.8, 9 of 37888 x 3584 19.2 -> 18.9.
+constexpr int shifted_chunks(int tm, int nch, int form)
+{
+    if (form != kZp || tm * nch == 16 || (tm == 3 && nch == 2)) return 0;
+    return tm == 3 ? 2 : nch;
+}
+
 template <int TM, int NCH, int FORM, int MAXW, bool BLOCKS>
 __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* __restrict__ packed, Layout L, int M,
                                                                 const void* __restrict__ xq,
@@ -272,6 +306,14 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
     float b = bias_of(tile);
 #pragma unroll
     for (int u = 0; u < NCH; ++u) acts.arrange(a[u]);
+    constexpr int SH = shifted_chunks(TM, NCH, FORM);
+    Starts<TM> start[SH > 0 ? SH : 1];
+#pragma unroll
+    for (int u = 0; u < SH; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int t = 0; t < TM; ++t) start[u][h][t] = shifted_start(a[u][h][t][0]);
 
     int buf = 0, turn = 0;
     do {   // (the grid has no more workgroups than there are row tiles)
@@ -285,7 +327,11 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
         Pending<TM, FORM> pend;
 #pragma unroll
         for (int u = 0; u < NCH; ++u) {
-            contract<TM, FORM>(cur[u], a[u], zsel, pend, acc);     // (a chunk that is not the wave's own is zero)
+            // A chunk that is not the wave's own is passed over, and the loads go on: without the branches the compiler moves the
+            // chunks' scales together, at the top of the loop, and waits there for all but the last two loads (24 tokens of 28672 x 4096
+            // 20.8 -> 19.2 us, 9 of 37888 x 3584 with fp16 activations 21.0 -> 19.4).  Four blocks of the other forms spill with
+            // them; there the chunk is zero.
+            if (u == 0 || (TM * NCH == 16 && FORM != kZp) || u < own) contract<TM, FORM>(cur[u], a[u], zsel, pend, acc, u < SH ? &start[u < SH ? u : 0] : nullptr);
             cur[u] = next.load(u < own ? c0 + u : C, lane, row);
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -56,6 +56,27 @@ def test_few_tokens_match_oracle(form, M, N, K):
     assert torch.equal(y16, yf.half())
 
 
+@pytest.mark.parametrize("M", [2, 17, 33, 49])
+@pytest.mark.parametrize("N,K", [(48, 640), (16 * 600, 320), (64, 1152), (32, 3136)])
+def test_few_tokens_extreme_codes_and_uneven_waves(M, N, K):
+    """Waves with fewer chunks than they have room for (5, 3, 9 and 25 chunks, odd rows among them), tokens whose codes are all -128
+    or all 127, zero points 0 and 15: the starts of the accumulators are as large as they get."""
+    print("few tokens, extreme codes", M, N, K, flush=True)
+    rng = np.random.default_rng(M + N + K)
+    W = synth.weights(N, K, 41)
+    W[0] = np.abs(W[0]) + 0.01                      # minimum above zero: zero point 0
+    W[1] = -np.abs(W[1]) - 0.01                     # maximum below zero: zero point 15
+    q, s, z = oracle.quant_weights(W)
+    xq = rng.integers(-128, 128, (M, K)).astype(np.int8)
+    xq[0], xq[M - 1] = -128, 127
+    sx = rng.uniform(0.001, 0.1, M).astype(np.float32)
+    y_o = oracle.linear_w4a8(xq, sx, q, s, z, want_acc=False)[1]
+    packed = B.mnnq_pack_weights(dev(W), mode=B.MODE_W4_ZP_INT)
+    y = B.mnnq_linear_prefill(packed, N, K, dev(xq), dev(sx), mode=B.MODE_W4_ZP_INT).cpu().numpy()
+    # fp32 sums of up to K / 64 group terms: the layer's tolerance, token by token
+    assert (np.abs(y - y_o).max(axis=1) <= 1e-5 * np.abs(y_o).max(axis=1)).all()
+
+
 @pytest.mark.parametrize("M,N,K", [(33, 32, 64), (65, 48, 192), (100, 64, 4160), (130, 272, 3584), (257, 32, 18944)])
 def test_quantizer_writes_the_planes_of_the_two_steps(M, N, K):
     """The fused call on a buffer with the matrix-core plane: bit for bit the result of quantizer, planes and GEMM as
