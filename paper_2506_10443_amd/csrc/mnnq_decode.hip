@@ -59,6 +59,35 @@ __device__ __forceinline__ ChunkRegs load_chunk(const u32x4* wp, const float2* s
     return r;
 }
 
+// The chunks of one wave behind buffer descriptors that end with its last one: every chunk of the registers is requested without a
+// branch, those past the end arrive as zeros without traffic, and the waits are counts.
+template <bool MINF>
+struct WaveChunks {
+    __amdgpu_buffer_rsrc_t w, s, z;
+    static constexpr int ZB = MINF ? 128 : 32;
+    __device__ __forceinline__ WaveChunks(const uint8_t* __restrict__ packed, const Layout& L, int64_t first, int n)
+        : w(rsrc(packed + first * 1024, n * 1024)), s(rsrc(packed + L.scales_off() + first * 128, n * 128)),
+          z(rsrc(packed + L.zeros_off() + first * ZB, n * ZB))
+    {
+    }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const uint8_t* p, int bytes)
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p), 0, bytes, 0x00020000);   // raw buffer (gfx9 family)
+    }
+    __device__ __forceinline__ ChunkRegs load(int u, int lane) const
+    {
+        const int row = lane & 15;
+        ChunkRegs r;
+        r.w = __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16 + u * 1024, 0, 2);     // (aux 2: passes once)
+        r.s = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(s, row * 8 + u * 128, 0, 0));
+        r.z = 0;
+        r.mn = make_float2(0.0f, 0.0f);
+        if (MINF) r.mn = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(z, row * 8 + u * 128, 0, 0));
+        else r.z = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(z, row * 2 + u * 32, 0, 0);
+        return r;
+    }
+};
+
 __device__ __forceinline__ int dot16(uint32_t wa, uint32_t wb, const int4& x)
 {
     int d = __builtin_amdgcn_sdot4((int)(wa & 0x0f0f0f0fu), x.x, 0, false);
@@ -81,14 +110,14 @@ __device__ __forceinline__ int dot16(uint32_t wa, uint32_t wb, const int4& x)
 // load, longer ones read the rest from memory.
 constexpr int kRowRegs = 2;
 
-template <int WAVES>
-__device__ __forceinline__ void preload_row(const float* __restrict__ x, const Layout& L, float4 (&xr)[kRowRegs])
+template <int WAVES, int XR>
+__device__ __forceinline__ void preload_row(const float* __restrict__ x, const Layout& L, float4 (&xr)[XR])
 {
     constexpr int THREADS = WAVES * 64;
     const int row_dw = (int)(L.Kx / 4);     // (a row the GEMV can stage has fewer than 2^17 values: 32-bit indices)
     const float4* x4 = reinterpret_cast<const float4*>(x);
 #pragma unroll
-    for (int j = 0; j < kRowRegs; ++j) {
+    for (int j = 0; j < XR; ++j) {
         const int i = (int)threadIdx.x + j * THREADS;
         xr[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (i < row_dw) xr[j] = x4[i];
@@ -150,8 +179,8 @@ struct RowQuantizer {
     }
 };
 
-template <int WAVES>
-__device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x, const float4 (&xr)[kRowRegs],
+template <int WAVES, int XR>
+__device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x, const float4 (&xr)[XR],
                                                      const Layout& L, int* lds_xd, int* lds_xs, float* lds_amax)
 {
     constexpr int THREADS = WAVES * 64;
@@ -163,19 +192,19 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
 
     float amax = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kRowRegs; ++j) amax = max_abs4(amax, xr[j]);   // zeros past the row do not change the maximum
-    for (int i = tid + kRowRegs * THREADS; i < row_dw; i += THREADS) amax = max_abs4(amax, x4[i]);
+    for (int j = 0; j < XR; ++j) amax = max_abs4(amax, xr[j]);   // zeros past the row do not change the maximum
+    for (int i = tid + XR * THREADS; i < row_dw; i += THREADS) amax = max_abs4(amax, x4[i]);
     const RowQuantizer q(workgroup_scale<WAVES>(amax, lds_amax), valid, lds_xd, lds_xs);
     // The row itself: first the elements already in registers, then the rest from memory.  (No
     // conditional between a register value and a load: it would select between two addresses and
     // force the registers into scratch memory.)  The row length is a multiple of 16 dwords, so the
     // four lanes of a block always take the same branch.
 #pragma unroll
-    for (int j = 0; j < kRowRegs; ++j) {
+    for (int j = 0; j < XR; ++j) {
         const int i = tid + j * THREADS;
         if (i < row_dw) q.put(i, xr[j]);
     }
-    for (int i = tid + kRowRegs * THREADS; i < row_dw; i += THREADS) q.put(i, x4[i]);
+    for (int i = tid + XR * THREADS; i < row_dw; i += THREADS) q.put(i, x4[i]);
     // Past the row: its second pass (int8 weights) and the zero padding of the last chunk.
     for (int i = row_dw + tid; i < dwords; i += THREADS) {
         float4 xv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -198,6 +227,13 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
 // only when the whole weight stream has arrived.  The launches of small layers, which are bound by
 // latency, gain 7 - 9 % from the overlap; layers whose waves hold clearly fewer chunks than UNROLL
 // lose (3 - 13 % measured) and keep the conditional form: the host decides (decode_config).
+//
+// Sixteen waves per row tile with the fused quantizer (rows beyond 8192 columns) take the form COUNTED: the weights come through
+// buffer descriptors that end with the wave's last chunk (WaveChunks), so that all loads are unconditional, and the whole row, not
+// its first 8192 values, is requested ahead of them.  The row is quantized while the weights arrive, and each chunk is waited for by count.
+// The conditional form, and the rest of a longer row behind the weights, had waited for the last weight before the row's maximum.  One
+// token, weights from HBM, us: 3584 x 18944 12.45 -> 11.9 (float minima 14.8 -> 13.4), 4096 x 14336 10.7 -> 9.9, 2048 x 12288 9.25 -> 7.7,
+// 4096 x 16384 12.2 -> 11.0, 1536 x 8960 6.75 -> 6.55.  Registers for more chunks than a wave has (eight for five) cost 12 % there.
 template <int WAVES, int KSPLIT, int UNROLL, int MODE, bool PREFETCH, bool MINF, bool EARLY = false>
 __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __restrict__ packed, Layout L,
                                                             const void* __restrict__ xin,
@@ -252,7 +288,8 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
 
     // Fused quantizer: the first elements of the row are requested ahead of the weights, so that
     // they arrive first (see quantize_row_to_lds).
-    float4 xr[kRowRegs];
+    constexpr bool COUNTED = MODE == kFused && !EARLY && !PREFETCH && KSPLIT == 16 && UNROLL <= 10;
+    float4 xr[COUNTED ? (UNROLL + 1) / 2 : kRowRegs];       // (16 UNROLL chunks are 512 float4 per unit)
     if (MODE == kFused) preload_row<WAVES>(static_cast<const float*>(xin), L, xr);
     // Quantized row given: the wave's own chunks of it in 16-byte units (unit u of its LDS region is unit
     // c0 * 8 + u of the row; the packed axis runs over the row at most twice); EARLY: requested here.
@@ -273,9 +310,12 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
     }
     // Start the weight stream before the activation row is touched: it does not depend on x.
     ChunkRegs cur[UNROLL];
+    const WaveChunks<MINF> chunks(packed, L, COUNTED ? first : 0, COUNTED ? (int)n_chunks : 0);
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-        if (EARLY) {
+        if (COUNTED) {
+            cur[u] = chunks.load(u, lane);
+        } else if (EARLY) {
             // (a repeated chunk: all lanes on its first 16 bytes, one cache line instead of sixteen)
             cur[u] = load_chunk<MINF>(u < n_chunks ? wp : wp - lane, sp, zp, u < n_chunks ? u : 0);
         } else if (u < n_chunks) {
@@ -283,6 +323,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
         } else {
             cur[u] = ChunkRegs{};
         }
+        if (COUNTED) __builtin_amdgcn_sched_barrier(0);     // (in this order: the waits are counts)
     }
 
     // ---- activation row -> LDS
@@ -320,8 +361,14 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
     for (int64_t i = 0; i < n_chunks; i += UNROLL) {
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            const ChunkRegs& r = cur[u];
             if (i + u < n_chunks) {
+                ChunkRegs r = cur[u];
+                if (COUNTED) {
+                    // (opaque here: the compiler would take scales and zero points of all chunks apart ahead of the first one, and wait for all of them)
+                    asm volatile("" : "+v"(r.s.x), "+v"(r.s.y));
+                    if (MINF) asm volatile("" : "+v"(r.mn.x), "+v"(r.mn.y));
+                    else asm volatile("" : "+v"(r.z));
+                }
                 const int64_t c = c0 + i + u;
                 const int64_t cl = cbase + i + u;
                 const int4 xa = lds_x[cl * 8 + kb];
@@ -615,6 +662,10 @@ DecodeCfg decode_config(const Layout& L, bool fused)
     if ((ks == 4 || ks == 16) && L.C == 7 * ks && !prefetch && !debug_option(kDbgDecodeKsplit)) unroll = 7;
     // ... and eight waves on a row tile with at most four chunks each (the fused form of small layers)
     if (fused && ks == 8 && (L.C + 7) / 8 <= 4 && !debug_option(kDbgDecodeKsplit)) unroll = 4;
+    // ... and sixteen waves of the fused form: registers for no more chunks than a wave has (nine as ten; see COUNTED)
+    const int64_t share = (L.C + 15) / 16;
+    const bool counted = fused && ks == 16 && share <= 10 && !debug_option(kDbgDecodeKsplit) && !debug_option(kDbgDecodeEarly);
+    if (counted) unroll = share <= 5 ? 5 : share <= 8 ? (int)share : 10;
     int waves = fused ? (ks > 8 ? 16 : 8) : (ks > 4 ? ks : 4);
     if (const char* e = debug_option(kDbgDecodeWaves)) {    // tuning only
         const int v = atoi(e);
@@ -625,7 +676,7 @@ DecodeCfg decode_config(const Layout& L, bool fused)
     // form is slower: down of Qwen2-1.5B, 4 - 5 chunks on sixteen waves, 5.1 -> 5.7 us), and those whose
     // waves all have exactly `unroll` chunks (nothing is loaded twice)
     const bool exact = L.C % ks == 0 && L.C / ks == unroll;
-    int early = !prefetch && (((int64_t)L.total() <= kEarlyMaxBytes && L.C / ks >= unroll - 2) || exact);
+    int early = !counted && !prefetch && (((int64_t)L.total() <= kEarlyMaxBytes && L.C / ks >= unroll - 2) || exact);
     if (const char* e = debug_option(kDbgDecodeEarly)) early = !prefetch && e[0] == '1';   // tests and tuning
     return DecodeCfg{waves, ks, unroll, prefetch, early};
 }
@@ -690,6 +741,11 @@ int dispatch(const uint8_t* packed, const Layout& L, int64_t M, const void* xin,
 #define MNNQ_CFG_W(K, U, P) MNNQ_CFG(4, K, U, P) MNNQ_CFG(8, K, U, P) MNNQ_CFG(16, K, U, P)
     MNNQ_CFG_W(1, 8, 0) MNNQ_CFG_W(2, 8, 0) MNNQ_CFG_W(4, 8, 0) MNNQ_CFG_W(4, 7, 0)
     MNNQ_CFG(8, 8, 8, 0) MNNQ_CFG(8, 8, 4, 0) MNNQ_CFG(16, 8, 8, 0) MNNQ_CFG(16, 16, 8, 0) MNNQ_CFG(16, 16, 7, 0) MNNQ_CFG(16, 16, 12, 0)
+#define MNNQ_COUNTED(U)                                                                                          \
+    if (waves == 16 && ks == 16 && unroll == U && !prefetch)                                                     \
+        return launch_cfg<16, 16, U, MODE, false>(packed, L, M, xin, sx, bias, y, acc, st);
+    if constexpr (MODE == kFused) { MNNQ_COUNTED(5) MNNQ_COUNTED(6) MNNQ_COUNTED(10) }
+#undef MNNQ_COUNTED
     MNNQ_CFG_W(1, 8, 1) MNNQ_CFG_W(2, 8, 1) MNNQ_CFG_W(4, 8, 1)
     MNNQ_CFG(8, 8, 8, 1) MNNQ_CFG(16, 8, 8, 1) MNNQ_CFG(16, 16, 8, 1)
 #undef MNNQ_CFG_W

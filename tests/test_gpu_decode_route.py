@@ -40,3 +40,27 @@ def test_fused_decode_route(N, K, mode, two):
     finally:
         B.mnnq_debug_set("MNNQ_FUSED_TWO_KERNEL_MIB", None)
     assert torch.equal(other, want)
+
+
+@pytest.mark.parametrize("K", [8256, 10240, 10304, 12288, 12352, 14272, 14336, 16384, 16448, 20480, 20544, 24576, 24640])
+@pytest.mark.parametrize("mode", [B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT, B.MODE_W8_MIN_FLOAT])
+def test_long_rows_quantized_under_the_weight_stream(mode, K):
+    """Sixteen waves per row tile: around the numbers of chunks a wave holds (5 to 10, then 12, then a window), waves with one chunk
+    fewer, odd numbers of groups, the last row tile alone in its workgroup.  Int8 nibble planes run over half the columns twice."""
+    if mode == B.MODE_W8_MIN_FLOAT:
+        K = K // 2 // 128 * 128
+    N = 48
+    print("long rows", K, mode, flush=True)
+    x = torch.from_numpy(synth.activations(1, K, 11)).cuda()
+    x[0, K - 1] = 500.0                             # the row's maximum is its last value
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    packed = B.mnnq_pack_weights(torch.randn((N, K), generator=gen, device="cuda").mul_(0.02), mode=mode)
+    xq, sx, _ = B.mnnq_quant_act(x)
+    assert abs(float(sx[0]) - 500.0 / 127) < 1e-5
+    guard = torch.full((N + 1,), 7.5, device="cuda")
+    out = B.mnnq_linear_decode_fused(packed, N, K, x[0].contiguous(), mode=mode, out=guard[:N])
+    # the same codes and the same order of the sums as quantizer and layer one after the other
+    assert torch.equal(out, B.mnnq_linear_decode(packed, N, K, xq[0].contiguous(), sx, mode=mode))
+    assert float(guard[N]) == 7.5
+    zero = B.mnnq_linear_decode_fused(packed, N, K, torch.zeros(K, device="cuda"), mode=mode)
+    assert bool((zero == 0).all())
