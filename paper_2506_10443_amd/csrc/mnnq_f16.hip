@@ -121,8 +121,8 @@ __device__ __forceinline__ float dot16_f16(uint32_t w0, uint32_t w1, uint32_t z,
 // and every wave issues all UNROLL chunk loads without a branch, a wave with fewer chunks repeating
 // its first one.  Loads return in order, and only for straight-line code does the compiler count
 // how many younger loads may still be in flight when x is first used (behind conditional loads it
-// waits for the whole weight stream before x is staged).  Used where it pays: small layers, and
-// layers whose waves all have exactly UNROLL chunks.
+// waits for the whole weight stream before x is staged).  Used where it pays: small layers, layers
+// whose waves all have exactly UNROLL chunks, and sixteen waves per row tile.
 template <int WAVES, int KSPLIT, int UNROLL, bool PREFETCH, bool MINF, bool EARLY = false>
 __global__ __launch_bounds__(WAVES * 64) void decode_f16_kernel(const uint8_t* __restrict__ packed, Layout L,
                                                                 const uint16_t* __restrict__ x16,
@@ -317,10 +317,17 @@ int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x1
     }
     // Rows of 28 chunks (K = 3584) on four waves: seven chunks each, with no register left unused
     if (ks == 4 && L.C == 28 && !prefetch && !debug_option(kDbgDecodeKsplit)) unroll = 7;
+    // ... and sixteen waves: registers for no more chunks than a wave has (nine as ten), so that at most one is loaded twice, and x
+    // ahead of the weights for every size.  Behind conditional loads x was staged when the last weight had arrived; us, weights from
+    // HBM: 4096 x 14336 10.4 -> 9.0, 3584 x 18944 13.2 -> 11.6, 8192 x 8448 13.4 -> 10.3, 16000 x 14336 34.9 -> 29.7, float minima
+    // 10.5 -> 9.8, 13.6 -> 12.6, 14.0 -> 10.7, 36.1 -> 32.5; nibble planes 4096 x 4608 8.6 -> 7.4.
+    const int64_t share = (L.C + 15) / 16;
+    const bool close = ks == 16 && share <= 10 && !debug_option(kDbgDecodeKsplit) && !debug_option(kDbgDecodeEarly);
+    if (close) unroll = share <= 5 ? 5 : share <= 8 ? (int)share : 10;
     // x staged under the weight stream: small layers whose waves have at most two chunks fewer than `unroll`,
     // and those whose waves all have exactly `unroll` chunks
     const bool exact = L.C % ks == 0 && L.C / ks == unroll;
-    bool early = !prefetch && (((int64_t)L.total() <= (16 << 20) && L.C / ks >= unroll - 2) || exact);
+    bool early = close || (!prefetch && (((int64_t)L.total() <= (16 << 20) && L.C / ks >= unroll - 2) || exact));
     if (const char* e = debug_option(kDbgDecodeEarly)) early = !prefetch && e[0] == '1';   // tests and tuning
 #define MNNQ_CFG(W, K, U, P)                                                              \
     if (ks == K && unroll == U && prefetch == P) {                                        \
@@ -331,6 +338,10 @@ int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x1
     }
     MNNQ_CFG(4, 1, 8, 0) MNNQ_CFG(4, 2, 8, 0) MNNQ_CFG(4, 4, 8, 0) MNNQ_CFG(4, 4, 7, 0) MNNQ_CFG(8, 8, 8, 0)
     MNNQ_CFG(16, 16, 8, 0) MNNQ_CFG(16, 16, 12, 0)
+#define MNNQ_CLOSE(U) \
+    if (close && unroll == U) return launch_decode_cfg<16, 16, U, false, true>(packed, L, x16, bias, y, st);
+    MNNQ_CLOSE(5) MNNQ_CLOSE(6) MNNQ_CLOSE(7) MNNQ_CLOSE(10)
+#undef MNNQ_CLOSE
     MNNQ_CFG(4, 1, 8, 1) MNNQ_CFG(4, 2, 8, 1) MNNQ_CFG(4, 4, 8, 1) MNNQ_CFG(8, 8, 8, 1) MNNQ_CFG(16, 16, 8, 1)
 #undef MNNQ_CFG
     return MNNQ_ERR_UNSUPPORTED;

@@ -64,3 +64,29 @@ def test_long_rows_quantized_under_the_weight_stream(mode, K):
     assert float(guard[N]) == 7.5
     zero = B.mnnq_linear_decode_fused(packed, N, K, torch.zeros(K, device="cuda"), mode=mode)
     assert bool((zero == 0).all())
+
+
+@pytest.mark.parametrize("K", [8256, 10304, 12288, 12352, 14336, 16384, 16448, 20480, 20544, 24640])
+@pytest.mark.parametrize("mode", [B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT, B.MODE_W8_MIN_FLOAT])
+def test_long_fp16_rows_staged_under_the_weight_stream(mode, K):
+    """The same with fp16 activations: the form that requests the row ahead of the weights against the one behind branches (the same
+    waves and order of the sums: bits), and against the kernel of two tokens."""
+    if mode == B.MODE_W8_MIN_FLOAT:
+        K = K // 2 // 128 * 128
+    N = 48
+    print("long fp16 rows", K, mode, flush=True)
+    x = torch.from_numpy(synth.activations(1, K, 13)).cuda().half()
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    packed = B.mnnq_pack_weights(torch.randn((N, K), generator=gen, device="cuda").mul_(0.02), mode=mode)
+    guard = torch.full((N + 1,), 7.5, device="cuda")
+    out = B.mnnq_linear_decode_f16(packed, N, K, x[0].contiguous(), mode=mode, out=guard[:N])
+    assert float(guard[N]) == 7.5
+    B.mnnq_debug_set("MNNQ_DECODE_EARLY", 0)
+    try:
+        other = B.mnnq_linear_decode_f16(packed, N, K, x[0].contiguous(), mode=mode)
+    finally:
+        B.mnnq_debug_set("MNNQ_DECODE_EARLY", None)
+    assert torch.equal(out, other)
+    two = B.mnnq_linear_prefill_f16(packed, N, K, torch.cat([x, x]), mode=mode)
+    # fp32 sums of up to 386 group terms in another order
+    assert float((two[0] - out).abs().max()) <= 1e-5 * float(two.abs().max())
