@@ -787,8 +787,8 @@ int fused_workgroups_per_cu(const Layout& L, const DecodeCfg& c)
 // others stream weights, so that with three of them on a CU it costs nothing, and with two it does.  Measured, one kernel / two
 // over 25 000 drawn calls:
 //   sixteen waves per row tile (rows beyond 8192 columns; bytes beyond 7168): at most one workgroup per CU 0.77 - 1.02
-//     (up to 20480 columns 0.83 - 1.02, from 28672 to 126976 0.76 - 0.93), but float minima of 16512 - 20480 columns and 2816 - 4096
-//     rows 0.99 - 1.11: their kernel of twelve chunks a wave spills seven registers; more workgroups - a second round, with a
+//     (up to 20480 columns 0.83 - 1.02, from 28672 to 126976 0.76 - 0.93), float minima of 16512 - 20480 columns and 2816 - 4096
+//     rows 0.99 - 1.11 with the kernel of twelve chunks a wave, 0.91 - 0.95 of that with the one of ten; more workgroups - a second round, with a
 //     second quantization behind the first - 1.02 - 1.28 up to 49152 columns;
 //   int8 bytes: up to four waves per tile 0.96 - 0.98 at 64 MiB as at 600 (152064 x 3584 90.0 -> 87.4 us), eight 0.99 at
 //     80 - 96 MiB, 1.03 - 1.06 beyond;
