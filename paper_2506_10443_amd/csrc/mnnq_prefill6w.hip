@@ -187,12 +187,15 @@ __global__ __launch_bounds__(64 * kWaves * KS, 2) void prefill6_wide_kernel(
             if (j == 0) {
                 if (row == 2 * TM - 1) {
                     // All of this wave's reads of the stage are done, and its pieces of the next one have landed: the loads younger
-                    // than those are NS - 2 stages and a chunk's weights and scales per chunk in between.
+                    // than those are NS - 2 stages and a chunk's weights and scales per chunk in between.  The count holds only while
+                    // a chunk issues exactly those loads and the direct ones ahead of the codes that follow them: what other waves
+                    // read rests on it, so the order is fixed below and checked in the compiled kernel (test_generated_code_cpu.py).
                     constexpr int kYounger = (NS - 2) * Cfg::NA + (NS - 1) * 6 * TN;
                     __builtin_amdgcn_s_waitcnt(wait_loads(kYounger < 63 ? kYounger : 63));
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
                     issue_a(c + NS, stage);
+                    __builtin_amdgcn_sched_barrier(0);
                     a[(row + 1) & 1] = read_a(next, 0, 0);
                 } else {
                     a[(row + 1) & 1] = read_a(stage, (row + 1) % TM, (row + 1) / TM);
