@@ -13,8 +13,9 @@
 // between the waves of a workgroup and they go straight from L2 into registers:
 //   resident form (few_resident_kernel): a wave's part is at most NCH chunks; its A operands stay in registers while
 //     the workgroup walks over row tiles (grid-stride), so that the loop streams weights and nothing else.  The
-//     registers of a chunk are refilled with the same chunk of the next row tile as soon as it has been unpacked,
-//     without a branch: only then does the compiler wait by count, with the refills in flight.
+//     registers of a chunk are refilled with the same chunk of the next row tile as soon as it has been contracted, by loads
+//     that no branch guards: only then does the compiler wait by count, with the refills in flight.  (The waves that store a
+//     row tile wait for all of their refills before the store.)  The last row tile of a workgroup stands behind the loop.
 //   streaming form (few_stream_kernel): longer rows; weights and activations of a chunk are requested together, DEPTH
 //     chunks ahead.
 //
@@ -25,6 +26,8 @@
 #include "mnnq_forms.h"
 
 #include <stdlib.h>
+
+#include <type_traits>
 
 namespace mnnq {
 
@@ -304,6 +307,7 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
         return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_bias, ((int)t * kTileN + row) * 4, 0, 0));
     };
     float b = bias_of(tile);
+    asm volatile("" ::: "memory");              // (all requested here: else the weights sink into the loop, behind the activations)
 #pragma unroll
     for (int u = 0; u < NCH; ++u) acts.arrange(a[u]);
     constexpr int SH = shifted_chunks(TM, NCH, FORM);
@@ -316,9 +320,10 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
             for (int t = 0; t < TM; ++t) start[u][h][t] = shifted_start(a[u][h][t][0]);
 
     int buf = 0, turn = 0;
-    do {   // (the grid has no more workgroups than there are row tiles)
-        const float b_next = bias_of(tile + gridDim.x);
-        const TileBuffers<FORM> next(packed, L, tile + gridDim.x);
+    auto row_tile = [&](auto refill) {
+        constexpr bool REFILL = decltype(refill)::value;
+        const float b_next = REFILL ? bias_of(tile + gridDim.x) : 0.0f;
+        const TileBuffers<FORM> next(packed, L, REFILL ? tile + gridDim.x : tile);
         float acc[TM][4];
 #pragma unroll
         for (int t = 0; t < TM; ++t)
@@ -327,13 +332,16 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
         Pending<TM, FORM> pend;
 #pragma unroll
         for (int u = 0; u < NCH; ++u) {
-            // A chunk that is not the wave's own is passed over, and the loads go on: without the branches the compiler moves the
+            // A chunk that is not the wave's own is passed over, and the refills go on: without the branches the compiler moves the
             // chunks' scales together, at the top of the loop, and waits there for all but the last two loads (24 tokens of 28672 x 4096
             // 20.8 -> 19.2 us, 9 of 37888 x 3584 with fp16 activations 21.0 -> 19.4).  Four blocks of the other forms spill with
-            // them; there the chunk is zero.
-            if (u == 0 || (TM * NCH == 16 && FORM != kZp) || u < own) contract<TM, FORM>(cur[u], a[u], zsel, pend, acc, u < SH ? &start[u < SH ? u : 0] : nullptr);
-            cur[u] = next.load(u < own ? c0 + u : C, lane, row);
-            __builtin_amdgcn_sched_barrier(0);
+            // them; there, and in the last row tile, the chunk is zero.
+            if (u == 0 || !REFILL || (TM * NCH == 16 && FORM != kZp) || u < own)
+                contract<TM, FORM>(cur[u], a[u], zsel, pend, acc, u < SH ? &start[u < SH ? u : 0] : nullptr);
+            if (REFILL) {
+                cur[u] = next.load(u < own ? c0 + u : C, lane, row);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         float4* part = lds_part + buf * KS * TM * 64;
 #pragma unroll
@@ -349,7 +357,15 @@ __global__ __launch_bounds__(MAXW * 64) void few_resident_kernel(const uint8_t* 
         b = b_next;
         buf ^= 1;
         tile += gridDim.x;
-    } while (tile < L.T);
+    };
+    // (The grid has no more workgroups than there are row tiles.)  The last row tile requests nothing and has no branches: with both it
+    // cost the launches of one row tile per workgroup, or little more, up to 9 % over the straight loop before them - requests past the
+    // matrix bring nothing but take their turn, and the stores wait for them.  us, straight loop / branches / branches, last tile apart:
+    // 9 tokens of 10720 x 2240, float minima 8.2 / 8.9 / 6.8; 5 of 10864 x 1152, nibble planes 8.2 / 8.9 / 6.8; 5 of 4032 x 2688,
+    // bytes 5.3 / 5.5 / 5.2; 31 of 5056 x 3584, float minima 7.7 / 7.9 / 7.5; over 560 shapes of 2 - 64 tokens 1 / 0.99 / 0.953,
+    // with fp16 activations 1 / 0.984 / 0.971.
+    while (tile + gridDim.x < L.T) row_tile(std::true_type{});
+    row_tile(std::false_type{});
 }
 
 template <int TM, int DEPTH, int FORM, int MAXW, bool BLOCKS>

@@ -64,3 +64,13 @@ def test_wide_fp6_ring_counts_its_own_loads(code):
         back = [x for x in ins[first:end] if x.startswith("buffer_load")]
         assert len(back) == 3 + 18, (name, len(back))
         assert sum(x.endswith("lds") for x in back) == 3
+
+
+def test_last_row_tile_of_few_tokens_requests_nothing(code):
+    """few_resident_kernel: ahead of the last barrier (of a workgroup's last row tile) stands a stretch without any load - the launches
+    of one row tile per workgroup must not pay for the next one's.  The loop's barrier is the other one."""
+    for name, ins in code(r"few_resident_kernel").items():
+        barriers = [i for i, x in enumerate(ins) if x.startswith("s_barrier")]
+        assert len(barriers) == 2, (name, len(barriers))
+        loads = [i for i, x in enumerate(ins) if x.startswith("buffer_load")]
+        assert loads and max(loads) < barriers[0], (name, max(loads), barriers)

@@ -1,6 +1,6 @@
 """Few tokens at once (the kernels behind mnnq_linear_prefill and mnnq_linear_prefill_fused for small M) against the
 oracle: token counts at the edges of the 16-token blocks, rows of one chunk, of an odd number of groups and beyond what a
-wave holds in registers, more row tiles than the chip holds workgroups, every weight form.  int8 rows given (row-major)
+wave holds in registers, one and several row tiles per workgroup, every weight form.  int8 rows given (row-major)
 and quantized by the call (codes in token blocks) run the same sums in the same order: equal bit for bit."""
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ FORMS = {
     "w8": (W8N, oracle.quant_weights8, oracle.linear_w8a8),
     "w8planes": (B.MODE_W8_MIN_FLOAT, oracle.quant_weights8, oracle.linear_w8a8),
 }
-# (M, N, K): the last ones walk over several row tiles per workgroup, and stream a long row
+# (M, N, K): the last ones have many row tiles, one per workgroup, and stream a long row
 SHAPES = [(2, 16, 64), (3, 48, 192), (15, 80, 1536), (16, 32, 4096), (17, 48, 4160), (32, 64, 960), (33, 48, 512),
           (48, 32, 8960), (49, 16, 320), (64, 80, 3584), (4, 16 * 1100, 128), (40, 16 * 600, 256), (5, 32, 18944),
           (2, 16, 24576), (81, 48, 1536), (128, 32, 320)]
@@ -130,7 +130,7 @@ def test_k_split_int8_gemm_matches_oracle(form, M, N, K):
 
 # fp16 activations: the few-token kernels (resident and streaming, both slices) and the K-split GEMM behind them
 F16_SHAPES = [(2, 16, 64), (15, 80, 1536), (16, 32, 8960), (17, 48, 4160), (33, 48, 1984), (40, 16 * 300, 2304), (64, 80, 2048),
-              (100, 48, 1536), (65, 48, 192), (130, 272, 1088), (3, 16 * 1100, 128), (200, 1040, 640), (129, 32, 8960), (65, 16 * 520, 2048)]
+              (100, 48, 1536), (65, 48, 192), (130, 272, 1088), (3, 16 * 1100, 128), (6, 16 * 515, 2176), (200, 1040, 640), (129, 32, 8960), (65, 16 * 520, 2048)]
 
 
 @pytest.mark.parametrize("M,N,K", F16_SHAPES)
@@ -259,3 +259,30 @@ def test_fp16_tiles_by_tiles_per_cu(mode, M, N, K):
     if B.mnnq_plan_debug(5, M, N, K, mode)[0] == 0:     # a row factor changes neither the tile nor the order of the sums
         ones = torch.ones(M, device="cuda:0")
         assert torch.equal(B.mnnq_linear_prefill_f16(packed, N, K, x, row_scale=ones, bias=bias, mode=mode), y)
+
+
+# One shape for each number of token blocks: nine waves (one block, sixteen waves on a CU) or five (eight) on a row tile, so that a CU
+# holds one workgroup, and 515 row tiles: every workgroup walks over two, three of them over three.  33 and 17 chunks: waves with
+# three and four of them, the last one half empty.
+@pytest.mark.parametrize("M,K", [(5, 4160), (20, 2112), (40, 2112), (56, 2112)])
+@pytest.mark.parametrize("form", list(FORMS))
+def test_few_tokens_walk_over_row_tiles(form, M, K):
+    mode, quant, linear = FORMS[form]
+    if form.startswith("w8"):
+        K = K // (2 if form == "w8planes" else 1) // 128 * 128 + 128
+    N = 16 * 515
+    print("few tokens, row tiles", form, M, N, K, flush=True)
+    plan = B.mnnq_plan_debug(4, M, N, K, mode=mode)
+    assert plan[0] == 1 and plan[4] // plan[3] == 1 and N // 16 > 2 * 256          # resident, one workgroup on each of 256 CUs
+    W = synth.weights(N, K, 71 + M)
+    xd = dev(synth.activations(M, K, 72 + M))
+    bias = synth.weights(1, N, 73)[0] * 10
+    q, s, z = quant(W)
+    packed = B.mnnq_pack_weights(dev(W), mode=mode)
+    xq, sx, _ = B.mnnq_quant_act(xd)
+    y_o = linear(xq.cpu().numpy(), sx.cpu().numpy(), q, s, z, bias=bias, want_acc=False)[1]
+    y = B.mnnq_linear_prefill(packed, N, K, xq, sx, bias=dev(bias), mode=mode)
+    # fp32 sums of up to 68 group terms: the layer's tolerance, row tile by row tile
+    err = np.abs(y.cpu().numpy() - y_o).reshape(M, 515, 16).max(axis=(0, 2))
+    assert (err <= 1e-5 * np.abs(y_o).reshape(M, 515, 16).max(axis=(0, 2))).all()
+    assert torch.equal(B.mnnq_linear_prefill_fused(packed, N, K, xd, bias=dev(bias), mode=mode), y)
