@@ -164,7 +164,8 @@ struct RowQuantizer {
     {
         lim = quant_fast_limit(scale, inv);
     }
-    __device__ __forceinline__ void put(int i, const float4 xv) const
+    // again: the dword's place in the row's second pass, that many dwords further on (0: there is none).
+    __device__ __forceinline__ void put(int i, const float4 xv, int again) const
     {
         int v = 0;
         if (i < valid && scale != 0.0f) v = quant4_fast(xv, scale, inv, lim);
@@ -172,6 +173,14 @@ struct RowQuantizer {
         int sum = __builtin_amdgcn_sdot4(v, 0x01010101, 0, false);
         sum += row_exchange<0xB1>(sum);      // the four dwords of a block: one quad of lanes
         sum += row_exchange<0x4E>(sum);
+        put_sum(i, sum);
+        if (again) {
+            lds_xd[i + again] = v;
+            put_sum(i + again, sum);
+        }
+    }
+    __device__ __forceinline__ void put_sum(int i, int sum) const
+    {
         if ((threadIdx.x & 3) == 0) {
             const int u = i >> 2;                       // 16-byte block; chunk u / 8
             lds_xs[(u & ~7) + (u & 3) * 2 + ((u >> 2) & 1)] = sum;
@@ -179,7 +188,10 @@ struct RowQuantizer {
     }
 };
 
-template <int WAVES, int XR>
+// TWICE: the packed axis may run over the row twice (nibble planes of int8 weights).  Both places of a dword are written together: a
+// second pass that read the row again waited for all weights (one token, us: 1504 x 7424 9.8 -> 9.2, 6496 x 6656
+// 18.0 -> 17.3, 138 shapes 0.937).
+template <int WAVES, bool TWICE, int XR>
 __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x, const float4 (&xr)[XR],
                                                      const Layout& L, int* lds_xd, int* lds_xs, float* lds_amax)
 {
@@ -188,6 +200,7 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
     const int dwords = (int)(L.C * 32);                  // padded row of the packed reduction axis
     const int valid = (int)(L.K / 4);
     const int row_dw = (int)(L.Kx / 4);                  // the activation row itself
+    const int again = TWICE ? valid - row_dw : 0;
     const float4* x4 = reinterpret_cast<const float4*>(x);
 
     float amax = 0.0f;
@@ -202,15 +215,11 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
 #pragma unroll
     for (int j = 0; j < XR; ++j) {
         const int i = tid + j * THREADS;
-        if (i < row_dw) q.put(i, xr[j]);
+        if (i < row_dw) q.put(i, xr[j], again);
     }
-    for (int i = tid + XR * THREADS; i < row_dw; i += THREADS) q.put(i, x4[i]);
-    // Past the row: its second pass (int8 weights) and the zero padding of the last chunk.
-    for (int i = row_dw + tid; i < dwords; i += THREADS) {
-        float4 xv = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (i < valid) xv = x4[i - row_dw];              // (the packed axis runs over the row at most twice)
-        q.put(i, xv);
-    }
+    for (int i = tid + XR * THREADS; i < row_dw; i += THREADS) q.put(i, x4[i], again);
+    // Past the data: the zero padding of the last chunk.
+    for (int i = valid + tid; i < dwords; i += THREADS) q.put(i, make_float4(0.0f, 0.0f, 0.0f, 0.0f), 0);
     lds_barrier();
     return q.scale;
 }
@@ -329,7 +338,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
     // ---- activation row -> LDS
     float scale = 0.0f;
     if (MODE == kFused) {
-        scale = quantize_row_to_lds<WAVES>(static_cast<const float*>(xin), xr, L, lds_xd, lds_xs, lds_amax);
+        scale = quantize_row_to_lds<WAVES, MINF>(static_cast<const float*>(xin), xr, L, lds_xd, lds_xs, lds_amax);
     } else {
         // This wave's chunks only.
         int4* lds_xw = reinterpret_cast<int4*>(xbase);
@@ -512,7 +521,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode8_kernel(const uint8_t* __re
     // ---- activation row -> LDS (the image of decode_kernel)
     float scale = 0.0f;
     if (MODE == kFused) {
-        scale = quantize_row_to_lds<WAVES>(static_cast<const float*>(xin), xr, L, lds_xd, lds_xs, lds_amax);
+        scale = quantize_row_to_lds<WAVES, false>(static_cast<const float*>(xin), xr, L, lds_xd, lds_xs, lds_amax);
     } else {
         // This wave's chunks only; the region is private to the wave, whose LDS operations complete in order.
         const int4* xq16 = reinterpret_cast<const int4*>(static_cast<const int8_t*>(xin));

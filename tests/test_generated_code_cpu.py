@@ -74,3 +74,13 @@ def test_last_row_tile_of_few_tokens_requests_nothing(code):
         assert len(barriers) == 2, (name, len(barriers))
         loads = [i for i, x in enumerate(ins) if x.startswith("buffer_load")]
         assert loads and max(loads) < barriers[0], (name, max(loads), barriers)
+
+
+def test_second_pass_over_the_row_reads_nothing(code):
+    """Fused one-token kernels with float minima (nibble planes: the packed axis runs over the row twice): behind the barrier of the row's
+    maximum the row is read in one place only, the loop for what the registers do not hold.  A second read, for the row's second
+    pass, would wait for all weights."""
+    for name, ins in code(r"13decode_kernelILi\d+ELi\d+ELi\d+ELi1ELb[01]ELb1E").items():
+        barriers = [i for i, x in enumerate(ins) if x.startswith("s_barrier")]
+        row = [x for x in ins[barriers[0]:barriers[1]] if "load_dwordx4" in x and not x.endswith(" nt")]
+        assert len(row) == 1, (name, row)
