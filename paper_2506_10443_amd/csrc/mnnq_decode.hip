@@ -242,7 +242,8 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
 // its first 8192 values, is requested ahead of them.  The row is quantized while the weights arrive, and each chunk is waited for by count.
 // The conditional form, and the rest of a longer row behind the weights, had waited for the last weight before the row's maximum.  One
 // token, weights from HBM, us: 3584 x 18944 12.45 -> 11.9 (float minima 14.8 -> 13.4), 4096 x 14336 10.7 -> 9.9, 2048 x 12288 9.25 -> 7.7,
-// 4096 x 16384 12.2 -> 11.0, 1536 x 8960 6.75 -> 6.55.  Registers for more chunks than a wave has (eight for five) cost 12 % there.
+// 4096 x 16384 12.2 -> 11.0, 1536 x 8960 6.75 -> 6.55.  Registers for more chunks than a wave has (eight for five) cost 12 % there; nine
+// chunks on ten with minima cost what the form gains and more (1280 x 8448 on nibble planes 11.1 us with branches, 11.6 on ten registers, 10.0 on nine).
 template <int WAVES, int KSPLIT, int UNROLL, int MODE, bool PREFETCH, bool MINF, bool EARLY = false>
 __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __restrict__ packed, Layout L,
                                                             const void* __restrict__ xin,
@@ -299,7 +300,18 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
     // they arrive first (see quantize_row_to_lds).
     constexpr bool COUNTED = MODE == kFused && !EARLY && !PREFETCH && KSPLIT == 16 && UNROLL <= 10;
     float4 xr[COUNTED ? (UNROLL + 1) / 2 : kRowRegs];       // (16 UNROLL chunks are 512 float4 per unit)
-    if (MODE == kFused) preload_row<WAVES>(static_cast<const float*>(xin), L, xr);
+    // (Ten chunks with minima: through a descriptor, which leaves the registers that two scales would be spilled from otherwise, behind a
+    // wait for all weights.  The other forms are 1 - 3 % faster with the branches.)
+    constexpr bool ROW_BUFFER = COUNTED && MINF && UNROLL == 10;
+    if (ROW_BUFFER) {
+        const __amdgpu_buffer_rsrc_t rs_x = WaveChunks<MINF>::rsrc(static_cast<const uint8_t*>(xin), (int)L.Kx * 4);
+#pragma unroll
+        for (int j = 0; j < (UNROLL + 1) / 2; ++j)
+            xr[ROW_BUFFER ? j : 0] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, tid * 16, j * WAVES * 1024, 0));
+        __builtin_amdgcn_sched_barrier(0);
+    } else if (MODE == kFused) {
+        preload_row<WAVES>(static_cast<const float*>(xin), L, xr);
+    }
     // Quantized row given: the wave's own chunks of it in 16-byte units (unit u of its LDS region is unit
     // c0 * 8 + u of the row; the packed axis runs over the row at most twice); EARLY: requested here.
     constexpr int XP = (UNROLL * 8 + 63) / 64;
@@ -671,10 +683,10 @@ DecodeCfg decode_config(const Layout& L, bool fused)
     if ((ks == 4 || ks == 16) && L.C == 7 * ks && !prefetch && !debug_option(kDbgDecodeKsplit)) unroll = 7;
     // ... and eight waves on a row tile with at most four chunks each (the fused form of small layers)
     if (fused && ks == 8 && (L.C + 7) / 8 <= 4 && !debug_option(kDbgDecodeKsplit)) unroll = 4;
-    // ... and sixteen waves of the fused form: registers for no more chunks than a wave has (nine as ten; see COUNTED)
+    // ... and sixteen waves of the fused form: registers for no more chunks than a wave has (see COUNTED)
     const int64_t share = (L.C + 15) / 16;
     const bool counted = fused && ks == 16 && share <= 10 && !debug_option(kDbgDecodeKsplit) && !debug_option(kDbgDecodeEarly);
-    if (counted) unroll = share <= 5 ? 5 : share <= 8 ? (int)share : 10;
+    if (counted) unroll = share <= 5 ? 5 : (int)share;
     int waves = fused ? (ks > 8 ? 16 : 8) : (ks > 4 ? ks : 4);
     if (const char* e = debug_option(kDbgDecodeWaves)) {    // tuning only
         const int v = atoi(e);
@@ -753,7 +765,7 @@ int dispatch(const uint8_t* packed, const Layout& L, int64_t M, const void* xin,
 #define MNNQ_COUNTED(U)                                                                                          \
     if (waves == 16 && ks == 16 && unroll == U && !prefetch)                                                     \
         return launch_cfg<16, 16, U, MODE, false>(packed, L, M, xin, sx, bias, y, acc, st);
-    if constexpr (MODE == kFused) { MNNQ_COUNTED(5) MNNQ_COUNTED(6) MNNQ_COUNTED(10) }
+    if constexpr (MODE == kFused) { MNNQ_COUNTED(5) MNNQ_COUNTED(6) MNNQ_COUNTED(9) MNNQ_COUNTED(10) }
 #undef MNNQ_COUNTED
     MNNQ_CFG_W(1, 8, 1) MNNQ_CFG_W(2, 8, 1) MNNQ_CFG_W(4, 8, 1)
     MNNQ_CFG(8, 8, 8, 1) MNNQ_CFG(16, 8, 8, 1) MNNQ_CFG(16, 16, 8, 1)
@@ -797,8 +809,8 @@ int fused_workgroups_per_cu(const Layout& L, const DecodeCfg& c)
 // over 25 000 drawn calls:
 //   sixteen waves per row tile (rows beyond 8192 columns; bytes beyond 7168): at most one workgroup per CU 0.77 - 1.02
 //     (up to 20480 columns 0.83 - 1.02, from 28672 to 126976 0.76 - 0.93), float minima of 16512 - 20480 columns and 2816 - 4096
-//     rows 0.99 - 1.11 with the kernel of twelve chunks a wave, 0.91 - 0.95 of that with the one of ten; more workgroups - a second round, with a
-//     second quantization behind the first - 1.02 - 1.28 up to 49152 columns;
+//     rows 0.99 - 1.11 with the kernel of twelve chunks a wave, 0.85 - 0.95 of that with those of nine and ten; more workgroups - a second round, with a
+//     second quantization behind the first - 1.02 - 1.28 up to 49152 columns (measured ahead of the form COUNTED);
 //   int8 bytes: up to four waves per tile 0.96 - 0.98 at 64 MiB as at 600 (152064 x 3584 90.0 -> 87.4 us), eight 0.99 at
 //     80 - 96 MiB, 1.03 - 1.06 beyond;
 //   int4, eight waves per tile: 1.02 at 32 - 40 MiB, 1.06 at 40 - 48, 1.08 at 48 - 56, 1.18 at 80 - 96, 1.23 - 1.34 beyond; up to

@@ -44,6 +44,19 @@ def code(tmp_path_factory):
         assert out, pattern
         return out
 
+    def registers(pattern):
+        """{name: (vector registers, spilled ones)} of the same kernels."""
+        out = {}
+        for o in objects:
+            notes = _run(os.path.join(LLVM, "llvm-readelf"), "--notes", o)
+            for entry in notes.split("  - .agpr_count:")[1:]:
+                value = lambda key: re.search(r"\.%s:\s+(\S+)" % key, entry).group(1)
+                if re.search(pattern, value("name")):
+                    out[value("name")] = (int(value("vgpr_count")), int(value("vgpr_spill_count")))
+        assert out, pattern
+        return out
+
+    kernels.registers = registers
     return kernels
 
 
@@ -84,3 +97,16 @@ def test_second_pass_over_the_row_reads_nothing(code):
         barriers = [i for i, x in enumerate(ins) if x.startswith("s_barrier")]
         row = [x for x in ins[barriers[0]:barriers[1]] if "load_dwordx4" in x and not x.endswith(" nt")]
         assert len(row) == 1, (name, row)
+
+
+def test_registers_follow_the_share_of_a_wave(code):
+    """Fused one-token call, sixteen waves per row tile: a kernel for every share of five to ten chunks, none of which spills - a spilled
+    scale is stored behind a wait for all weights, which the form is there to avoid."""
+    for mode in (B.MODE_W4_ZP_INT, B.MODE_W4_MIN_FLOAT):
+        for chunks in range(65, 161):
+            waves, ks, unroll, prefetch = B.mnnq_plan_debug(2, 1, 48, 128 * chunks, mode)[:4]
+            assert (waves, ks, unroll, prefetch) == (16, 16, -(-chunks // 16), 0), chunks
+    kernels = code.registers(r"13decode_kernelILi16ELi16ELi([5-9]|10)ELi1ELb0ELb[01]ELb0E")
+    assert len(kernels) == 12
+    for name, (vector, spilled) in kernels.items():
+        assert spilled == 0 and vector <= 128, (name, vector, spilled)
