@@ -595,12 +595,16 @@ int choose_tiled6(const Layout& L, int64_t M)
         return (double)(t / (2 * cus)) * full + last;
     };
     // More than one 128 x 128 tile per CU, but one 64 x 384 tile: a CU has three quarters of two such tiles to contract rather than both.
-    // On 73 shapes of 119 - 2048 tokens, K 1088 - 16320, weights from HBM, 0.91 of the time of 128 x 128 tiles in the mean, three of
-    // them slower by up to 3 % (259 - 272 tiles of 128 x 128, few groups); us, 128 x 128 / 64 x 384 with one / with two K parts: 1024
-    // tokens of 4608 x 3584 38.5 / 35.5 / 35.3, of 6144 x 1152 19.4 / 17.6 / 19.4; 256 of 17264 x 2944 36.1 / 30.6 / 31.4; 2048 of
-    // 3024 x 6848 76.7 / 65.2 / 64.3; 1990 of 2672 x 12352 117.0 / 103.1 / 98.7.  Two K parts (eight waves on the CU rather than four) are
-    // 1.05 of one part below 2500 columns of K, even around 4096, 0.96 above 4500.
-    if (tiles6(L, M, 64, 384) <= cus) return L.Gx >= 64 ? 3 : 4;
+    // On 73 shapes of 119 - 2048 tokens, K 1088 - 16320, weights from HBM, 0.91 of the time of 128 x 128 tiles in the mean; us, 128 x 128 /
+    // 64 x 384 with one / with two K parts: 1024 tokens of 4608 x 3584 38.5 / 35.5 / 35.3, of 6144 x 1152 19.4 / 17.6 / 19.4; 256 of
+    // 17264 x 2944 36.1 / 30.6 / 31.4; 2048 of 3024 x 6848 76.7 / 65.2 / 64.3; 1990 of 2672 x 12352 117.0 / 103.1 / 98.7.  Two K parts (eight
+    // waves on the CU rather than four) are 1.05 of one part below 2500 columns of K, even around 4096, 0.96 above 4500.
+    // Up to eight tiles of 128 x 128 beyond one per CU - one per XCD - are no second round where three or more rows of them share the weights:
+    // 1.02 of their time on 37 shapes (0.98 - 1.065; 754 tokens of 5440 x 3904 35.0 / 37.3 us, 268 of 11232 x 3008 28.6 / 30.3).  One and two
+    // rows take 0.86 and 0.98 there, two K parts 0.94 - 0.996; with 9 - 16 tiles beyond 0.89 (two rows), 0.955, 1.00 (five rows and more),
+    // with 25 - 32 0.88, 0.92, 0.97.
+    const bool square = t0 <= cus + 8 && M > 2 * 128 && L.Gx < 64;
+    if (tiles6(L, M, 64, 384) <= cus && !square) return L.Gx >= 64 ? 3 : 4;
     const double c0 = cost(128, 27, 42), c2 = cost(256, 49, 68), c5 = cost(320, 54, 88);
     if (c5 < c2 && c5 < 0.97 * c0) return 5;
     return c2 < 0.97 * c0 ? 2 : 0;

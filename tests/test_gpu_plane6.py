@@ -108,6 +108,15 @@ def test_one_wide_tile_per_cu_takes_the_wide_tiles():
     assert tile(1024, 6160, 1152)[0] == 128                    # 272 of them
 
 
+def test_few_second_tiles_keep_the_square_tiles():
+    """At most eight more 128 x 128 tiles than CUs in three and more rows; not in one or two rows, nor with 64 groups, nor nine."""
+    tile = lambda M, N, K: B.mnnq_plan_debug(0, M, N, K, mode=MODE)[:2]
+    for M, N, K in ((754, 5440, 3904), (268, 11232, 3008), (302, 11136, 1600), (954, 4224, 4032)):
+        assert tile(M, N, K) == [128, 128], (M, N, K)
+    for M, N, K in ((122, 33408, 1984), (161, 16704, 1216), (1346, 2992, 8448), (268, 11232, 4096), (559, 6704, 1024)):
+        assert tile(M, N, K) == [64, 384], (M, N, K)
+
+
 @pytest.mark.parametrize("M,N,K", [(200, 400 - 400 % 16, 1536), (129, 592, 448), (40, 48, 64)])
 def test_prefill6_deeper_rings(M, N, K):
     """Three and four stages in the LDS rings (MNNQ_PREFILL6_STAGES) for the plans that have them."""
