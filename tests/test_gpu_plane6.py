@@ -125,7 +125,7 @@ def test_prefill6_deeper_rings(M, N, K):
     packed = B.mnnq_pack_weights(dev(W), mode=MODE)
     ws = torch.empty(B.mnnq_workspace_size(M, N, K, 64, MODE), dtype=torch.uint8, device="cuda:0")
     try:
-        for plan, stages in ((0, 3), (0, 4), (1, 3), (1, 4), (2, 3), (3, 3)):
+        for plan, stages in ((0, 3), (0, 4), (1, 3), (1, 4), (2, 3)):
             note("prefill6 plan", plan, "stages", stages, "M", M, "N", N, "K", K)
             B.mnnq_debug_set("MNNQ_PREFILL6_PLAN", plan)
             B.mnnq_debug_set("MNNQ_PREFILL6_STAGES", stages)
@@ -190,7 +190,7 @@ def test_prefill6_bias_fused_and_fallbacks():
     assert np.array_equal(ys, yf)
 
 
-@pytest.mark.parametrize("plan", [0, 1, 2, 5])
+@pytest.mark.parametrize("plan", [0, 1, 2, 3, 4, 5])
 def test_prefill6_binary16_output_and_bias(plan):
     """The output stage of the fp6 GEMM (row segments through an LDS patch, 128-bit stores; 64-bit ones for
     binary16) on ragged shapes: the binary16 call must give the fp32 result rounded once."""
