@@ -219,7 +219,10 @@ __device__ __forceinline__ float quantize_row_to_lds(const float* __restrict__ x
     }
     for (int i = tid + XR * THREADS; i < row_dw; i += THREADS) q.put(i, x4[i], again);
     // Past the data: the zero padding of the last chunk.
-    for (int i = valid + tid; i < dwords; i += THREADS) q.put(i, make_float4(0.0f, 0.0f, 0.0f, 0.0f), 0);
+    for (int i = valid + tid; i < dwords; i += THREADS) {
+        lds_xd[i] = 0;
+        q.put_sum(i, 0);
+    }
     lds_barrier();
     return q.scale;
 }
