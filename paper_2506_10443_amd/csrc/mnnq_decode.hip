@@ -35,6 +35,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum Mode { kXQ = 0, kFused = 1, kAcc = 2 };
 
+// The form COUNTED of decode_kernel, where it does not loop with a prefetch.
+template <int MODE>
+constexpr bool is_counted(int ksplit, int unroll)
+{
+    return MODE == kFused && ksplit == 16 && unroll <= 10;
+}
+
 struct ChunkRegs {
     u32x4 w;      // 32 codes: .x,.y group 2c ; .z,.w group 2c+1
     float2 s;     // scales of the lane's row for both groups
@@ -301,7 +308,8 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const uint8_t* __res
 
     // Fused quantizer: the first elements of the row are requested ahead of the weights, so that
     // they arrive first (see quantize_row_to_lds).
-    constexpr bool COUNTED = MODE == kFused && !EARLY && !PREFETCH && KSPLIT == 16 && UNROLL <= 10;
+    constexpr bool COUNTED = is_counted<MODE>(KSPLIT, UNROLL) && !PREFETCH;
+    static_assert(!COUNTED || !EARLY, "COUNTED has the row under the weight stream by itself");
     float4 xr[COUNTED ? (UNROLL + 1) / 2 : kRowRegs];       // (16 UNROLL chunks are 512 float4 per unit)
     // (Ten chunks with minima: through a descriptor, which leaves the registers that two scales would be spilled from otherwise, behind a
     // wait for all weights.  The other forms are 1 - 3 % faster with the branches.)
@@ -757,7 +765,7 @@ int dispatch(const uint8_t* packed, const Layout& L, int64_t M, const void* xin,
     const int waves = c.waves, ks = c.ks, unroll = c.unroll, prefetch = c.prefetch;
 #define MNNQ_CFG(W, K, U, P)                                                    \
     if (waves == W && ks == K && unroll == U && prefetch == P) {                \
-        if constexpr (MODE != kAcc && P == 0) {                                 \
+        if constexpr (MODE != kAcc && P == 0 && !is_counted<MODE>(K, U)) {      \
             if (c.early) return launch_cfg<W, K, U, MODE, false, true>(packed, L, M, xin, sx, bias, y, acc, st); \
         }                                                                       \
         return launch_cfg<W, K, U, MODE, (P != 0)>(packed, L, M, xin, sx, bias, y, acc, st); \
