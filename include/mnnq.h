@@ -292,7 +292,8 @@ int mnnq_debug_set(const char *key, const char *value);
  * what = 1: mnnq_linear_decode; what = 2: mnnq_linear_decode_fused without workspace; out8 = {waves per
  *           workgroup, waves per row tile, weight chunks a wave holds in registers, 1 if it loops with a
  *           prefetch, LDS bytes per workgroup, workgroups, row tiles per workgroup, 1 if the activation
- *           row is requested ahead of the weights and handled while they arrive}.
+ *           row is requested ahead of the weights and handled while they arrive (what = 2: 0 for sixteen waves
+ *           per row tile with up to ten chunks each, which do so in every call)}.
  * what = 4: the kernel behind mnnq_linear_prefill_fused given mnnq_workspace_size bytes, what = 5: behind
  *           mnnq_linear_prefill_f16 without row_scale; out8 = {0 tiled, 1 few tokens with the activations
  *           in registers, 2 few tokens streaming both operands, 3 K split over the waves, 6 tiled fp6, 7 fp6 with K

@@ -123,6 +123,10 @@ __device__ __forceinline__ float dot16_f16(uint32_t w0, uint32_t w1, uint32_t z,
 // how many younger loads may still be in flight when x is first used (behind conditional loads it
 // waits for the whole weight stream before x is staged).  Used where it pays: small layers, layers
 // whose waves all have exactly UNROLL chunks, and sixteen waves per row tile.
+// Lanes that load nothing of x are cleared behind a branch, with a wait for the load: a wave whose slice is not a multiple
+// of 64 units (four chunks) has its x before it requests the first weight.  That costs nothing to speak of.  Without the wait - cleared
+// when staged; or x, or both, through buffer descriptors - 252 shapes took 0.995 - 1.01 of the time, single ones up to 1.11; descriptors for
+// both 0.92 - 0.94 of it beyond 64 MiB (4 waves, 3584 columns), 1.02 - 1.05 below 16 MiB.
 template <int WAVES, int KSPLIT, int UNROLL, bool PREFETCH, bool MINF, bool EARLY = false>
 __global__ __launch_bounds__(WAVES * 64) void decode_f16_kernel(const uint8_t* __restrict__ packed, Layout L,
                                                                 const uint16_t* __restrict__ x16,
@@ -317,9 +321,9 @@ int launch_decode_f16(const uint8_t* packed, const Layout& L, const uint16_t* x1
     }
     // Rows of 28 chunks (K = 3584) on four waves: seven chunks each, with no register left unused
     if (ks == 4 && L.C == 28 && !prefetch && !debug_option(kDbgDecodeKsplit)) unroll = 7;
-    // ... and sixteen waves: registers for no more chunks than a wave has (nine as ten), so that at most one is loaded twice, and x
-    // ahead of the weights for every size.  Behind conditional loads x was staged when the last weight had arrived; us, weights from
-    // HBM: 4096 x 14336 10.4 -> 9.0, 3584 x 18944 13.2 -> 11.6, 8192 x 8448 13.4 -> 10.3, 16000 x 14336 34.9 -> 29.7, float minima
+    // ... and sixteen waves: registers for no more chunks than a wave has (nine as ten, which most waves of such a row fill with eight:
+    // two are requested twice), all of them requested without a branch.  Behind conditional loads x was staged when the last weight had
+    // arrived; us, weights from HBM: 4096 x 14336 10.4 -> 9.0, 3584 x 18944 13.2 -> 11.6, 8192 x 8448 13.4 -> 10.3, 16000 x 14336 34.9 -> 29.7, float minima
     // 10.5 -> 9.8, 13.6 -> 12.6, 14.0 -> 10.7, 36.1 -> 32.5; nibble planes 4096 x 4608 8.6 -> 7.4.
     const int64_t share = (L.C + 15) / 16;
     const bool close = ks == 16 && share <= 10 && !debug_option(kDbgDecodeKsplit) && !debug_option(kDbgDecodeEarly);

@@ -95,7 +95,8 @@ __global__ __launch_bounds__(64 * KS, 2) void ksplit_kernel(const uint8_t* __res
         const int off = c + (kb >> 1) < c1 ? (kb >> 1) * ZB + row * 8 + (kb & 1) * 4 : kOutOfRange;
         mn_next[j] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_z, off, uniform((j * C + c) * ZB), 0));
     };
-    // in the order of the loop's refills: the waits are counts
+    // In the order of the loop's refills: the waits are counts.  (Not so with group minima: they are requested last here and first in
+    // the loop, whose head waits for the smaller count, all but three loads, once per turn of two chunks.)
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
