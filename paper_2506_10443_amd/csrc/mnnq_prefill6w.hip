@@ -8,7 +8,7 @@
 //
 // Bound: matrix and vector issue, as in mnnq_prefill6.hip.  A tile is three quarters of what a CU contracts as two tiles of
 // 128 x 128, and one of them keeps a CU as busy as those two: it is for layers that are one wide tile per CU and more than one
-// 128 x 128 tile (the rule and what it measured: choose_plan6).
+// 128 x 128 tile (the rule and what it measured: choose_tiled6).
 #include "mnnq_common.h"
 
 namespace mnnq {
